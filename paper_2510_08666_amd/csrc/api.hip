@@ -203,7 +203,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.loop_flags = cv.take((size_t)(MAX_LOOP_STEPS + 1) * 4);   // inner loop: "step i is still needed" words
   w.loop_steps = cv.take(4);                     // inner loop: steps that ran
   w.lm_rows = cv.take((size_t)(1 + T) * 4);      // LM head: rows of the undecided positions
-  w.work = cv.take((size_t)(1 + expert_work_items(MAX_EXPERTS, (int)(T * K))) * 4);
+  w.work = cv.take((size_t)(1 + expert_work_items(MAX_EXPERTS, (int)(T * K), 2)) * 4);
   w.y = cv.take(planes * T * K * I * es);
   w.o = cv.take(T * K * H * 4);
   w.lm_part = cv.take((size_t)lm_head_waves(c.vocab) * T * 4 * 4);

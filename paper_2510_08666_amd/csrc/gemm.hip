@@ -1151,7 +1151,8 @@ template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a
     router_kernel<E, 1, 8><<<dim3(1, groups), 8 * WAVE, ksplit_lds<1, 8>(), st>>>(
         W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
         a.topk_w, 0, a.cnt, a.off, a.perm, a.pos_of_pair, a.part, a.tickets, live_word());
-    launch_permute(a.topk_idx, a.T * a.top_k, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work, st);
+    launch_permute(a.topk_idx, a.T * a.top_k, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work,
+                   expert_group_tiles(a.E, a.T * a.top_k), st);
   }
 }
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {

@@ -215,7 +215,8 @@ __device__ inline uint64_t chunk_ballots(unsigned long long* mine, int lane, int
 __global__ __launch_bounds__(1024) void permute_kernel(const int32_t* __restrict__ expert_of_pair, int n_pairs,
                                                         int n_exp, int32_t* __restrict__ cnt, int32_t* __restrict__ off,
                                                         int32_t* __restrict__ perm, int32_t* __restrict__ pos_of_pair,
-                                                        int32_t* __restrict__ work, const int32_t* __restrict__ live) {
+                                                        int32_t* __restrict__ work, int group_tiles,
+                                                        const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   extern __shared__ uint16_t s_pre[];                       // [n_chunks][MAX_EXPERTS]
   __shared__ unsigned long long s_ballot[16 * MAX_EXPERTS];
@@ -262,13 +263,13 @@ __global__ __launch_bounds__(1024) void permute_kernel(const int32_t* __restrict
       off[STAT_ACTIVE_SUM] += __popcll(has_rows);
       off[STAT_PERMUTATIONS] += 1;
     }
-    // Work list of the many-token expert GEMMs: one item per (expert, group of up to 128 rows), the groups with
-    // the most 32-row tiles first, so that the long workgroups start first and the short ones fill the tail.
+    // Work list of the many-token expert GEMMs: one item per (expert, group of up to group_tiles 32-row tiles), the
+    // groups with the most tiles first, so that the long workgroups start first and the short ones fill the tail.
     // work[0] = number of items, work[1 + i] = expert << 16 | group.
-    const int full = tot / (4 * TILE), rem_tiles = (tot % (4 * TILE) + TILE - 1) / TILE;
+    const int rows_per = group_tiles * TILE, full = tot / rows_per, rem_tiles = (tot % rows_per + TILE - 1) / TILE;
     int at = 0;
-    for (int k = 4; k >= 1; --k) {
-      const int mine_k = (k == 4 ? full : 0) + (rem_tiles == k ? 1 : 0);   // the remainder group has index `full`
+    for (int k = group_tiles; k >= 1; --k) {
+      const int mine_k = (k == group_tiles ? full : 0) + (rem_tiles == k ? 1 : 0);   // the remainder group has index `full`
       int incl_k = mine_k;
 #pragma unroll
       for (int o = 1; o < WAVE; o <<= 1) {
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(1024) void permute_kernel(const int32_t* __restrict
         if (lane >= o) incl_k += up;
       }
       const int first = at + incl_k - mine_k;
-      if (k == 4) {
+      if (k == group_tiles) {
         for (int g = 0; g < mine_k; ++g) work[1 + first + g] = (lane << 16) | g;
       } else if (mine_k) {
         work[1 + first] = (lane << 16) | full;
@@ -306,10 +307,10 @@ bool configure_permute() {
 constexpr int PERMUTE_MAX_PAIRS = 65535;
 int permute_max_pairs() { return PERMUTE_MAX_PAIRS; }
 void launch_permute(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm,
-                    int32_t* pos_of_pair, int32_t* work, hipStream_t st) {
+                    int32_t* pos_of_pair, int32_t* work, int group_tiles, hipStream_t st) {
   const int n_chunks = (n_pairs + WAVE - 1) / WAVE;
   permute_kernel<<<1, 1024, (size_t)n_chunks * MAX_EXPERTS * sizeof(uint16_t), st>>>(topk_idx, n_pairs, E, cnt, off, perm,
-                                                                                     pos_of_pair, work, live_word());
+                                                                                     pos_of_pair, work, group_tiles, live_word());
 }
 
 // ---------------------------------------------------------------- LM-head partial merge

@@ -28,7 +28,7 @@ __device__ inline float silu_w(float x) { return x / (1.f + __expf(-x)); }
 
 // ------------------------------------------------------------------------------------------------
 // Routed experts, rows of expert e = pairs perm[off[e] .. off[e]+cnt[e]).  Grid (tasks / 8, work items): a work item
-// is an (expert, group of up to 128 rows) pair; the permutation kernel lists them heaviest first.
+// is an (expert, group of up to 64 or 128 rows) pair; the permutation kernel lists them heaviest first.
 //   GEMM 1: task = 32 gate features + the same 32 up features;  y = silu(gate) * up  -> Y[sorted row][I]
 //   GEMM 2: task = 64 adjacent output features of the down projection                -> O[token*top_k + slot][H]
 // ------------------------------------------------------------------------------------------------
@@ -170,6 +170,15 @@ constexpr int SMALL_WW = 2;
 // lasts as long as those; 32 one-task workgroups per expert put 1.75 MB on the fullest unit (78 -> 70 us for such
 // layers, 69.1 -> 65.7 us on average at batch 1, though every workgroup now stages the activation rows for itself).
 constexpr int GU1_WW = 1;
+// More than 64 tokens, up to MID_ROWS rows per expert on average: two token tiles and four tasks per workgroup, so
+// that two workgroups share a compute unit (trace ids 20, 21).  With eight tasks an expert is four workgroups of a
+// whole compute unit each, and a step whose masked rows touch half of the experts leaves half of the chip idle
+// (gate/up + down in microseconds at 96 / 128 / 160 tokens of a fully masked block batch: 73 + 46, 91 + 55, 89 + 53
+// with eight tasks, 45 + 31, 71 + 44, 72 + 46 with four; where all 64 experts have rows, 91 + 51 against 87 + 53 at
+// 96 tokens and 99 + 58 against 96 + 59 at 160).  Beyond, the rows weigh more than the balance: every workgroup
+// fetches its expert's rows for itself (256 tokens: 102 + 64 with eight tasks, 120 + 73 with four).
+constexpr int MID_WW = 4, MID_WT = 2, MID_ROWS = 24;
+int expert_group_tiles(int E, int n_pairs) { return n_pairs <= MID_ROWS * E ? MID_WT : WT; }
 
 template <typename E> static void launch_gate_up_wide_t(const ExpertArgs& a, hipStream_t st) {
   const int n_tasks = a.I / TILE;
@@ -182,9 +191,14 @@ template <typename E> static void launch_gate_up_wide_t(const ExpertArgs& a, hip
     expert_gemm1_wide_kernel<E, 2, SMALL_WW, 17, true><<<dim3((n_tasks + SMALL_WW - 1) / SMALL_WW, a.E), SMALL_WW * WAVE,
                                                          wide_lds<E, 17, 2>(), st>>>(
         w, xn, a.rinv, (E*)a.y, a.cnt, a.off, a.perm, a.work, a.T, a.H, a.I, a.top_k, a.topk_w, live_word());
+  } else if (expert_group_tiles(a.E, a.T * a.top_k) == MID_WT) {
+    expert_gemm1_wide_kernel<E, MID_WT, MID_WW, 20, false>
+        <<<dim3((n_tasks + MID_WW - 1) / MID_WW, expert_work_items(a.E, a.T * a.top_k, MID_WT)), MID_WW * WAVE,
+           wide_lds<E, 20, MID_WT>(), st>>>(w, xn, a.rinv, (E*)a.y, a.cnt, a.off, a.perm, a.work, a.T, a.H, a.I, a.top_k,
+                                       a.topk_w, live_word());
   } else {
     expert_gemm1_wide_kernel<E, WT, EXPERT_WW, 10, false>
-        <<<dim3((n_tasks + EXPERT_WW - 1) / EXPERT_WW, expert_work_items(a.E, a.T * a.top_k)), EXPERT_WW * WAVE,
+        <<<dim3((n_tasks + EXPERT_WW - 1) / EXPERT_WW, expert_work_items(a.E, a.T * a.top_k, WT)), EXPERT_WW * WAVE,
            wide_lds<E, 10, WT>(), st>>>(w, xn, a.rinv, (E*)a.y, a.cnt, a.off, a.perm, a.work, a.T, a.H, a.I, a.top_k,
                                         a.topk_w, live_word());
   }
@@ -200,9 +214,13 @@ template <typename E> static void launch_down_wide_t(const ExpertArgs& a, hipStr
     expert_gemm2_wide_kernel<E, 2, SMALL_WW, 19, true><<<dim3((n_tasks + SMALL_WW - 1) / SMALL_WW, a.E), SMALL_WW * WAVE,
                                                          wide_lds<E, 19, 2>(), st>>>(
         w, y, a.o, a.cnt, a.off, a.perm, a.work, n_pairs, a.H, a.I, live_word());
+  } else if (expert_group_tiles(a.E, n_pairs) == MID_WT) {
+    expert_gemm2_wide_kernel<E, MID_WT, MID_WW, 21, false>
+        <<<dim3((n_tasks + MID_WW - 1) / MID_WW, expert_work_items(a.E, n_pairs, MID_WT)), MID_WW * WAVE,
+           wide_lds<E, 21, MID_WT>(), st>>>(w, y, a.o, a.cnt, a.off, a.perm, a.work, n_pairs, a.H, a.I, live_word());
   } else {
     expert_gemm2_wide_kernel<E, WT, EXPERT_WW, 11, false>
-        <<<dim3((n_tasks + EXPERT_WW - 1) / EXPERT_WW, expert_work_items(a.E, n_pairs)), EXPERT_WW * WAVE,
+        <<<dim3((n_tasks + EXPERT_WW - 1) / EXPERT_WW, expert_work_items(a.E, n_pairs, WT)), EXPERT_WW * WAVE,
            wide_lds<E, 11, WT>(), st>>>(w, y, a.o, a.cnt, a.off, a.perm, a.work, n_pairs, a.H, a.I, live_word());
   }
 }
@@ -242,13 +260,16 @@ __global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __rest
   // the list's length: the grid is sized for all T rows, and the workgroups left over at its end return at once.
   const int n_rows = rows ? min(rows[0], T) : T;
   if (n_rows == 0) return;              // uniform over the workgroup
-  const int groups = (n_rows + WT * TILE - 1) / (WT * TILE);
+  // The token groups take equal numbers of tiles: they stream the same weights side by side, and a group of one tile
+  // beside one of four runs ahead of it and fetches them from memory again (160 tokens: 248 us as 4 + 1, 209 as 3 + 2).
+  const int tiles = (n_rows + TILE - 1) / TILE, groups = (tiles + WT - 1) / WT, per_group = (tiles + groups - 1) / groups;
   const int turn = blockIdx.x / XCDS;
   const int tgroup = (turn / groups) * XCDS + blockIdx.x % XCDS;
   const int n_tasks = (V + 2 * TILE - 1) / (2 * TILE);
   if (tgroup * WW >= n_tasks) return;   // uniform over the workgroup
-  const int tok0 = (turn % groups) * WT * TILE;
-  const int nt = min(WT, (n_rows - tok0 + TILE - 1) / TILE);
+  const int tok0 = (turn % groups) * per_group * TILE;
+  const int nt = min(per_group, tiles - (turn % groups) * per_group);
+  if (nt <= 0) return;                  // uniform: fewer tiles than groups * per_group
   const int slot = tgroup * WW + wave, task = min(slot, n_tasks - 1);
   const int ksteps = H / KS;
   auto row_of = [&](int i) { return rows ? min(max(rows[1 + min(i, n_rows - 1)], 0), T - 1) : min(i, T - 1); };

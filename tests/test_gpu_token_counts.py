@@ -1,0 +1,41 @@
+"""Steps at the token counts where the expert GEMMs and the LM head change their form: the first count above the
+64-token forms, both sides of the line between two and four row tiles per work item, token groups of unequal size."""
+import pytest
+
+import dinfer_inputs as di
+from harness import GpuRun, OracleRun, bars_for, compare_logits, compare_step, make_case
+from test_gpu_tiny import _skew_router
+
+pytestmark = pytest.mark.gpu
+
+# (sequences, block length, skewed router).  64 experts, 8 per token: two-tile work items up to 192 tokens.
+SIZES = [(5, 13, False), (3, 32, False), (4, 32, True), (5, 32, False), (5, 32, True), (3, 64, False), (4, 49, False),
+         (4, 50, True)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_seq,block,skew", SIZES)
+def test_step_at_token_count(n_seq, block, skew, dtype):
+    tiny = di.model_preset("tiny")
+    cfg = di.configs.scaled(tiny, n_heads=2, head_dim=128, n_experts=64, top_k=8, moe_inter=192, vocab=1100, dtype=dtype,
+                            logit_scale=8.0 if dtype == "f32" else 1.0)
+    wl = di.Workload("tokens", cfg, n_seq, block, 3, 70, precommit=True, threshold=0.9, seed_index=50 + n_seq)
+    cfg, w, inp = make_case(wl)
+    if skew:
+        _skew_router(cfg, w)
+    cap = int(inp.prefix_len.max()) + 2 * block + 16
+    ora = OracleRun(cfg, w, inp, cap)
+    gpu = GpuRun(cfg, w, inp, n_seq * block, cap)
+    bars = bars_for(cfg)
+    gpu.inject_prefix(ora.caches)
+    gpu.set_state(inp.block_tokens, inp.mask_bits, inp.prefix_len)
+    got = gpu.step(wl.threshold)
+    logits = gpu.logits(n_seq * block).reshape(n_seq, block, cfg.vocab)
+    routing = gpu.routing().reshape(cfg.n_layers, n_seq, block, cfg.top_k)
+    for s in range(n_seq):
+        ref, _ = ora.step_following(s, inp.block_tokens[s], int(inp.mask_bits[s]), int(inp.prefix_len[s]), wl.threshold, 0,
+                                    routing[:, s], bars)
+        compare_logits(ref["logits"], logits[s], bars)
+        compare_step(ref, got["tokens"][s], got["mask"][s], got["conf"][s], got["argmax"][s], got["n_committed"][s],
+                     inp.block_tokens[s], inp.mask_bits[s], wl.threshold, 0, bars, ref["logits"], logits[s])
+    gpu.close()
