@@ -206,7 +206,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.work = cv.take((size_t)(1 + expert_work_items(MAX_EXPERTS, (int)(T * K), 2)) * 4);
   w.y = cv.take(planes * T * K * I * es);
   w.o = cv.take(T * K * H * 4);
-  w.lm_part = cv.take((size_t)lm_head_waves(c.vocab) * T * 4 * 4);
+  w.lm_part = cv.take((size_t)lm_head_most_parts(c.vocab) * T * 4 * 4);
   w.lm_stats = cv.take(T * 2 * 4);
   w.conf = cv.take(T * 4);
   w.argmax = cv.take(T * 4);

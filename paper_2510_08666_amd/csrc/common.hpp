@@ -149,6 +149,22 @@ __device__ inline float row_rinv(const float* __restrict__ ssq, int n_ssq, int T
   return rsqrtf(s / H + eps);
 }
 
+// (max, sum-exp, id) partials of a row of logits combine associatively: the larger max wins (lower id on equal max)
+// and the sums are rescaled to it.
+struct LmStat {
+  float m, s;
+  int id;
+};
+__device__ inline LmStat lm_combine(LmStat a, LmStat b) {
+  if (b.m > a.m || (b.m == a.m && b.id < a.id)) {
+    const LmStat t = a;
+    a = b;
+    b = t;
+  }
+  if (b.m > -INFINITY) a.s += b.s * __expf(b.m - a.m);
+  return a;
+}
+
 // Data handed from one workgroup to another INSIDE a kernel goes through device-coherent accesses (they bypass
 // the per-XCD L2, which is not coherent across the chip): no cache-wide write-back or invalidate is needed then.
 __device__ inline void coherent_store(float* p, float v) {

@@ -1184,8 +1184,6 @@ void launch_expert_down_fused(bool bf16, const ExpertArgs& a, const OprojArgs& r
 // The routed-expert GEMMs and the LM head live in wide.hip (shared-operand forms for every token count).
 void launch_expert_gate_up(bool bf16, const ExpertArgs& a, hipStream_t st) { launch_expert_gate_up_wide(bf16, a, st); }
 void launch_expert_down(bool bf16, const ExpertArgs& a, hipStream_t st) { launch_expert_down_wide(bf16, a, st); }
-int lm_head_waves(int V) { return lm_head_wide_parts(V); }
-int lm_head_parts(int V, int) { return lm_head_wide_parts(V); }
 void launch_lm_head(bool bf16, const LmArgs& a, hipStream_t st) { launch_lm_head_wide(bf16, a, st); }
 
 bool configure_kernels() {

@@ -314,22 +314,9 @@ void launch_permute(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, i
 }
 
 // ---------------------------------------------------------------- LM-head partial merge
-// (max, sum-exp, id) partials combine associatively: the larger max wins (lower id on equal max) and the
-// sums are rescaled to it.  One workgroup per token row, fixed tree -> deterministic.
-struct LmStat {
-  float m, s;
-  int id;
-};
-__device__ inline LmStat lm_combine(LmStat a, LmStat b) {
-  if (b.m > a.m || (b.m == a.m && b.id < a.id)) {
-    const LmStat t = a;
-    a = b;
-    b = t;
-  }
-  if (b.m > -INFINITY) a.s += b.s * __expf(b.m - a.m);
-  return a;
-}
-__global__ __launch_bounds__(256) void lm_merge_kernel(const float* __restrict__ part, int n_waves, int T,
+// One workgroup per token row over the LmStat partials of the LM head's workgroups (lm_combine), fixed tree ->
+// deterministic.  The partials of a row lie next to each other: part[token][n_parts].
+__global__ __launch_bounds__(256) void lm_merge_kernel(const f32x4* __restrict__ part, int n_parts,
                                                         float* __restrict__ conf, int32_t* __restrict__ argmax,
                                                         float* __restrict__ stats, const uint64_t* __restrict__ mask,
                                                         int block_len, const int32_t* __restrict__ live) {
@@ -338,8 +325,8 @@ __global__ __launch_bounds__(256) void lm_merge_kernel(const float* __restrict__
   const int t = blockIdx.x;
   if (mask && !((mask[t / block_len] >> (t % block_len)) & 1ull)) return;   // a decided position: nothing was computed
   LmStat a{-INFINITY, 0.f, 0x7fffffff};
-  for (int w = threadIdx.x; w < n_waves; w += 256) {
-    const float* p = part + ((int64_t)w * T + t) * 4;
+  for (int w = threadIdx.x; w < n_parts; w += 256) {
+    const f32x4 p = part[(int64_t)t * n_parts + w];
     a = lm_combine(a, LmStat{p[0], p[1], __float_as_int(p[2])});
   }
 #pragma unroll
@@ -359,9 +346,9 @@ __global__ __launch_bounds__(256) void lm_merge_kernel(const float* __restrict__
     }
   }
 }
-void launch_lm_merge(const float* part, int n_lm_waves, int T, float* conf, int32_t* argmax, float* stats,
+void launch_lm_merge(const float* part, int n_parts, int T, float* conf, int32_t* argmax, float* stats,
                      hipStream_t st, const uint64_t* mask, int block_len) {
-  lm_merge_kernel<<<T, 256, 0, st>>>(part, n_lm_waves, T, conf, argmax, stats, mask, block_len, live_word());
+  lm_merge_kernel<<<T, 256, 0, st>>>((const f32x4*)part, n_parts, conf, argmax, stats, mask, block_len, live_word());
 }
 
 // Row list of the LM head when only undecided positions are wanted: lane s counts the set bits of sequence s,

@@ -21,7 +21,7 @@ constexpr int LM_WW = 8, LM_PRE = 2;
 // the dispatcher deals them evenly, so a launch lasts as long as the compute units with one workgroup more than the
 // others: 614 workgroups of four tasks put 3 MB on some units and 2 MB on others (112 us), 1228 of two tasks 2.5 or
 // 2 MB (108 us).
-constexpr int LM_SMALL_WW = 2;
+constexpr int LM_SMALL_WW = 2, LM_MID_WW = 4;   // up to 32, up to 64 tokens
 constexpr int XCDS = 8;      // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
 
 __device__ inline float silu_w(float x) { return x / (1.f + __expf(-x)); }
@@ -236,7 +236,7 @@ void launch_expert_down_wide(bool bf16, const ExpertArgs& a, hipStream_t st) {
 // ------------------------------------------------------------------------------------------------
 // LM head fused with the confidence reduction, many-token form.  A workgroup takes one task group (8 tasks = 512
 // vocabulary ids) and one group of 128 tokens; a wave turns its accumulators (64 vocabulary ids x 128 tokens) into
-// one (max, sum-exp, lowest arg max) partial per token: part[task group * 8 + wave][token].  Logits are never
+// one (max, sum-exp, lowest arg max) partial per token, the workgroup folds them: part[token][task group].  Logits are never
 // stored (unless the debug pointer is set).
 // The token groups of one task group stream the same weights.  Workgroups go to the dies in turn, so the launch is
 // one-dimensional and workgroup i = die (i % 8), turn (i / 8): consecutive turns of ONE die take the token groups
@@ -266,12 +266,16 @@ __global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __rest
   const int turn = blockIdx.x / XCDS;
   const int tgroup = (turn / groups) * XCDS + blockIdx.x % XCDS;
   const int n_tasks = (V + 2 * TILE - 1) / (2 * TILE);
-  if (tgroup * WW >= n_tasks) return;   // uniform over the workgroup
+  const int n_parts = (n_tasks + WW - 1) / WW;
+  if (tgroup >= n_parts) return;        // uniform over the workgroup
+  LmStat* s_stat = reinterpret_cast<LmStat*>(lds_raw);   // [WW][WT * TILE], once the fragments are done with
+  static_assert(WW * WT * TILE * sizeof(LmStat) <= wide_lds<E, KID, WT>(), "the statistics fit the staging area");
   const int tok0 = (turn % groups) * per_group * TILE;
   const int nt = min(per_group, tiles - (turn % groups) * per_group);
   if (nt <= 0) return;                  // uniform: fewer tiles than groups * per_group
   const int slot = tgroup * WW + wave, task = min(slot, n_tasks - 1);
   const int ksteps = H / KS;
+  const bool quads = V % 4 == 0 && ((uintptr_t)logits_out & 15) == 0;   // rows of logits start on 16-byte boundaries
   auto row_of = [&](int i) { return rows ? min(max(rows[1 + min(i, n_rows - 1)], 0), T - 1) : min(i, T - 1); };
   int tok_of[WT];
   float zs[WT];
@@ -303,54 +307,59 @@ __global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __rest
           m = z[i];
           best = id;
         }
-        if (logits_out && tok < T && id < V) logits_out[(int64_t)tok * V + id] = z[i];
+        if (logits_out && !quads && tok < T && id < V) logits_out[(int64_t)tok * V + id] = z[i];
+      }
+      if (logits_out && quads && tok < T) {
+        // every lane stores into a row of its own, so the address unit takes the 64 lanes one by one: four
+        // consecutive ids per store (32 tokens: LM head with stored logits 137 us, element by element)
+#pragma unroll
+        for (int i = 0; i < 32; i += 4) {
+          const int id = (2 * task + (i >> 4)) * TILE + acc_row(i & 15, half);
+          if (id < V) *reinterpret_cast<f32x4*>(logits_out + (int64_t)tok * V + id) = f32x4{z[i], z[i + 1], z[i + 2], z[i + 3]};
+        }
       }
       if (m > -INFINITY) {
 #pragma unroll
         for (int i = 0; i < 32; ++i) sum += __expf(z[i] - m);
       }
     }
-    // fold the two half-waves (same token, other rows)
-    const float om = __shfl_xor(m, 32, WAVE), os = __shfl_xor(sum, 32, WAVE);
-    const int ob = __shfl_xor(best, 32, WAVE);
-    float M = m, S = sum;
-    int B = best;
-    if (om > M || (om == M && ob < B)) {
-      S = (M > -INFINITY ? S * __expf(M - om) : 0.f) + os;
-      M = om;
-      B = ob;
-    } else if (om > -INFINITY) {
-      S += os * __expf(om - M);
-    }
-    if (half == 0 && tok < T && t < nt) {
-      float* p = part + ((int64_t)slot * T + tok) * 4;
-      p[0] = M;
-      p[1] = S;
-      p[2] = __int_as_float(B);
-      p[3] = 0.f;
-    }
+    // fold the two half-waves (same token, other rows), then the workgroup's waves (other ids) through LDS: one partial
+    // per workgroup and token instead of one per wave, and a row's partials next to each other, are what the merge
+    // kernel reads (512 tokens: 27 us over 2456 partials a stride of 8 KB apart; see lm_merge_kernel)
+    const LmStat w = lm_combine(LmStat{m, sum, best}, LmStat{__shfl_xor(m, 32, WAVE), __shfl_xor(sum, 32, WAVE), __shfl_xor(best, 32, WAVE)});
+    if (t == 0) __syncthreads();   // the staged fragments have been read by every wave
+    if (half == 0) s_stat[wave * WT * TILE + t * TILE + col] = w;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nt * TILE; i += WW * WAVE) {
+    LmStat a = s_stat[i];
+#pragma unroll
+    for (int w = 1; w < WW; ++w) a = lm_combine(a, s_stat[w * WT * TILE + i]);
+    if (tok0 + i < n_rows)
+      *reinterpret_cast<f32x4*>(part + ((int64_t)row_of(tok0 + i) * n_parts + tgroup) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
   }
 }
 
-int lm_head_wide_parts(int V) { return ((V + 63) / 64 + LM_WW - 1) / LM_WW * LM_WW; }
+// Tasks (waves) per workgroup by token count, and the partials a row receives: one per workgroup.
+static int lm_tasks_per_wg(int T) { return T <= TILE ? LM_SMALL_WW : T <= 2 * TILE ? LM_MID_WW : LM_WW; }
+int lm_head_parts(int V, int T) { return ((V + 63) / 64 + lm_tasks_per_wg(T) - 1) / lm_tasks_per_wg(T); }
+int lm_head_most_parts(int V) { return lm_head_parts(V, 1); }
 
 // Up to 64 tokens: two token tiles per workgroup and both activation planes (trace id 14): there the weight stream
 // is the bound, and sharing the activation fragments of eight tasks relieves the address unit, which would
 // otherwise take every lane's own activation row one by one.  More tokens: four tiles, high plane only (id 9).
 template <typename E> static void launch_lm_wide_t(const LmArgs& a, hipStream_t st) {
+  const int tgroups = lm_head_parts(a.V, a.T);
   if (a.T <= TILE) {   // one token tile (trace id 15)
-    const int tgroups = lm_head_wide_parts(a.V) / LM_SMALL_WW;
     lm_head_wide_kernel<E, 1, 15, LM_SMALL_WW><<<(tgroups + XCDS - 1) / XCDS * XCDS, LM_SMALL_WW * WAVE, wide_lds<E, 15, 1>(), st>>>(
         (const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows, live_word());
     return;
   }
   if (a.T <= 2 * TILE) {   // four tasks per workgroup (two: 144 against 119 us, the activation fragments of 64 rows are shared by too few)
-    const int tgroups = lm_head_wide_parts(a.V) / 4;
-    lm_head_wide_kernel<E, 2, 14, 4><<<(tgroups + XCDS - 1) / XCDS * XCDS, 4 * WAVE, wide_lds<E, 14, 2>(), st>>>(
+    lm_head_wide_kernel<E, 2, 14, LM_MID_WW><<<(tgroups + XCDS - 1) / XCDS * XCDS, LM_MID_WW * WAVE, wide_lds<E, 14, 2>(), st>>>(
         (const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows, live_word());
     return;
   }
-  const int tgroups = lm_head_wide_parts(a.V) / LM_WW;
   const int groups = (a.T + WT * TILE - 1) / (WT * TILE);
   lm_head_wide_kernel<E, WT, 9, LM_WW><<<(tgroups + XCDS - 1) / XCDS * XCDS * groups, LM_WW * WAVE, wide_lds<E, 9, WT>(), st>>>(
       (const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows, live_word());
