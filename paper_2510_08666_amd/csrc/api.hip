@@ -169,12 +169,10 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
       const size_t tile = (size_t)2 * tt * 16 * WAVE * 4;
       const size_t qkv = (size_t)(3 * D / 64) * gemm_slices(bf, H, tt * TILE) * tile;
       const size_t opr = (size_t)(H / 64) * gemm_slices(bf, D, tt * TILE) * tile;
-      const size_t smooth = (size_t)(H / 64) * SMOOTH_SLICES * tile;   // expected-embedding contraction
       const size_t down = (size_t)(H / 64) * down_fused_slices() * tile;   // fused down projection
       most = down > most ? down : most;
       most = qkv > most ? qkv : most;
       most = opr > most ? opr : most;
-      most = smooth > most ? smooth : most;
     }
     w.tk_part = cv.take(most);
     const int units = 3 * D / 64 > H / 64 ? 3 * D / 64 : H / 64;
@@ -672,8 +670,7 @@ static int smooth_impl(dinfer_ctx* c, int32_t n_seq, int32_t block_len, int32_t*
     launch_lm_head(c->bf16, la, st);
   }
   launch_lm_merge(la.part, lm_head_parts(f.vocab, T), T, d_conf, d_argmax, stats, st);
-  SmoothArgs sa{c->weights + c->wm.emb_t, logits, stats, probs, d_mask, block_len, d_delta, T, f.hidden, f.vocab,
-                at<float>(c->ws, c->wsm.tk_part), at<int32_t>(c->ws, c->wsm.tickets)};
+  SmoothArgs sa{c->weights + c->wm.emb_t, logits, stats, probs, d_mask, block_len, d_delta, T, f.hidden, f.vocab};
   launch_expected_embedding(c->bf16, sa, st);
   launch_commit(d_conf, d_argmax, n_seq, block_len, block_len, 0, d_block_tokens, d_mask, commit_rule(decode), d_n_committed,
                 nullptr, nullptr, st, next_live, steps);

@@ -223,38 +223,6 @@ template <typename E> struct ResidualEpi {
   __device__ void row_sum(int task, int tok, float s) const { ssq[(int64_t)task * T + tok] = s; }
 };
 
-// Iteration smoothing: the contraction of the probabilities with the embedding matrix; a row of a position that
-// is still masked receives the expected embedding, the other rows are left alone.
-struct SmoothEpi {
-  static constexpr bool ROWSUM = false;
-  float* delta;         // [T][H]
-  int H;
-  const uint64_t* mask;
-  int block_len;
-  template <int PER> struct Pre {
-    bool on;
-  };
-  template <int PER> __device__ Pre<PER> prefetch(int, int tok, bool valid, int, int) const {
-    Pre<PER> p;
-    p.on = valid && ((mask[tok / block_len] >> (tok % block_len)) & 1ull);
-    return p;
-  }
-  template <int PER> __device__ void prefetch2(Pre<PER>&, int, int, int) const {}
-  template <int PER>
-  __device__ float apply(const Pre<PER>& pre, int task, int tok, bool, int half, int v0, const float (&a0)[PER],
-                         const float (&a1)[PER]) const {
-    if (!pre.on) return 0.f;
-    float* p0 = delta + (int64_t)tok * H + (2 * task) * TILE + acc_row(v0, half);
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      p0[i] = a0[i];
-      p0[TILE + i] = a1[i];
-    }
-    return 0.f;
-  }
-  __device__ void row_sum(int, int, float) const {}
-};
-
 // Every wave leaves its partial accumulators in LDS: red[wave][t*32 + tile*16 + v][lane].
 template <int TT, int ROWS>
 __device__ inline void spill_partials(float* red, int wave, int lane, const f32x16 (&acc0)[TT], const f32x16 (&acc1)[TT]) {
@@ -440,15 +408,15 @@ static int ksplit_slices(bool bf16, int K, int T, int n_tasks) {
 
 template <typename E, class Epi>
 static void launch_ksplit(bool bf16, const E* W, int ksteps, const E* B, int T, int K, int n_tasks,
-                          float* part, int32_t* tickets, const Epi& epi, hipStream_t st, int forced_slices = 0) {
-  const int slices = forced_slices ? forced_slices : single_slice() ? 1 : ksplit_slices(bf16, K, T, n_tasks);
+                          float* part, int32_t* tickets, const Epi& epi, hipStream_t st) {
+  const int slices = single_slice() ? 1 : ksplit_slices(bf16, K, T, n_tasks);
   if (T <= 32) {
     gemm_ksplit_kernel<E, 1, 4, Epi><<<dim3(slices, n_tasks, 1), 4 * WAVE, ksplit_lds<1, 4>(), st>>>(W, ksteps, B, T, K, part, tickets, epi, live_word());
   } else if (T <= 64) {
     gemm_ksplit_kernel<E, 2, 4, Epi><<<dim3(slices, n_tasks, 1), 4 * WAVE, ksplit_lds<2, 4>(), st>>>(W, ksteps, B, T, K, part, tickets, epi, live_word());
   } else {
     const int groups = (T + 4 * TILE - 1) / (4 * TILE);
-    gemm_ksplit_kernel<E, 4, 4, Epi><<<dim3(forced_slices ? forced_slices : 1, n_tasks, groups), 4 * WAVE, ksplit_lds<4, 4>(), st>>>(W, ksteps, B, T, K, part, tickets, epi, live_word());
+    gemm_ksplit_kernel<E, 4, 4, Epi><<<dim3(1, n_tasks, groups), 4 * WAVE, ksplit_lds<4, 4>(), st>>>(W, ksteps, B, T, K, part, tickets, epi, live_word());
   }
 }
 
@@ -840,25 +808,146 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st) {
   else launch_oproj_t<float>(false, a, st);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Iteration smoothing: delta = probabilities . W_emb, a contraction over the whole vocabulary with few output features
+// (32 tasks at hidden 2048), so the launch is filled by cutting the contraction: a workgroup takes SMOOTH_TASKS tasks,
+// up to WT token tiles and one K slice, which its two teams of waves halve (as in gemm_dense_kernel), and leaves its
+// sums in part[slice][token][feature]; smooth_reduce_kernel adds the slices in order and writes the rows of masked
+// positions.  Bound: the stream of the transposed embedding matrix (644 MB at vocabulary 157184).  The activation
+// fragments of a slice go through LDS once per SMOOTH_TASKS tasks: in the split-K form, where every wave fetched its own,
+// they took as many of a compute unit's outstanding requests as the weights (32 tokens: 149 us, 4.3 TB/s), and above
+// 64 tokens the unsliced shared-operand form had 24 workgroups at 160 tokens.
+// Workgroup i = die (i % 8), turn (i / 8): the token groups of one (task group, slice) are consecutive turns of one
+// die and share its weights in the L2; slices vary fastest over the dies, so that a die's task groups share the
+// probabilities of its slices.
+// ------------------------------------------------------------------------------------------------
+constexpr int SMOOTH_TASKS = 4, SMOOTH_KH = 2, SMOOTH_PRE = 2, SMOOTH_WGS = 256;
+template <typename E, int KID, int WT> constexpr size_t smooth_lds() {
+  const size_t stage = SMOOTH_KH * wide_lds<E, KID, WT>();
+  const size_t fold = (size_t)(SMOOTH_KH - 1) * SMOOTH_TASKS * 2 * WT * 16 * WAVE * 4;
+  return stage > fold ? stage : fold;
+}
+
+template <typename E, int WT, int KID>
+__global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partial_kernel(const E* __restrict__ W, int ksteps,
+                                                                                       const E* __restrict__ B, int T, int H,
+                                                                                       int n_slices, float* __restrict__ part,
+                                                                                       const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  typedef typename ET<E>::vec vec;
+  extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
+  constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int team = wave / SMOOTH_TASKS, rank = wave % SMOOTH_TASKS;
+  const int n_tasks = H / (2 * TILE), tgroups = (n_tasks + SMOOTH_TASKS - 1) / SMOOTH_TASKS;
+  const int tiles = (T + TILE - 1) / TILE, groups = (tiles + WT - 1) / WT, per_group = (tiles + groups - 1) / groups;
+  const int turn = blockIdx.x / 8, unit = (turn / groups) * 8 + blockIdx.x % 8;
+  if (unit >= tgroups * n_slices) return;               // uniform over the workgroup
+  const int tgroup = unit / n_slices, slice = unit % n_slices;
+  const int nt = min(per_group, tiles - (turn % groups) * per_group);
+  if (nt <= 0) return;
+  const int tok0 = (turn % groups) * per_group * TILE;
+  const int slot = tgroup * SMOOTH_TASKS + rank, task = min(slot, n_tasks - 1);
+  // the slice's chunks, the same number for both teams (they share the workgroup's barriers); see smooth_kpad
+  const int pairs = ksteps / (WKC * SMOOTH_KH);
+  const int p0 = (int)((int64_t)pairs * slice / n_slices), p1 = (int)((int64_t)pairs * (slice + 1) / n_slices);
+  const int chunks = p1 - p0;
+  const int64_t ks0 = ((int64_t)p0 * SMOOTH_KH + (int64_t)team * chunks) * WKC;
+  vec* sb = reinterpret_cast<vec*>(lds_raw + team * wide_lds<E, KID, WT>());
+  const E* brow = B + ks0 * T * (NP * KS) + (int64_t)min(tok0 + (rank % WT) * TILE + col, T - 1) * (NP * KS) + half * G;
+  f32x16 acc0[WT], acc1[WT];
+  zero_acc<WT>(acc0);
+  zero_acc<WT>(acc1);
+  wide_stream<E, WT, SMOOTH_TASKS, SMOOTH_PRE, KID>(
+      W + (int64_t)task * task_stride_elems<E>(ksteps) + ks0 * (2 * WAVE * G) + lane * G, chunks, [&] { return brow; },
+      (int64_t)T * (NP * KS), sb, nt, acc0, acc1, rank);
+  float* red = reinterpret_cast<float*>(lds_raw);
+  float* r = red + (int64_t)rank * (2 * WT * 16) * WAVE + lane;
+  __syncthreads();   // the staging areas are done with
+  if (team > 0) {
+#pragma unroll
+    for (int t = 0; t < WT; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        r[(t * 32 + v) * WAVE] = acc0[t][v];
+        r[(t * 32 + 16 + v) * WAVE] = acc1[t][v];
+      }
+  }
+  __syncthreads();
+  if (team > 0 || slot >= n_tasks) return;
+#pragma unroll
+  for (int t = 0; t < WT; ++t) {
+    const int tok = tok0 + t * TILE + col;
+    if (t < nt && tok < T) {
+      float* out = part + ((int64_t)slice * T + tok) * H + (2 * task) * TILE;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 a, b;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          a[i] = acc0[t][4 * g + i] + r[(t * 32 + 4 * g + i) * WAVE];
+          b[i] = acc1[t][4 * g + i] + r[(t * 32 + 16 + 4 * g + i) * WAVE];
+        }
+        *reinterpret_cast<f32x4*>(out + acc_row(4 * g, half)) = a;
+        *reinterpret_cast<f32x4*>(out + TILE + acc_row(4 * g, half)) = b;
+      }
+    }
+  }
+}
+
+// delta[t][f] = sum over the slices, in slice order, for the rows of masked positions (the others are left alone).
+__global__ __launch_bounds__(256) void smooth_reduce_kernel(const float* __restrict__ part, int n_slices, int T, int H,
+                                                             const uint64_t* __restrict__ mask, int block_len,
+                                                             float* __restrict__ delta, const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, n = (int64_t)T * H;
+  if (i >= n) return;
+  const int t = (int)(i / H);
+  if (!((mask[t / block_len] >> (t % block_len)) & 1ull)) return;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int k = 0; k < n_slices; ++k) s += *reinterpret_cast<const f32x4*>(part + k * n + i);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) delta[i + q] = s[q];   // the caller's buffer: only 4-byte alignment is known
+}
+
+// The vocabulary in whole multiples of 512 k-steps (zero weights and probabilities past its end): every slice of the
+// kernel above gets whole chunks for both of its teams.
 int smooth_kpad(bool bf16, int V) {
-  const int unit = (bf16 ? 16 : 8) * 4 * 8 * SMOOTH_SLICES;   // k-step x waves x burst x slices
+  const int unit = (bf16 ? 16 : 8) * 512;
   return (V + unit - 1) / unit * unit;
 }
-template <typename E> static void launch_smooth_t(bool bf16, const SmoothArgs& a, hipStream_t st) {
-  const int Kpad = smooth_kpad(bf16, a.V);
-  SmoothEpi epi{a.delta, a.H, a.mask, a.block_len};
-  // More than 64 tokens: the shared-operand form, with the most token tiles per workgroup whatever the fill -- every
-  // token group streams the whole transposed embedding matrix, so fewer, larger groups move fewer bytes.
-  if (dense_applies(a.T, Kpad / ET<E>::KS))
-    launch_dense_as<E, DENSE_WT, 4, SmoothEpi>((const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H / 64, epi, st);
-  else
-    launch_ksplit<E>(bf16, (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, Kpad, a.H / 64, a.part,
-                     a.tickets, epi, st, SMOOTH_SLICES);
+template <typename E, int WT, int KID> static void launch_smooth_as(const SmoothArgs& a, int Kpad, hipStream_t st) {
+  const int tgroups = (a.H / 64 + SMOOTH_TASKS - 1) / SMOOTH_TASKS, tiles = (a.T + TILE - 1) / TILE;
+  const int groups = (tiles + WT - 1) / WT, pairs = Kpad / ET<E>::KS / (WKC * SMOOTH_KH);
+  // About one workgroup per compute unit (two waves on every SIMD); a multiple of eight slices keeps a slice on one
+  // die.  The partial sums live where the logits were (T * V floats), which the probabilities have replaced.
+  int slices = SMOOTH_WGS / (tgroups * groups);
+  slices = slices < a.V / a.H ? slices : a.V / a.H;
+  slices = slices < pairs ? slices : pairs;
+  slices = single_slice() || slices < 1 ? 1 : slices >= 8 ? slices / 8 * 8 : slices;
+  const int units = (tgroups * slices + 7) / 8 * 8;
+  float* part = a.logits;
+  smooth_partial_kernel<E, WT, KID><<<units * groups, SMOOTH_TASKS * SMOOTH_KH * WAVE, smooth_lds<E, KID, WT>(), st>>>(
+      (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H, slices, part, live_word());
+  const int64_t quads = (int64_t)a.T * a.H / 4;
+  smooth_reduce_kernel<<<(unsigned)((quads + 255) / 256), 256, 0, st>>>(part, slices, a.T, a.H, a.mask, a.block_len, a.delta,
+                                                                        live_word());
+}
+template <typename E> static void launch_smooth_t(const SmoothArgs& a, int Kpad, hipStream_t st) {
+  if (a.T <= TILE) launch_smooth_as<E, 1, 23>(a, Kpad, st);
+  else if (a.T <= 2 * TILE) launch_smooth_as<E, 2, 23>(a, Kpad, st);
+  else launch_smooth_as<E, 4, 24>(a, Kpad, st);
 }
 void launch_expected_embedding(bool bf16, const SmoothArgs& a, hipStream_t st) {
-  launch_prob_planes(bf16, a.logits, a.stats, a.T, a.V, smooth_kpad(bf16, a.V), a.probs, st);
-  if (bf16) launch_smooth_t<bf16_t>(true, a, st);
-  else launch_smooth_t<float>(false, a, st);
+  const int Kpad = smooth_kpad(bf16, a.V);
+  launch_prob_planes(bf16, a.logits, a.stats, a.T, a.V, Kpad, a.probs, st);
+  if (bf16) launch_smooth_t<bf16_t>(a, Kpad, st);
+  else launch_smooth_t<float>(a, Kpad, st);
+}
+template <typename E> static bool configure_smooth() {
+  return opt_in_lds((const void*)smooth_partial_kernel<E, 1, 23>) && opt_in_lds((const void*)smooth_partial_kernel<E, 2, 23>) &&
+         opt_in_lds((const void*)smooth_partial_kernel<E, 4, 24>);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1189,10 +1278,9 @@ void launch_lm_head(bool bf16, const LmArgs& a, hipStream_t st) { launch_lm_head
 bool configure_kernels() {
   bool ok = configure_ksplit<bf16_t, QkvEpi<bf16_t>>() && configure_ksplit<float, QkvEpi<float>>() &&
             configure_ksplit<bf16_t, ResidualEpi<bf16_t>>() && configure_ksplit<float, ResidualEpi<float>>() &&
-            configure_ksplit<bf16_t, SmoothEpi>() && configure_ksplit<float, SmoothEpi>();
+            configure_smooth<bf16_t>() && configure_smooth<float>();
   ok = ok && configure_dense<bf16_t, QkvEpi<bf16_t>>() && configure_dense<float, QkvEpi<float>>() &&
-       configure_dense<bf16_t, ResidualEpi<bf16_t>>() && configure_dense<float, ResidualEpi<float>>() &&
-       configure_dense<bf16_t, SmoothEpi>() && configure_dense<float, SmoothEpi>();
+       configure_dense<bf16_t, ResidualEpi<bf16_t>>() && configure_dense<float, ResidualEpi<float>>();
   ok = ok && opt_in_lds((const void*)expert_down_fused_kernel<bf16_t, 1, DOWN_KW, 8>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<bf16_t, 1, DOWN_KW, 4>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<float, 1, DOWN_KW, 8>) &&

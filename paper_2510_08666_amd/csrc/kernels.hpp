@@ -142,21 +142,19 @@ struct OprojArgs {
 void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st);
 
 // Iteration smoothing: delta[t] = softmax(logits[t]) . W_emb for the rows of positions that are still masked.
-//   probs: scratch for the probabilities as a k-major activation matrix [T][Kpad]; logits [T][V] float32;
+//   probs: scratch for the probabilities as a k-major activation matrix [T][Kpad]; logits [T][V] float32, overwritten
+//   with partial sums;
 //   stats [T][2] = (largest logit, sum exp(z - max)) of every row; w_emb_t: launch_pack_transposed's layout.
-constexpr int SMOOTH_SLICES = 16;     // workgroups that share the vocabulary range of one 64-column task
-int smooth_kpad(bool bf16, int V);    // the vocabulary rounded up so that every wave of every slice gets whole bursts
+int smooth_kpad(bool bf16, int V);    // the vocabulary rounded up so that every K slice is whole chunks
 struct SmoothArgs {
   const void* w_emb_t;
-  const float* logits;
+  float* logits;
   const float* stats;
   void* probs;
   const uint64_t* mask;
   int block_len;
   float* delta;             // [T][H] in/out
   int T, H, V;
-  float* part;
-  int32_t* tickets;
 };
 void launch_expected_embedding(bool bf16, const SmoothArgs& a, hipStream_t st);
 void launch_prob_planes(bool bf16, const float* logits, const float* stats, int T, int V, int Kpad, void* probs,

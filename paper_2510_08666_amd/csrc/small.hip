@@ -121,24 +121,46 @@ void launch_embed(bool bf16, const int32_t* tokens, const void* emb, int T, int 
 
 // ---------------------------------------------------------------- iteration smoothing: probabilities
 // p[t][v] = exp(z[t][v] - max_t) / sum_t as a k-major activation matrix [T][Kpad] (zero past the vocabulary):
-// the B operand of the expected-embedding contraction.
+// the B operand of the expected-embedding contraction.  Bound by its 2 x 4 * T * V bytes of traffic: neighbouring
+// threads take the quads of one token and k-step, then the next token, so that a wave stores one contiguous piece; it
+// reads 128 bytes (two k-steps) of every row.
 template <typename E>
 __global__ __launch_bounds__(256) void prob_planes_kernel(const float* __restrict__ logits, const float* __restrict__ stats,
                                                            int T, int V, int Kpad, E* __restrict__ probs,
                                                            const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
-  const int t = blockIdx.y;
-  const float m = stats[2 * t], inv = 1.f / stats[2 * t + 1];
-  for (int v0 = (blockIdx.x * 256 + threadIdx.x) * 4; v0 < Kpad; v0 += gridDim.x * 256 * 4) {
-    f32x4 p;
+  constexpr int KS = ET<E>::KS, Q = KS / 4, U = 32 / KS;   // U k-steps = 128 bytes of logits
+  const int64_t n = (int64_t)(Kpad / (KS * U)) * T * Q;
+  const bool aligned = V % 4 == 0;                          // rows of logits start on 16-byte boundaries
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int quad = (int)(i % Q), t = (int)(i / Q % T);
+    const int v0 = (int)(i / (Q * T)) * (KS * U) + quad * 4;
+    const float m = stats[2 * t], inv = 1.f / stats[2 * t + 1];
+    const float* row = logits + (int64_t)t * V;
+    f32x4 z[U];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = v0 + i < V ? __expf(logits[(int64_t)t * V + v0 + i] - m) * inv : 0.f;
-    store_actk4<E>(probs, T, t, v0, p);
+    for (int u = 0; u < U; ++u) {
+      const int v = v0 + u * KS;
+      if (aligned && v + 4 <= V) {
+        z[u] = *reinterpret_cast<const f32x4*>(row + v);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[u][e] = v + e < V ? row[v + e] : -INFINITY;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      f32x4 p;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[e] = __expf(z[u][e] - m) * inv;
+      store_actk4<E>(probs, T, t, v0 + u * KS, p);
+    }
   }
 }
 void launch_prob_planes(bool bf16, const float* logits, const float* stats, int T, int V, int Kpad, void* probs,
                         hipStream_t st) {
-  dim3 grid(64, T);
+  const int64_t threads = (int64_t)(Kpad / 32) * T * (bf16 ? 4 : 2);
+  const unsigned grid = (unsigned)(threads / 256 + 1 < 8192 ? threads / 256 + 1 : 8192);
   if (bf16) prob_planes_kernel<bf16_t><<<grid, 256, 0, st>>>(logits, stats, T, V, Kpad, (bf16_t*)probs, live_word());
   else prob_planes_kernel<float><<<grid, 256, 0, st>>>(logits, stats, T, V, Kpad, (float*)probs, live_word());
 }

@@ -12,10 +12,10 @@ namespace dinfer {
 constexpr int WKC = 4;     // k-steps per staged chunk
 // LDS fragments read ahead of the matrix instructions that use them (pinned by scheduling barriers, see the chunk
 // body), and the chunks of activation fragments a wave holds in registers on their way to LDS: two everywhere
-// except in the many-token expert GEMMs (trace ids 10, 11), whose 128 accumulator registers and two activation
+// except in the many-token expert GEMMs and smoothing contraction (trace ids 10, 11, 24), whose 128 accumulator registers and two activation
 // planes leave room for one only (with two, the pinned read-ahead spills and they run at half speed).
 constexpr int WIDE_FD = 4;
-template <int KID> constexpr int wide_bdepth() { return (KID == 10 || KID == 11) ? 1 : 2; }
+template <int KID> constexpr int wide_bdepth() { return (KID == 10 || KID == 11 || KID == 24) ? 1 : 2; }
 
 // Planes of the activations a kernel (by its trace id) feeds to the matrix cores.  The LM head with hundreds of
 // token rows is bound by the matrix cores, and its rounding error is not carried into later layers: it takes the
