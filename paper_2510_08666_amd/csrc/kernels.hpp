@@ -122,6 +122,7 @@ struct AttnArgs {
   void* out;                // [T][D] k-major
   int T;
   L2Prefetch pf;            // fetched by extra workgroups of the launch when it has few of its own (see L2Prefetch)
+  SeqSpan span;             // tokens of the sequences in this forward
 };
 size_t attn_part_floats(int n_qtiles, int n_heads, int n_splits, int head_dim);
 void launch_attention(bool bf16, const AttnArgs& a, hipStream_t st);
