@@ -138,7 +138,7 @@ int attn_splits(int n_qtiles, int n_heads, int key_bound) {
 
 struct Workspace {
   size_t cos_tab, sin_tab, tok_seq, tok_pos, seq_nkeys, qtile, x, xn, ssq, ssq_a, tk_part, tickets, tickets_bytes, attn_tickets, attn_tickets_bytes, rinv_f, q, a, attn_part, topk_idx, topk_w, cnt, off,
-      perm, pos_of_pair, work, run_tokens, run_base, n_finished, loop_flags, loop_steps, lm_rows, y, o, lm_part, lm_stats, conf, argmax, total;
+      perm, pos_of_pair, work, hist, run_tokens, run_base, n_finished, loop_flags, loop_steps, lm_rows, y, o, lm_part, lm_stats, conf, argmax, total;
 };
 
 Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
@@ -202,6 +202,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.loop_steps = cv.take(4);                     // inner loop: steps that ran
   w.lm_rows = cv.take((size_t)(1 + T) * 4);      // LM head: rows of the undecided positions
   w.work = cv.take((size_t)(1 + expert_work_items(MAX_EXPERTS, (int)(T * K), 2)) * 4);
+  w.hist = cv.take((T + TILE - 1) / TILE * MAX_EXPERTS * 4);   // pairs per expert of every 32 tokens
   w.y = cv.take(planes * T * K * I * es);
   w.o = cv.take(T * K * H * 4);
   w.lm_part = cv.take((size_t)lm_head_most_parts(c.vocab) * T * 4 * 4);
@@ -344,7 +345,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
     }
     RouterArgs ra{c->weights + lw.router, xn, at<float>(ws, w.ssq), f.rms_eps, T, H, f.n_experts, f.top_k,
                   f.norm_topk, rinv_f, topk_idx, topk_w, at<int32_t>(ws, w.cnt), at<int32_t>(ws, w.off),
-                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.pos_of_pair), at<int32_t>(ws, w.work), tk_part, tickets};
+                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.pos_of_pair), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), tk_part, tickets};
     {
       StageTimer tm(c, DINFER_STAGE_ROUTER, st);
       launch_router(bf, ra, st);
@@ -488,7 +489,7 @@ int dinfer_create(const dinfer_config* cfg, void* d_weights, size_t weights_byte
     delete c;
     return fail(DINFER_EHIP, "hipHostMalloc failed");
   }
-  if (!configure_kernels() || !configure_attention() || !configure_permute() || !configure_wide()) {
+  if (!configure_kernels() || !configure_attention() || !configure_wide()) {
     (void)hipHostFree(c->h_mask_pinned);
     delete c;
     return fail(DINFER_EHIP, "the runtime refused the kernels' LDS sizes");

@@ -98,6 +98,13 @@ template <> __device__ inline void store_elems4<bf16_t>(bf16_t* dst, const f32x4
   *reinterpret_cast<bf16x4*>(dst) = o;
 }
 
+template <typename E> __device__ inline f32x4 load_elems4(const E* src);   // src 8- or 16-byte aligned
+template <> __device__ inline f32x4 load_elems4<float>(const float* src) { return *reinterpret_cast<const f32x4*>(src); }
+template <> __device__ inline f32x4 load_elems4<bf16_t>(const bf16_t* src) {
+  const bf16x4 v = *reinterpret_cast<const bf16x4*>(src);
+  return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+
 // acc[32 x 32] += A[32 x KS] * B[KS x 32].  Lane l supplies row (A) / column (B) l%32 and the G consecutive
 // k values that start at (l/32)*G; result: lane l holds column l%32, rows 8*(v/4) + 4*(l/32) + v%4.
 __device__ inline void mfma32(f32x16& acc, const bf16x8& a, const bf16x8& b) {

@@ -1082,7 +1082,8 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
                                                             float* __restrict__ topk_w, int fuse_permute,
                                                             int32_t* __restrict__ cnt, int32_t* __restrict__ off,
                                                             int32_t* __restrict__ perm,
-                                                            int32_t* __restrict__ pos_of_pair, float* __restrict__ part,
+                                                            int32_t* __restrict__ pos_of_pair, int32_t* __restrict__ hist,
+                                                            float* __restrict__ part,
                                                             int32_t* __restrict__ tickets, const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   extern __shared__ float red[];   // [KW][2*TT*16][64] partials
@@ -1210,7 +1211,15 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
     }
   }
   TRACE_MARK(3, 4);
-  if (!fuse_permute) return;
+  if (!fuse_permute) {   // many tokens: the permutation kernel takes the group's pairs per expert
+    if (threadIdx.x < MAX_EXPERTS) s_cc[threadIdx.x] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < NTOK * top_k; i += NTHREADS)
+      if (s_idx[i] >= 0) atomicAdd(&s_cc[s_idx[i]], 1);
+    __syncthreads();
+    if (threadIdx.x < MAX_EXPERTS) hist[group * MAX_EXPERTS + threadIdx.x] = s_cc[threadIdx.x];
+    return;
+  }
   __syncthreads();
   ballot_permute_small(s_idx, T * top_k, n_exp, cnt, off, perm, pos_of_pair, s_ballot, s_cc);
   TRACE_MARK(3, 5);
@@ -1230,17 +1239,17 @@ template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a
   if (a.T <= 32) {
     router_kernel<E, 1, 8><<<dim3(slices, 1), 8 * WAVE, ksplit_lds<1, 8>(), st>>>(
         W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
-        a.topk_w, 1, a.cnt, a.off, a.perm, a.pos_of_pair, a.part, a.tickets, live_word());
+        a.topk_w, 1, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
   } else if (a.T <= 64) {
     router_kernel<E, 2, 8><<<dim3(slices, 1), 8 * WAVE, ksplit_lds<2, 8>(), st>>>(
         W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
-        a.topk_w, 1, a.cnt, a.off, a.perm, a.pos_of_pair, a.part, a.tickets, live_word());
+        a.topk_w, 1, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
   } else {
     const int groups = (a.T + TILE - 1) / TILE;   // 32 tokens per workgroup: one round of the top-k lanes, more workgroups
     router_kernel<E, 1, 8><<<dim3(1, groups), 8 * WAVE, ksplit_lds<1, 8>(), st>>>(
         W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
-        a.topk_w, 0, a.cnt, a.off, a.perm, a.pos_of_pair, a.part, a.tickets, live_word());
-    launch_permute(a.topk_idx, a.T * a.top_k, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work,
+        a.topk_w, 0, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
+    launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work,
                    expert_group_tiles(a.E, a.T * a.top_k), st);
   }
 }

@@ -177,18 +177,19 @@ struct RouterArgs {
   int32_t* perm;
   int32_t* pos_of_pair;
   int32_t* work;            // [1 + expert_work_items at two tiles per group]: work list of the many-token expert GEMMs (T > 64 only)
+  int32_t* hist;            // [ceil(T / 32)][MAX_EXPERTS]: pairs per expert of every 32 tokens (T > 64 only)
   float* part;
   int32_t* tickets;
 };
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st);
-void launch_permute(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm,
-                    int32_t* pos_of_pair, int32_t* work, int group_tiles, hipStream_t st);
+// hist: the router's histograms, see RouterArgs.
+void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
+                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, hipStream_t st);
 // Token tiles per work item (expert, group of rows) of the expert GEMMs above 64 tokens.
 int expert_group_tiles(int E, int n_pairs);
 // Work items that many groups can add up to for n_pairs routed pairs.
 inline int expert_work_items(int E, int n_pairs, int group_tiles) { return E + n_pairs / (group_tiles * TILE); }
 int permute_max_pairs();      // most (token, slot) pairs one forward may route
-bool configure_permute();
 
 struct ExpertArgs {
   const void* w_gate_up;    // packed [E][I/32 tasks]

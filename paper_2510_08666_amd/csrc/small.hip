@@ -46,17 +46,15 @@ __device__ inline void token_meta(const SeqSpan& span, const int32_t* __restrict
     }
     if (threadIdx.x == 0) seq_nkeys[s] = base + len;
   }
-  if (threadIdx.x == 0) {
-    int n = 0;
-    for (int s = 0; s < span.n_seq; ++s) {
-      const int o = span.off[s], len = span.off[s + 1] - o;
-      for (int i = 0; i < len; i += TILE) {
-        qtile[n * 3 + 0] = s;
-        qtile[n * 3 + 1] = o + i;
-        qtile[n * 3 + 2] = min(TILE, len - i);
-        ++n;
-      }
+  int n = 0;
+  for (int s = 0; s < span.n_seq; ++s) {
+    const int o = span.off[s], len = span.off[s + 1] - o, tiles = (len + TILE - 1) / TILE;
+    for (int i = threadIdx.x; i < tiles; i += blockDim.x) {
+      qtile[(n + i) * 3 + 0] = s;
+      qtile[(n + i) * 3 + 1] = o + i * TILE;
+      qtile[(n + i) * 3 + 2] = min(TILE, len - i * TILE);
     }
+    n += tiles;
   }
 }
 
@@ -76,6 +74,9 @@ __device__ inline float block_sum_256(float v, float* sh) {
 
 // x[t] = emb[token[t]];  ssq[t] = sum(x[t]^2);  xn[t] = planes of x[t] * gain.  Workgroup T, one past the tokens,
 // writes the token bookkeeping of the forward instead (nothing here reads it): one launch less per forward.
+// Bound by its traffic (a row read, the float32 row and its planes written): a thread takes four consecutive columns
+// at a time (hidden is a multiple of 64), since element by element the 2-byte plane stores fill the store path
+// (4287 rows of 2048: 39 us).
 template <typename E>
 __global__ __launch_bounds__(NORM_THREADS) void embed_kernel(const int32_t* __restrict__ tokens, const E* __restrict__ emb,
                                                              int H, int V, float* __restrict__ x,
@@ -96,12 +97,19 @@ __global__ __launch_bounds__(NORM_THREADS) void embed_kernel(const int32_t* __re
   // iteration smoothing: a still-masked position adds alpha times what the previous iteration retained for it
   const bool smooth = sm.delta && ((sm.mask[t / sm.block_len] >> (t % sm.block_len)) & 1ull);
   float ss = 0.f;
-  for (int c = threadIdx.x; c < H; c += NORM_THREADS) {
-    float v = to_f32(row[c]);
-    if (smooth) v += sm.alpha * sm.delta[(int64_t)t * H + c];
-    x[(int64_t)t * H + c] = v;
-    store_actk<E>(xn, T, t, c, v * gain[c]);
-    ss += v * v;
+#pragma unroll 2
+  for (int c = 4 * threadIdx.x; c < H; c += 4 * NORM_THREADS) {
+    f32x4 v = load_elems4<E>(row + c);
+    const f32x4 g = *reinterpret_cast<const f32x4*>(gain + c);
+    f32x4 n;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (smooth) v[i] += sm.alpha * sm.delta[(int64_t)t * H + c + i];
+      n[i] = v[i] * g[i];
+      ss += v[i] * v[i];
+    }
+    *reinterpret_cast<f32x4*>(x + (int64_t)t * H + c) = v;
+    store_actk4<E>(xn, T, t, c, n);
   }
   ss = block_sum_256(ss, sh);
   if (threadIdx.x == 0) ssq[t] = ss;
@@ -221,118 +229,114 @@ void launch_combine(bool bf16, float* x, const float* O, const float* topk_w, in
 }
 
 // ---------------------------------------------------------------- token -> expert permutation
-// Stand-alone form (many tokens); small forwards run the same idea inside the router kernel.  Stable counting
-// sort of the (token, slot) pairs by expert, one workgroup.  A wave takes 64 consecutive pairs (a chunk) at a time
-// and forms the chunk's ballots "which lanes go to expert e" for all experts at once by OR-ing lane bits into its
-// own 64 LDS words; the population of ballot e is the chunk's count for e, the bits below a lane in its expert's
-// ballot the pair's rank inside the chunk.  pre[chunk][e] then becomes the number of pairs of e in earlier chunks
-// (a 16-bit count: at most 65535 pairs), and position = off[e] + pre[chunk][e] + rank.
-__device__ inline uint64_t chunk_ballots(unsigned long long* mine, int lane, int e) {
-  mine[lane] = 0ull;
-  __builtin_amdgcn_wave_barrier();     // LDS operations of one wave complete in order
-  if (e >= 0) atomicOr(&mine[e], 1ull << lane);
-  __builtin_amdgcn_wave_barrier();
-  return mine[lane];                   // ballot of expert `lane`
-}
-__global__ __launch_bounds__(1024) void permute_kernel(const int32_t* __restrict__ expert_of_pair, int n_pairs,
-                                                        int n_exp, int32_t* __restrict__ cnt, int32_t* __restrict__ off,
+// Stand-alone form (many tokens); small forwards run the same idea inside the router kernel.  Stable counting sort of
+// the (token, slot) pairs by expert.  The router's workgroups have left the histogram of their 32 tokens,
+// hist[group][MAX_EXPERTS]; workgroup g of this launch adds up the groups before its own and all of them, which
+// gives the place of its first pair of every expert, and places its group's pairs: a wave takes 64 consecutive pairs
+// (a chunk) and forms the ballots "which lanes go to expert e" for all experts at once by OR-ing lane bits into its own
+// 64 LDS words; the population of ballot e is the chunk's count for e, the bits below a lane in its expert's ballot
+// the pair's rank inside the chunk.  Workgroup 0 also writes the tables.  A few dependent round trips, whatever the
+// number of pairs (a single workgroup over all pairs: 41 us for 34296 of them, 9 for 4096, 6 for 1280).
+constexpr int PERMUTE_WAVES = 4;
+static_assert(TILE * MAX_TOPK <= PERMUTE_WAVES * WAVE, "a group's pairs are at most one chunk per wave");
+__global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int32_t* __restrict__ expert_of_pair, int n_pairs, int pairs_per_group,
+                                                        const int32_t* __restrict__ hist, int n_exp,
+                                                        int32_t* __restrict__ cnt, int32_t* __restrict__ off,
                                                         int32_t* __restrict__ perm, int32_t* __restrict__ pos_of_pair,
                                                         int32_t* __restrict__ work, int group_tiles,
                                                         const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
-  extern __shared__ uint16_t s_pre[];                       // [n_chunks][MAX_EXPERTS]
-  __shared__ unsigned long long s_ballot[16 * MAX_EXPERTS];
-  __shared__ int32_t s_off[MAX_EXPERTS + 1];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
-  const int n_chunks = (n_pairs + WAVE - 1) / WAVE;
+  __shared__ unsigned long long s_ballot[PERMUTE_WAVES * MAX_EXPERTS];
+  __shared__ int32_t s_before[PERMUTE_WAVES * MAX_EXPERTS], s_total[PERMUTE_WAVES * MAX_EXPERTS], s_first[MAX_EXPERTS];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, group = blockIdx.x, n_groups = gridDim.x;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  unsigned long long* mine = s_ballot + wave * MAX_EXPERTS;
-  for (int c = wave; c < n_chunks; c += n_waves) {
-    const int p = c * WAVE + lane;
-    const int e = p < n_pairs ? expert_of_pair[p] : -1;
-    s_pre[c * MAX_EXPERTS + lane] = (uint16_t)__popcll(chunk_ballots(mine, lane, e));
-    __builtin_amdgcn_wave_barrier();
+  const int in_group = wave * WAVE + lane, p = group * pairs_per_group + in_group;
+  const int e = in_group < pairs_per_group && p < n_pairs ? expert_of_pair[p] : -1;
+  {
+    int before = 0, total = 0;                              // lane = expert
+#pragma unroll 8
+    for (int g = wave; g < n_groups; g += PERMUTE_WAVES) {
+      const int n = hist[g * MAX_EXPERTS + lane];
+      total += n;
+      before += g < group ? n : 0;
+    }
+    s_before[wave * MAX_EXPERTS + lane] = before;
+    s_total[wave * MAX_EXPERTS + lane] = total;
+    s_ballot[wave * MAX_EXPERTS + lane] = 0ull;
   }
   __syncthreads();
+  if (e >= 0) atomicOr(&s_ballot[wave * MAX_EXPERTS + e], 1ull << lane);
   if (wave == 0) {
-    int run = 0;                                            // lane = expert: exclusive scan over the chunks
-    for (int c = 0; c < n_chunks; ++c) {
-      const int n = s_pre[c * MAX_EXPERTS + lane];
-      s_pre[c * MAX_EXPERTS + lane] = (uint16_t)run;
-      run += n;
+    int tot = 0, mine = 0;
+#pragma unroll
+    for (int w = 0; w < PERMUTE_WAVES; ++w) {
+      tot += s_total[w * MAX_EXPERTS + lane];
+      mine += s_before[w * MAX_EXPERTS + lane];
     }
-    const int tot = lane < n_exp ? run : 0;
+    if (lane >= n_exp) tot = 0;
     int incl = tot;                                         // inclusive scan over the lanes (experts)
 #pragma unroll
     for (int o = 1; o < WAVE; o <<= 1) {
       const int up = __shfl_up(incl, o, WAVE);
       if (lane >= o) incl += up;
     }
-    s_off[lane] = incl - tot;
-    if (lane < n_exp) {
-      cnt[lane] = tot;
-      off[lane] = incl - tot;
-      if (lane == n_exp - 1) off[n_exp] = incl;
-    }
-    const uint64_t has_rows = __ballot(tot > 0);            // dense list of the experts that received rows
-    if (tot > 0) {
-      const int at = __popcll(has_rows & below);
-      off[ACTIVE_LIST + at] = lane;
-      *reinterpret_cast<int4*>(off + ACTIVE_RECORDS + 4 * at) = make_int4(lane, incl - tot, tot, 0);
-    }
-    if (lane == 0) {
-      off[ACTIVE_LIST + MAX_EXPERTS] = __popcll(has_rows);
-      off[STAT_ACTIVE_SUM] += __popcll(has_rows);
-      off[STAT_PERMUTATIONS] += 1;
-    }
-    // Work list of the many-token expert GEMMs: one item per (expert, group of up to group_tiles 32-row tiles), the
-    // groups with the most tiles first, so that the long workgroups start first and the short ones fill the tail.
-    // work[0] = number of items, work[1 + i] = expert << 16 | group.
-    const int rows_per = group_tiles * TILE, full = tot / rows_per, rem_tiles = (tot % rows_per + TILE - 1) / TILE;
-    int at = 0;
-    for (int k = group_tiles; k >= 1; --k) {
-      const int mine_k = (k == group_tiles ? full : 0) + (rem_tiles == k ? 1 : 0);   // the remainder group has index `full`
-      int incl_k = mine_k;
+    s_first[lane] = incl - tot + mine;
+    if (group == 0) {
+      if (lane < n_exp) {
+        cnt[lane] = tot;
+        off[lane] = incl - tot;
+        if (lane == n_exp - 1) off[n_exp] = incl;
+      }
+      const uint64_t has_rows = __ballot(tot > 0);          // dense list of the experts that received rows
+      if (tot > 0) {
+        const int at = __popcll(has_rows & below);
+        off[ACTIVE_LIST + at] = lane;
+        *reinterpret_cast<int4*>(off + ACTIVE_RECORDS + 4 * at) = make_int4(lane, incl - tot, tot, 0);
+      }
+      if (lane == 0) {
+        off[ACTIVE_LIST + MAX_EXPERTS] = __popcll(has_rows);
+        off[STAT_ACTIVE_SUM] += __popcll(has_rows);
+        off[STAT_PERMUTATIONS] += 1;
+      }
+      // Work list of the many-token expert GEMMs: one item per (expert, group of up to group_tiles 32-row tiles), the
+      // groups with the most tiles first, so that the long workgroups start first and the short ones fill the tail.
+      // work[0] = number of items, work[1 + i] = expert << 16 | group.
+      const int rows_per = group_tiles * TILE, full = tot / rows_per, rem_tiles = (tot % rows_per + TILE - 1) / TILE;
+      int at = 0;
+      for (int k = group_tiles; k >= 1; --k) {
+        const int mine_k = (k == group_tiles ? full : 0) + (rem_tiles == k ? 1 : 0);   // the remainder group has index `full`
+        int incl_k = mine_k;
 #pragma unroll
-      for (int o = 1; o < WAVE; o <<= 1) {
-        const int up = __shfl_up(incl_k, o, WAVE);
-        if (lane >= o) incl_k += up;
+        for (int o = 1; o < WAVE; o <<= 1) {
+          const int up = __shfl_up(incl_k, o, WAVE);
+          if (lane >= o) incl_k += up;
+        }
+        const int first = at + incl_k - mine_k;
+        if (k == group_tiles) {
+          for (int g = 0; g < mine_k; ++g) work[1 + first + g] = (lane << 16) | g;
+        } else if (mine_k) {
+          work[1 + first] = (lane << 16) | full;
+        }
+        at += __shfl(incl_k, WAVE - 1, WAVE);
       }
-      const int first = at + incl_k - mine_k;
-      if (k == group_tiles) {
-        for (int g = 0; g < mine_k; ++g) work[1 + first + g] = (lane << 16) | g;
-      } else if (mine_k) {
-        work[1 + first] = (lane << 16) | full;
-      }
-      at += __shfl(incl_k, WAVE - 1, WAVE);
+      if (lane == 0) work[0] = at;
     }
-    if (lane == 0) work[0] = at;
   }
   __syncthreads();
-  for (int c = wave; c < n_chunks; c += n_waves) {
-    const int p = c * WAVE + lane;
-    const int e = p < n_pairs ? expert_of_pair[p] : -1;
-    chunk_ballots(mine, lane, e);
-    __builtin_amdgcn_wave_barrier();
-    if (e >= 0) {
-      const int r = s_off[e] + s_pre[c * MAX_EXPERTS + e] + __popcll(mine[e] & below);
-      perm[r] = p;
-      pos_of_pair[p] = r;
-    }
-    __builtin_amdgcn_wave_barrier();
+  if (e >= 0) {
+    int r = s_first[e] + __popcll(s_ballot[wave * MAX_EXPERTS + e] & below);
+    for (int w = 0; w < wave; ++w) r += __popcll(s_ballot[w * MAX_EXPERTS + e]);
+    perm[r] = p;
+    pos_of_pair[p] = r;
   }
-}
-bool configure_permute() {
-  return hipFuncSetAttribute((const void*)permute_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024) ==
-         hipSuccess;
 }
 constexpr int PERMUTE_MAX_PAIRS = 65535;
 int permute_max_pairs() { return PERMUTE_MAX_PAIRS; }
-void launch_permute(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm,
-                    int32_t* pos_of_pair, int32_t* work, int group_tiles, hipStream_t st) {
-  const int n_chunks = (n_pairs + WAVE - 1) / WAVE;
-  permute_kernel<<<1, 1024, (size_t)n_chunks * MAX_EXPERTS * sizeof(uint16_t), st>>>(topk_idx, n_pairs, E, cnt, off, perm,
-                                                                                     pos_of_pair, work, group_tiles, live_word());
+void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
+                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, hipStream_t st) {
+  const int per_group = TILE * top_k;
+  permute_kernel<<<(n_pairs + per_group - 1) / per_group, PERMUTE_WAVES * WAVE, 0, st>>>(
+      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, pos_of_pair, work, group_tiles, live_word());
 }
 
 // ---------------------------------------------------------------- LM-head partial merge

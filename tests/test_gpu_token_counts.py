@@ -1,8 +1,10 @@
 """Steps at the token counts where the expert GEMMs and the LM head change their form: the first count above the
 64-token forms, both sides of the line between two and four row tiles per work item, token groups of unequal size."""
+import numpy as np
 import pytest
 
 import dinfer_inputs as di
+import oracle
 from harness import GpuRun, OracleRun, bars_for, compare_logits, compare_step, make_case
 from test_gpu_tiny import _skew_router
 
@@ -32,6 +34,11 @@ def test_step_at_token_count(n_seq, block, skew, dtype):
     got = gpu.step(wl.threshold)
     logits = gpu.logits(n_seq * block).reshape(n_seq, block, cfg.vocab)
     routing = gpu.routing().reshape(cfg.n_layers, n_seq, block, cfg.top_k)
+    # the token -> expert permutation of the last layer is a stable counting sort of its routing
+    n_pairs = n_seq * block * cfg.top_k
+    tables = [gpu.ctx.debug_get(w, (n,), gpu.torch.int32).cpu().numpy() for w, n in ((3, 64), (4, 65), (5, n_pairs))]
+    for got_table, want in zip(tables, oracle.permutation(routing[-1].reshape(-1), cfg.n_experts)):
+        assert np.array_equal(got_table, want)
     for s in range(n_seq):
         ref, _ = ora.step_following(s, inp.block_tokens[s], int(inp.mask_bits[s]), int(inp.prefix_len[s]), wl.threshold, 0,
                                     routing[:, s], bars)
