@@ -236,7 +236,7 @@ void launch_expert_down_wide(bool bf16, const ExpertArgs& a, hipStream_t st) {
 // ------------------------------------------------------------------------------------------------
 // LM head fused with the confidence reduction, many-token form.  A workgroup takes one task group (8 tasks = 512
 // vocabulary ids) and one group of 128 tokens; a wave turns its accumulators (64 vocabulary ids x 128 tokens) into
-// one (max, sum-exp, lowest arg max) partial per token, the workgroup folds them: part[token][task group].  Logits are never
+// one (max, sum-exp, lowest arg max) partial per token: part[token][task group, wave].  Logits are never
 // stored (unless the debug pointer is set).
 // The token groups of one task group stream the same weights.  Workgroups go to the dies in turn, so the launch is
 // one-dimensional and workgroup i = die (i % 8), turn (i / 8): consecutive turns of ONE die take the token groups
@@ -266,8 +266,13 @@ __global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __rest
   const int turn = blockIdx.x / XCDS;
   const int tgroup = (turn / groups) * XCDS + blockIdx.x % XCDS;
   const int n_tasks = (V + 2 * TILE - 1) / (2 * TILE);
-  const int n_parts = (n_tasks + WW - 1) / WW;
-  if (tgroup >= n_parts) return;        // uniform over the workgroup
+  const int n_groups = (n_tasks + WW - 1) / WW;
+  if (tgroup >= n_groups) return;       // uniform over the workgroup
+  // Partials of a row lie next to each other for the merge kernel (a stride of 8 KB apart it took 27 us for 512 tokens).
+  // Up to 64 tokens a workgroup leaves one per row, more tokens: its waves one each (folding them there costs the
+  // launch 8 us at 512 tokens, more than the merge saves).
+  constexpr bool FOLD = KID != 9;
+  const int n_parts = FOLD ? n_groups : n_groups * WW;
   LmStat* s_stat = reinterpret_cast<LmStat*>(lds_raw);   // [WW][WT * TILE], once the fragments are done with
   static_assert(WW * WT * TILE * sizeof(LmStat) <= wide_lds<E, KID, WT>(), "the statistics fit the staging area");
   const int tok0 = (turn % groups) * per_group * TILE;
@@ -323,33 +328,41 @@ __global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __rest
         for (int i = 0; i < 32; ++i) sum += __expf(z[i] - m);
       }
     }
-    // fold the two half-waves (same token, other rows), then the workgroup's waves (other ids) through LDS: one partial
-    // per workgroup and token instead of one per wave, and a row's partials next to each other, are what the merge
-    // kernel reads (512 tokens: 27 us over 2456 partials a stride of 8 KB apart; see lm_merge_kernel)
+    // fold the two half-waves (same token, other rows); up to 64 tokens also the workgroup's waves (other ids), through LDS
     const LmStat w = lm_combine(LmStat{m, sum, best}, LmStat{__shfl_xor(m, 32, WAVE), __shfl_xor(sum, 32, WAVE), __shfl_xor(best, 32, WAVE)});
-    if (t == 0) __syncthreads();   // the staged fragments have been read by every wave
-    if (half == 0) s_stat[wave * WT * TILE + t * TILE + col] = w;
+    if constexpr (FOLD) {
+      if (t == 0) __syncthreads();   // the staged fragments have been read by every wave
+      if (half == 0) s_stat[wave * WT * TILE + t * TILE + col] = w;
+    } else if (half == 0 && t < nt && tok < T) {
+      *reinterpret_cast<f32x4*>(part + ((int64_t)tok * n_parts + slot) * 4) = f32x4{w.m, w.s, __int_as_float(w.id), 0.f};
+    }
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nt * TILE; i += WW * WAVE) {
-    LmStat a = s_stat[i];
+  if constexpr (FOLD) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < nt * TILE; i += WW * WAVE) {
+      LmStat a = s_stat[i];
 #pragma unroll
-    for (int w = 1; w < WW; ++w) a = lm_combine(a, s_stat[w * WT * TILE + i]);
-    if (tok0 + i < n_rows)
-      *reinterpret_cast<f32x4*>(part + ((int64_t)row_of(tok0 + i) * n_parts + tgroup) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
+      for (int w = 1; w < WW; ++w) a = lm_combine(a, s_stat[w * WT * TILE + i]);
+      if (tok0 + i < n_rows)
+        *reinterpret_cast<f32x4*>(part + ((int64_t)row_of(tok0 + i) * n_parts + tgroup) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
+    }
   }
 }
 
-// Tasks (waves) per workgroup by token count, and the partials a row receives: one per workgroup.
-static int lm_tasks_per_wg(int T) { return T <= TILE ? LM_SMALL_WW : T <= 2 * TILE ? LM_MID_WW : LM_WW; }
-int lm_head_parts(int V, int T) { return ((V + 63) / 64 + lm_tasks_per_wg(T) - 1) / lm_tasks_per_wg(T); }
-int lm_head_most_parts(int V) { return lm_head_parts(V, 1); }
+// Workgroups that share the vocabulary (tasks over waves per workgroup, by token count), and the partials a row
+// receives: one per workgroup up to 64 tokens, one per wave above.
+static int lm_task_groups(int V, int T) {
+  const int ww = T <= TILE ? LM_SMALL_WW : T <= 2 * TILE ? LM_MID_WW : LM_WW;
+  return ((V + 63) / 64 + ww - 1) / ww;
+}
+int lm_head_parts(int V, int T) { return lm_task_groups(V, T) * (T <= 2 * TILE ? 1 : LM_WW); }
+int lm_head_most_parts(int V) { return lm_head_parts(V, 2 * TILE + 1); }   // one per task, rounded up: the most
 
 // Up to 64 tokens: two token tiles per workgroup and both activation planes (trace id 14): there the weight stream
 // is the bound, and sharing the activation fragments of eight tasks relieves the address unit, which would
 // otherwise take every lane's own activation row one by one.  More tokens: four tiles, high plane only (id 9).
 template <typename E> static void launch_lm_wide_t(const LmArgs& a, hipStream_t st) {
-  const int tgroups = lm_head_parts(a.V, a.T);
+  const int tgroups = lm_task_groups(a.V, a.T);
   if (a.T <= TILE) {   // one token tile (trace id 15)
     lm_head_wide_kernel<E, 1, 15, LM_SMALL_WW><<<(tgroups + XCDS - 1) / XCDS * XCDS, LM_SMALL_WW * WAVE, wide_lds<E, 15, 1>(), st>>>(
         (const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows, live_word());
