@@ -201,7 +201,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.loop_flags = cv.take((size_t)(MAX_LOOP_STEPS + 1) * 4);   // inner loop: "step i is still needed" words
   w.loop_steps = cv.take(4);                     // inner loop: steps that ran
   w.lm_rows = cv.take((size_t)(1 + T) * 4);      // LM head: rows of the undecided positions
-  w.work = cv.take((size_t)(1 + expert_work_items(MAX_EXPERTS, (int)(T * K), 2)) * 4);
+  w.work = cv.take((size_t)(WORK_ITEMS + 4 * expert_work_items(MAX_EXPERTS, (int)(T * K), 2)) * 4);
   w.hist = cv.take((T + TILE - 1) / TILE * MAX_EXPERTS * 4);   // pairs per expert of every 32 tokens
   w.y = cv.take(planes * T * K * I * es);
   w.o = cv.take(T * K * H * 4);
@@ -344,7 +344,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
       launch_oproj(bf, oa, st);
     }
     RouterArgs ra{c->weights + lw.router, xn, at<float>(ws, w.ssq), f.rms_eps, T, H, f.n_experts, f.top_k,
-                  f.norm_topk, rinv_f, topk_idx, topk_w, at<int32_t>(ws, w.cnt), at<int32_t>(ws, w.off),
+                  f.norm_topk, f.moe_inter, rinv_f, topk_idx, topk_w, at<int32_t>(ws, w.cnt), at<int32_t>(ws, w.off),
                   at<int32_t>(ws, w.perm), at<int32_t>(ws, w.pos_of_pair), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), tk_part, tickets};
     {
       StageTimer tm(c, DINFER_STAGE_ROUTER, st);

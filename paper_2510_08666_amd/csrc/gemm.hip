@@ -223,41 +223,6 @@ template <typename E> struct ResidualEpi {
   __device__ void row_sum(int task, int tok, float s) const { ssq[(int64_t)task * T + tok] = s; }
 };
 
-// Every wave leaves its partial accumulators in LDS: red[wave][t*32 + tile*16 + v][lane].
-template <int TT, int ROWS>
-__device__ inline void spill_partials(float* red, int wave, int lane, const f32x16 (&acc0)[TT], const f32x16 (&acc1)[TT]) {
-  float* r = red + (int64_t)wave * ROWS * WAVE + lane;
-#pragma unroll
-  for (int t = 0; t < TT; ++t)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      r[(t * 32 + v) * WAVE] = acc0[t][v];
-      r[(t * 32 + 16 + v) * WAVE] = acc1[t][v];
-    }
-}
-
-// Sum over the KW waves' partials in LDS: wave w takes accumulator registers w*PER .. w*PER+PER-1 of both tiles.
-template <int TT, int KW, int PER>
-__device__ inline void fold_partials(const float* red, int lane, int v0, float (&a0)[TT][PER], float (&a1)[TT][PER]) {
-  constexpr int ROWS = 2 * TT * 16;
-#pragma unroll
-  for (int t = 0; t < TT; ++t) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      a0[t][i] = 0.f;
-      a1[t][i] = 0.f;
-    }
-    for (int w = 0; w < KW; ++w) {
-      const float* r = red + ((int64_t)w * ROWS + t * 32 + v0) * WAVE + lane;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        a0[t][i] += r[i * WAVE];
-        a1[t][i] += r[(16 + i) * WAVE];
-      }
-    }
-  }
-}
-
 // The workgroup's sums leave for / come back from the cross-workgroup buffer.  A thread holds PER consecutive
 // accumulator registers (v0 .. v0+PER-1) of each tile; they travel as one PER-float piece:
 //   part[unit][slice][token tile][weight tile][v0 / PER][lane][PER]
@@ -1250,7 +1215,7 @@ template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a
         W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
         a.topk_w, 0, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
     launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work,
-                   expert_group_tiles(a.E, a.T * a.top_k), st);
+                   expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
   }
 }
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {

@@ -133,6 +133,41 @@ template <int TT> __device__ inline void zero_acc(f32x16 (&a)[TT]) {
     for (int v = 0; v < 16; ++v) a[t][v] = 0.f;
 }
 
+// Every wave leaves its partial accumulators in LDS: red[wave][t*32 + tile*16 + v][lane].
+template <int TT, int ROWS>
+__device__ inline void spill_partials(float* red, int wave, int lane, const f32x16 (&acc0)[TT], const f32x16 (&acc1)[TT]) {
+  float* r = red + (int64_t)wave * ROWS * WAVE + lane;
+#pragma unroll
+  for (int t = 0; t < TT; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      r[(t * 32 + v) * WAVE] = acc0[t][v];
+      r[(t * 32 + 16 + v) * WAVE] = acc1[t][v];
+    }
+}
+
+// Sum over the KW waves' partials in LDS: wave w takes accumulator registers w*PER .. w*PER+PER-1 of both tiles.
+template <int TT, int KW, int PER>
+__device__ inline void fold_partials(const float* red, int lane, int v0, float (&a0)[TT][PER], float (&a1)[TT][PER]) {
+  constexpr int ROWS = 2 * TT * 16;
+#pragma unroll
+  for (int t = 0; t < TT; ++t) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      a0[t][i] = 0.f;
+      a1[t][i] = 0.f;
+    }
+    for (int w = 0; w < KW; ++w) {
+      const float* r = red + ((int64_t)w * ROWS + t * 32 + v0) * WAVE + lane;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        a0[t][i] += r[i * WAVE];
+        a1[t][i] += r[(16 + i) * WAVE];
+      }
+    }
+  }
+}
+
 // The offset array is followed by the list of experts that received at least one row: off[ACTIVE_LIST + i] is
 // the i-th such expert (ascending), off[ACTIVE_LIST + MAX_EXPERTS] their number.  The grouped GEMMs index their
 // grid through it, so that workgroups of experts without rows sit at the end of the grid instead of leaving

@@ -169,6 +169,7 @@ struct RouterArgs {
   const float* ssq;         // [H/64][T]
   float eps;
   int T, H, E, top_k, norm_topk;
+  int I;                    // expert width (plan of the expert GEMMs)
   float* rinv;              // [T] out: 1/rms of the residual rows
   int32_t* topk_idx;        // [T][top_k] out
   float* topk_w;            // [T][top_k] out
@@ -176,17 +177,23 @@ struct RouterArgs {
   int32_t* off;
   int32_t* perm;
   int32_t* pos_of_pair;
-  int32_t* work;            // [1 + expert_work_items at two tiles per group]: work list of the many-token expert GEMMs (T > 64 only)
+  int32_t* work;            // [WORK_ITEMS + 4 * expert_work_items at two tiles per group]: work list of the many-token
+                            // expert GEMMs (T > 64 only), 16-byte aligned
   int32_t* hist;            // [ceil(T / 32)][MAX_EXPERTS]: pairs per expert of every 32 tokens (T > 64 only)
   float* part;
   int32_t* tickets;
 };
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st);
-// hist: the router's histograms, see RouterArgs.
+// hist: the router's histograms, see RouterArgs; round: expert_round_items.
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
-                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, hipStream_t st);
-// Token tiles per work item (expert, group of rows) of the expert GEMMs above 64 tokens.
+                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, hipStream_t st);
+// Work list of the expert GEMMs above 64 tokens: number of items [WORK_BIG] taken by whole workgroups, of all items
+// [WORK_ALL] (the rest in pieces of one task), then 16-byte items {expert, first sorted row, rows, 0}.
+constexpr int WORK_BIG = 0, WORK_ALL = 1, WORK_ITEMS = 4;
+// Token tiles per work item of the expert GEMMs above 64 tokens.
 int expert_group_tiles(int E, int n_pairs);
+// Items whose workgroups fill the chip once, for launch_permute (a huge number: no item is handed out in pieces; never more than half of them are).
+int expert_round_items(int E, int n_pairs, int H, int I);
 // Work items that many groups can add up to for n_pairs routed pairs.
 inline int expert_work_items(int E, int n_pairs, int group_tiles) { return E + n_pairs / (group_tiles * TILE); }
 int permute_max_pairs();      // most (token, slot) pairs one forward may route

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
                                                         const int32_t* __restrict__ hist, int n_exp,
                                                         int32_t* __restrict__ cnt, int32_t* __restrict__ off,
                                                         int32_t* __restrict__ perm, int32_t* __restrict__ pos_of_pair,
-                                                        int32_t* __restrict__ work, int group_tiles,
+                                                        int32_t* __restrict__ work, int group_tiles, int round,
                                                         const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   __shared__ unsigned long long s_ballot[PERMUTE_WAVES * MAX_EXPERTS];
@@ -299,12 +299,13 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
         off[STAT_PERMUTATIONS] += 1;
       }
       // Work list of the many-token expert GEMMs: one item per (expert, group of up to group_tiles 32-row tiles), the
-      // groups with the most tiles first, so that the long workgroups start first and the short ones fill the tail.
-      // work[0] = number of items, work[1 + i] = expert << 16 | group.
-      const int rows_per = group_tiles * TILE, full = tot / rows_per, rem_tiles = (tot % rows_per + TILE - 1) / TILE;
-      int at = 0;
+      // groups with the most tiles first, so that the long ones start first.
+      const int rows_per = group_tiles * TILE, full = tot / rows_per, rem = tot % rows_per, rem_tiles = (rem + TILE - 1) / TILE;
+      int4* items = reinterpret_cast<int4*>(work + WORK_ITEMS);
+      const int start = incl - tot;
+      int at = 0, light = 0;                                // items so far; of them those with one or two tiles
       for (int k = group_tiles; k >= 1; --k) {
-        const int mine_k = (k == group_tiles ? full : 0) + (rem_tiles == k ? 1 : 0);   // the remainder group has index `full`
+        const int mine_k = (k == group_tiles ? full : 0) + (rem_tiles == k ? 1 : 0);
         int incl_k = mine_k;
 #pragma unroll
         for (int o = 1; o < WAVE; o <<= 1) {
@@ -313,13 +314,22 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
         }
         const int first = at + incl_k - mine_k;
         if (k == group_tiles) {
-          for (int g = 0; g < mine_k; ++g) work[1 + first + g] = (lane << 16) | g;
+          for (int g = 0; g < full; ++g) items[first + g] = make_int4(lane, start + g * rows_per, rows_per, 0);
+          if (rem_tiles == k) items[first + full] = make_int4(lane, start + full * rows_per, rem, 0);
         } else if (mine_k) {
-          work[1 + first] = (lane << 16) | full;
+          items[first] = make_int4(lane, start + full * rows_per, rem, 0);
         }
-        at += __shfl(incl_k, WAVE - 1, WAVE);
+        const int n_k = __shfl(incl_k, WAVE - 1, WAVE);
+        at += n_k;
+        if (k <= 2) light += n_k;
       }
-      if (lane == 0) work[0] = at;
+      if (lane == 0) {
+        // Items that would begin another, mostly empty round of the chip (which takes `round` items at a time) are
+        // handed out in small pieces instead, provided that they are light and few.
+        const int over = at > round ? at % round : 0;
+        work[WORK_BIG] = over <= light && over <= round / 2 ? at - over : at;
+        work[WORK_ALL] = at;
+      }
     }
   }
   __syncthreads();
@@ -333,10 +343,10 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
 constexpr int PERMUTE_MAX_PAIRS = 65535;
 int permute_max_pairs() { return PERMUTE_MAX_PAIRS; }
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
-                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, hipStream_t st) {
+                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, hipStream_t st) {
   const int per_group = TILE * top_k;
   permute_kernel<<<(n_pairs + per_group - 1) / per_group, PERMUTE_WAVES * WAVE, 0, st>>>(
-      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, pos_of_pair, work, group_tiles, live_word());
+      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, pos_of_pair, work, group_tiles, round, live_word());
 }
 
 // ---------------------------------------------------------------- LM-head partial merge

@@ -16,6 +16,8 @@ constexpr int WT = 4;      // token tiles per workgroup above 64 tokens
 // (Measured at 512 tokens: four waves with two, four or six weight chunks in flight are slower for the expert
 // GEMMs, 131 to 134 against 120 microseconds; four waves in the LM head, 450 against 352.)
 constexpr int EXPERT_WW = 8, EXPERT_PRE = 2;
+constexpr int EXPERT_CUS = 256;                // compute units: a workgroup of the many-row expert GEMMs fills one
+constexpr int EXPERT_MANY_LDS = 128 * 1024;    // its LDS: staged fragments, or two tiles of eight waves' partial sums
 constexpr int LM_WW = 8, LM_PRE = 2;
 // Tasks per workgroup of the LM head up to 32 tokens.  All workgroups of these launches are resident at once and
 // the dispatcher deals them evenly, so a launch lasts as long as the compute units with one workgroup more than the
@@ -24,125 +26,107 @@ constexpr int LM_WW = 8, LM_PRE = 2;
 constexpr int LM_SMALL_WW = 2, LM_MID_WW = 4;   // up to 32, up to 64 tokens
 constexpr int XCDS = 8;      // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
 
-__device__ inline float silu_w(float x) { return x / (1.f + __expf(-x)); }
-
 // ------------------------------------------------------------------------------------------------
-// Routed experts, rows of expert e = pairs perm[off[e] .. off[e]+cnt[e]).  Grid (tasks / 8, work items): a work item
-// is an (expert, group of up to 64 or 128 rows) pair; the permutation kernel lists them heaviest first.
+// Routed experts.  An item is a run of an expert's sorted rows, {expert, first sorted row, rows, 0}: up to 64 tokens all
+// rows of an expert (the records the router's fused permutation leaves), beyond groups of up to 64 or 128 rows, heaviest
+// first (the work list of the permutation kernel).  Pair of sorted row r: perm[r].
 //   GEMM 1: task = 32 gate features + the same 32 up features;  y = silu(gate) * up  -> Y[sorted row][I]
 //   GEMM 2: task = 64 adjacent output features of the down projection                -> O[token*top_k + slot][H]
 // ------------------------------------------------------------------------------------------------
-// What a workgroup of the expert GEMMs works on.  RECORDS: the y-th expert with rows, from the records the router's
-// fused permutation leaves (at most 64 tokens, one row group per expert); otherwise the y-th item of the work list.
-struct ExpertItem {
-  int e, base, n_rows, row0;
-};
-template <int WT, bool RECORDS>
-__device__ inline bool expert_item(const int32_t* __restrict__ cnt, const int32_t* __restrict__ off,
-                                   const int32_t* __restrict__ work, ExpertItem& it) {
-  if constexpr (RECORDS) {
-    if ((int)blockIdx.y >= off[ACTIVE_LIST + MAX_EXPERTS]) return false;   // uniform over the block
-    const int4 rec = *reinterpret_cast<const int4*>(off + ACTIVE_RECORDS + 4 * blockIdx.y);
-    it = ExpertItem{rec.x, rec.y, rec.z, 0};
-  } else {
-    if ((int)blockIdx.y >= work[0]) return false;
-    const int item = work[1 + blockIdx.y], e = item >> 16;
-    it = ExpertItem{e, off[e], cnt[e], (item & 0xffff) * WT * TILE};
+template <typename E> struct GateUp {
+  const E* W;
+  const E* xn;
+  const float* rinv;
+  E* Y;
+  const int32_t* perm;
+  int T, H, I, top_k;
+  const float* topk_w;   // the routing weight, when the down projection sums the experts itself; else null
+  __device__ int ksteps() const { return H / ET<E>::KS; }
+  __device__ int n_tasks() const { return I / TILE; }
+  __device__ const E* act() const { return xn; }
+  __device__ int64_t act_rows() const { return T; }
+  __device__ int act_row(int r) const { return perm[r] / top_k; }
+  // what the lane needs to know about sorted row r
+  struct Row {
+    int act;         // its row among the activations
+    float r, wgt;
+  };
+  __device__ Row row(int r) const {
+    const int pair = perm[r], tok = pair / top_k;
+    return Row{tok, rinv[tok], topk_w ? topk_w[pair] : 1.f};
   }
-  return true;
-}
+  __device__ static float silu(float x) { return x / (1.f + __expf(-x)); }
+  // accumulator registers 4g .. 4g+3 of both tiles of `task`: four consecutive features of sorted row r
+  __device__ void store(const Row& w, int r, int task, int g, int half, const f32x4& a, const f32x4& b) const {
+    f32x4 y;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = silu(a[i] * w.r) * (b[i] * w.r) * w.wgt;
+    store_actk4<E>(Y, (int64_t)T * top_k, r, task * TILE + acc_row(4 * g, half), y);
+  }
+};
+template <typename E> struct Down {
+  const E* W;
+  const E* Y;
+  float* O;
+  const int32_t* perm;
+  int n_pairs, H, I;
+  __device__ int ksteps() const { return I / ET<E>::KS; }
+  __device__ int n_tasks() const { return H / (2 * TILE); }
+  __device__ const E* act() const { return Y; }
+  __device__ int64_t act_rows() const { return n_pairs; }
+  __device__ int act_row(int r) const { return r; }
+  struct Row {
+    int act, pair;
+  };
+  __device__ Row row(int r) const { return Row{r, perm[r]}; }
+  __device__ void store(const Row& w, int, int task, int g, int half, const f32x4& a, const f32x4& b) const {
+    float* o = O + (int64_t)w.pair * H + (2 * task) * TILE + acc_row(4 * g, half);
+    *reinterpret_cast<f32x4*>(o) = a;
+    *reinterpret_cast<f32x4*>(o + TILE) = b;
+  }
+};
 
-template <typename E, int WT, int WW, int KID, bool RECORDS>
-__global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_gemm1_wide_kernel(const E* __restrict__ W, const E* __restrict__ xn,
-                                                                      const float* __restrict__ rinv, E* __restrict__ Y,
-                                                                      const int32_t* __restrict__ cnt,
-                                                                      const int32_t* __restrict__ off,
-                                                                      const int32_t* __restrict__ perm,
-                                                                      const int32_t* __restrict__ work, int T, int H, int I,
-                                                                      int top_k, const float* __restrict__ topk_w, const int32_t* __restrict__ live) {
-  if (step_is_dead(live)) return;
+// One item and WW tasks (task group tg) by a workgroup: every wave streams its task's whole K range.
+template <typename E, int WT, int WW, int KID, class Op>
+__device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* lds) {
   typedef typename ET<E>::vec vec;
-  extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
-  vec* sb = reinterpret_cast<vec*>(lds_raw);
   constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N;
-  ExpertItem it;
-  if (!expert_item<WT, RECORDS>(cnt, off, work, it)) return;
-  const int e = it.e, base = it.base, n_rows = it.n_rows, row0 = it.row0;
-  const int nt = min(WT, (n_rows - row0 + TILE - 1) / TILE);
+  const int e = it.x, base = it.y, n_rows = it.z;
+  const int nt = min(WT, (n_rows + TILE - 1) / TILE);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-  const int n_tasks = I / TILE, task = min((int)blockIdx.x * WW + wave, n_tasks - 1);
-  const int ksteps = H / KS;
-  float r[WT], wgt[WT];
-  // the token rows hang on the permutation: that chain is resolved while the first weights are in flight
+  const int n_tasks = op.n_tasks(), task = min(tg * WW + wave, n_tasks - 1), ksteps = op.ksteps();
+  // The rows hang on the permutation: that chain is resolved while the first weights are in flight.  What the epilogue
+  // needs of them waits in registers; where the accumulators of four tiles leave too few, it is asked for again there.
+  constexpr bool AGAIN = WT >= 4;
+  typename Op::Row rows[WT];
+  auto row_of = [&](int t) { return op.row(base + min(t * TILE + col, n_rows - 1)); };
   auto brow = [&]() {
-    int tok[WT];
+    int staged;
+    if constexpr (AGAIN) {
+      staged = op.act_row(base + min((wave % WT) * TILE + col, n_rows - 1));
+    } else {
 #pragma unroll
-    for (int t = 0; t < WT; ++t) {
-      const int pair = perm[base + min(row0 + t * TILE + col, n_rows - 1)];
-      tok[t] = pair / top_k;
-      r[t] = rinv[tok[t]];
-      wgt[t] = topk_w ? topk_w[pair] : 1.f;   // the routing weight, when the down projection sums the experts itself
+      for (int t = 0; t < WT; ++t) rows[t] = row_of(t);
+      staged = rows[0].act;
+#pragma unroll
+      for (int t = 1; t < WT; ++t)
+        if (wave % WT == t) staged = rows[t].act;
     }
-    int stage_tok = tok[0];
-#pragma unroll
-    for (int t = 1; t < WT; ++t)
-      if (wave % WT == t) stage_tok = tok[t];
-    return xn + (int64_t)stage_tok * (NP * KS) + half * G;
+    return op.act() + (int64_t)staged * (NP * KS) + half * G;
   };
   f32x16 acc0[WT], acc1[WT];
   zero_acc<WT>(acc0);
   zero_acc<WT>(acc1);
-  wide_stream<E, WT, WW, EXPERT_PRE, KID>(W + ((int64_t)e * n_tasks + task) * task_stride_elems<E>(ksteps) + lane * G,
-                                          ksteps / WKC, brow, (int64_t)T * (NP * KS), sb, nt, acc0, acc1);
-  if ((int)blockIdx.x * WW + wave >= n_tasks) return;
+  wide_stream<E, WT, WW, EXPERT_PRE, KID>(op.W + ((int64_t)e * n_tasks + task) * task_stride_elems<E>(ksteps) + lane * G,
+                                          ksteps / WKC, brow, op.act_rows() * (NP * KS), reinterpret_cast<vec*>(lds), nt, acc0, acc1);
+  if (tg * WW + wave >= n_tasks) return;
+  if constexpr (AGAIN) {
 #pragma unroll
-  for (int t = 0; t < WT; ++t) {
-    const int row = row0 + t * TILE + col;
-    if (t < nt && row < n_rows) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {   // accumulator registers 4g .. 4g+3 are four consecutive features
-        f32x4 y;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) y[i] = silu_w(acc0[t][4 * g + i] * r[t]) * (acc1[t][4 * g + i] * r[t]) * wgt[t];
-        store_actk4<E>(Y, (int64_t)T * top_k, base + row, task * TILE + acc_row(4 * g, half), y);
-      }
-    }
+    for (int t = 0; t < WT; ++t) rows[t] = row_of(t);
   }
-}
-
-template <typename E, int WT, int WW, int KID, bool RECORDS>
-__global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_gemm2_wide_kernel(const E* __restrict__ W, const E* __restrict__ Y,
-                                                                      float* __restrict__ O, const int32_t* __restrict__ cnt,
-                                                                      const int32_t* __restrict__ off,
-                                                                      const int32_t* __restrict__ perm,
-                                                                      const int32_t* __restrict__ work, int n_pairs, int H,
-                                                                      int I, const int32_t* __restrict__ live) {
-  if (step_is_dead(live)) return;
-  typedef typename ET<E>::vec vec;
-  extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
-  vec* sb = reinterpret_cast<vec*>(lds_raw);
-  constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N;
-  ExpertItem it;
-  if (!expert_item<WT, RECORDS>(cnt, off, work, it)) return;
-  const int e = it.e, base = it.base, n_rows = it.n_rows, row0 = it.row0;
-  const int nt = min(WT, (n_rows - row0 + TILE - 1) / TILE);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-  const int n_tasks = H / (2 * TILE), task = min((int)blockIdx.x * WW + wave, n_tasks - 1);
-  const int ksteps = I / KS;
-  int pair[WT];
-#pragma unroll
-  for (int t = 0; t < WT; ++t) pair[t] = perm[base + min(row0 + t * TILE + col, n_rows - 1)];   // for the epilogue
-  auto brow = [&]() { return Y + (int64_t)(base + min(row0 + (wave % WT) * TILE + col, n_rows - 1)) * (NP * KS) + half * G; };
-  f32x16 acc0[WT], acc1[WT];
-  zero_acc<WT>(acc0);
-  zero_acc<WT>(acc1);
-  wide_stream<E, WT, WW, EXPERT_PRE, KID>(W + ((int64_t)e * n_tasks + task) * task_stride_elems<E>(ksteps) + lane * G,
-                                          ksteps / WKC, brow, (int64_t)n_pairs * (NP * KS), sb, nt, acc0, acc1);
-  if ((int)blockIdx.x * WW + wave >= n_tasks) return;
 #pragma unroll
   for (int t = 0; t < WT; ++t) {
-    if (t < nt && row0 + t * TILE + col < n_rows) {
-      float* orow = O + (int64_t)pair[t] * H + (2 * task) * TILE;
+    if (t < nt && t * TILE + col < n_rows) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         f32x4 a, b;
@@ -151,11 +135,75 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
           a[i] = acc0[t][4 * g + i];
           b[i] = acc1[t][4 * g + i];
         }
-        *reinterpret_cast<f32x4*>(orow + acc_row(4 * g, half)) = a;
-        *reinterpret_cast<f32x4*>(orow + TILE + acc_row(4 * g, half)) = b;
+        op.store(rows[t], base + t * TILE + col, task, g, half, a, b);
       }
     }
   }
+}
+
+// One item of up to TT tiles and ONE task by a workgroup of eight waves, which cut the task's K range and meet in LDS.
+template <typename E, int TT, class Op>
+__device__ inline void expert_piece(const Op& op, const int4& it, int task, char* lds) {
+  constexpr int KW = EXPERT_WW, PER = 4, EW = 16 / PER;
+  const int e = it.x, base = it.y, n_rows = it.z;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int ksteps = op.ksteps(), per = (ksteps + KW - 1) / KW, ks0 = min(ksteps, wave * per), ks1 = min(ksteps, ks0 + per);
+  typename Op::Row rows[TT];
+  PlaneLoader<E, TT> ld;
+#pragma unroll
+  for (int t = 0; t < TT; ++t) {
+    rows[t] = op.row(base + min(t * TILE + col, n_rows - 1));
+    ld.set(t, op.act(), op.act_rows(), rows[t].act, half);
+  }
+  f32x16 acc0[TT], acc1[TT];
+  zero_acc<TT>(acc0);
+  zero_acc<TT>(acc1);
+  stream_task<E, TT, (TT == 1 ? 8 : 4)>(op.W + ((int64_t)e * op.n_tasks() + task) * task_stride_elems<E>(ksteps), ks0, ks1, ld, acc0, acc1);
+  float* red = reinterpret_cast<float*>(lds);
+  spill_partials<TT, 2 * TT * 16>(red, wave, lane, acc0, acc1);
+  __syncthreads();
+  if (wave >= EW) return;
+  float a0[TT][PER], a1[TT][PER];
+  fold_partials<TT, KW, PER>(red, lane, wave * PER, a0, a1);
+#pragma unroll
+  for (int t = 0; t < TT; ++t)
+    if (t * TILE + col < n_rows)
+      op.store(rows[t], base + t * TILE + col, task, wave, half, f32x4{a0[t][0], a0[t][1], a0[t][2], a0[t][3]},
+               f32x4{a1[t][0], a1[t][1], a1[t][2], a1[t][3]});
+}
+
+// Grid (task groups, items): one workgroup each.
+template <typename E, int WT, int WW, int KID, class Op>
+__global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_kernel(Op op, const int32_t* __restrict__ n_items,
+                                                                                                 const int4* __restrict__ items,
+                                                                                                 const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
+  if ((int)blockIdx.y >= *n_items) return;          // uniform over the block
+  expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+}
+
+// Many rows per expert: a workgroup fills a compute unit.  Grid (task groups, rows): the first rows are items in whole
+// task groups (eight tasks, one per wave), the workgroups of the further ones take the remaining, light items task
+// by task, the last ones find nothing and return.  Without the pieces, two experts with a few rows more than 128 began
+// a second round of the chip for eight workgroups: at 512 tokens the launch's 256 others ended between 70 and 100 us,
+// those at 137 (gate/up 142 us a launch, 109 with the pieces, which the units that finish early pick up; down 87 and 71).
+template <typename E, int KID, class Op>
+__global__ __launch_bounds__(EXPERT_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_many_kernel(Op op, const int32_t* __restrict__ work,
+                                                                                                            const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
+  const int4* items = reinterpret_cast<const int4*>(work + WORK_ITEMS);
+  const int n_big = work[WORK_BIG];
+  if ((int)blockIdx.y < n_big) {
+    expert_tasks<E, WT, EXPERT_WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+    return;
+  }
+  const int piece = ((int)blockIdx.y - n_big) * gridDim.x + blockIdx.x, n_tasks = op.n_tasks();
+  if (piece >= (work[WORK_ALL] - n_big) * n_tasks) return;   // uniform over the block
+  const int4 it = items[n_big + piece / n_tasks];
+  if (it.z <= TILE) expert_piece<E, 1, Op>(op, it, piece % n_tasks, lds_raw);
+  else expert_piece<E, 2, Op>(op, it, piece % n_tasks, lds_raw);
 }
 
 // Up to 32 / 64 tokens: one / two token tiles and SMALL_WW tasks per workgroup, experts from the router's records
@@ -180,49 +228,45 @@ constexpr int GU1_WW = 1;
 constexpr int MID_WW = 4, MID_WT = 2, MID_ROWS = 24;
 int expert_group_tiles(int E, int n_pairs) { return n_pairs <= MID_ROWS * E ? MID_WT : WT; }
 
-template <typename E> static void launch_gate_up_wide_t(const ExpertArgs& a, hipStream_t st) {
-  const int n_tasks = a.I / TILE;
-  const E *w = (const E*)a.w_gate_up, *xn = (const E*)a.xn;
-  if (a.T <= TILE) {
-    expert_gemm1_wide_kernel<E, 1, GU1_WW, 16, true><<<dim3((n_tasks + GU1_WW - 1) / GU1_WW, a.E), GU1_WW * WAVE,
-                                                         wide_lds<E, 16, 1>(), st>>>(
-        w, xn, a.rinv, (E*)a.y, a.cnt, a.off, a.perm, a.work, a.T, a.H, a.I, a.top_k, a.topk_w, live_word());
-  } else if (a.T <= 2 * TILE) {
-    expert_gemm1_wide_kernel<E, 2, SMALL_WW, 17, true><<<dim3((n_tasks + SMALL_WW - 1) / SMALL_WW, a.E), SMALL_WW * WAVE,
-                                                         wide_lds<E, 17, 2>(), st>>>(
-        w, xn, a.rinv, (E*)a.y, a.cnt, a.off, a.perm, a.work, a.T, a.H, a.I, a.top_k, a.topk_w, live_word());
-  } else if (expert_group_tiles(a.E, a.T * a.top_k) == MID_WT) {
-    expert_gemm1_wide_kernel<E, MID_WT, MID_WW, 20, false>
-        <<<dim3((n_tasks + MID_WW - 1) / MID_WW, expert_work_items(a.E, a.T * a.top_k, MID_WT)), MID_WW * WAVE,
-           wide_lds<E, 20, MID_WT>(), st>>>(w, xn, a.rinv, (E*)a.y, a.cnt, a.off, a.perm, a.work, a.T, a.H, a.I, a.top_k,
-                                       a.topk_w, live_word());
+int expert_round_items(int E, int n_pairs, int H, int I) {
+  if (expert_group_tiles(E, n_pairs) != WT) return 0x7fffffff;
+  const int up = (I / TILE + EXPERT_WW - 1) / EXPERT_WW, down = (H / (2 * TILE) + EXPERT_WW - 1) / EXPERT_WW;
+  const int most = up > down ? up : down;
+  return most < EXPERT_CUS ? EXPERT_CUS / most : 1;
+}
+
+// KID: trace ids of the forms for up to 32, up to 64, few rows per expert, many rows per expert
+template <typename E, int WW1, int K1, int K2, int K3, int K4, class Op>
+static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hipStream_t st) {
+  const int n_pairs = a.T * a.top_k;
+  const int4* listed = reinterpret_cast<const int4*>(a.work + WORK_ITEMS);
+  auto grid = [&](int ww, int items) { return dim3((n_tasks + ww - 1) / ww, items); };
+  if (a.T <= 2 * TILE) {
+    const int32_t* n_items = a.off + ACTIVE_LIST + MAX_EXPERTS;
+    const int4* records = reinterpret_cast<const int4*>(a.off + ACTIVE_RECORDS);
+    if (a.T <= TILE)
+      expert_kernel<E, 1, WW1, K1, Op><<<grid(WW1, a.E), WW1 * WAVE, wide_lds<E, K1, 1>(), st>>>(op, n_items, records, live_word());
+    else
+      expert_kernel<E, 2, SMALL_WW, K2, Op><<<grid(SMALL_WW, a.E), SMALL_WW * WAVE, wide_lds<E, K2, 2>(), st>>>(op, n_items, records, live_word());
+  } else if (expert_group_tiles(a.E, n_pairs) == MID_WT) {
+    expert_kernel<E, MID_WT, MID_WW, K3, Op><<<grid(MID_WW, expert_work_items(a.E, n_pairs, MID_WT)), MID_WW * WAVE, wide_lds<E, K3, MID_WT>(), st>>>(
+        op, a.work + WORK_ALL, listed, live_word());
   } else {
-    expert_gemm1_wide_kernel<E, WT, EXPERT_WW, 10, false>
-        <<<dim3((n_tasks + EXPERT_WW - 1) / EXPERT_WW, expert_work_items(a.E, a.T * a.top_k, WT)), EXPERT_WW * WAVE,
-           wide_lds<E, 10, WT>(), st>>>(w, xn, a.rinv, (E*)a.y, a.cnt, a.off, a.perm, a.work, a.T, a.H, a.I, a.top_k,
-                                        a.topk_w, live_word());
+    const dim3 whole = grid(EXPERT_WW, expert_work_items(a.E, n_pairs, WT));
+    const int pieces = expert_round_items(a.E, n_pairs, a.H, a.I) / 2 * n_tasks;   // the most the permutation hands out
+    expert_many_kernel<E, K4, Op><<<dim3(whole.x, whole.y + (pieces + whole.x - 1) / whole.x), EXPERT_WW * WAVE, EXPERT_MANY_LDS, st>>>(
+        op, a.work, live_word());
   }
 }
+template <typename E> static GateUp<E> gate_up_op(const ExpertArgs& a) {
+  return GateUp<E>{(const E*)a.w_gate_up, (const E*)a.xn, a.rinv, (E*)a.y, a.perm, a.T, a.H, a.I, a.top_k, a.topk_w};
+}
+template <typename E> static void launch_gate_up_wide_t(const ExpertArgs& a, hipStream_t st) {
+  launch_expert_op<E, GU1_WW, 16, 17, 20, 10>(gate_up_op<E>(a), a, a.I / TILE, st);
+}
 template <typename E> static void launch_down_wide_t(const ExpertArgs& a, hipStream_t st) {
-  const int n_tasks = a.H / (2 * TILE), n_pairs = a.T * a.top_k;
-  const E *w = (const E*)a.w_down, *y = (const E*)a.y;
-  if (a.T <= TILE) {
-    expert_gemm2_wide_kernel<E, 1, SMALL_WW, 18, true><<<dim3((n_tasks + SMALL_WW - 1) / SMALL_WW, a.E), SMALL_WW * WAVE,
-                                                         wide_lds<E, 18, 1>(), st>>>(
-        w, y, a.o, a.cnt, a.off, a.perm, a.work, n_pairs, a.H, a.I, live_word());
-  } else if (a.T <= 2 * TILE) {
-    expert_gemm2_wide_kernel<E, 2, SMALL_WW, 19, true><<<dim3((n_tasks + SMALL_WW - 1) / SMALL_WW, a.E), SMALL_WW * WAVE,
-                                                         wide_lds<E, 19, 2>(), st>>>(
-        w, y, a.o, a.cnt, a.off, a.perm, a.work, n_pairs, a.H, a.I, live_word());
-  } else if (expert_group_tiles(a.E, n_pairs) == MID_WT) {
-    expert_gemm2_wide_kernel<E, MID_WT, MID_WW, 21, false>
-        <<<dim3((n_tasks + MID_WW - 1) / MID_WW, expert_work_items(a.E, n_pairs, MID_WT)), MID_WW * WAVE,
-           wide_lds<E, 21, MID_WT>(), st>>>(w, y, a.o, a.cnt, a.off, a.perm, a.work, n_pairs, a.H, a.I, live_word());
-  } else {
-    expert_gemm2_wide_kernel<E, WT, EXPERT_WW, 11, false>
-        <<<dim3((n_tasks + EXPERT_WW - 1) / EXPERT_WW, expert_work_items(a.E, n_pairs, WT)), EXPERT_WW * WAVE,
-           wide_lds<E, 11, WT>(), st>>>(w, y, a.o, a.cnt, a.off, a.perm, a.work, n_pairs, a.H, a.I, live_word());
-  }
+  const Down<E> op{(const E*)a.w_down, (const E*)a.y, a.o, a.perm, a.T * a.top_k, a.H, a.I};
+  launch_expert_op<E, SMALL_WW, 18, 19, 21, 11>(op, a, a.H / (2 * TILE), st);
 }
 void launch_expert_gate_up_wide(bool bf16, const ExpertArgs& a, hipStream_t st) {
   if (bf16) launch_gate_up_wide_t<bf16_t>(a, st);
@@ -383,14 +427,13 @@ void launch_lm_head_wide(bool bf16, const LmArgs& a, hipStream_t st) {
 }
 
 bool configure_wide() {
-  const void* fns[6] = {(const void*)expert_gemm1_wide_kernel<bf16_t, WT, EXPERT_WW, 10, false>,
-                        (const void*)expert_gemm1_wide_kernel<float, WT, EXPERT_WW, 10, false>,
-                        (const void*)expert_gemm2_wide_kernel<bf16_t, WT, EXPERT_WW, 11, false>,
-                        (const void*)expert_gemm2_wide_kernel<float, WT, EXPERT_WW, 11, false>,
-                        (const void*)lm_head_wide_kernel<bf16_t, WT, 9, LM_WW>, (const void*)lm_head_wide_kernel<float, WT, 9, LM_WW>};
-  for (const void* f : fns)
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess) return false;
-  return true;
+  auto opt_in = [](const void* f, int bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; };
+  const void* many[4] = {(const void*)expert_many_kernel<bf16_t, 10, GateUp<bf16_t>>, (const void*)expert_many_kernel<float, 10, GateUp<float>>,
+                           (const void*)expert_many_kernel<bf16_t, 11, Down<bf16_t>>, (const void*)expert_many_kernel<float, 11, Down<float>>};
+  for (const void* f : many)
+    if (!opt_in(f, EXPERT_MANY_LDS)) return false;
+  return opt_in((const void*)lm_head_wide_kernel<bf16_t, WT, 9, LM_WW>, 128 * 1024) &&
+         opt_in((const void*)lm_head_wide_kernel<float, WT, 9, LM_WW>, 128 * 1024);
 }
 
 TRACE_READER(trace_read_wide)
