@@ -192,7 +192,7 @@ void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32
 constexpr int WORK_BIG = 0, WORK_ALL = 1, WORK_ITEMS = 4;
 // Token tiles per work item of the expert GEMMs above 64 tokens.
 int expert_group_tiles(int E, int n_pairs);
-// Items whose workgroups fill the chip once, for launch_permute (a huge number: no item is handed out in pieces; never more than half of them are).
+// Items whose workgroups fill the chip once, for launch_permute: at most half as many are handed out in pieces.
 int expert_round_items(int E, int n_pairs, int H, int I);
 // Work items that many groups can add up to for n_pairs routed pairs.
 inline int expert_work_items(int E, int n_pairs, int group_tiles) { return E + n_pairs / (group_tiles * TILE); }

@@ -16,8 +16,7 @@ constexpr int WT = 4;      // token tiles per workgroup above 64 tokens
 // (Measured at 512 tokens: four waves with two, four or six weight chunks in flight are slower for the expert
 // GEMMs, 131 to 134 against 120 microseconds; four waves in the LM head, 450 against 352.)
 constexpr int EXPERT_WW = 8, EXPERT_PRE = 2;
-constexpr int EXPERT_CUS = 256;                // compute units: a workgroup of the many-row expert GEMMs fills one
-constexpr int EXPERT_MANY_LDS = 128 * 1024;    // its LDS: staged fragments, or two tiles of eight waves' partial sums
+constexpr int EXPERT_CUS = 256;   // compute units; eight waves of the many-token expert GEMMs fill one
 constexpr int LM_WW = 8, LM_PRE = 2;
 // Tasks per workgroup of the LM head up to 32 tokens.  All workgroups of these launches are resident at once and
 // the dispatcher deals them evenly, so a launch lasts as long as the compute units with one workgroup more than the
@@ -141,10 +140,11 @@ __device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* 
   }
 }
 
-// One item of up to TT tiles and ONE task by a workgroup of eight waves, which cut the task's K range and meet in LDS.
-template <typename E, int TT, class Op>
+// One item of up to TT tiles and ONE task by a workgroup of KW waves, which cut the task's K range and meet in LDS.
+template <typename E, int TT, int KW, class Op>
 __device__ inline void expert_piece(const Op& op, const int4& it, int task, char* lds) {
-  constexpr int KW = EXPERT_WW, PER = 4, EW = 16 / PER;
+  constexpr int PER = 4, EW = 16 / PER;
+  static_assert(KW >= EW, "the first EW waves run the epilogue");
   const int e = it.x, base = it.y, n_rows = it.z;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int ksteps = op.ksteps(), per = (ksteps + KW - 1) / KW, ks0 = min(ksteps, wave * per), ks1 = min(ksteps, ks0 + per);
@@ -183,27 +183,28 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
   expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
 }
 
-// Many rows per expert: a workgroup fills a compute unit.  Grid (task groups, rows): the first rows are items in whole
-// task groups (eight tasks, one per wave), the workgroups of the further ones take the remaining, light items task
-// by task, the last ones find nothing and return.  Without the pieces, two experts with a few rows more than 128 began
-// a second round of the chip for eight workgroups: at 512 tokens the launch's 256 others ended between 70 and 100 us,
-// those at 137 (gate/up 142 us a launch, 109 with the pieces, which the units that finish early pick up; down 87 and 71).
-template <typename E, int KID, class Op>
-__global__ __launch_bounds__(EXPERT_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_many_kernel(Op op, const int32_t* __restrict__ work,
+// More than 64 tokens.  Grid (task groups, rows): the first rows are items in whole task groups (WW tasks, one per
+// wave), the workgroups of the further ones take the remaining, light items task by task, the last ones find nothing and
+// return.  All workgroups of whole items are resident at once (eight waves fill a compute unit), so that items beyond a
+// full round of the chip begin another one: at 512 tokens two experts with a few rows more than 128 did so for eight
+// workgroups, and the launch's 256 others ended between 70 and 100 us, those at 137 (gate/up 142 us a launch, 109 with
+// the pieces, which the units that finish early pick up; down 87 and 71).
+template <typename E, int WT, int WW, int KID, class Op>
+__global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_many_kernel(Op op, const int32_t* __restrict__ work,
                                                                                                             const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
   const int4* items = reinterpret_cast<const int4*>(work + WORK_ITEMS);
   const int n_big = work[WORK_BIG];
   if ((int)blockIdx.y < n_big) {
-    expert_tasks<E, WT, EXPERT_WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+    expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
     return;
   }
   const int piece = ((int)blockIdx.y - n_big) * gridDim.x + blockIdx.x, n_tasks = op.n_tasks();
   if (piece >= (work[WORK_ALL] - n_big) * n_tasks) return;   // uniform over the block
   const int4 it = items[n_big + piece / n_tasks];
-  if (it.z <= TILE) expert_piece<E, 1, Op>(op, it, piece % n_tasks, lds_raw);
-  else expert_piece<E, 2, Op>(op, it, piece % n_tasks, lds_raw);
+  if (it.z <= TILE) expert_piece<E, 1, WW, Op>(op, it, piece % n_tasks, lds_raw);
+  else expert_piece<E, 2, WW, Op>(op, it, piece % n_tasks, lds_raw);
 }
 
 // Up to 32 / 64 tokens: one / two token tiles and SMALL_WW tasks per workgroup, experts from the router's records
@@ -222,24 +223,25 @@ constexpr int GU1_WW = 1;
 // that two workgroups share a compute unit (trace ids 20, 21).  With eight tasks an expert is four workgroups of a
 // whole compute unit each, and a step whose masked rows touch half of the experts leaves half of the chip idle
 // (gate/up + down in microseconds at 96 / 128 / 160 tokens of a fully masked block batch: 73 + 46, 91 + 55, 89 + 53
-// with eight tasks, 45 + 31, 71 + 44, 72 + 46 with four; where all 64 experts have rows, 91 + 51 against 87 + 53 at
-// 96 tokens and 99 + 58 against 96 + 59 at 160).  Beyond, the rows weigh more than the balance: every workgroup
+// with eight tasks, 45 + 31, 71 + 44, 72 + 46 with four; where all 64 experts have rows, 92 + 52 against 87 + 52 at
+// 96 tokens and 98 + 59 against 95 + 59 at 160).  Beyond, the rows weigh more than the balance: every workgroup
 // fetches its expert's rows for itself (256 tokens: 102 + 64 with eight tasks, 120 + 73 with four).
 constexpr int MID_WW = 4, MID_WT = 2, MID_ROWS = 24;
 int expert_group_tiles(int E, int n_pairs) { return n_pairs <= MID_ROWS * E ? MID_WT : WT; }
+// LDS of expert_many_kernel: staged fragments, or two tiles of WW waves' partial sums
+template <int WW> constexpr size_t many_lds() { return (size_t)WW * 2 * 2 * 16 * WAVE * 4; }
 
 int expert_round_items(int E, int n_pairs, int H, int I) {
-  if (expert_group_tiles(E, n_pairs) != WT) return 0x7fffffff;
-  const int up = (I / TILE + EXPERT_WW - 1) / EXPERT_WW, down = (H / (2 * TILE) + EXPERT_WW - 1) / EXPERT_WW;
+  const int ww = expert_group_tiles(E, n_pairs) == MID_WT ? MID_WW : EXPERT_WW, slots = EXPERT_CUS * (EXPERT_WW / ww);
+  const int up = (I / TILE + ww - 1) / ww, down = (H / (2 * TILE) + ww - 1) / ww;
   const int most = up > down ? up : down;
-  return most < EXPERT_CUS ? EXPERT_CUS / most : 1;
+  return most < slots ? slots / most : 1;
 }
 
 // KID: trace ids of the forms for up to 32, up to 64, few rows per expert, many rows per expert
 template <typename E, int WW1, int K1, int K2, int K3, int K4, class Op>
 static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hipStream_t st) {
   const int n_pairs = a.T * a.top_k;
-  const int4* listed = reinterpret_cast<const int4*>(a.work + WORK_ITEMS);
   auto grid = [&](int ww, int items) { return dim3((n_tasks + ww - 1) / ww, items); };
   if (a.T <= 2 * TILE) {
     const int32_t* n_items = a.off + ACTIVE_LIST + MAX_EXPERTS;
@@ -248,14 +250,14 @@ static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hip
       expert_kernel<E, 1, WW1, K1, Op><<<grid(WW1, a.E), WW1 * WAVE, wide_lds<E, K1, 1>(), st>>>(op, n_items, records, live_word());
     else
       expert_kernel<E, 2, SMALL_WW, K2, Op><<<grid(SMALL_WW, a.E), SMALL_WW * WAVE, wide_lds<E, K2, 2>(), st>>>(op, n_items, records, live_word());
-  } else if (expert_group_tiles(a.E, n_pairs) == MID_WT) {
-    expert_kernel<E, MID_WT, MID_WW, K3, Op><<<grid(MID_WW, expert_work_items(a.E, n_pairs, MID_WT)), MID_WW * WAVE, wide_lds<E, K3, MID_WT>(), st>>>(
-        op, a.work + WORK_ALL, listed, live_word());
   } else {
-    const dim3 whole = grid(EXPERT_WW, expert_work_items(a.E, n_pairs, WT));
-    const int pieces = expert_round_items(a.E, n_pairs, a.H, a.I) / 2 * n_tasks;   // the most the permutation hands out
-    expert_many_kernel<E, K4, Op><<<dim3(whole.x, whole.y + (pieces + whole.x - 1) / whole.x), EXPERT_WW * WAVE, EXPERT_MANY_LDS, st>>>(
-        op, a.work, live_word());
+    auto many = [&](auto kernel, int wt, int ww, size_t lds) {
+      const dim3 whole = grid(ww, expert_work_items(a.E, n_pairs, wt));
+      const int pieces = expert_round_items(a.E, n_pairs, a.H, a.I) / 2 * n_tasks;   // the most the permutation hands out
+      kernel<<<dim3(whole.x, whole.y + (pieces + whole.x - 1) / whole.x), ww * WAVE, lds, st>>>(op, a.work, live_word());
+    };
+    if (expert_group_tiles(a.E, n_pairs) == MID_WT) many(expert_many_kernel<E, MID_WT, MID_WW, K3, Op>, MID_WT, MID_WW, many_lds<MID_WW>());
+    else many(expert_many_kernel<E, WT, EXPERT_WW, K4, Op>, WT, EXPERT_WW, many_lds<EXPERT_WW>());
   }
 }
 template <typename E> static GateUp<E> gate_up_op(const ExpertArgs& a) {
@@ -428,10 +430,12 @@ void launch_lm_head_wide(bool bf16, const LmArgs& a, hipStream_t st) {
 
 bool configure_wide() {
   auto opt_in = [](const void* f, int bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; };
-  const void* many[4] = {(const void*)expert_many_kernel<bf16_t, 10, GateUp<bf16_t>>, (const void*)expert_many_kernel<float, 10, GateUp<float>>,
-                           (const void*)expert_many_kernel<bf16_t, 11, Down<bf16_t>>, (const void*)expert_many_kernel<float, 11, Down<float>>};
+  const void* many[4] = {(const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 10, GateUp<bf16_t>>,
+                         (const void*)expert_many_kernel<float, WT, EXPERT_WW, 10, GateUp<float>>,
+                         (const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 11, Down<bf16_t>>,
+                         (const void*)expert_many_kernel<float, WT, EXPERT_WW, 11, Down<float>>};
   for (const void* f : many)
-    if (!opt_in(f, EXPERT_MANY_LDS)) return false;
+    if (!opt_in(f, (int)many_lds<EXPERT_WW>())) return false;
   return opt_in((const void*)lm_head_wide_kernel<bf16_t, WT, 9, LM_WW>, 128 * 1024) &&
          opt_in((const void*)lm_head_wide_kernel<float, WT, 9, LM_WW>, 128 * 1024);
 }
