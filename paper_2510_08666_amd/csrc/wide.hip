@@ -23,6 +23,7 @@ constexpr int LM_WW = 8, LM_PRE = 2;
 // others: 614 workgroups of four tasks put 3 MB on some units and 2 MB on others (112 us), 1228 of two tasks 2.5 or
 // 2 MB (108 us).
 constexpr int LM_SMALL_WW = 2, LM_MID_WW = 4;   // up to 32, up to 64 tokens
+constexpr int LM_PIECE_WW = 8;                  // waves per task of a small vocabulary
 constexpr int XCDS = 8;      // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
 
 // ------------------------------------------------------------------------------------------------
@@ -183,6 +184,17 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
   expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
 }
 
+// Grid (tasks, items): every task in pieces (up to 64 tokens, few tasks: see launch_expert_op).
+template <typename E, int TT, class Op>
+__global__ __launch_bounds__(EXPERT_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_pieces_kernel(Op op, const int32_t* __restrict__ n_items,
+                                                                                                              const int4* __restrict__ items,
+                                                                                                              const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  extern __shared__ __align__(16) char lds_raw[];
+  if ((int)blockIdx.y >= *n_items) return;          // uniform over the block
+  expert_piece<E, TT, EXPERT_WW, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+}
+
 // More than 64 tokens.  Grid (task groups, rows): the first rows are items in whole task groups (WW tasks, one per
 // wave), the workgroups of the further ones take the remaining, light items task by task, the last ones find nothing and
 // return.  All workgroups of whole items are resident at once (eight waves fill a compute unit), so that items beyond a
@@ -246,7 +258,14 @@ static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hip
   if (a.T <= 2 * TILE) {
     const int32_t* n_items = a.off + ACTIVE_LIST + MAX_EXPERTS;
     const int4* records = reinterpret_cast<const int4*>(a.off + ACTIVE_RECORDS);
-    if (a.T <= TILE)
+    // Few tasks over all experts (one per compute unit or less): a workgroup of eight waves each, since a wave alone with
+    // a task is bound by its chain of loads and matrix instructions (8 experts of 512, hidden 256, float32: gate/up 14.6
+    // -> 9.6 us at 32 tokens, 23 -> 13 at 64, down at 64 tokens 37 -> 17.5).
+    if (a.E * n_tasks <= EXPERT_CUS && a.T <= TILE)
+      expert_pieces_kernel<E, 1, Op><<<dim3(n_tasks, a.E), EXPERT_WW * WAVE, many_lds<EXPERT_WW>() / 2, st>>>(op, n_items, records, live_word());
+    else if (a.E * n_tasks <= EXPERT_CUS)
+      expert_pieces_kernel<E, 2, Op><<<dim3(n_tasks, a.E), EXPERT_WW * WAVE, many_lds<EXPERT_WW>(), st>>>(op, n_items, records, live_word());
+    else if (a.T <= TILE)
       expert_kernel<E, 1, WW1, K1, Op><<<grid(WW1, a.E), WW1 * WAVE, wide_lds<E, K1, 1>(), st>>>(op, n_items, records, live_word());
     else
       expert_kernel<E, 2, SMALL_WW, K2, Op><<<grid(SMALL_WW, a.E), SMALL_WW * WAVE, wide_lds<E, K2, 2>(), st>>>(op, n_items, records, live_word());
@@ -290,11 +309,11 @@ void launch_expert_down_wide(bool bf16, const ExpertArgs& a, hipStream_t st) {
 // HBM per launch for 0.64 GB of weights, where four separate passes would fetch 2.6 GB).
 // ------------------------------------------------------------------------------------------------
 template <typename E, int WT, int KID, int WW>
-__global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __restrict__ W, const E* __restrict__ xn,
+__global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT == 1 && WW == LM_SMALL_WW ? 3 : 2))) void lm_head_wide_kernel(const E* __restrict__ W, const E* __restrict__ xn,
                                                                   RowNorm norm, int T, int H, int V,
                                                                   float scale, float* __restrict__ part,
                                                                   float* __restrict__ logits_out,
-                                                                  const int32_t* __restrict__ rows,
+                                                                  const int32_t* __restrict__ rows, int n_whole,
                                                                   const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   typedef typename ET<E>::vec vec;
@@ -312,22 +331,80 @@ __global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __rest
   const int turn = blockIdx.x / XCDS;
   const int tgroup = (turn / groups) * XCDS + blockIdx.x % XCDS;
   const int n_tasks = (V + 2 * TILE - 1) / (2 * TILE);
-  const int n_groups = (n_tasks + WW - 1) / WW;
-  if (tgroup >= n_groups) return;       // uniform over the workgroup
   // Partials of a row lie next to each other for the merge kernel (a stride of 8 KB apart it took 27 us for 512 tokens).
   // Up to 64 tokens a workgroup leaves one per row, more tokens: its waves one each (folding them there costs the
   // launch 8 us at 512 tokens, more than the merge saves).
   constexpr bool FOLD = KID != 9;
-  const int n_parts = FOLD ? n_groups : n_groups * WW;
+  const int n_groups = min(n_whole, (n_tasks + WW - 1) / WW), first_piece = min(n_tasks, n_groups * WW);
+  const int n_parts = FOLD ? n_groups + n_tasks - first_piece : n_groups * WW;
+  if (tgroup >= n_groups + n_tasks - first_piece) return;   // uniform over the workgroup
   LmStat* s_stat = reinterpret_cast<LmStat*>(lds_raw);   // [WW][WT * TILE], once the fragments are done with
   static_assert(WW * WT * TILE * sizeof(LmStat) <= wide_lds<E, KID, WT>(), "the statistics fit the staging area");
+  const bool quads = V % 4 == 0 && ((uintptr_t)logits_out & 15) == 0;   // rows of logits start on 16-byte boundaries
+  auto row_of = [&](int i) { return rows ? min(max(rows[1 + min(i, n_rows - 1)], 0), T - 1) : min(i, T - 1); };
+  constexpr bool ONLY_PIECES = FOLD && WW == LM_PIECE_WW;
+  if constexpr (FOLD && WW >= LM_MID_WW) {
+    if (ONLY_PIECES || tgroup >= n_groups) {
+      // One task, its K range cut over the waves (one token group: n_rows <= WT * TILE): a wave ends up with PER
+      // accumulator registers of both weight tiles.
+      constexpr int PER = 16 / WW;
+      const int task = first_piece + tgroup - n_groups, ksteps = H / KS, per = (ksteps + WW - 1) / WW;
+      const int ks0 = min(ksteps, wave * per), ks1 = min(ksteps, ks0 + per);
+      PlaneLoader<E, WT> ld;
+      float zs[WT];
+#pragma unroll
+      for (int t = 0; t < WT; ++t) {
+        const int tok = row_of(t * TILE + col);
+        ld.set(t, xn, T, tok, half);
+        zs[t] = row_rinv(norm.ssq, norm.n_ssq, T, tok, H, norm.eps) * scale;
+      }
+      f32x16 acc0[WT], acc1[WT];
+      zero_acc<WT>(acc0);
+      zero_acc<WT>(acc1);
+      stream_task<E, WT, (WT == 1 ? 8 : 4)>(W + (int64_t)task * task_stride_elems<E>(ksteps), ks0, ks1, ld, acc0, acc1);
+      float* red = reinterpret_cast<float*>(lds_raw);
+      spill_partials<WT, 2 * WT * 16>(red, wave, lane, acc0, acc1);
+      __syncthreads();
+      float a0[WT][PER], a1[WT][PER];
+      fold_partials<WT, WW, PER>(red, lane, wave * PER, a0, a1);
+      __syncthreads();   // the partial sums have been read: s_stat takes their place
+#pragma unroll
+      for (int t = 0; t < WT; ++t) {
+        LmStat st{-INFINITY, 0.f, 0x7fffffff};
+        float z[2 * PER];
+#pragma unroll
+        for (int i = 0; i < 2 * PER; ++i) {
+          const int id = (2 * task + i / PER) * TILE + acc_row(wave * PER + i % PER, half);
+          z[i] = id < V ? (i < PER ? a0[t][i % PER] : a1[t][i % PER]) * zs[t] : -INFINITY;
+          if (z[i] > st.m) {
+            st.m = z[i];
+            st.id = id;
+          }
+          if (logits_out && t * TILE + col < n_rows && id < V) logits_out[(int64_t)row_of(t * TILE + col) * V + id] = z[i];
+        }
+        if (st.m > -INFINITY) {
+#pragma unroll
+          for (int i = 0; i < 2 * PER; ++i) st.s += __expf(z[i] - st.m);
+        }
+        st = lm_combine(st, LmStat{__shfl_xor(st.m, 32, WAVE), __shfl_xor(st.s, 32, WAVE), __shfl_xor(st.id, 32, WAVE)});
+        if (half == 0) s_stat[wave * WT * TILE + t * TILE + col] = st;
+      }
+      __syncthreads();
+      for (int i = threadIdx.x; i < min(n_rows, WT * TILE); i += WW * WAVE) {
+        LmStat a = s_stat[i];
+#pragma unroll
+        for (int w = 1; w < WW; ++w) a = lm_combine(a, s_stat[w * WT * TILE + i]);
+        *reinterpret_cast<f32x4*>(part + ((int64_t)row_of(i) * n_parts + tgroup) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
+      }
+      return;
+    }
+  }
+  if constexpr (!ONLY_PIECES) {
   const int tok0 = (turn % groups) * per_group * TILE;
   const int nt = min(per_group, tiles - (turn % groups) * per_group);
   if (nt <= 0) return;                  // uniform: fewer tiles than groups * per_group
   const int slot = tgroup * WW + wave, task = min(slot, n_tasks - 1);
   const int ksteps = H / KS;
-  const bool quads = V % 4 == 0 && ((uintptr_t)logits_out & 15) == 0;   // rows of logits start on 16-byte boundaries
-  auto row_of = [&](int i) { return rows ? min(max(rows[1 + min(i, n_rows - 1)], 0), T - 1) : min(i, T - 1); };
   int tok_of[WT];
   float zs[WT];
 #pragma unroll
@@ -393,35 +470,59 @@ __global__ __launch_bounds__(WW * WAVE) void lm_head_wide_kernel(const E* __rest
         *reinterpret_cast<f32x4*>(part + ((int64_t)row_of(tok0 + i) * n_parts + tgroup) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
     }
   }
+  }
 }
 
-// Workgroups that share the vocabulary (tasks over waves per workgroup, by token count), and the partials a row
-// receives: one per workgroup up to 64 tokens, one per wave above.
-static int lm_task_groups(int V, int T) {
-  const int ww = T <= TILE ? LM_SMALL_WW : T <= 2 * TILE ? LM_MID_WW : LM_WW;
-  return ((V + 63) / 64 + ww - 1) / ww;
+// How the vocabulary is dealt out: task groups of ww tasks taken whole, one task per wave, and the tasks behind them one
+// per workgroup, with the K range cut over its waves.
+//  - Few tasks (one per compute unit or less): all in pieces, since a wave alone with a task is bound by its chain of
+//    loads and matrix instructions (4096 ids of float32, hidden 256: 16.5 -> 11 us at 32 tokens, 27 -> 13.4 at 64).
+//  - 33 to 64 tokens: two workgroups of four waves fill a compute unit, so the groups beyond 512 would begin a second
+//    round of the chip; they go out in pieces where they are less than half a round (157184 ids: 126 -> 124.5 us).
+//  - Up to 32 tokens: three waves per SIMD (168 registers) hold all workgroups of 157184 ids at once (114 -> 108 us
+//    against two per SIMD, where 1024 of 1228 fit).  More than 64 tokens: whole groups.
+struct LmPlan {
+  int ww, whole, pieces;
+};
+static LmPlan lm_plan(int V, int T) {
+  const int tasks = (V + 63) / 64;
+  if (T <= 2 * TILE && tasks <= EXPERT_CUS) return LmPlan{LM_PIECE_WW, 0, tasks};
+  const int ww = T <= TILE ? LM_SMALL_WW : T <= 2 * TILE ? LM_MID_WW : LM_WW, groups = (tasks + ww - 1) / ww;
+  const int round = EXPERT_CUS * (8 / LM_MID_WW);
+  if (ww == LM_MID_WW && groups > round && groups % round < round / 2) {
+    const int whole = groups / round * round;
+    return LmPlan{ww, whole, tasks - whole * ww};
+  }
+  return LmPlan{ww, groups, 0};
 }
-int lm_head_parts(int V, int T) { return lm_task_groups(V, T) * (T <= 2 * TILE ? 1 : LM_WW); }
-int lm_head_most_parts(int V) { return lm_head_parts(V, 2 * TILE + 1); }   // one per task, rounded up: the most
+int lm_head_parts(int V, int T) {
+  const LmPlan p = lm_plan(V, T);
+  return T <= 2 * TILE ? p.whole + p.pieces : p.whole * LM_WW;
+}
+int lm_head_most_parts(int V) { return ((V + 63) / 64 + LM_WW - 1) / LM_WW * LM_WW; }   // one per task, rounded up: the most
 
-// Up to 64 tokens: two token tiles per workgroup and both activation planes (trace id 14): there the weight stream
-// is the bound, and sharing the activation fragments of eight tasks relieves the address unit, which would
-// otherwise take every lane's own activation row one by one.  More tokens: four tiles, high plane only (id 9).
+// Up to 64 tokens: one or two token tiles per workgroup and both activation planes (trace ids 15, 14): there the weight
+// stream is the bound, and sharing the activation fragments relieves the address unit, which would otherwise take every
+// lane's own activation row one by one.  (33 to 64 tokens in workgroups of two tasks: 144 against 119 us, the fragments
+// of 64 rows are shared by too few.)  More tokens: four tiles, high plane only (id 9).
+template <int WW, int WT> constexpr size_t lm_piece_lds() { return (size_t)WW * 2 * WT * 16 * WAVE * 4; }
 template <typename E> static void launch_lm_wide_t(const LmArgs& a, hipStream_t st) {
-  const int tgroups = lm_task_groups(a.V, a.T);
-  if (a.T <= TILE) {   // one token tile (trace id 15)
-    lm_head_wide_kernel<E, 1, 15, LM_SMALL_WW><<<(tgroups + XCDS - 1) / XCDS * XCDS, LM_SMALL_WW * WAVE, wide_lds<E, 15, 1>(), st>>>(
-        (const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows, live_word());
-    return;
+  const LmPlan p = lm_plan(a.V, a.T);
+  const int groups = a.T <= 2 * TILE ? 1 : (a.T + WT * TILE - 1) / (WT * TILE);
+  const int wgs = (p.whole + p.pieces + XCDS - 1) / XCDS * XCDS * groups;
+  auto go = [&](auto kernel, int ww, size_t lds) {
+    kernel<<<wgs, ww * WAVE, lds, st>>>((const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows,
+                                        p.whole, live_word());
+  };
+  if (a.T <= TILE) {
+    if (p.ww == LM_PIECE_WW) go(lm_head_wide_kernel<E, 1, 15, LM_PIECE_WW>, LM_PIECE_WW, lm_piece_lds<LM_PIECE_WW, 1>());
+    else go(lm_head_wide_kernel<E, 1, 15, LM_SMALL_WW>, LM_SMALL_WW, wide_lds<E, 15, 1>());
+  } else if (a.T <= 2 * TILE) {
+    if (p.ww == LM_PIECE_WW) go(lm_head_wide_kernel<E, 2, 14, LM_PIECE_WW>, LM_PIECE_WW, lm_piece_lds<LM_PIECE_WW, 2>());
+    else go(lm_head_wide_kernel<E, 2, 14, LM_MID_WW>, LM_MID_WW, lm_piece_lds<LM_MID_WW, 2>());
+  } else {
+    go(lm_head_wide_kernel<E, WT, 9, LM_WW>, LM_WW, wide_lds<E, 9, WT>());
   }
-  if (a.T <= 2 * TILE) {   // four tasks per workgroup (two: 144 against 119 us, the activation fragments of 64 rows are shared by too few)
-    lm_head_wide_kernel<E, 2, 14, LM_MID_WW><<<(tgroups + XCDS - 1) / XCDS * XCDS, LM_MID_WW * WAVE, wide_lds<E, 14, 2>(), st>>>(
-        (const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows, live_word());
-    return;
-  }
-  const int groups = (a.T + WT * TILE - 1) / (WT * TILE);
-  lm_head_wide_kernel<E, WT, 9, LM_WW><<<(tgroups + XCDS - 1) / XCDS * XCDS * groups, LM_WW * WAVE, wide_lds<E, 9, WT>(), st>>>(
-      (const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows, live_word());
 }
 void launch_lm_head_wide(bool bf16, const LmArgs& a, hipStream_t st) {
   if (bf16) launch_lm_wide_t<bf16_t>(a, st);
@@ -430,12 +531,18 @@ void launch_lm_head_wide(bool bf16, const LmArgs& a, hipStream_t st) {
 
 bool configure_wide() {
   auto opt_in = [](const void* f, int bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; };
-  const void* many[4] = {(const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 10, GateUp<bf16_t>>,
+  const void* many[8] = {(const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 10, GateUp<bf16_t>>,
                          (const void*)expert_many_kernel<float, WT, EXPERT_WW, 10, GateUp<float>>,
                          (const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 11, Down<bf16_t>>,
-                         (const void*)expert_many_kernel<float, WT, EXPERT_WW, 11, Down<float>>};
+                         (const void*)expert_many_kernel<float, WT, EXPERT_WW, 11, Down<float>>,
+                         (const void*)expert_pieces_kernel<bf16_t, 2, GateUp<bf16_t>>, (const void*)expert_pieces_kernel<float, 2, GateUp<float>>,
+                         (const void*)expert_pieces_kernel<bf16_t, 2, Down<bf16_t>>, (const void*)expert_pieces_kernel<float, 2, Down<float>>};
   for (const void* f : many)
     if (!opt_in(f, (int)many_lds<EXPERT_WW>())) return false;
+  const void* pieces[4] = {(const void*)lm_head_wide_kernel<bf16_t, 1, 15, LM_PIECE_WW>, (const void*)lm_head_wide_kernel<float, 1, 15, LM_PIECE_WW>,
+                           (const void*)lm_head_wide_kernel<bf16_t, 2, 14, LM_PIECE_WW>, (const void*)lm_head_wide_kernel<float, 2, 14, LM_PIECE_WW>};
+  for (const void* f : pieces)
+    if (!opt_in(f, 128 * 1024)) return false;
   return opt_in((const void*)lm_head_wide_kernel<bf16_t, WT, 9, LM_WW>, 128 * 1024) &&
          opt_in((const void*)lm_head_wide_kernel<float, WT, 9, LM_WW>, 128 * 1024);
 }
