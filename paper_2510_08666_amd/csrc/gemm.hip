@@ -924,44 +924,44 @@ template <typename E> static bool configure_smooth() {
 // Router.  The single weight task holds experts 0-31 (tile 0) and 32-63 (tile 1); per token group its K range is
 // shared by `slices` workgroups of KW waves exactly as in the split-K kernel above.  The workgroup that holds the
 // complete sums turns them into logits[token][expert] (times the row's 1/rms, which it derives from the per-task
-// sums of squares the output projection left), then groups of 16 lanes (4 experts per lane) take one token each
+// sums of squares the output projection left), then groups of 16 or 8 lanes take one token each
 // through softmax and the k selection rounds (ties to the lower expert id).  With a single token group the same
 // workgroup goes on to build the token->expert permutation.
 // ------------------------------------------------------------------------------------------------
 // Cross-lane moves inside rows of 16 lanes on the data-parallel-primitive path (no LDS round trip).  The four
-// controls below form a butterfly: after them every lane of a 16-lane group holds the group's result, provided
-// the combining step is symmetric.
+// controls below form a butterfly: after them (the first three) every lane of a 16-lane (8-lane) group holds the group's
+// result, provided the combining step is symmetric.
 template <int CTRL> __device__ inline int dpp_i(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
 template <int CTRL> __device__ inline float dpp_f(float v) { return __int_as_float(dpp_i<CTRL>(__float_as_int(v))); }
 constexpr int DPP_SWAP1 = 0xB1;         // quad_perm [1,0,3,2]
 constexpr int DPP_SWAP2 = 0x4E;         // quad_perm [2,3,0,1]
 constexpr int DPP_HALF_MIRROR = 0x141;  // lane i <- lane 7-i of its group of 8
 constexpr int DPP_MIRROR = 0x140;       // lane i <- lane 15-i of its row
-__device__ inline float group16_max(float v) {
+// L (8 or 16) lanes form a group; every lane ends with the same bits.
+template <int L> __device__ inline float group_max(float v) {
   v = fmaxf(v, dpp_f<DPP_SWAP1>(v));
   v = fmaxf(v, dpp_f<DPP_SWAP2>(v));
   v = fmaxf(v, dpp_f<DPP_HALF_MIRROR>(v));
-  return fmaxf(v, dpp_f<DPP_MIRROR>(v));
+  return L == 16 ? fmaxf(v, dpp_f<DPP_MIRROR>(v)) : v;
 }
-// Sum over the group in a fixed tree; every lane ends with the same bits (each step adds the same two values on
-// both sides, and float addition commutes).
-__device__ inline float group16_sum(float v) {
+// Sum over the group in a fixed tree (each step adds the same two values on both sides, and float addition commutes).
+template <int L> __device__ inline float group_sum(float v) {
   v += dpp_f<DPP_SWAP1>(v);
   v += dpp_f<DPP_SWAP2>(v);
   v += dpp_f<DPP_HALF_MIRROR>(v);
-  return v + dpp_f<DPP_MIRROR>(v);
+  return L == 16 ? v + dpp_f<DPP_MIRROR>(v) : v;
 }
-__device__ inline int group16_min(int v) {
+template <int L> __device__ inline int group_min(int v) {
   v = min(v, dpp_i<DPP_SWAP1>(v));
   v = min(v, dpp_i<DPP_SWAP2>(v));
   v = min(v, dpp_i<DPP_HALF_MIRROR>(v));
-  return min(v, dpp_i<DPP_MIRROR>(v));
+  return L == 16 ? min(v, dpp_i<DPP_MIRROR>(v)) : v;
 }
 // Largest value of the group and the lowest id that holds it: the largest value first, then the lowest id among
 // the lanes whose own best equals it (two plain butterflies instead of one with a compound comparison).
-__device__ inline void group16_argmax(float& bv, int& bi) {
-  const float mx = group16_max(bv);
-  bi = group16_min(bv == mx ? bi : 0x7fffffff);
+template <int L> __device__ inline void group_argmax(float& bv, int& bi) {
+  const float mx = group_max<L>(bv);
+  bi = group_min<L>(bv == mx ? bi : 0x7fffffff);
   bv = mx;
 }
 
@@ -1130,41 +1130,44 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
   }
   __syncthreads();
   TRACE_MARK(3, 3);
-  // 16 lanes per token, 4 consecutive experts per lane
-  const int grp = threadIdx.x >> 4, sub = threadIdx.x & 15;
-  for (int tl = grp; tl < NTOK; tl += NTHREADS / 16) {
-    float p[4];
+  // 16 lanes per token with 4 consecutive experts each; with 64 tokens 8 lanes and 8 experts, so that one pass does
+  // (two passes of 32 tokens: 3.3 us).  A lane can keep one of the at most eight selections either way.
+  constexpr int LPT = NTHREADS / NTOK >= 16 ? 16 : 8, EPL = MAX_EXPERTS / LPT;
+  static_assert(LPT >= MAX_TOPK, "lane j keeps the j-th selection");
+  const int grp = threadIdx.x / LPT, sub = threadIdx.x % LPT;
+  for (int tl = grp; tl < NTOK; tl += NTHREADS / LPT) {
+    float p[EPL];
     float m = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      p[i] = 4 * sub + i < n_exp ? s_logit[tl * LOGIT_STRIDE + 4 * sub + i] : -INFINITY;
+    for (int i = 0; i < EPL; ++i) {
+      p[i] = EPL * sub + i < n_exp ? s_logit[tl * LOGIT_STRIDE + EPL * sub + i] : -INFINITY;
       m = fmaxf(m, p[i]);
     }
-    m = group16_max(m);
+    m = group_max<LPT>(m);
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      p[i] = 4 * sub + i < n_exp ? expf(p[i] - m) : 0.f;
+    for (int i = 0; i < EPL; ++i) {
+      p[i] = EPL * sub + i < n_exp ? expf(p[i] - m) : 0.f;
       sum += p[i];
     }
-    const float inv = 1.f / group16_sum(sum);
+    const float inv = 1.f / group_sum<LPT>(sum);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = 4 * sub + i < n_exp ? p[i] * inv : -1.f;
+    for (int i = 0; i < EPL; ++i) p[i] = EPL * sub + i < n_exp ? p[i] * inv : -1.f;
     float wsel = 0.f, sel_sum = 0.f;   // lane j of the group keeps the j-th selection
     int isel = 0;
     for (int j = 0; j < top_k; ++j) {
       float bv = -1.f;
       int bi = 0x7fffffff;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < EPL; ++i)
         if (p[i] > bv) {               // ids ascend with i: strict '>' keeps the lowest id
           bv = p[i];
-          bi = 4 * sub + i;
+          bi = EPL * sub + i;
         }
-      group16_argmax(bv, bi);
+      group_argmax<LPT>(bv, bi);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (4 * sub + i == bi) p[i] = -1.f;
+      for (int i = 0; i < EPL; ++i)
+        if (EPL * sub + i == bi) p[i] = -1.f;
       if (sub == j) {
         wsel = bv;
         isel = bi;
