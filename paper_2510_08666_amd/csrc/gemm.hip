@@ -783,9 +783,10 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st) {
 // (32 tasks at hidden 2048), so the launch is filled by cutting the contraction: a workgroup takes SMOOTH_TASKS tasks,
 // up to WT token tiles and one K slice, which its two teams of waves halve (as in gemm_dense_kernel), and leaves its
 // sums in part[slice][token][feature]; smooth_reduce_kernel adds the slices in order and writes the rows of masked
-// positions.  Bound: the stream of the transposed embedding matrix (644 MB at vocabulary 157184).  The activation
-// fragments of a slice go through LDS once per SMOOTH_TASKS tasks: in the split-K form, where every wave fetched its own,
-// they took as many of a compute unit's outstanding requests as the weights (32 tokens: 149 us, 4.3 TB/s), and above
+// positions.  A single slice (many tokens, or a vocabulary smaller than two rows of features) writes them itself.
+// Bound: the stream of the transposed embedding matrix (644 MB at vocabulary 157184; 32 tokens: 149 -> 123 us, 5.2 TB/s).
+// The activation fragments of a slice go through LDS once per SMOOTH_TASKS tasks: in the split-K form, where every wave
+// fetched its own, they took as many of a compute unit's outstanding requests as the weights (4.3 TB/s), and above
 // 64 tokens the unsliced shared-operand form had 24 workgroups at 160 tokens.
 // Workgroup i = die (i % 8), turn (i / 8): the token groups of one (task group, slice) are consecutive turns of one
 // die and share its weights in the L2; slices vary fastest over the dies, so that a die's task groups share the
@@ -802,6 +803,8 @@ template <typename E, int WT, int KID>
 __global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partial_kernel(const E* __restrict__ W, int ksteps,
                                                                                        const E* __restrict__ B, int T, int H,
                                                                                        int n_slices, float* __restrict__ part,
+                                                                                       const uint64_t* __restrict__ mask, int block_len,
+                                                                                       float* __restrict__ delta,
                                                                                        const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   typedef typename ET<E>::vec vec;
@@ -850,16 +853,27 @@ __global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partia
     const int tok = tok0 + t * TILE + col;
     if (t < nt && tok < T) {
       float* out = part + ((int64_t)slice * T + tok) * H + (2 * task) * TILE;
+      const bool wanted = n_slices > 1 || ((mask[tok / block_len] >> (tok % block_len)) & 1ull);
+      float* row = delta + (int64_t)tok * H + (2 * task) * TILE;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
+        if (!wanted) continue;
         f32x4 a, b;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           a[i] = acc0[t][4 * g + i] + r[(t * 32 + 4 * g + i) * WAVE];
           b[i] = acc1[t][4 * g + i] + r[(t * 32 + 16 + 4 * g + i) * WAVE];
         }
-        *reinterpret_cast<f32x4*>(out + acc_row(4 * g, half)) = a;
-        *reinterpret_cast<f32x4*>(out + TILE + acc_row(4 * g, half)) = b;
+        if (n_slices > 1) {
+          *reinterpret_cast<f32x4*>(out + acc_row(4 * g, half)) = a;
+          *reinterpret_cast<f32x4*>(out + TILE + acc_row(4 * g, half)) = b;
+        } else {           // the caller's buffer: only 4-byte alignment is known
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            row[acc_row(4 * g, half) + i] = a[i];
+            row[TILE + acc_row(4 * g, half) + i] = b[i];
+          }
+        }
       }
     }
   }
@@ -899,7 +913,8 @@ template <typename E, int WT, int KID> static void launch_smooth_as(const Smooth
   const int units = (tgroups * slices + 7) / 8 * 8;
   float* part = a.logits;
   smooth_partial_kernel<E, WT, KID><<<units * groups, SMOOTH_TASKS * SMOOTH_KH * WAVE, smooth_lds<E, KID, WT>(), st>>>(
-      (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H, slices, part, live_word());
+      (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H, slices, part, a.mask, a.block_len, a.delta, live_word());
+  if (slices == 1) return;
   const int64_t quads = (int64_t)a.T * a.H / 4;
   smooth_reduce_kernel<<<(unsigned)((quads + 255) / 256), 256, 0, st>>>(part, slices, a.T, a.H, a.mask, a.block_len, a.delta,
                                                                         live_word());

@@ -4,7 +4,8 @@
 // accumulators in registers (no split of K, no fold), and the activation fragments go through LDS once per
 // workgroup.  With hundreds of token rows a wave that fetched its own activation operands would pull several
 // times more bytes through the L2 than it streams weights from HBM; with few rows it still keeps the compute
-// unit's address path busy with 64 separate rows per load.  Above 64 tokens: 8 tasks x 128 rows per workgroup.
+// unit's address path busy with 64 separate rows per load.  Work that would leave most of the chip idle (a few items
+// beyond a full round, small models) goes out in pieces instead: one task per workgroup, K cut over its waves.
 #include "kernels.hpp"
 #include "wide_stream.hpp"
 
