@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "common.hpp"
+#include "lm_plan.hpp"
 
 namespace dinfer {
 
@@ -238,8 +239,6 @@ struct LmArgs {
 };
 // rows[0] = number of undecided positions over all sequences, rows[1 ..] = their token rows n_seq-major, ascending.
 void launch_lm_rows(const uint64_t* mask, int n_seq, int block_len, int32_t* rows, hipStream_t st);
-int lm_head_most_parts(int V);     // upper bound of partials per token row (workspace sizing)
-int lm_head_parts(int V, int T);   // partials per token row launch_lm_head writes for T tokens
 void launch_lm_head(bool bf16, const LmArgs& a, hipStream_t st);        // picks the form by a.T
 void launch_lm_head_wide(bool bf16, const LmArgs& a, hipStream_t st);
 // stats (may be null): [T][2] = the row's largest logit and sum exp(z - max)

@@ -1,0 +1,50 @@
+// How the LM head deals the vocabulary out to workgroups, and with it how many softmax partials it leaves per token row.
+// Plain host C++: the launcher, the kernel (as an argument) and the merge behind it all take the numbers from here.
+#pragma once
+
+namespace dinfer {
+
+constexpr int LM_TASK_IDS = 64;                 // vocabulary ids of a task
+constexpr int LM_CUS = 256;                     // compute units
+// Tasks per workgroup (one per wave).  Up to 32 tokens all workgroups are resident at once and the dispatcher deals them
+// evenly, so a launch lasts as long as the compute units with one workgroup more than the others: 614 workgroups of
+// four tasks put 3 MB on some units and 2 MB on others (112 us), 1228 of two tasks 2.5 or 2 MB (108 us).  Above 64 tokens
+// eight waves share the activation fragments of 128 rows (four in the LM head at 512 tokens: 450 us against 352).
+constexpr int LM_SMALL_WW = 2, LM_MID_WW = 4;   // up to 32, up to 64 tokens
+constexpr int LM_WW = 8;                        // more tokens
+constexpr int LM_PIECE_WW = 8;                  // waves per task of a small vocabulary
+constexpr int LM_SMALL_T = 32, LM_MID_T = 64;
+
+// Workgroups 0 .. whole-1 take ww consecutive tasks each (the last one possibly fewer), together the tasks in front of
+// first_piece; every task from there on has a workgroup of its own, which cuts the K range over its waves.
+struct LmPlan {
+  int tasks;          // of the vocabulary
+  int ww;             // tasks per whole group, or waves per task where all are pieces
+  int whole;          // whole groups
+  int first_piece;    // = tasks where there are no pieces
+  int parts;          // partials per token row: one per workgroup up to LM_MID_T tokens, one per wave above
+};
+//  - Few tasks (one per compute unit or less): all in pieces, since a wave alone with a task is bound by its chain of
+//    loads and matrix instructions (4096 ids of float32, hidden 256: 16.5 -> 11 us at 32 tokens, 27 -> 13.4 at 64).
+//  - 33 to 64 tokens: two workgroups of four waves fill a compute unit, so the groups beyond 512 would begin a second
+//    round of the chip; they go out in pieces where there are some and they are less than half a round (157184 ids:
+//    126 -> 124.5 us).
+//  - Up to 32 tokens: three waves per SIMD (168 registers) hold all workgroups of 157184 ids at once (114 -> 108 us
+//    against two per SIMD, where 1024 of 1228 fit).  More than 64 tokens: whole groups.
+inline LmPlan lm_plan(int V, int T) {
+  LmPlan p;
+  p.tasks = (V + LM_TASK_IDS - 1) / LM_TASK_IDS;
+  const bool few = T <= LM_MID_T && p.tasks <= LM_CUS;
+  p.ww = few ? LM_PIECE_WW : T <= LM_SMALL_T ? LM_SMALL_WW : T <= LM_MID_T ? LM_MID_WW : LM_WW;
+  p.whole = few ? 0 : (p.tasks + p.ww - 1) / p.ww;
+  const int round = LM_CUS * (8 / LM_MID_WW), over = p.whole % round;
+  if (p.ww == LM_MID_WW && p.whole > round && over > 0 && over < round / 2) p.whole -= over;
+  p.first_piece = p.whole * p.ww < p.tasks ? p.whole * p.ww : p.tasks;
+  p.parts = T <= LM_MID_T ? p.whole + p.tasks - p.first_piece : p.whole * p.ww;
+  return p;
+}
+// Upper bound of the partials per token row, whatever the token count (workspace sizing): one per task, rounded up.
+inline int lm_head_most_parts(int V) { return ((V + LM_TASK_IDS - 1) / LM_TASK_IDS + LM_WW - 1) / LM_WW * LM_WW; }
+inline int lm_head_parts(int V, int T) { return lm_plan(V, T).parts; }
+
+}  // namespace dinfer

@@ -18,13 +18,8 @@ constexpr int WT = 4;      // token tiles per workgroup above 64 tokens
 // GEMMs, 131 to 134 against 120 microseconds; four waves in the LM head, 450 against 352.)
 constexpr int EXPERT_WW = 8, EXPERT_PRE = 2;
 constexpr int EXPERT_CUS = 256;   // compute units; eight waves of the many-token expert GEMMs fill one
-constexpr int LM_WW = 8, LM_PRE = 2;
-// Tasks per workgroup of the LM head up to 32 tokens.  All workgroups of these launches are resident at once and
-// the dispatcher deals them evenly, so a launch lasts as long as the compute units with one workgroup more than the
-// others: 614 workgroups of four tasks put 3 MB on some units and 2 MB on others (112 us), 1228 of two tasks 2.5 or
-// 2 MB (108 us).
-constexpr int LM_SMALL_WW = 2, LM_MID_WW = 4;   // up to 32, up to 64 tokens
-constexpr int LM_PIECE_WW = 8;                  // waves per task of a small vocabulary
+constexpr int LM_PRE = 2;         // (tasks per workgroup of the LM head: lm_plan.hpp)
+static_assert(LM_SMALL_T == TILE && LM_MID_T == 2 * TILE, "the forms of the LM head take one, two and four token tiles");
 constexpr int XCDS = 8;      // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
 
 // ------------------------------------------------------------------------------------------------
@@ -314,7 +309,7 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
                                                                   RowNorm norm, int T, int H, int V,
                                                                   float scale, float* __restrict__ part,
                                                                   float* __restrict__ logits_out,
-                                                                  const int32_t* __restrict__ rows, int n_whole,
+                                                                  const int32_t* __restrict__ rows, LmPlan plan,
                                                                   const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   typedef typename ET<E>::vec vec;
@@ -331,13 +326,12 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
   const int tiles = (n_rows + TILE - 1) / TILE, groups = (tiles + WT - 1) / WT, per_group = (tiles + groups - 1) / groups;
   const int turn = blockIdx.x / XCDS;
   const int tgroup = (turn / groups) * XCDS + blockIdx.x % XCDS;
-  const int n_tasks = (V + 2 * TILE - 1) / (2 * TILE);
+  const int n_tasks = plan.tasks;
   // Partials of a row lie next to each other for the merge kernel (a stride of 8 KB apart it took 27 us for 512 tokens).
   // Up to 64 tokens a workgroup leaves one per row, more tokens: its waves one each (folding them there costs the
   // launch 8 us at 512 tokens, more than the merge saves).
   constexpr bool FOLD = KID != 9;
-  const int n_groups = min(n_whole, (n_tasks + WW - 1) / WW), first_piece = min(n_tasks, n_groups * WW);
-  const int n_parts = FOLD ? n_groups + n_tasks - first_piece : n_groups * WW;
+  const int n_groups = plan.whole, first_piece = plan.first_piece, n_parts = plan.parts;
   if (tgroup >= n_groups + n_tasks - first_piece) return;   // uniform over the workgroup
   LmStat* s_stat = reinterpret_cast<LmStat*>(lds_raw);   // [WW][WT * TILE], once the fragments are done with
   static_assert(WW * WT * TILE * sizeof(LmStat) <= wide_lds<E, KID, WT>(), "the statistics fit the staging area");
@@ -474,34 +468,6 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
   }
 }
 
-// How the vocabulary is dealt out: task groups of ww tasks taken whole, one task per wave, and the tasks behind them one
-// per workgroup, with the K range cut over its waves.
-//  - Few tasks (one per compute unit or less): all in pieces, since a wave alone with a task is bound by its chain of
-//    loads and matrix instructions (4096 ids of float32, hidden 256: 16.5 -> 11 us at 32 tokens, 27 -> 13.4 at 64).
-//  - 33 to 64 tokens: two workgroups of four waves fill a compute unit, so the groups beyond 512 would begin a second
-//    round of the chip; they go out in pieces where they are less than half a round (157184 ids: 126 -> 124.5 us).
-//  - Up to 32 tokens: three waves per SIMD (168 registers) hold all workgroups of 157184 ids at once (114 -> 108 us
-//    against two per SIMD, where 1024 of 1228 fit).  More than 64 tokens: whole groups.
-struct LmPlan {
-  int ww, whole, pieces;
-};
-static LmPlan lm_plan(int V, int T) {
-  const int tasks = (V + 63) / 64;
-  if (T <= 2 * TILE && tasks <= EXPERT_CUS) return LmPlan{LM_PIECE_WW, 0, tasks};
-  const int ww = T <= TILE ? LM_SMALL_WW : T <= 2 * TILE ? LM_MID_WW : LM_WW, groups = (tasks + ww - 1) / ww;
-  const int round = EXPERT_CUS * (8 / LM_MID_WW);
-  if (ww == LM_MID_WW && groups > round && groups % round < round / 2) {
-    const int whole = groups / round * round;
-    return LmPlan{ww, whole, tasks - whole * ww};
-  }
-  return LmPlan{ww, groups, 0};
-}
-int lm_head_parts(int V, int T) {
-  const LmPlan p = lm_plan(V, T);
-  return T <= 2 * TILE ? p.whole + p.pieces : p.whole * LM_WW;
-}
-int lm_head_most_parts(int V) { return ((V + 63) / 64 + LM_WW - 1) / LM_WW * LM_WW; }   // one per task, rounded up: the most
-
 // Up to 64 tokens: one or two token tiles per workgroup and both activation planes (trace ids 15, 14): there the weight
 // stream is the bound, and sharing the activation fragments relieves the address unit, which would otherwise take every
 // lane's own activation row one by one.  (33 to 64 tokens in workgroups of two tasks: 144 against 119 us, the fragments
@@ -510,10 +476,10 @@ template <int WW, int WT> constexpr size_t lm_piece_lds() { return (size_t)WW * 
 template <typename E> static void launch_lm_wide_t(const LmArgs& a, hipStream_t st) {
   const LmPlan p = lm_plan(a.V, a.T);
   const int groups = a.T <= 2 * TILE ? 1 : (a.T + WT * TILE - 1) / (WT * TILE);
-  const int wgs = (p.whole + p.pieces + XCDS - 1) / XCDS * XCDS * groups;
+  const int wgs = (p.whole + p.tasks - p.first_piece + XCDS - 1) / XCDS * XCDS * groups;
   auto go = [&](auto kernel, int ww, size_t lds) {
     kernel<<<wgs, ww * WAVE, lds, st>>>((const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows,
-                                        p.whole, live_word());
+                                        p, live_word());
   };
   if (a.T <= TILE) {
     if (p.ww == LM_PIECE_WW) go(lm_head_wide_kernel<E, 1, 15, LM_PIECE_WW>, LM_PIECE_WW, lm_piece_lds<LM_PIECE_WW, 1>());

@@ -1,0 +1,53 @@
+"""The LM head's division of the vocabulary (csrc/lm_plan.hpp), compiled for the host: at every vocabulary size the whole
+groups and the pieces cover each task exactly once, and the number of partials the merge reads per row is the number of
+workgroups (above 64 tokens: waves) that write one."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = """
+#include "lm_plan.hpp"
+extern "C" void plans(int T, int v0, int n, int* out) {
+  for (int i = 0; i < n; ++i) {
+    const dinfer::LmPlan p = dinfer::lm_plan(v0 + i, T);
+    int* o = out + 6 * i;
+    o[0] = p.tasks, o[1] = p.ww, o[2] = p.whole, o[3] = p.first_piece, o[4] = p.parts, o[5] = dinfer::lm_head_most_parts(v0 + i);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    d = tmp_path_factory.mktemp("lm_plan")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "shim.so")
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC",
+                           "-I" + os.path.join(ROOT, "paper_2510_08666_amd", "csrc"), str(d / "shim.cpp"), "-o", so])
+    lib = ctypes.CDLL(so)
+
+    def table(T, v0, n):
+        out = np.empty((n, 6), dtype=np.int32)
+        lib.plans(T, v0, n, out.ctypes.data_as(ctypes.c_void_p))
+        return out.T.astype(np.int64)
+    return table
+
+
+@pytest.mark.parametrize("T", [1, 32, 33, 48, 64, 65, 4096])
+def test_every_vocabulary(plans, T):
+    tasks, ww, whole, first, parts, most = plans(T, 2, 1 << 20)
+    vocab = np.arange(2, 2 + (1 << 20))
+    ok = tasks == -(-vocab // 64)
+    ok &= (first == np.minimum(tasks, whole * ww)) & (whole >= 0)      # the whole groups take the tasks in front of first
+    ok &= (whole == 0) | ((whole - 1) * ww < tasks)                    # none of them is empty
+    pieces = tasks - first                                             # the others one workgroup each
+    ok &= pieces >= 0
+    ok &= parts == (whole + pieces if T <= 64 else whole * ww)
+    ok &= (parts <= most) & (parts > 0)
+    if T > 64:
+        ok &= pieces == 0
+    assert ok.all(), "vocabulary %d" % vocab[~ok][0]
