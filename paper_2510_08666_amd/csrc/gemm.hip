@@ -1167,7 +1167,11 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
     }
     const float inv = 1.f / group_sum<LPT>(sum);
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) p[i] = EPL * sub + i < n_exp ? p[i] * inv : -1.f;
+    for (int i = 0; i < EPL; ++i) {
+      // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its
+      // expert ids would be no ids, and the permutation would index with them
+      p[i] = EPL * sub + i < n_exp ? fmaxf(p[i] * inv, 0.f) : -1.f;
+    }
     float wsel = 0.f, sel_sum = 0.f;   // lane j of the group keeps the j-th selection
     int isel = 0;
     for (int j = 0; j < top_k; ++j) {
