@@ -359,8 +359,8 @@ __global__ __launch_bounds__(ATTN_WAVES * WAVE) void attention_kernel(const E* _
 // keeps its queries (both planes) and output in registers, nothing is folded, and two workgroups of four waves share
 // a compute unit, so that one multiplies while the other waits at its barrier or works on its softmax.
 // ------------------------------------------------------------------------------------------------
-constexpr int ROWS_MIN_WGS = 256;
-constexpr int ROWS_WAVES = 4, ROWS_TOK = ROWS_WAVES * TILE;
+constexpr int ROWS_TOK = ROWS_WAVES * TILE;
+static_assert(ROWS_TILE == TILE, "attn_rows_groups counts tiles of this size");
 
 template <int HD>
 __global__ __launch_bounds__(ROWS_WAVES * WAVE, 2) void attention_rows_kernel(
@@ -526,15 +526,6 @@ template <typename E, int HD> static void launch_attention_t(const AttnArgs& a, 
       a.tickets, (E*)a.out, a.T, a.n_qtiles, fetch ? a.pf : L2Prefetch{nullptr, 0, 0}, live_word());
 }
 
-// Workgroups of the rows form per head, or 0 where the splitting form takes the call.  A wave of the rows form walks all
-// keys alone, so it needs a launch that fills the chip without splitting them (one prompt, 16 heads, rows / splitting
-// form in microseconds: 1024 tokens, 128 workgroups, 45 / 37; 2048 tokens, 256 workgroups, 89 / 103; 4096 tokens 266 /
-// 345; prompts of 1811 + 333 + 825 + 1318, 576 workgroups, 136 / 169), and queries for three of its four waves.
-static int rows_groups(const AttnArgs& a) {
-  int groups = 0;
-  for (int s = 0; s < a.span.n_seq; ++s) groups += (a.span.off[s + 1] - a.span.off[s] + ROWS_TOK - 1) / ROWS_TOK;
-  return groups * a.geom.n_heads >= ROWS_MIN_WGS && 4 * a.n_qtiles >= 3 * ROWS_WAVES * groups ? groups : 0;
-}
 template <int HD> constexpr size_t rows_lds() { return (size_t)2 * 4 * (HD / ET<bf16_t>::KS) * WAVE * 16; }
 template <int HD> static void launch_attention_rows(const AttnArgs& a, int groups, hipStream_t st) {
   attention_rows_kernel<HD><<<dim3(a.geom.n_heads, groups), ROWS_WAVES * WAVE, rows_lds<HD>(), st>>>(
@@ -556,7 +547,7 @@ bool configure_attention() {
 
 void launch_attention(bool bf16, const AttnArgs& a, hipStream_t st) {
   const int hd = a.geom.head_dim;
-  const int groups = bf16 ? rows_groups(a) : 0;
+  const int groups = bf16 ? attn_rows_groups(a.span.off, a.span.n_seq, a.geom.n_heads, a.from_zero) : 0;
   if (groups > 0) {
     if (hd == 128) launch_attention_rows<128>(a, groups, st);
     else launch_attention_rows<64>(a, groups, st);

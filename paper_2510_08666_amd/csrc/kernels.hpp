@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_plan.hpp"
 #include "common.hpp"
 #include "lm_plan.hpp"
 
@@ -124,6 +125,7 @@ struct AttnArgs {
   int T;
   L2Prefetch pf;            // fetched by extra workgroups of the launch when it has few of its own (see L2Prefetch)
   SeqSpan span;             // tokens of the sequences in this forward
+  bool from_zero;           // every sequence starts at position 0 (prompts): no cached keys in front of its tokens
 };
 size_t attn_part_floats(int n_qtiles, int n_heads, int n_splits, int head_dim);
 void launch_attention(bool bf16, const AttnArgs& a, hipStream_t st);

@@ -2,13 +2,12 @@
 groups and the pieces cover each task exactly once, and the number of partials the merge reads per row is the number of
 workgroups (above 64 tokens: waves) that write one."""
 import ctypes
-import os
-import subprocess
 
 import numpy as np
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+import host_shim
+
 SHIM = """
 #include "lm_plan.hpp"
 extern "C" void plans(int T, int v0, int n, int* out) {
@@ -23,12 +22,7 @@ extern "C" void plans(int T, int v0, int n, int* out) {
 
 @pytest.fixture(scope="module")
 def plans(tmp_path_factory):
-    d = tmp_path_factory.mktemp("lm_plan")
-    (d / "shim.cpp").write_text(SHIM)
-    so = str(d / "shim.so")
-    subprocess.check_call([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-shared", "-fPIC",
-                           "-I" + os.path.join(ROOT, "paper_2510_08666_amd", "csrc"), str(d / "shim.cpp"), "-o", so])
-    lib = ctypes.CDLL(so)
+    lib = host_shim.load(tmp_path_factory.mktemp("lm_plan"), SHIM)
 
     def table(T, v0, n):
         out = np.empty((n, 6), dtype=np.int32)
