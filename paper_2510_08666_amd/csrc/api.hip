@@ -138,7 +138,7 @@ int attn_splits(int n_qtiles, int n_heads, int key_bound) {
 
 struct Workspace {
   size_t cos_tab, sin_tab, tok_seq, tok_pos, seq_nkeys, qtile, x, xn, ssq, ssq_a, tk_part, tickets, tickets_bytes, attn_tickets, attn_tickets_bytes, rinv_f, q, a, attn_part, topk_idx, topk_w, cnt, off,
-      perm, pos_of_pair, work, hist, run_tokens, run_base, n_finished, loop_flags, loop_steps, lm_rows, y, o, lm_part, lm_stats, conf, argmax, total;
+      perm, pos_of_pair, work, hist, run_tokens, run_base, n_finished, loop_flags, loop_steps, lm_rows, y, o, lm_part, smooth_part, lm_stats, conf, argmax, total;
 };
 
 Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
@@ -206,6 +206,8 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.y = cv.take(planes * T * K * I * es);
   w.o = cv.take(T * K * H * 4);
   w.lm_part = cv.take((size_t)lm_head_most_parts(c.vocab) * T * 4 * 4);
+  const bool bf16 = c.dtype == DINFER_BF16;
+  w.smooth_part = cv.take(smooth_part_bytes(H, c.vocab, smooth_kpad(bf16, c.vocab) / (bf16 ? ET<bf16_t>::KS : ET<float>::KS), max_tokens));
   w.lm_stats = cv.take(T * 2 * 4);
   w.conf = cv.take(T * 4);
   w.argmax = cv.take(T * 4);
@@ -671,7 +673,8 @@ static int smooth_impl(dinfer_ctx* c, int32_t n_seq, int32_t block_len, int32_t*
     launch_lm_head(c->bf16, la, st);
   }
   launch_lm_merge(la.part, lm_head_parts(f.vocab, T), T, d_conf, d_argmax, stats, st);
-  SmoothArgs sa{c->weights + c->wm.emb_t, logits, stats, probs, d_mask, block_len, d_delta, T, f.hidden, f.vocab};
+  SmoothArgs sa{c->weights + c->wm.emb_t, logits, stats, probs, d_mask, block_len, d_delta, T, f.hidden, f.vocab,
+                at<float>(c->ws, c->wsm.smooth_part)};
   launch_expected_embedding(c->bf16, sa, st);
   launch_commit(d_conf, d_argmax, n_seq, block_len, block_len, 0, d_block_tokens, d_mask, commit_rule(decode), d_n_committed,
                 nullptr, nullptr, st, next_live, steps);

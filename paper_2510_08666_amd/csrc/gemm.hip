@@ -783,7 +783,7 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st) {
 // (32 tasks at hidden 2048), so the launch is filled by cutting the contraction: a workgroup takes SMOOTH_TASKS tasks,
 // up to WT token tiles and one K slice, which its two teams of waves halve (as in gemm_dense_kernel), and leaves its
 // sums in part[slice][token][feature]; smooth_reduce_kernel adds the slices in order and writes the rows of masked
-// positions.  A single slice (many tokens, or a vocabulary smaller than two rows of features) writes them itself.
+// positions.  A single slice (many tokens) writes them itself.
 // Bound: the stream of the transposed embedding matrix (644 MB at vocabulary 157184; 32 tokens: 149 -> 123 us, 5.2 TB/s).
 // The activation fragments of a slice go through LDS once per SMOOTH_TASKS tasks: in the split-K form, where every wave
 // fetched its own, they took as many of a compute unit's outstanding requests as the weights (4.3 TB/s), and above
@@ -792,7 +792,8 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st) {
 // die and share its weights in the L2; slices vary fastest over the dies, so that a die's task groups share the
 // probabilities of its slices.
 // ------------------------------------------------------------------------------------------------
-constexpr int SMOOTH_TASKS = 4, SMOOTH_KH = 2, SMOOTH_PRE = 2, SMOOTH_WGS = 256;
+constexpr int SMOOTH_PRE = 2;
+static_assert(SMOOTH_TILE == TILE && SMOOTH_CHUNK == WKC, "smooth_plan counts in these units");
 template <typename E, int KID, int WT> constexpr size_t smooth_lds() {
   const size_t stage = SMOOTH_KH * wide_lds<E, KID, WT>();
   const size_t fold = (size_t)(SMOOTH_KH - 1) * SMOOTH_TASKS * 2 * WT * 16 * WAVE * 4;
@@ -901,18 +902,12 @@ int smooth_kpad(bool bf16, int V) {
   const int unit = (bf16 ? 16 : 8) * 512;
   return (V + unit - 1) / unit * unit;
 }
-template <typename E, int WT, int KID> static void launch_smooth_as(const SmoothArgs& a, int Kpad, hipStream_t st) {
-  const int tgroups = (a.H / 64 + SMOOTH_TASKS - 1) / SMOOTH_TASKS, tiles = (a.T + TILE - 1) / TILE;
-  const int groups = (tiles + WT - 1) / WT, pairs = Kpad / ET<E>::KS / (WKC * SMOOTH_KH);
-  // About one workgroup per compute unit (two waves on every SIMD); a multiple of eight slices keeps a slice on one
-  // die.  The partial sums live where the logits were (T * V floats), which the probabilities have replaced.
-  int slices = SMOOTH_WGS / (tgroups * groups);
-  slices = slices < a.V / a.H ? slices : a.V / a.H;
-  slices = slices < pairs ? slices : pairs;
-  slices = single_slice() || slices < 1 ? 1 : slices >= 8 ? slices / 8 * 8 : slices;
-  const int units = (tgroups * slices + 7) / 8 * 8;
-  float* part = a.logits;
-  smooth_partial_kernel<E, WT, KID><<<units * groups, SMOOTH_TASKS * SMOOTH_KH * WAVE, smooth_lds<E, KID, WT>(), st>>>(
+template <typename E, int WT, int KID> static void launch_smooth_as(const SmoothArgs& a, int Kpad, const SmoothPlan& p, hipStream_t st) {
+  // the partial sums live where the logits were (T * V floats), which the probabilities have replaced, or if these leave
+  // too little room in the workspace
+  const int slices = single_slice() ? 1 : p.slices, units = (p.task_groups * slices + 7) / 8 * 8;
+  float* part = p.in_logits ? a.logits : a.part;
+  smooth_partial_kernel<E, WT, KID><<<units * p.token_groups, SMOOTH_TASKS * SMOOTH_KH * WAVE, smooth_lds<E, KID, WT>(), st>>>(
       (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H, slices, part, a.mask, a.block_len, a.delta, live_word());
   if (slices == 1) return;
   const int64_t quads = (int64_t)a.T * a.H / 4;
@@ -920,9 +915,10 @@ template <typename E, int WT, int KID> static void launch_smooth_as(const Smooth
                                                                         live_word());
 }
 template <typename E> static void launch_smooth_t(const SmoothArgs& a, int Kpad, hipStream_t st) {
-  if (a.T <= TILE) launch_smooth_as<E, 1, 23>(a, Kpad, st);
-  else if (a.T <= 2 * TILE) launch_smooth_as<E, 2, 23>(a, Kpad, st);
-  else launch_smooth_as<E, 4, 24>(a, Kpad, st);
+  const SmoothPlan p = smooth_plan(a.H, a.V, Kpad / ET<E>::KS, a.T);
+  if (p.wt == 1) launch_smooth_as<E, 1, 23>(a, Kpad, p, st);
+  else if (p.wt == 2) launch_smooth_as<E, 2, 23>(a, Kpad, p, st);
+  else launch_smooth_as<E, 4, 24>(a, Kpad, p, st);
 }
 void launch_expected_embedding(bool bf16, const SmoothArgs& a, hipStream_t st) {
   const int Kpad = smooth_kpad(bf16, a.V);

@@ -7,6 +7,7 @@
 #include "attn_plan.hpp"
 #include "common.hpp"
 #include "lm_plan.hpp"
+#include "smooth_plan.hpp"
 
 namespace dinfer {
 
@@ -147,7 +148,7 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st);
 
 // Iteration smoothing: delta[t] = softmax(logits[t]) . W_emb for the rows of positions that are still masked.
 //   probs: scratch for the probabilities as a k-major activation matrix [T][Kpad]; logits [T][V] float32, overwritten
-//   with partial sums;
+//   with partial sums where these fit (smooth_plan);
 //   stats [T][2] = (largest logit, sum exp(z - max)) of every row; w_emb_t: launch_pack_transposed's layout.
 int smooth_kpad(bool bf16, int V);    // the vocabulary rounded up so that every K slice is whole chunks
 struct SmoothArgs {
@@ -159,6 +160,7 @@ struct SmoothArgs {
   int block_len;
   float* delta;             // [T][H] in/out
   int T, H, V;
+  float* part;              // smooth_part_bytes: partial sums for which the logits leave too little room
 };
 void launch_expected_embedding(bool bf16, const SmoothArgs& a, hipStream_t st);
 void launch_prob_planes(bool bf16, const float* logits, const float* stats, int T, int V, int Kpad, void* probs,

@@ -1,0 +1,53 @@
+// How the expected-embedding contraction of iteration smoothing is cut into workgroups.  Plain host C++.
+#pragma once
+#include <stddef.h>
+
+namespace dinfer {
+
+// A workgroup takes SMOOTH_TASKS tasks (64 output features each), one group of token tiles and one K slice, which
+// SMOOTH_KH teams of waves halve; a slice is a whole number of pairs of chunks.
+constexpr int SMOOTH_TASKS = 4, SMOOTH_KH = 2, SMOOTH_WGS = 256, SMOOTH_TILE = 32, SMOOTH_CHUNK = 4;
+// Pairs of chunks a slice has at least: one leaves more partial sums than it saves, eight leave compute units idle
+// (float32, hidden 256, 4096 ids, a step of 32 / 512 tokens: 102.1 / 332 us with one, 101.7 / 338 with two, 107.6 / 355
+// with four, 115.6 / 382 with eight; bf16 hidden 1024, 5000 ids, 64 tokens: 112.4, 108.3, 109.6, 114.4).
+constexpr int SMOOTH_MIN_PAIRS = 2;
+
+struct SmoothPlan {
+  int wt;             // token tiles per workgroup, at most: 1, 2 or 4
+  int task_groups, token_groups;
+  int pairs;          // pairs of chunks in the padded vocabulary
+  int slices;         // 1: the workgroups write the rows themselves
+  bool in_logits;     // the partial sums [slices][T][H] fit where the logits [T][V] were
+};
+// Kpad_steps: k-steps of the padded vocabulary (smooth_kpad).  About one workgroup per compute unit (two waves on every
+// SIMD); a multiple of eight slices keeps a slice on one die.  The number of slices does not follow the room the logits
+// leave: limited to that, 32000 ids at hidden 2048 had eight slices, 64 workgroups (a bf16 step of 32 tokens 167 us, 144
+// with 32 slices; float32 354 and 254).
+inline SmoothPlan smooth_plan(int H, int V, int Kpad_steps, int T) {
+  SmoothPlan p;
+  const int tiles = (T + SMOOTH_TILE - 1) / SMOOTH_TILE;
+  p.wt = tiles <= 2 ? tiles : 4;
+  p.task_groups = (H / 64 + SMOOTH_TASKS - 1) / SMOOTH_TASKS;
+  p.token_groups = (tiles + p.wt - 1) / p.wt;
+  p.pairs = Kpad_steps / (SMOOTH_CHUNK * SMOOTH_KH);
+  int s = SMOOTH_WGS / (p.task_groups * p.token_groups);
+  const int most = p.pairs / SMOOTH_MIN_PAIRS;
+  s = s < most ? s : most;
+  p.slices = s < 1 ? 1 : s >= 8 ? s / 8 * 8 : s;
+  p.in_logits = p.slices <= V / H;
+  return p;
+}
+// Bytes for the partial sums of any forward of up to max_tokens tokens whose logits leave too little room (a vocabulary
+// of few rows of features: 0 at 157184 ids and hidden 2048, 8 MB at 32000).
+inline size_t smooth_part_bytes(int H, int V, int Kpad_steps, int max_tokens) {
+  size_t most = 0;
+  for (int t = SMOOTH_TILE; t < max_tokens + SMOOTH_TILE; t += SMOOTH_TILE) {
+    const int T = t < max_tokens ? t : max_tokens;
+    const SmoothPlan p = smooth_plan(H, V, Kpad_steps, T);
+    const size_t bytes = p.slices > 1 && !p.in_logits ? (size_t)p.slices * T * H * 4 : 0;
+    most = bytes > most ? bytes : most;
+  }
+  return most;
+}
+
+}  // namespace dinfer

@@ -1,5 +1,6 @@
 """The expected-embedding contraction of the smoothing step at the sizes where its form changes (one, two and four token
-tiles, one and several token groups, K slices limited by the vocabulary, a vocabulary of no particular multiple),
+tiles, one and several token groups, one slice, partial sums in place of the logits and in the workspace, a vocabulary
+of no particular multiple),
 against softmax(logits) . W_emb in 64 bits over the logits the same step produced."""
 import numpy as np
 import pytest
@@ -14,7 +15,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n_seq,block,vocab,hidden", [(1, 1, 1001, 256), (1, 32, 5000, 320), (3, 11, 4096, 256),
                                                       (2, 32, 2051, 128), (5, 13, 4096, 256), (4, 32, 1030, 64),
                                                       (3, 43, 4095, 192), (8, 40, 3000, 256), (2, 20, 100, 256),
-                                                      (2, 20, 130, 1024), (3, 43, 700, 512), (20, 64, 4096, 1024)])
+                                                      (2, 20, 130, 1024), (3, 43, 700, 512), (20, 64, 4096, 1024),
+                                                      (20, 60, 1030, 4096)])
 def test_expected_embedding(n_seq, block, vocab, hidden, dtype):
     tiny = di.model_preset("tiny")
     cfg = di.configs.scaled(tiny, n_layers=1, hidden=hidden, vocab=vocab, dtype=dtype, logit_scale=4.0)
