@@ -1,5 +1,6 @@
 """Prompt prefill where attention takes its many-rows form (bf16, at least 256 workgroups of four query tiles): prompt
-lengths at the edges of its key turns (64 keys), query tiles (32) and groups (128), against the oracle."""
+lengths at the edges of its key turns (64 keys), query tiles (32) and groups (128), one prompt of a single turn, against
+the oracle."""
 from dataclasses import replace
 
 import numpy as np
@@ -12,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n_heads,head_dim,lens", [(32, 64, [385, 416, 447, 97]), (32, 128, [384, 353, 129, 200]),
-                                                   (64, 64, [512, 97])])
+                                                   (64, 64, [512, 97]), (64, 64, [500, 40])])
 def test_prefill_rows_form(n_heads, head_dim, lens):
     tiny = di.model_preset("tiny")
     cfg = di.configs.scaled(tiny, hidden=128, n_heads=n_heads, head_dim=head_dim, n_experts=8, moe_inter=64, vocab=500,
