@@ -353,7 +353,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
       launch_router(bf, ra, st);
     }
     ExpertArgs ea{c->weights + lw.gate_up, c->weights + lw.down, xn, rinv_f,
-                  ws + w.y, at<float>(ws, w.o), at<int32_t>(ws, w.cnt), at<int32_t>(ws, w.off),
+                  ws + w.y, at<float>(ws, w.o), at<int32_t>(ws, w.off),
                   at<int32_t>(ws, w.perm), at<int32_t>(ws, w.work), T, H, f.moe_inter, f.n_experts, f.top_k,
                   fused_down ? topk_w : nullptr, topk_idx, at<int32_t>(ws, w.pos_of_pair)};
     {

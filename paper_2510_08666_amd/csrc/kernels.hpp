@@ -210,7 +210,6 @@ struct ExpertArgs {
   const float* rinv;        // [T]
   void* y;                  // [T*k][I] k-major
   float* o;                 // [T*k][H], row = token*top_k + slot (many-token form only)
-  const int32_t* cnt;
   const int32_t* off;
   const int32_t* perm;
   const int32_t* work;      // see RouterArgs

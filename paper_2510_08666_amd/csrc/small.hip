@@ -340,6 +340,8 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
     pos_of_pair[p] = r;
   }
 }
+// The bound that the interface states for a context (dinfer_workspace_bytes); counts and positions are 32-bit and the grid of
+// the expert GEMMs grows with a 128th of the pairs, so the kernels themselves do not need it.
 constexpr int PERMUTE_MAX_PAIRS = 65535;
 int permute_max_pairs() { return PERMUTE_MAX_PAIRS; }
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,

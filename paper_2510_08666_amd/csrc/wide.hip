@@ -247,6 +247,8 @@ int expert_round_items(int E, int n_pairs, int H, int I) {
 }
 
 // KID: trace ids of the forms for up to 32, up to 64, few rows per expert, many rows per expert
+// (Up to 32 tokens the down projection takes its first form, ids 18 and the pieces of one tile, only under the single-slice
+// test switch: expert_down_fused_kernel has it otherwise.)
 template <typename E, int WW1, int K1, int K2, int K3, int K4, class Op>
 static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hipStream_t st) {
   const int n_pairs = a.T * a.top_k;

@@ -12,8 +12,9 @@ namespace dinfer {
 constexpr int WKC = 4;     // k-steps per staged chunk
 // LDS fragments read ahead of the matrix instructions that use them (pinned by scheduling barriers, see the chunk
 // body), and the chunks of activation fragments a wave holds in registers on their way to LDS: two everywhere
-// except in the many-token expert GEMMs and smoothing contraction (trace ids 10, 11, 24), whose 128 accumulator registers and two activation
-// planes leave room for one only (with two, the pinned read-ahead spills and they run at half speed).
+// except in the many-token expert GEMMs and smoothing contraction (trace ids 10, 11, 24), whose 128 accumulator registers
+// and two activation planes leave room for one only (with two, the pinned read-ahead spills and the expert GEMMs run at half
+// speed; with one they still spill 2 registers of 256 in bf16, the smoothing contraction 14).
 constexpr int WIDE_FD = 4;
 template <int KID> constexpr int wide_bdepth() { return (KID == 10 || KID == 11 || KID == 24) ? 1 : 2; }
 
