@@ -27,8 +27,10 @@ struct LmPlan {
 //  - Few tasks (one per compute unit or less): all in pieces, since a wave alone with a task is bound by its chain of
 //    loads and matrix instructions (4096 ids of float32, hidden 256: 16.5 -> 11 us at 32 tokens, 27 -> 13.4 at 64).
 //  - 33 to 64 tokens: two workgroups of four waves fill a compute unit, so the groups beyond 512 would begin a second
-//    round of the chip; they go out in pieces where there are some and they are less than half a round (157184 ids:
-//    126 -> 124.5 us).
+//    round of the chip; they go out in pieces where these are at most a fifth of a round.  A piece fetches the activation
+//    rows for itself, so that more of them cost as much as the round would (one layer and LM head in bf16 at hidden 2048,
+//    35 / 64 tokens, whole groups -> pieces: 2 groups beyond 192 / 198 -> 177 / 186 us, 102 of them 202 / 202 -> 196 / 202,
+//    150 of them 198 / 204 -> 204 / 221, 220 of them 207 / 214 -> 219 / 238; 157184 ids are 102 beyond).
 //  - Up to 32 tokens: three waves per SIMD (168 registers) hold all workgroups of 157184 ids at once (114 -> 108 us
 //    against two per SIMD, where 1024 of 1228 fit).  More than 64 tokens: whole groups.
 inline LmPlan lm_plan(int V, int T) {
@@ -38,7 +40,7 @@ inline LmPlan lm_plan(int V, int T) {
   p.ww = few ? LM_PIECE_WW : T <= LM_SMALL_T ? LM_SMALL_WW : T <= LM_MID_T ? LM_MID_WW : LM_WW;
   p.whole = few ? 0 : (p.tasks + p.ww - 1) / p.ww;
   const int round = LM_CUS * (8 / LM_MID_WW), over = p.whole % round;
-  if (p.ww == LM_MID_WW && p.whole > round && over > 0 && over < round / 2) p.whole -= over;
+  if (p.ww == LM_MID_WW && p.whole > round && 5 * over <= round) p.whole -= over;
   p.first_piece = p.whole * p.ww < p.tasks ? p.whole * p.ww : p.tasks;
   p.parts = T <= LM_MID_T ? p.whole + p.tasks - p.first_piece : p.whole * p.ww;
   return p;

@@ -45,3 +45,12 @@ def test_every_vocabulary(plans, T):
     if T > 64:
         ok &= pieces == 0
     assert ok.all(), "vocabulary %d" % vocab[~ok][0]
+
+
+def test_pieces_are_few(plans):
+    """33 to 64 tokens: the groups of four tasks beyond a round of 512 go out task by task where they are at most a fifth of
+    one, whole otherwise."""
+    for rounds in (1, 2, 3):
+        for over, in_pieces in ((0, 0), (1, 1), (102, 102), (103, 0), (187, 0), (255, 0), (511, 0)):
+            tasks, ww, whole, first, parts, _ = plans(48, (512 * rounds + over) * 256, 1)[:, 0]
+            assert ww == 4 and whole == 512 * rounds + over - in_pieces and tasks - first == 4 * in_pieces, (rounds, over)
