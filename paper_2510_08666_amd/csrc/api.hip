@@ -206,8 +206,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.y = cv.take(planes * T * K * I * es);
   w.o = cv.take(T * K * H * 4);
   w.lm_part = cv.take((size_t)lm_head_most_parts(c.vocab) * T * 4 * 4);
-  const bool bf16 = c.dtype == DINFER_BF16;
-  w.smooth_part = cv.take(smooth_part_bytes(H, c.vocab, smooth_kpad(bf16, c.vocab) / (bf16 ? ET<bf16_t>::KS : ET<float>::KS), max_tokens));
+  w.smooth_part = cv.take(smooth_part_bytes(H, c.vocab, c.dtype == DINFER_BF16 ? ET<bf16_t>::KS : ET<float>::KS, max_tokens));
   w.lm_stats = cv.take(T * 2 * 4);
   w.conf = cv.take(T * 4);
   w.argmax = cv.take(T * 4);

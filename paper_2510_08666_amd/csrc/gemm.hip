@@ -803,7 +803,7 @@ template <typename E, int KID, int WT> constexpr size_t smooth_lds() {
 template <typename E, int WT, int KID>
 __global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partial_kernel(const E* __restrict__ W, int ksteps,
                                                                                        const E* __restrict__ B, int T, int H,
-                                                                                       int n_slices, float* __restrict__ part,
+                                                                                       int n_slices, int pairs, float* __restrict__ part,
                                                                                        const uint64_t* __restrict__ mask, int block_len,
                                                                                        float* __restrict__ delta,
                                                                                        const int32_t* __restrict__ live) {
@@ -823,7 +823,6 @@ __global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partia
   const int tok0 = (turn % groups) * per_group * TILE;
   const int slot = tgroup * SMOOTH_TASKS + rank, task = min(slot, n_tasks - 1);
   // the slice's chunks, the same number for both teams (they share the workgroup's barriers); see smooth_kpad
-  const int pairs = ksteps / (WKC * SMOOTH_KH);
   const int p0 = (int)((int64_t)pairs * slice / n_slices), p1 = (int)((int64_t)pairs * (slice + 1) / n_slices);
   const int chunks = p1 - p0;
   const int64_t ks0 = ((int64_t)p0 * SMOOTH_KH + (int64_t)team * chunks) * WKC;
@@ -908,14 +907,14 @@ template <typename E, int WT, int KID> static void launch_smooth_as(const Smooth
   const int slices = single_slice() ? 1 : p.slices, units = (p.task_groups * slices + 7) / 8 * 8;
   float* part = p.in_logits ? a.logits : a.part;
   smooth_partial_kernel<E, WT, KID><<<units * p.token_groups, SMOOTH_TASKS * SMOOTH_KH * WAVE, smooth_lds<E, KID, WT>(), st>>>(
-      (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H, slices, part, a.mask, a.block_len, a.delta, live_word());
+      (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H, slices, p.pairs, part, a.mask, a.block_len, a.delta, live_word());
   if (slices == 1) return;
   const int64_t quads = (int64_t)a.T * a.H / 4;
   smooth_reduce_kernel<<<(unsigned)((quads + 255) / 256), 256, 0, st>>>(part, slices, a.T, a.H, a.mask, a.block_len, a.delta,
                                                                         live_word());
 }
 template <typename E> static void launch_smooth_t(const SmoothArgs& a, int Kpad, hipStream_t st) {
-  const SmoothPlan p = smooth_plan(a.H, a.V, Kpad / ET<E>::KS, a.T);
+  const SmoothPlan p = smooth_plan(a.H, a.V, ET<E>::KS, a.T);
   if (p.wt == 1) launch_smooth_as<E, 1, 23>(a, Kpad, p, st);
   else if (p.wt == 2) launch_smooth_as<E, 2, 23>(a, Kpad, p, st);
   else launch_smooth_as<E, 4, 24>(a, Kpad, p, st);

@@ -15,21 +15,23 @@ constexpr int SMOOTH_MIN_PAIRS = 2;
 struct SmoothPlan {
   int wt;             // token tiles per workgroup, at most: 1, 2 or 4
   int task_groups, token_groups;
-  int pairs;          // pairs of chunks in the padded vocabulary
+  int pairs;          // pairs of chunks that hold ids of the vocabulary (what it is padded to beyond them is zeros)
   int slices;         // 1: the workgroups write the rows themselves
   bool in_logits;     // the partial sums [slices][T][H] fit where the logits [T][V] were
 };
-// Kpad_steps: k-steps of the padded vocabulary (smooth_kpad).  About one workgroup per compute unit (two waves on every
-// SIMD); a multiple of eight slices keeps a slice on one die.  The number of slices does not follow the room the logits
-// leave: limited to that, 32000 ids at hidden 2048 had eight slices, 64 workgroups (a bf16 step of 32 tokens 167 us, 144
-// with 32 slices; float32 354 and 254).
-inline SmoothPlan smooth_plan(int H, int V, int Kpad_steps, int T) {
+// ks: features of a k-step.  The vocabulary is stored padded (smooth_kpad) and contracted as far as it goes: 497 ids padded
+// to 8192, 2240 tokens at hidden 1216, took 500 us a step, 353 without the padding.
+// About one workgroup per compute unit (two waves on every SIMD); a multiple of eight slices keeps a slice on one die.
+// The number of slices does not follow the room the logits leave: limited to that, 32000 ids at hidden 2048 had eight
+// slices, 64 workgroups (a bf16 step of 32 tokens 167 us, 144 with 32 slices; float32 354 and 254).
+inline SmoothPlan smooth_plan(int H, int V, int ks, int T) {
   SmoothPlan p;
   const int tiles = (T + SMOOTH_TILE - 1) / SMOOTH_TILE;
   p.wt = tiles <= 2 ? tiles : 4;
   p.task_groups = (H / 64 + SMOOTH_TASKS - 1) / SMOOTH_TASKS;
   p.token_groups = (tiles + p.wt - 1) / p.wt;
-  p.pairs = Kpad_steps / (SMOOTH_CHUNK * SMOOTH_KH);
+  const int pair = ks * SMOOTH_CHUNK * SMOOTH_KH;
+  p.pairs = (V + pair - 1) / pair;
   int s = SMOOTH_WGS / (p.task_groups * p.token_groups);
   const int most = p.pairs / SMOOTH_MIN_PAIRS;
   s = s < most ? s : most;
@@ -39,11 +41,11 @@ inline SmoothPlan smooth_plan(int H, int V, int Kpad_steps, int T) {
 }
 // Bytes for the partial sums of any forward of up to max_tokens tokens whose logits leave too little room (a vocabulary
 // of few rows of features: 0 at 157184 ids and hidden 2048, 8 MB at 32000).
-inline size_t smooth_part_bytes(int H, int V, int Kpad_steps, int max_tokens) {
+inline size_t smooth_part_bytes(int H, int V, int ks, int max_tokens) {
   size_t most = 0;
   for (int t = SMOOTH_TILE; t < max_tokens + SMOOTH_TILE; t += SMOOTH_TILE) {
     const int T = t < max_tokens ? t : max_tokens;
-    const SmoothPlan p = smooth_plan(H, V, Kpad_steps, T);
+    const SmoothPlan p = smooth_plan(H, V, ks, T);
     const size_t bytes = p.slices > 1 && !p.in_logits ? (size_t)p.slices * T * H * 4 : 0;
     most = bytes > most ? bytes : most;
   }

@@ -9,12 +9,12 @@ import host_shim
 
 SHIM = """
 #include "smooth_plan.hpp"
-extern "C" void plan(int H, int V, int steps, int T, int* o) {
-  const dinfer::SmoothPlan p = dinfer::smooth_plan(H, V, steps, T);
+extern "C" void plan(int H, int V, int ks, int T, int* o) {
+  const dinfer::SmoothPlan p = dinfer::smooth_plan(H, V, ks, T);
   o[0] = p.wt, o[1] = p.task_groups, o[2] = p.token_groups, o[3] = p.pairs, o[4] = p.slices, o[5] = p.in_logits;
 }
-extern "C" long long part_bytes(int H, int V, int steps, int max_tokens) {
-  return (long long)dinfer::smooth_part_bytes(H, V, steps, max_tokens);
+extern "C" long long part_bytes(int H, int V, int ks, int max_tokens) {
+  return (long long)dinfer::smooth_part_bytes(H, V, ks, max_tokens);
 }
 """
 HIDDEN = [64, 128, 256, 320, 1024, 2048, 2880, 4096]
@@ -29,9 +29,9 @@ def lib(tmp_path_factory):
     return so
 
 
-def _plan(lib, H, V, steps, T):
+def _plan(lib, H, V, ks, T):
     o = (ctypes.c_int * 6)()
-    lib.plan(H, V, steps, T, o)
+    lib.plan(H, V, ks, T, o)
     return dict(zip(("wt", "task_groups", "token_groups", "pairs", "slices", "in_logits"), o))
 
 
@@ -39,11 +39,11 @@ def _plan(lib, H, V, steps, T):
 @pytest.mark.parametrize("H", HIDDEN)
 def test_partial_sums_fit_and_the_chip_is_filled(lib, H, ks):
     for V in VOCAB:
-        steps = -(-V // (ks * 512)) * 512
-        room = {m: lib.part_bytes(H, V, steps, m) for m in TOKENS}
+        room = {m: lib.part_bytes(H, V, ks, m) for m in TOKENS}
         for T in TOKENS:
-            p = _plan(lib, H, V, steps, T)
+            p = _plan(lib, H, V, ks, T)
             assert p["wt"] in (1, 2, 4) and p["wt"] * p["token_groups"] * 32 >= T
+            assert p["pairs"] == -(-V // (ks * 8))                      # nothing is contracted for padding
             assert 1 <= p["slices"] <= p["pairs"]                       # every slice has whole chunks for both teams
             if p["slices"] > 1:
                 need = p["slices"] * T * H * 4
@@ -56,7 +56,7 @@ def test_partial_sums_fit_and_the_chip_is_filled(lib, H, ks):
 
 
 def test_vocabulary_of_few_rows_of_features(lib):
-    p = _plan(lib, 2048, 32000, 2048, 32)
+    p = _plan(lib, 2048, 32000, 16, 32)
     assert p["slices"] * p["task_groups"] == 256 and not p["in_logits"]
-    assert lib.part_bytes(2048, 32000, 2048, 32) == 8 << 20
-    assert lib.part_bytes(2048, 157184, 20 * 512, 512) == 0
+    assert lib.part_bytes(2048, 32000, 16, 32) == 8 << 20
+    assert lib.part_bytes(2048, 157184, 16, 512) == 0
