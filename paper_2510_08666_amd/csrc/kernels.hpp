@@ -6,6 +6,7 @@
 
 #include "attn_plan.hpp"
 #include "common.hpp"
+#include "expert_plan.hpp"
 #include "lm_plan.hpp"
 #include "smooth_plan.hpp"
 
@@ -195,12 +196,6 @@ void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32
 // Work list of the expert GEMMs above 64 tokens: number of items [WORK_BIG] taken by whole workgroups, of all items
 // [WORK_ALL] (the rest in pieces of one task), then 16-byte items {expert, first sorted row, rows, 0}.
 constexpr int WORK_BIG = 0, WORK_ALL = 1, WORK_ITEMS = 4;
-// Token tiles per work item of the expert GEMMs above 64 tokens.
-int expert_group_tiles(int E, int n_pairs);
-// Items whose workgroups fill the chip once, for launch_permute: at most half as many are handed out in pieces.
-int expert_round_items(int E, int n_pairs, int H, int I);
-// Work items that many groups can add up to for n_pairs routed pairs.
-inline int expert_work_items(int E, int n_pairs, int group_tiles) { return E + n_pairs / (group_tiles * TILE); }
 int permute_max_pairs();      // most (token, slot) pairs one forward may route
 
 struct ExpertArgs {

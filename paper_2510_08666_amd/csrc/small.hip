@@ -324,10 +324,7 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
         if (k <= 2) light += n_k;
       }
       if (lane == 0) {
-        // Items that would begin another, mostly empty round of the chip (which takes `round` items at a time) are
-        // handed out in small pieces instead, provided that they are light and few.
-        const int over = at > round ? at % round : 0;
-        work[WORK_BIG] = over <= light && over <= round / 2 ? at - over : at;
+        work[WORK_BIG] = at - expert_piece_items(at, light, round);
         work[WORK_ALL] = at;
       }
     }

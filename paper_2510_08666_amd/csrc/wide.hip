@@ -16,8 +16,8 @@ constexpr int WT = 4;      // token tiles per workgroup above 64 tokens
 // computes while the other waits for LDS or memory, and the activation fragments are shared by eight tasks.
 // (Measured at 512 tokens: four waves with two, four or six weight chunks in flight are slower for the expert
 // GEMMs, 131 to 134 against 120 microseconds; four waves in the LM head, 450 against 352.)
-constexpr int EXPERT_WW = 8, EXPERT_PRE = 2;
-constexpr int EXPERT_CUS = 256;   // compute units; eight waves of the many-token expert GEMMs fill one
+constexpr int EXPERT_PRE = 2;
+static_assert(EXPERT_WT == WT && EXPERT_TILE == TILE, "expert_plan.hpp counts in these units");
 constexpr int LM_PRE = 2;         // (tasks per workgroup of the LM head: lm_plan.hpp)
 static_assert(LM_SMALL_T == TILE && LM_MID_T == 2 * TILE, "the forms of the LM head take one, two and four token tiles");
 constexpr int XCDS = 8;      // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
@@ -227,24 +227,9 @@ constexpr int SMALL_WW = 2;
 // lasts as long as those; 32 one-task workgroups per expert put 1.75 MB on the fullest unit (78 -> 70 us for such
 // layers, 69.1 -> 65.7 us on average at batch 1, though every workgroup now stages the activation rows for itself).
 constexpr int GU1_WW = 1;
-// More than 64 tokens, up to MID_ROWS rows per expert on average: two token tiles and four tasks per workgroup, so
-// that two workgroups share a compute unit (trace ids 20, 21).  With eight tasks an expert is four workgroups of a
-// whole compute unit each, and a step whose masked rows touch half of the experts leaves half of the chip idle
-// (gate/up + down in microseconds at 96 / 128 / 160 tokens of a fully masked block batch: 73 + 46, 91 + 55, 89 + 53
-// with eight tasks, 45 + 31, 71 + 44, 72 + 46 with four; where all 64 experts have rows, 92 + 52 against 87 + 52 at
-// 96 tokens and 98 + 59 against 95 + 59 at 160).  Beyond, the rows weigh more than the balance: every workgroup
-// fetches its expert's rows for itself (256 tokens: 102 + 64 with eight tasks, 120 + 73 with four).
-constexpr int MID_WW = 4, MID_WT = 2, MID_ROWS = 24;
-int expert_group_tiles(int E, int n_pairs) { return n_pairs <= MID_ROWS * E ? MID_WT : WT; }
+// More than 64 tokens: expert_plan.hpp (trace ids 20, 21 for the form of few rows per expert, 10, 11 for the other).
 // LDS of expert_many_kernel: staged fragments, or two tiles of WW waves' partial sums
 template <int WW> constexpr size_t many_lds() { return (size_t)WW * 2 * 2 * 16 * WAVE * 4; }
-
-int expert_round_items(int E, int n_pairs, int H, int I) {
-  const int ww = expert_group_tiles(E, n_pairs) == MID_WT ? MID_WW : EXPERT_WW, slots = EXPERT_CUS * (EXPERT_WW / ww);
-  const int up = (I / TILE + ww - 1) / ww, down = (H / (2 * TILE) + ww - 1) / ww;
-  const int most = up > down ? up : down;
-  return most < slots ? slots / most : 1;
-}
 
 // KID: trace ids of the forms for up to 32, up to 64, few rows per expert, many rows per expert
 // (Up to 32 tokens the down projection takes its first form, ids 18 and the pieces of one tile, only under the single-slice
@@ -270,7 +255,7 @@ static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hip
   } else {
     auto many = [&](auto kernel, int wt, int ww, size_t lds) {
       const dim3 whole = grid(ww, expert_work_items(a.E, n_pairs, wt));
-      const int pieces = expert_round_items(a.E, n_pairs, a.H, a.I) / 2 * n_tasks;   // the most the permutation hands out
+      const int pieces = expert_most_piece_items(a.E, n_pairs, a.H, a.I) * n_tasks;
       kernel<<<dim3(whole.x, whole.y + (pieces + whole.x - 1) / whole.x), ww * WAVE, lds, st>>>(op, a.work, live_word());
     };
     if (expert_group_tiles(a.E, n_pairs) == MID_WT) many(expert_many_kernel<E, MID_WT, MID_WW, K3, Op>, MID_WT, MID_WW, many_lds<MID_WW>());
