@@ -2,11 +2,7 @@
 // says so.
 #pragma once
 
-#if defined(__HIPCC__)
-#define DINFER_HOST_DEVICE __host__ __device__
-#else
-#define DINFER_HOST_DEVICE
-#endif
+#include "host_device.hpp"
 
 namespace dinfer {
 

@@ -788,9 +788,6 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st) {
 // The activation fragments of a slice go through LDS once per SMOOTH_TASKS tasks: in the split-K form, where every wave
 // fetched its own, they took as many of a compute unit's outstanding requests as the weights (4.3 TB/s), and above
 // 64 tokens the unsliced shared-operand form had 24 workgroups at 160 tokens.
-// Workgroup i = die (i % 8), turn (i / 8): the token groups of one (task group, slice) are consecutive turns of one
-// die and share its weights in the L2; slices vary fastest over the dies, so that a die's task groups share the
-// probabilities of its slices.
 // ------------------------------------------------------------------------------------------------
 constexpr int SMOOTH_PRE = 2;
 static_assert(SMOOTH_TILE == TILE && SMOOTH_CHUNK == WKC, "smooth_plan counts in these units");
@@ -815,12 +812,12 @@ __global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partia
   const int team = wave / SMOOTH_TASKS, rank = wave % SMOOTH_TASKS;
   const int n_tasks = H / (2 * TILE), tgroups = (n_tasks + SMOOTH_TASKS - 1) / SMOOTH_TASKS;
   const int tiles = (T + TILE - 1) / TILE, groups = (tiles + WT - 1) / WT, per_group = (tiles + groups - 1) / groups;
-  const int turn = blockIdx.x / 8, unit = (turn / groups) * 8 + blockIdx.x % 8;
-  if (unit >= tgroups * n_slices) return;               // uniform over the workgroup
-  const int tgroup = unit / n_slices, slice = unit % n_slices;
-  const int nt = min(per_group, tiles - (turn % groups) * per_group);
+  const SmoothItem item = smooth_item(blockIdx.x, groups, tgroups, n_slices);
+  if (!item.valid) return;                              // uniform over the workgroup
+  const int slice = item.slice, tgroup = item.task_group;
+  const int nt = min(per_group, tiles - item.token_group * per_group);
   if (nt <= 0) return;
-  const int tok0 = (turn % groups) * per_group * TILE;
+  const int tok0 = item.token_group * per_group * TILE;
   const int slot = tgroup * SMOOTH_TASKS + rank, task = min(slot, n_tasks - 1);
   // the slice's chunks, the same number for both teams (they share the workgroup's barriers); see smooth_kpad
   const int p0 = (int)((int64_t)pairs * slice / n_slices), p1 = (int)((int64_t)pairs * (slice + 1) / n_slices);
@@ -904,9 +901,9 @@ int smooth_kpad(bool bf16, int V) {
 template <typename E, int WT, int KID> static void launch_smooth_as(const SmoothArgs& a, int Kpad, const SmoothPlan& p, hipStream_t st) {
   // the partial sums live where the logits were (T * V floats), which the probabilities have replaced, or if these leave
   // too little room in the workspace
-  const int slices = single_slice() ? 1 : p.slices, units = (p.task_groups * slices + 7) / 8 * 8;
+  const int slices = single_slice() ? 1 : p.slices, wgs = (p.task_groups * p.token_groups * slices + 7) / 8 * 8;
   float* part = p.in_logits ? a.logits : a.part;
-  smooth_partial_kernel<E, WT, KID><<<units * p.token_groups, SMOOTH_TASKS * SMOOTH_KH * WAVE, smooth_lds<E, KID, WT>(), st>>>(
+  smooth_partial_kernel<E, WT, KID><<<wgs, SMOOTH_TASKS * SMOOTH_KH * WAVE, smooth_lds<E, KID, WT>(), st>>>(
       (const E*)a.w_emb_t, Kpad / ET<E>::KS, (const E*)a.probs, a.T, a.H, slices, p.pairs, part, a.mask, a.block_len, a.delta, live_word());
   if (slices == 1) return;
   const int64_t quads = (int64_t)a.T * a.H / 4;

@@ -1,6 +1,9 @@
-// How the expected-embedding contraction of iteration smoothing is cut into workgroups.  Plain host C++.
+// How the expected-embedding contraction of iteration smoothing is cut into workgroups.  Host C++, and device code where a
+// function says so.
 #pragma once
 #include <stddef.h>
+
+#include "host_device.hpp"
 
 namespace dinfer {
 
@@ -50,6 +53,23 @@ inline size_t smooth_part_bytes(int H, int V, int ks, int max_tokens) {
     most = bytes > most ? bytes : most;
   }
   return most;
+}
+
+// Workgroup i = die (i % 8), turn (i / 8).  Up to 128 tokens the slices vary fastest over the dies, so that a die's task
+// groups share the probabilities of its slices.  With several token groups a die takes an eighth of the list [slice][task
+// group][token group] in its order: the token groups of one (slice, task group) are consecutive turns and share its
+// weights in the L2, and no die has more than one workgroup more than another (whole (slice, task group) units dealt out
+// to the dies in turn: 20 of them with 12 token groups each, hidden 2368 and 1536 tokens, put 36 workgroups on the 32
+// compute units of four dies; with 25022 ids the step took 1400 us, now 1010).
+struct SmoothItem {
+  int token_group, task_group, slice;
+  bool valid;
+};
+DINFER_HOST_DEVICE inline SmoothItem smooth_item(int i, int token_groups, int task_groups, int slices) {
+  const int total = token_groups * task_groups * slices, per_die = (total + 7) / 8;
+  if (token_groups == 1) return SmoothItem{0, i / slices, i % slices, i < total};
+  const int at = (i % 8) * per_die + i / 8;
+  return SmoothItem{at % token_groups, at / token_groups % task_groups, at / (token_groups * task_groups), at < total};
 }
 
 }  // namespace dinfer

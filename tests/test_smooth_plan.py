@@ -13,6 +13,10 @@ extern "C" void plan(int H, int V, int ks, int T, int* o) {
   const dinfer::SmoothPlan p = dinfer::smooth_plan(H, V, ks, T);
   o[0] = p.wt, o[1] = p.task_groups, o[2] = p.token_groups, o[3] = p.pairs, o[4] = p.slices, o[5] = p.in_logits;
 }
+extern "C" int item(int i, int token_groups, int task_groups, int slices) {
+  const dinfer::SmoothItem t = dinfer::smooth_item(i, token_groups, task_groups, slices);
+  return t.valid ? (t.token_group * task_groups + t.task_group) * slices + t.slice : -1;
+}
 extern "C" long long part_bytes(int H, int V, int ks, int max_tokens) {
   return (long long)dinfer::smooth_part_bytes(H, V, ks, max_tokens);
 }
@@ -60,3 +64,14 @@ def test_vocabulary_of_few_rows_of_features(lib):
     assert p["slices"] * p["task_groups"] == 256 and not p["in_logits"]
     assert lib.part_bytes(2048, 32000, 16, 32) == 8 << 20
     assert lib.part_bytes(2048, 157184, 16, 512) == 0
+
+
+@pytest.mark.parametrize("token_groups,task_groups,slices", [(1, 8, 32), (1, 3, 5), (1, 1, 1), (2, 8, 16), (3, 2, 7), (12, 10, 2),
+                                                             (24, 10, 1), (32, 16, 1), (5, 1, 48)])
+def test_items_over_the_dies(lib, token_groups, task_groups, slices):
+    """Workgroup i runs on die i % 8: every item once, and as many on each die as on any other, or one fewer."""
+    total = token_groups * task_groups * slices
+    seen = [lib.item(i, token_groups, task_groups, slices) for i in range(-(-total // 8) * 8)]
+    assert sorted(v for v in seen if v >= 0) == list(range(total))
+    on_die = [sum(v >= 0 for v in seen[d::8]) for d in range(8)]
+    assert max(on_die) == -(-total // 8)
