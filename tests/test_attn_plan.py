@@ -38,3 +38,13 @@ def test_runs_behind_cached_prefixes_keep_the_splitting_form(groups):
     for run in (65, 80, 96, 128):                         # vicinity steps: blocks of 64 with up to 64 neighbours
         for n_seq in (8, 16, 64):
             assert groups([run] * n_seq, 16, False) == 0
+
+
+def test_prompts_of_one_length_a_little_beyond_a_round_keep_the_splitting_form(groups):
+    assert groups([2048], 16, True) == 16 and groups([2049], 16, True) == 0            # 256 and 272 workgroups
+    assert groups([2560], 16, True) == 0 and groups([2688], 16, True) == 21            # 320 and 336
+    assert groups([1132], 32, True) == 9                                               # 288, but a short walk
+    assert groups([1536, 1024, 512], 16, True) == 24 and groups([1408, 1280], 16, True) == 21
+    assert groups([1152, 1152], 16, True) == 18 and groups([2304, 2304], 8, True) == 0
+    assert groups([6016], 8, True) == 0 and groups([6252], 8, True) == 49              # 376 and 392 workgroups, a long walk
+    assert groups([8300], 8, True) == 0 and groups([4332], 16, True) == 0 and groups([4716], 16, True) == 37
