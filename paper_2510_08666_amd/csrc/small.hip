@@ -33,28 +33,48 @@ void launch_rope_table(float* cos_tab, float* sin_tab, int max_pos, int head_dim
 // ---------------------------------------------------------------- token bookkeeping
 // `limit` = positions a sequence may use (rotary table and page-table row); a prefix length that would
 // leave it is pulled back so that no later kernel indexes outside its buffers.
-// Runs in one workgroup (the extra one of the embedding launch).
+// Runs in one workgroup (the extra one of the embedding launch), token by token: sequence by sequence, each behind the
+// loads of its offset and base, the launch took as long as its sequences (hidden 2048, 60 of 32 tokens 23.5 us, 16 of them
+// 7.5; now 10.0 and 5.6).
 __device__ inline void token_meta(const SeqSpan& span, const int32_t* __restrict__ d_base, int limit,
                                   int32_t* __restrict__ tok_seq, int32_t* __restrict__ tok_pos,
                                   int32_t* __restrict__ seq_nkeys, int32_t* __restrict__ qtile) {
-  for (int s = 0; s < span.n_seq; ++s) {
-    const int o = span.off[s], len = span.off[s + 1] - o;
-    const int base = d_base ? max(0, min(d_base[s], limit - len)) : 0;
-    for (int i = threadIdx.x; i < len; i += blockDim.x) {
-      tok_seq[o + i] = s;
-      tok_pos[o + i] = base + i;
+  __shared__ int32_t s_off[MAX_SEQS + 1], s_base[MAX_SEQS], s_tile[MAX_SEQS];
+  static_assert(MAX_SEQS <= WAVE, "one lane per sequence");
+  const int n_seq = span.n_seq;
+  if (threadIdx.x < WAVE) {
+    const int s = min((int)threadIdx.x, n_seq - 1), o = span.off[s], len = span.off[s + 1] - o;
+    const int base = d_base ? max(0, min(d_base[s], limit - len)) : 0, tiles = (len + TILE - 1) / TILE;
+    int incl = (int)threadIdx.x < n_seq ? tiles : 0;
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+      const int up = __shfl_up(incl, d, WAVE);
+      if ((int)threadIdx.x >= d) incl += up;
     }
-    if (threadIdx.x == 0) seq_nkeys[s] = base + len;
+    if ((int)threadIdx.x < n_seq) {
+      s_off[s] = o;
+      s_base[s] = base;
+      s_tile[s] = incl - tiles;
+      seq_nkeys[s] = base + len;
+      if (s == n_seq - 1) s_off[n_seq] = o + len;
+    }
   }
-  int n = 0;
-  for (int s = 0; s < span.n_seq; ++s) {
-    const int o = span.off[s], len = span.off[s + 1] - o, tiles = (len + TILE - 1) / TILE;
-    for (int i = threadIdx.x; i < tiles; i += blockDim.x) {
-      qtile[(n + i) * 3 + 0] = s;
-      qtile[(n + i) * 3 + 1] = o + i * TILE;
-      qtile[(n + i) * 3 + 2] = min(TILE, len - i * TILE);
+  __syncthreads();
+  const int T = s_off[n_seq];
+  for (int i = threadIdx.x; i < T; i += blockDim.x) {
+    int s = 0;                                  // the last sequence that begins at or before token i
+#pragma unroll
+    for (int step = MAX_SEQS / 2; step > 0; step >>= 1)
+      if (s + step < n_seq && s_off[s + step] <= i) s += step;
+    const int at = i - s_off[s];
+    tok_seq[i] = s;
+    tok_pos[i] = s_base[s] + at;
+    if (at % TILE == 0) {
+      int32_t* q = qtile + (s_tile[s] + at / TILE) * 3;
+      q[0] = s;
+      q[1] = i;
+      q[2] = min(TILE, s_off[s + 1] - i);
     }
-    n += tiles;
   }
 }
 
