@@ -610,12 +610,7 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
 // workgroup 102 / 95 (too few workgroups); two tasks per workgroup 57 / 19 (the output projection, with 32 tasks,
 // then fills the chip with 256 workgroups).
 constexpr int DENSE_PRE = 2, DENSE_KH = 2, DENSE_WT = 2;
-// One round of the chip takes 41 us (QKV, four tasks and two tiles), 25 (four tasks, one tile) or 20 (two tasks, one tile):
-// four tasks and one tile while their workgroups are one round (352 tokens: 264 of them, two rounds, 46 us; with two
-// tiles 39; output projection at 1100 tokens 46 and 38), two tasks where four would leave nearly half the chip idle (192
-// tokens: 288 workgroups of two tasks, two rounds, 28 us; 144 of four, 26.7).
-constexpr int DENSE_CUS = 256;    // compute units: a workgroup fills one
-constexpr int DENSE_FILL = 140;   // workgroups a launch of four tasks and one tile each must keep
+static_assert(DENSE_TILE == TILE && DENSE_WT == 2, "dense_plan.hpp counts in these units");
 
 template <typename E, int KID, int WT, int DENSE_TASKS> constexpr size_t dense_lds() {
   const size_t stage = DENSE_KH * wide_lds<E, KID, WT>();
@@ -730,9 +725,9 @@ static void launch_dense_as(const E* W, int ksteps, const E* B, int T, int n_tas
 // More tasks and token tiles per workgroup cut the operand traffic, but only while the launch still fills the chip.
 template <typename E, class Epi>
 static void launch_dense(const E* W, int ksteps, const E* B, int T, int n_tasks, const Epi& epi, hipStream_t st) {
-  auto wgs = [&](int tasks, int wt) { return ((n_tasks + tasks - 1) / tasks) * ((T + wt * TILE - 1) / (wt * TILE)); };
-  if (wgs(4, 1) > DENSE_CUS) launch_dense_as<E, DENSE_WT, 4, Epi>(W, ksteps, B, T, n_tasks, epi, st);
-  else if (wgs(4, 1) >= DENSE_FILL) launch_dense_as<E, 1, 4, Epi>(W, ksteps, B, T, n_tasks, epi, st);
+  const DenseForm f = dense_form(sizeof(E) == 2, n_tasks, T);
+  if (f.tiles == DENSE_WT) launch_dense_as<E, DENSE_WT, 4, Epi>(W, ksteps, B, T, n_tasks, epi, st);
+  else if (f.tasks == 4) launch_dense_as<E, 1, 4, Epi>(W, ksteps, B, T, n_tasks, epi, st);
   else launch_dense_as<E, 1, 2, Epi>(W, ksteps, B, T, n_tasks, epi, st);
 }
 

@@ -6,6 +6,7 @@
 
 #include "attn_plan.hpp"
 #include "common.hpp"
+#include "dense_plan.hpp"
 #include "expert_plan.hpp"
 #include "lm_plan.hpp"
 #include "smooth_plan.hpp"

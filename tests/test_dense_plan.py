@@ -1,0 +1,33 @@
+"""Which form the dense projections of more than 64 tokens take (csrc/dense_plan.hpp), compiled for the host."""
+import ctypes
+
+import pytest
+
+import host_shim
+
+SHIM = """
+#include "dense_plan.hpp"
+extern "C" int form(int bf16, int n_tasks, int T) {
+  const dinfer::DenseForm f = dinfer::dense_form(bf16 != 0, n_tasks, T);
+  return 10 * f.tasks + f.tiles;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def form(tmp_path_factory):
+    lib = host_shim.load(tmp_path_factory.mktemp("dense_plan"), SHIM)
+    return lambda dtype, n_tasks, T: divmod(lib.form(int(dtype == "bf16"), n_tasks, T), 10)
+
+
+def test_two_tiles_follow_the_type(form):
+    assert form("bf16", 96, 320) == (4, 1) and form("bf16", 96, 352) == (4, 2)        # 240 and 264 workgroups of one tile
+    assert form("f32", 48, 704) == (4, 1) and form("f32", 48, 768) == (4, 1)          # 264 and 288
+    assert form("f32", 144, 256) == (4, 1) and form("f32", 96, 416) == (4, 2)         # 288; 312, 168 of two tiles
+    assert form("f32", 48, 832) == (4, 1) and form("f32", 48, 896) == (4, 2)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_two_tasks_where_four_leave_the_chip_idle(form, dtype):
+    assert form(dtype, 96, 96) == (2, 1) and form(dtype, 96, 160) == (2, 1) and form(dtype, 96, 192) == (4, 1)
+    assert form(dtype, 32, 512) == (2, 1) and form(dtype, 32, 560) == (4, 1)
