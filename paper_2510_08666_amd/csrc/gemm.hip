@@ -779,7 +779,7 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st) {
 // up to WT token tiles and one K slice, which its two teams of waves halve (as in gemm_dense_kernel), and leaves its
 // sums in part[slice][token][feature]; smooth_reduce_kernel adds the slices in order and writes the rows of masked
 // positions.  A single slice (many tokens) writes them itself.
-// Bound: the stream of the transposed embedding matrix (644 MB at vocabulary 157184; 32 tokens: 149 -> 123 us, 5.2 TB/s).
+// Bound: the stream of the transposed embedding matrix (644 MB at vocabulary 157184; 32 tokens: 149 -> 119 us, 5.4 TB/s).
 // The activation fragments of a slice go through LDS once per SMOOTH_TASKS tasks: in the split-K form, where every wave
 // fetched its own, they took as many of a compute unit's outstanding requests as the weights (4.3 TB/s), and above
 // 64 tokens the unsliced shared-operand form had 24 workgroups at 160 tokens.
