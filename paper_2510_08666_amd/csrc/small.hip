@@ -497,7 +497,10 @@ __global__ __launch_bounds__(256) void credit_kernel(const E* __restrict__ W, co
   const int n = s_n;
   const int ksteps = H / KS;
   const float zs = row_rinv(norm.ssq, norm.n_ssq, T, row, H, norm.eps) * scale;
+  // an id outside the vocabulary (a row of NaN has no candidate and leaves one in the list) is no row of the LM head
+  auto listed = [&](int k) { return (unsigned)s_ids[k] < (unsigned)V; };
   for (int k = wave; k < n; k += 4) {
+    if (!listed(k)) continue;
     const int v = s_ids[k];
     float z;
     if (v == v_top) {
@@ -525,10 +528,12 @@ __global__ __launch_bounds__(256) void credit_kernel(const E* __restrict__ W, co
   if (threadIdx.x == 0) {
     // equation 2 on the listed logits; every other term of the softmax is unchanged
     float Mt = M;
-    for (int k = 0; k < n; ++k) Mt = fmaxf(Mt, s_z[k] + alpha * log1pf(s_val[k]));
+    for (int k = 0; k < n; ++k)
+      if (listed(k)) Mt = fmaxf(Mt, s_z[k] + alpha * log1pf(s_val[k]));
     float St = S * __expf(M - Mt);
     int best = 0x7fffffff;
     for (int k = 0; k < n; ++k) {
+      if (!listed(k)) continue;
       const float zt = s_z[k] + alpha * log1pf(s_val[k]);
       St += __expf(zt - Mt) - __expf(s_z[k] - Mt);
       if (zt == Mt && s_ids[k] < best) best = s_ids[k];
