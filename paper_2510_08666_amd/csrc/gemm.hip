@@ -609,7 +609,7 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
 // 41 / 29 after the epilogue stores were widened, four teams of one token tile 94 / 37; four token tiles per
 // workgroup 102 / 95 (too few workgroups); two tasks per workgroup 57 / 19 (the output projection, with 32 tasks,
 // then fills the chip with 256 workgroups).
-constexpr int DENSE_PRE = 2, DENSE_KH = 2, DENSE_WT = 2;
+constexpr int DENSE_KH = 2, DENSE_WT = 2;
 static_assert(DENSE_TILE == TILE && DENSE_WT == 2, "dense_plan.hpp counts in these units");
 
 template <typename E, int KID, int WT, int DENSE_TASKS> constexpr size_t dense_lds() {
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(DENSE_TASKS * DENSE_KH * WAVE) void gemm_dense_kern
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
   constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N, PER = 4;
   constexpr int KID = Epi::ROWSUM ? 13 : 12;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int team = wave / DENSE_TASKS, rank = wave % DENSE_TASKS;
   const int slot = blockIdx.x * DENSE_TASKS + rank, task = min(slot, n_tasks - 1);
   const int tok0 = blockIdx.y * WT * TILE;
@@ -635,12 +635,12 @@ __global__ __launch_bounds__(DENSE_TASKS * DENSE_KH * WAVE) void gemm_dense_kern
   const int chunks = ksteps / WKC / DENSE_KH;          // per team
   const int ks0 = team * chunks * WKC;
   vec* sb = reinterpret_cast<vec*>(lds_raw + team * wide_lds<E, KID, WT>());
-  const E* brow = B + (int64_t)ks0 * T * (NP * KS) + (int64_t)min(tok0 + (rank % WT) * TILE + col, T - 1) * (NP * KS) + half * G;
+  auto row_of = [&](int r) { return min(tok0 + (rank % WT) * TILE + r, T - 1); };
   f32x16 acc0[WT], acc1[WT];
   zero_acc<WT>(acc0);
   zero_acc<WT>(acc1);
-  wide_stream<E, WT, DENSE_TASKS, DENSE_PRE, KID>(
-      W + (int64_t)task * task_stride_elems<E>(ksteps) + (int64_t)ks0 * (2 * WAVE * G) + lane * G, chunks, [&] { return brow; },
+  wide_stream<E, WT, DENSE_TASKS, KID>(
+      W + (int64_t)task * task_stride_elems<E>(ksteps) + (int64_t)ks0 * (2 * WAVE * G), chunks * WKC, B + (int64_t)ks0 * T * (NP * KS), row_of,
       (int64_t)T * (NP * KS), sb, nt, acc0, acc1, rank);
   if (DENSE_KH > 1) {
     // fold: team h > 0 leaves its sums at red[h-1][rank][t*32 + tile*16 + v][lane], team 0 adds them up
@@ -784,7 +784,6 @@ void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st) {
 // fetched its own, they took as many of a compute unit's outstanding requests as the weights (4.3 TB/s), and above
 // 64 tokens the unsliced shared-operand form had 24 workgroups at 160 tokens.
 // ------------------------------------------------------------------------------------------------
-constexpr int SMOOTH_PRE = 2;
 static_assert(SMOOTH_TILE == TILE && SMOOTH_CHUNK == WKC, "smooth_plan counts in these units");
 template <typename E, int KID, int WT> constexpr size_t smooth_lds() {
   const size_t stage = SMOOTH_KH * wide_lds<E, KID, WT>();
@@ -803,7 +802,7 @@ __global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partia
   typedef typename ET<E>::vec vec;
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
   constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int team = wave / SMOOTH_TASKS, rank = wave % SMOOTH_TASKS;
   const int n_tasks = H / (2 * TILE), tgroups = (n_tasks + SMOOTH_TASKS - 1) / SMOOTH_TASKS;
   const int tiles = (T + TILE - 1) / TILE, groups = (tiles + WT - 1) / WT, per_group = (tiles + groups - 1) / groups;
@@ -819,12 +818,12 @@ __global__ __launch_bounds__(SMOOTH_TASKS * SMOOTH_KH * WAVE) void smooth_partia
   const int chunks = p1 - p0;
   const int64_t ks0 = ((int64_t)p0 * SMOOTH_KH + (int64_t)team * chunks) * WKC;
   vec* sb = reinterpret_cast<vec*>(lds_raw + team * wide_lds<E, KID, WT>());
-  const E* brow = B + ks0 * T * (NP * KS) + (int64_t)min(tok0 + (rank % WT) * TILE + col, T - 1) * (NP * KS) + half * G;
+  auto row_of = [&](int r) { return min(tok0 + (rank % WT) * TILE + r, T - 1); };
   f32x16 acc0[WT], acc1[WT];
   zero_acc<WT>(acc0);
   zero_acc<WT>(acc1);
-  wide_stream<E, WT, SMOOTH_TASKS, SMOOTH_PRE, KID>(
-      W + (int64_t)task * task_stride_elems<E>(ksteps) + ks0 * (2 * WAVE * G) + lane * G, chunks, [&] { return brow; },
+  wide_stream<E, WT, SMOOTH_TASKS, KID>(
+      W + (int64_t)task * task_stride_elems<E>(ksteps) + ks0 * (2 * WAVE * G), chunks * WKC, B + ks0 * T * (NP * KS), row_of,
       (int64_t)T * (NP * KS), sb, nt, acc0, acc1, rank);
   float* red = reinterpret_cast<float*>(lds_raw);
   float* r = red + (int64_t)rank * (2 * WT * 16) * WAVE + lane;

@@ -16,9 +16,8 @@ constexpr int WT = 4;      // token tiles per workgroup above 64 tokens
 // computes while the other waits for LDS or memory, and the activation fragments are shared by eight tasks.
 // (Measured at 512 tokens: four waves with two, four or six weight chunks in flight are slower for the expert
 // GEMMs, 131 to 134 against 120 microseconds; four waves in the LM head, 450 against 352.)
-constexpr int EXPERT_PRE = 2;
 static_assert(EXPERT_WT == WT && EXPERT_TILE == TILE, "expert_plan.hpp counts in these units");
-constexpr int LM_PRE = 2;         // (tasks per workgroup of the LM head: lm_plan.hpp)
+// (tasks per workgroup of the LM head: lm_plan.hpp)
 static_assert(LM_SMALL_T == TILE && LM_MID_T == 2 * TILE, "the forms of the LM head take one, two and four token tiles");
 constexpr int XCDS = 8;      // accelerator dies, each with its own L2; workgroup i of a launch runs on die i % 8
 
@@ -86,35 +85,26 @@ template <typename E> struct Down {
 template <typename E, int WT, int WW, int KID, class Op>
 __device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* lds) {
   typedef typename ET<E>::vec vec;
-  constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N;
+  constexpr int KS = ET<E>::KS, NP = Planes<E>::N;
+  TRACE_MARK(KID, 3);
   const int e = it.x, base = it.y, n_rows = it.z;
   const int nt = min(WT, (n_rows + TILE - 1) / TILE);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int n_tasks = op.n_tasks(), task = min(tg * WW + wave, n_tasks - 1), ksteps = op.ksteps();
   // The rows hang on the permutation: that chain is resolved while the first weights are in flight.  What the epilogue
   // needs of them waits in registers; where the accumulators of four tiles leave too few, it is asked for again there.
   constexpr bool AGAIN = WT >= 4;
   typename Op::Row rows[WT];
   auto row_of = [&](int t) { return op.row(base + min(t * TILE + col, n_rows - 1)); };
-  auto brow = [&]() {
-    int staged;
-    if constexpr (AGAIN) {
-      staged = op.act_row(base + min((wave % WT) * TILE + col, n_rows - 1));
-    } else {
+  auto staged = [&](int r) { return op.act_row(base + min((wave % WT) * TILE + r, n_rows - 1)); };
+  if constexpr (!AGAIN) {
 #pragma unroll
-      for (int t = 0; t < WT; ++t) rows[t] = row_of(t);
-      staged = rows[0].act;
-#pragma unroll
-      for (int t = 1; t < WT; ++t)
-        if (wave % WT == t) staged = rows[t].act;
-    }
-    return op.act() + (int64_t)staged * (NP * KS) + half * G;
-  };
+    for (int t = 0; t < WT; ++t) rows[t] = row_of(t);
+  }
   f32x16 acc0[WT], acc1[WT];
   zero_acc<WT>(acc0);
   zero_acc<WT>(acc1);
-  wide_stream<E, WT, WW, EXPERT_PRE, KID>(op.W + ((int64_t)e * n_tasks + task) * task_stride_elems<E>(ksteps) + lane * G,
-                                          ksteps / WKC, brow, op.act_rows() * (NP * KS), reinterpret_cast<vec*>(lds), nt, acc0, acc1);
+  wide_stream<E, WT, WW, KID>(op.W + ((int64_t)e * n_tasks + task) * task_stride_elems<E>(ksteps), ksteps, op.act(), staged, op.act_rows() * (NP * KS), reinterpret_cast<vec*>(lds), nt, acc0, acc1, wave);
   if (tg * WW + wave >= n_tasks) return;
   if constexpr (AGAIN) {
 #pragma unroll
@@ -135,6 +125,7 @@ __device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* 
       }
     }
   }
+  TRACE_MARK(KID, 7);
 }
 
 // One item of up to TT tiles and ONE task by a workgroup of KW waves, which cut the task's K range and meet in LDS.
@@ -143,7 +134,7 @@ __device__ inline void expert_piece(const Op& op, const int4& it, int task, char
   constexpr int PER = 4, EW = 16 / PER;
   static_assert(KW >= EW, "the first EW waves run the epilogue");
   const int e = it.x, base = it.y, n_rows = it.z;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int ksteps = op.ksteps(), per = (ksteps + KW - 1) / KW, ks0 = min(ksteps, wave * per), ks1 = min(ksteps, ks0 + per);
   typename Op::Row rows[TT];
   PlaneLoader<E, TT> ld;
@@ -302,8 +293,8 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
   typedef typename ET<E>::vec vec;
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
   vec* sb = reinterpret_cast<vec*>(lds_raw);
-  constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  constexpr int KS = ET<E>::KS, NP = Planes<E>::N;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   // With a row list the workgroup's 128 "tokens" are entries of the list, and the token groups are counted from
   // the list's length: the grid is sized for all T rows, and the workgroups left over at its end return at once.
   const int n_rows = rows ? min(rows[0], T) : T;
@@ -385,6 +376,7 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
   const int tok0 = (turn % groups) * per_group * TILE;
   const int nt = min(per_group, tiles - (turn % groups) * per_group);
   if (nt <= 0) return;                  // uniform: fewer tiles than groups * per_group
+  TRACE_MARK(KID, 3);
   const int slot = tgroup * WW + wave, task = min(slot, n_tasks - 1);
   const int ksteps = H / KS;
   int tok_of[WT];
@@ -394,12 +386,11 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
     tok_of[t] = row_of(tok0 + t * TILE + col);
     zs[t] = row_rinv(norm.ssq, norm.n_ssq, T, tok_of[t], H, norm.eps) * scale;
   }
-  const E* brow = xn + (int64_t)row_of(tok0 + (wave % WT) * TILE + col) * (NP * KS) + half * G;
   f32x16 acc0[WT], acc1[WT];
   zero_acc<WT>(acc0);
   zero_acc<WT>(acc1);
-  wide_stream<E, WT, WW, LM_PRE, KID>(W + (int64_t)task * task_stride_elems<E>(ksteps) + lane * G, ksteps / WKC, [&] { return brow; }, (int64_t)T * (NP * KS),
-                 sb, nt, acc0, acc1);
+  wide_stream<E, WT, WW, KID>(W + (int64_t)task * task_stride_elems<E>(ksteps), ksteps, xn,
+                                      [&](int r) { return row_of(tok0 + (wave % WT) * TILE + r); }, (int64_t)T * (NP * KS), sb, nt, acc0, acc1, wave);
 #pragma unroll
   for (int t = 0; t < WT; ++t) {
     const bool listed = tok0 + t * TILE + col < n_rows;
@@ -452,6 +443,7 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
         *reinterpret_cast<f32x4*>(part + ((int64_t)row_of(tok0 + i) * n_parts + tgroup) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
     }
   }
+  TRACE_MARK(KID, 7);
   }
 }
 

@@ -1,7 +1,7 @@
 // Shared-operand weight streaming for forwards with many token rows: a workgroup of WW waves covers WW tasks
 // (64 output features each) and WT tiles of 32 token rows.  Each wave streams the weights of its task from memory
 // into registers for the whole K range; the activation fragments of the WT token tiles go through LDS, staged
-// chunk by chunk (WKC k-steps) and double buffered, so that every fragment is fetched once per workgroup.
+// chunk by chunk, so that every fragment is fetched once per workgroup.
 #pragma once
 #include <type_traits>
 
@@ -9,14 +9,24 @@
 
 namespace dinfer {
 
-constexpr int WKC = 4;     // k-steps per staged chunk
-// LDS fragments read ahead of the matrix instructions that use them (pinned by scheduling barriers, see the chunk
-// body), and the chunks of activation fragments a wave holds in registers on their way to LDS: two everywhere
-// except in the many-token expert GEMMs and smoothing contraction (trace ids 10, 11, 24), whose 128 accumulator registers
-// and two activation planes leave room for one only (with two, the pinned read-ahead spills and the expert GEMMs run at half
-// speed; with one they still spill 2 registers of 256 in bf16, the smoothing contraction 14).
-constexpr int WIDE_FD = 4;
-template <int KID> constexpr int wide_bdepth() { return (KID == 10 || KID == 11 || KID == 24) ? 1 : 2; }
+// How a kernel (by its trace id) with WT token tiles moves its operands.  KC: k-steps per chunk; PRE: chunks of weights in
+// the registers of a wave; BD: chunks of activation fragments in its registers on their way to LDS; NB: chunks of fragments
+// in LDS.
+// The forms of four tiles and eight waves (LM head, expert GEMMs) have one workgroup per compute unit and 128 accumulator
+// registers per lane: short chunks with one barrier each let four of them be under way in the registers that two of four
+// k-steps took, and a third LDS buffer carries a wave over the barrier (see the ring below).  Bit for bit the sums of the
+// longer chunks (KC 4, PRE 2, NB 2); LM head at 512 / 160 tokens 366 -> 342 / 220 -> 195 us, gate/up + down at 4287 tokens
+// 534 + 312 -> 526 + 308, no spills (2 registers before).  With chunks of four k-steps and three buffers 539 + 318.  Two workgroups of four waves per compute unit stage the fragments twice: LM head 404.
+template <int KID, int WT> struct WideShape {
+  static constexpr int KC = 4, PRE = 2, BD = KID == 24 ? 1 : 2, NB = 2;
+};
+struct WideShape4x8 {
+  static constexpr int KC = 2, PRE = 4, BD = 1, NB = 3;
+};
+template <> struct WideShape<9, 4> : WideShape4x8 {};
+template <> struct WideShape<10, 4> : WideShape4x8 {};
+template <> struct WideShape<11, 4> : WideShape4x8 {};
+constexpr int WKC = 4;     // K is cut in units of this many k-steps
 
 // Planes of the activations a kernel (by its trace id) feeds to the matrix cores.  The LM head with hundreds of
 // token rows is bound by the matrix cores, and its rounding error is not carried into later layers: it takes the
@@ -33,145 +43,170 @@ template <int N, class F, int I = 0> __device__ inline void static_for(F&& f) {
   }
 }
 
-template <typename E, int KID, int WT> constexpr size_t wide_lds() { return (size_t)2 * WKC * WT * WidePlanes<E, KID>::N * WAVE * 16; }
+// One k-step of a token tile in LDS: 32 rows of PIECES 16-byte pieces, as they lie in memory (plane by plane, half by half).
+// A load covers 64 / PIECES whole rows: neighbouring lanes take the pieces of one row, so that the address unit finds them in
+// one cache line.  In LDS a row's pieces are permuted by the row number (in groups of 16 / PIECES rows), so that neither the
+// writes nor the fragment reads (one piece of 32 rows each) meet in a bank: SQ_LDS_BANK_CONFLICT is 0.
+template <typename E, int KID> struct WidePieces {
+  static constexpr int N = 2 * WidePlanes<E, KID>::N, TILE_VECS = TILE * N, ROWS = WAVE / N;
+  __device__ static int slot(int row, int piece) { return row * N + (piece ^ ((row / (16 / N)) & (N - 1))); }
+};
+template <typename E, int KID, int WT> constexpr size_t wide_lds() {
+  return (size_t)WideShape<KID, WT>::NB * WideShape<KID, WT>::KC * WT * WidePieces<E, KID>::TILE_VECS * 16;
+}
 
-// Accumulate all n_chunks * WKC k-steps.  wp: this wave's task (k-step 0) + lane * G.  brow_of(): the k-major
-// activation row this lane stages (row of token tile `wave % WT`) + (lane / 32) * G; bkstride: its k-step stride.
-// sb: LDS [2][WKC][WT][planes][64] operand vectors.  NT: token tiles that hold rows.  wave: 0 .. WW-1, the
+// Accumulate ksteps k-steps (a multiple of KC).  w: this wave's task (k-step 0).  act: the k-major activations (k-step
+// 0), bkstride: their k-step stride; row_of(r): the activation row that row r of token tile `wave % WT` stands for.
+// sb: LDS [buffers][KC][WT][32 rows][pieces].  NT: token tiles that hold rows.  wave: 0 .. WW-1 (uniform), the
 // wave's rank among the WW waves that share sb (every wave of the workgroup must make the call: it holds the
 // workgroup's barriers).
-// Pipeline per chunk c: barrier; the fragments of chunk c+1 go from registers to LDS buffer (c+1)&1 and the
-// loads of chunk c+3 take their place; chunk c is multiplied out of buffer c&1; the weights of chunk c+WPRE are
-// requested.  Loads past the end are clamped to the last chunk (never used), so the loop body has no branch
-// around a load.  A wave stays within 256 registers, so that the eight waves of a workgroup fit on a compute unit.
-template <typename E, int WT, int NT, int WW, int WPRE, int KID, class BRow>
-__device__ inline void wide_stream_nt(const E* __restrict__ wp, int n_chunks, BRow&& brow_of, int64_t bkstride,
+template <typename E, int WT, int NT, int WW, int KID, class RowOf>
+__device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const E* __restrict__ act, RowOf&& row_of, int64_t bkstride,
                                       typename ET<E>::vec* sb, f32x16 (&acc0)[WT], f32x16 (&acc1)[WT], int wave) {
   typedef typename ET<E>::vec vec;
-  constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = WidePlanes<E, KID>::N;   // planes used; the rows hold Planes<E>::N
-  constexpr int64_t STEP = 2 * WAVE * G;
+  typedef WidePieces<E, KID> Pc;
+  typedef WideShape<KID, WT> Sh;
+  constexpr int KC = Sh::KC, PRE = Sh::PRE, BD = Sh::BD, NB = Sh::NB;
+  constexpr int NP = WidePlanes<E, KID>::N, ROW_BYTES = Planes<E>::N * ET<E>::KS * (int)sizeof(E);   // planes used; a row's k-step
+  constexpr int STEP = 2 * WAVE * 16;              // bytes of a task's k-step
+  static_assert(PRE % BD == 0 && (NB == 2 || NB == 3), "register sets are taken from the unrolled index");
+  static_assert(WW % WT == 0 && (KC * WT) % WW == 0, "every wave stages whole k-steps of one token tile");
+  const int lane = threadIdx.x & 63;
+  const int n_chunks = ksteps / KC, last = n_chunks - 1;
+  TRACE_MARK(KID, 0);
+  constexpr int SKS = KC * WT / WW;                // k-steps of a chunk this wave stages (of token tile wave % WT)
+  const int st = wave % WT, sk0 = (wave / WT) * SKS;
+  constexpr int BUF = KC * WT * Pc::TILE_VECS;
   // Weights that are streamed once (experts, LM head) are loaded non-temporally; those of the dense projections
   // (kernel ids 12, 13: a few MB that every token group reads again) must stay in the L2.
-  auto wload = [](const E* p) { return (KID == 12 || KID == 13) ? load16<E>(p) : load16_stream<E>(p); };
-  static_assert(WPRE % 2 == 0, "buffer parities are taken from the unrolled index");
-  static_assert(WW % WT == 0 && (WKC * WT) % WW == 0, "every wave stages whole k-steps of one token tile");
-  const int lane = threadIdx.x & 63;
-  const int last = n_chunks - 1;
-  TRACE_MARK(KID, 0);
-  constexpr int SKS = WKC * WT / WW;               // k-steps of a chunk this wave stages (of token tile wave % WT)
-  const int st = wave % WT, sk0 = (wave / WT) * SKS;
-  vec wa0[WPRE][WKC], wa1[WPRE][WKC];
-  constexpr int BD = wide_bdepth<KID>();
-  vec bset[BD][SKS][NP];                           // fragments of the next BD chunks, on their way to LDS
-  auto sb_at = [&](int buf, int ks, int t, int q) -> vec& { return sb[((((buf * WKC + ks) * WT + t) * NP + q) * WAVE) + lane]; };
-  // Prologue: the weights of the first WPRE chunks are requested before anything else, since they hang on nothing;
-  // brow_of() then resolves the activation row this lane stages (for the experts a chain of dependent loads through
-  // the permutation), and the fragments of chunks 0 (to LDS), 1 and 2 (to registers) follow.
+  const uint32_t wlane = lane * 16;
+  auto wload = [&](int c, int ks, int tile) {
+    const char* base = (const char*)w + (int64_t)(min(c, last) * KC + ks) * STEP + tile * (WAVE * 16);
+        return (KID == 12 || KID == 13) ? load16<E>((const E*)(base + wlane)) : load16_stream<E>((const E*)(base + wlane));
+  };
+  vec wa0[PRE][KC], wa1[PRE][KC];
+  vec bset[BD][SKS][NP];                           // fragments of later chunks, on their way to LDS
+  // what this lane stages: piece lane % N of NP rows
+  uint32_t src[NP];                                // byte offset in a k-step
+  int dst[NP];
+  // (asked for before the weights: for the experts they hang on the permutation, and loads return in order)
 #pragma unroll
-  for (int i = 0; i < WPRE; ++i) {
-    const int c = min(i, last);
+  for (int j = 0; j < NP; ++j) src[j] = (uint32_t)row_of(j * Pc::ROWS + lane / Pc::N);
 #pragma unroll
-    for (int ks = 0; ks < WKC; ++ks) {
-      wa0[i][ks] = wload(wp + (int64_t)(c * WKC + ks) * STEP);
-      wa1[i][ks] = wload(wp + (int64_t)(c * WKC + ks) * STEP + WAVE * G);
+  for (int i = 0; i < PRE; ++i)
+#pragma unroll
+    for (int ks = 0; ks < KC; ++ks) {
+      wa0[i][ks] = wload(i, ks, 0);
+      wa1[i][ks] = wload(i, ks, 1);
     }
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    const int r = j * Pc::ROWS + lane / Pc::N;
+    src[j] = src[j] * (uint32_t)ROW_BYTES + (lane % Pc::N) * 16;
+    dst[j] = (sk0 * WT + st) * Pc::TILE_VECS + Pc::slot(r, lane % Pc::N);
   }
-  const E* __restrict__ brow = brow_of();
+  auto fetch = [&](int c, vec (&b)[SKS][NP]) {
+    const char* base = (const char*)(act + (int64_t)(min(c, last) * KC + sk0) * bkstride);
+#pragma unroll
+    for (int ks = 0; ks < SKS; ++ks)
+#pragma unroll
+      for (int j = 0; j < NP; ++j) b[ks][j] = load16<E>((const E*)(base + ks * bkstride * (int64_t)sizeof(E) + src[j]));
+  };
+  auto put = [&](int buf, const vec (&b)[SKS][NP]) {
+#pragma unroll
+    for (int ks = 0; ks < SKS; ++ks)
+#pragma unroll
+      for (int j = 0; j < NP; ++j) sb[buf + ks * WT * Pc::TILE_VECS + dst[j]] = b[ks][j];
+  };
   {
-    vec b0[SKS][NP];
-    const int c1 = min(1, last), c2 = min(2, last);
+    vec b0[NB - 1][SKS][NP];
 #pragma unroll
-    for (int ks = 0; ks < SKS; ++ks)
+    for (int i = 0; i < NB - 1; ++i) fetch(i, b0[i]);
 #pragma unroll
-      for (int q = 0; q < NP; ++q) b0[ks][q] = load16<E>(brow + (int64_t)(sk0 + ks) * bkstride + q * KS);
+    for (int i = 0; i < BD; ++i) fetch(NB - 1 + i, bset[(NB - 1 + i) % BD]);
 #pragma unroll
-    for (int ks = 0; ks < SKS; ++ks)
-#pragma unroll
-      for (int q = 0; q < NP; ++q) {
-        bset[1 % BD][ks][q] = load16<E>(brow + (int64_t)(c1 * WKC + sk0 + ks) * bkstride + q * KS);
-        if constexpr (BD == 2) bset[0][ks][q] = load16<E>(brow + (int64_t)(c2 * WKC + sk0 + ks) * bkstride + q * KS);
-      }
-#pragma unroll
-    for (int ks = 0; ks < SKS; ++ks)
-#pragma unroll
-      for (int q = 0; q < NP; ++q) sb_at(0, sk0 + ks, st, q) = b0[ks][q];
+    for (int i = 0; i < NB - 1; ++i) put(i * BUF, b0[i]);
   }
-  // One chunk; i = c % WPRE picks the weight registers and the LDS buffer parities at compile time.
+  int rd[NP];                                      // this lane's vector of plane q in a k-step of a tile
+#pragma unroll
+  for (int q = 0; q < NP; ++q) rd[q] = Pc::slot(lane & 31, 2 * q + (lane >> 5));
+  // Fragments in the order (k-step, token tile, plane).  The LDS read of fragment f + FD is issued before the matrix
+  // instructions of fragment f, and a scheduling barrier keeps the compiler from sinking it back next to its use (left
+  // alone it keeps only two reads in flight and the matrix pipe waits for LDS after every four instructions; measured at
+  // 512 tokens: LM head 362 -> 322 us, QKV 41.7 -> 38.7 us, expert gate/up 118 -> 113 us).  With three buffers the ring runs
+  // on over the barrier.
+  constexpr int F = KC * NT * NP;
+  constexpr int FD = F % 4 == 0 ? 4 : F % 3 == 0 ? 3 : 2;
+  static_assert(F % FD == 0, "the ring goes on over chunks");
+  vec ring[FD];
+  auto frag = [&](int buf, int f) { return sb[buf + ((f / (NT * NP)) * WT + (f / NP) % NT) * Pc::TILE_VECS + rd[f % NP]]; };
+  int cur = 0;                                     // buffer of chunk c
+  if constexpr (NB == 3) {
+    __syncthreads();
+    static_for<FD>([&](auto J) { ring[decltype(J)::value] = frag(0, decltype(J)::value); });
+  }
+  // One chunk; i = c % PRE picks the registers at compile time.  Barrier; the fragments of chunk c + NB - 1 go from registers
+  // to LDS and a later chunk's take their place; chunk c is multiplied; the weights of chunk c + PRE are requested.  Loads
+  // past the end are clamped to the last chunk (never used), so the loop body has no branch around a load.
   auto chunk = [&](auto I, int c) {
     constexpr int i = decltype(I)::value;
     __syncthreads();
     if (c == 0) TRACE_MARK(KID, 1);
     if (c == 1) TRACE_MARK(KID, 2);
-    if (c == 2) TRACE_MARK(KID, 3);
     if (c == 16) TRACE_MARK(KID, 4);
-    if (c == 17) TRACE_MARK(KID, 5);
-    constexpr int nb = (i + 1) & 1, cb = i & 1;   // WPRE is even: parities of c+1 and c
-#pragma unroll
-    for (int ks = 0; ks < SKS; ++ks)
-#pragma unroll
-      for (int q = 0; q < NP; ++q) sb_at(nb, sk0 + ks, st, q) = bset[nb % BD][ks][q];
-    const int cn = min(c + 1 + BD, last);
-#pragma unroll
-    for (int ks = 0; ks < SKS; ++ks)
-#pragma unroll
-      for (int q = 0; q < NP; ++q)
-        bset[nb % BD][ks][q] = load16<E>(brow + (int64_t)(cn * WKC + sk0 + ks) * bkstride + q * KS);
-    // Fragment pipeline: the LDS read of fragment f + FD is issued before the matrix instructions of fragment f, and
-    // a scheduling barrier keeps the compiler from sinking it back next to its use (left alone it keeps only two
-    // reads in flight and the matrix pipe waits for LDS after every four instructions; measured at 512 tokens: LM
-    // head 362 -> 322 us, QKV 41.7 -> 38.7 us, expert gate/up 118 -> 113 us).  Fragments in the order (k-step, token tile, plane).
-    constexpr int F = WKC * NT * NP;
-    constexpr int FD = WIDE_FD < F ? WIDE_FD : F;
-    vec ring[FD];
-    auto frag = [&](int f) -> vec& { return sb_at(cb, f / (NT * NP), (f / NP) % NT, f % NP); };
-    static_for<FD>([&](auto J) { ring[decltype(J)::value] = frag(decltype(J)::value); });
+    if (c == 32) TRACE_MARK(KID, 5);
+    const int nxt = cur + BUF < NB * BUF ? cur + BUF : 0;
+    auto& b = bset[(i + NB - 1) % BD];
+    if constexpr (NB == 3) put(nxt + BUF < NB * BUF ? nxt + BUF : 0, b);
+    else put(nxt, b);
+    fetch(c + NB - 1 + BD, b);
+    if constexpr (NB == 2) static_for<FD>([&](auto J) { ring[decltype(J)::value] = frag(cur, decltype(J)::value); });
     static_for<F>([&](auto Fi) {
       constexpr int f = decltype(Fi)::value, ks = f / (NT * NP), t = (f / NP) % NT;
       const vec b = ring[f % FD];
-      if constexpr (f + FD < F) ring[f % FD] = frag(f + FD);
+      if constexpr (f + FD < F) ring[f % FD] = frag(cur, f + FD);
+      else if constexpr (NB == 3) ring[f % FD] = frag(nxt, f + FD - F);
       __builtin_amdgcn_sched_barrier(0);
       mfma32(acc0[t], wa0[i][ks], b);
       mfma32(acc1[t], wa1[i][ks], b);
     });
-    const int cw = min(c + WPRE, last);
 #pragma unroll
-    for (int ks = 0; ks < WKC; ++ks) {
-      wa0[i][ks] = wload(wp + (int64_t)(cw * WKC + ks) * STEP);
-      wa1[i][ks] = wload(wp + (int64_t)(cw * WKC + ks) * STEP + WAVE * G);
+    for (int ks = 0; ks < KC; ++ks) {
+      wa0[i][ks] = wload(c + PRE, ks, 0);
+      wa1[i][ks] = wload(c + PRE, ks, 1);
     }
+    cur = nxt;
   };
-  // Whole rounds of WPRE chunks run without a test between the chunks: a branch there gives the compiler a path from
+  // Whole rounds of PRE chunks run without a test between the chunks: a branch there gives the compiler a path from
   // one chunk straight back to the loop top, for which it drains every load in flight at each iteration.
   // The first round stands in front of the loop: the prologue leaves the loads in another order than a round does
   // (all weights first, then the fragments), and the wait counts the compiler puts at the loop top are the smaller
   // of what its two ways in allow -- entered straight from the prologue, every chunk waited until all but four of
   // the loads in flight had returned, the weights requested one chunk earlier included, and a wave had one chunk
-  // of weights under way instead of WPRE.
+  // of weights under way instead of PRE.
   int c0 = 0;
-  if (n_chunks >= WPRE) {
-    static_for<WPRE>([&](auto I) { chunk(I, decltype(I)::value); });
-    for (c0 = WPRE; c0 + WPRE <= n_chunks; c0 += WPRE) static_for<WPRE>([&](auto I) { chunk(I, c0 + decltype(I)::value); });
+  if (n_chunks >= PRE) {
+    static_for<PRE>([&](auto I) { chunk(I, decltype(I)::value); });
+    for (c0 = PRE; c0 + PRE <= n_chunks; c0 += PRE) static_for<PRE>([&](auto I) { chunk(I, c0 + decltype(I)::value); });
   }
-  static_for<WPRE - 1>([&](auto I) {
+  static_for<PRE - 1>([&](auto I) {
     if (c0 + decltype(I)::value < n_chunks) chunk(I, c0 + decltype(I)::value);   // uniform over the workgroup
   });
   TRACE_MARK(KID, 6);
 }
 
 // nt: token tiles that hold rows (the others are skipped); the tile count is a compile-time constant of the loop.
-// brow: a callable that returns the activation row pointer the lane stages (see wide_stream_nt).
-template <typename E, int WT, int WW, int WPRE, int KID, class BRow>
-__device__ inline void wide_stream(const E* __restrict__ wp, int n_chunks, BRow&& brow, int64_t bkstride,
-                                   typename ET<E>::vec* sb, int nt, f32x16 (&acc0)[WT], f32x16 (&acc1)[WT],
-                                   int wave = threadIdx.x >> 6) {
+template <typename E, int WT, int WW, int KID, class RowOf>
+__device__ inline void wide_stream(const E* __restrict__ w, int ksteps, const E* __restrict__ act, RowOf&& row_of, int64_t bkstride,
+                                   typename ET<E>::vec* sb, int nt, f32x16 (&acc0)[WT], f32x16 (&acc1)[WT], int wave) {
   if constexpr (WT >= 4) {
-    if (nt >= 4) return wide_stream_nt<E, WT, 4, WW, WPRE, KID>(wp, n_chunks, brow, bkstride, sb, acc0, acc1, wave);
-    if (nt == 3) return wide_stream_nt<E, WT, 3, WW, WPRE, KID>(wp, n_chunks, brow, bkstride, sb, acc0, acc1, wave);
+    if (nt >= 4) return wide_stream_nt<E, WT, 4, WW, KID>(w, ksteps, act, row_of, bkstride, sb, acc0, acc1, wave);
+    if (nt == 3) return wide_stream_nt<E, WT, 3, WW, KID>(w, ksteps, act, row_of, bkstride, sb, acc0, acc1, wave);
   }
   if constexpr (WT >= 2) {
-    if (nt >= 2) return wide_stream_nt<E, WT, 2, WW, WPRE, KID>(wp, n_chunks, brow, bkstride, sb, acc0, acc1, wave);
+    if (nt >= 2) return wide_stream_nt<E, WT, 2, WW, KID>(w, ksteps, act, row_of, bkstride, sb, acc0, acc1, wave);
   }
-  wide_stream_nt<E, WT, 1, WW, WPRE, KID>(wp, n_chunks, brow, bkstride, sb, acc0, acc1, wave);
+  wide_stream_nt<E, WT, 1, WW, KID>(w, ksteps, act, row_of, bkstride, sb, acc0, acc1, wave);
 }
 
 }  // namespace dinfer
