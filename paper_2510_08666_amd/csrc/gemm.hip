@@ -595,7 +595,7 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
 }
 
 // ------------------------------------------------------------------------------------------------
-// Dense projections over many token rows (more than 64).  A workgroup takes TASKS (four or two) tasks and WT token
+// Dense projections over many token rows (more than 64).  A workgroup takes TASKS (eight, four or two) tasks and up to WT token
 // tiles; its TASKS * KH waves are KH teams, each team with its own share of the K range, its own LDS staging area for the
 // activation fragments (wide_stream.hpp) and one wave per task, which streams that task's weights once and keeps
 // the accumulators of 64 features x WT*32 rows.  The teams' sums are folded through LDS at the end and team 0
@@ -609,45 +609,45 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
 // 41 / 29 after the epilogue stores were widened, four teams of one token tile 94 / 37; four token tiles per
 // workgroup 102 / 95 (too few workgroups); two tasks per workgroup 57 / 19 (the output projection, with 32 tasks,
 // then fills the chip with 256 workgroups).
-constexpr int DENSE_KH = 2, DENSE_WT = 2;
-static_assert(DENSE_TILE == TILE && DENSE_WT == 2, "dense_plan.hpp counts in these units");
+constexpr int DENSE_KH = 2;
+static_assert(DENSE_TILE == TILE, "dense_plan.hpp counts in these units");
 
-template <typename E, int KID, int WT, int DENSE_TASKS> constexpr size_t dense_lds() {
-  const size_t stage = DENSE_KH * wide_lds<E, KID, WT>();
-  const size_t fold = (size_t)(DENSE_KH - 1) * DENSE_TASKS * 2 * WT * 16 * WAVE * 4;
+template <typename E, int KID, int WT, int TASKS, int KH> constexpr size_t dense_lds() {
+  const size_t stage = KH * wide_lds<E, KID, WT>();
+  const size_t fold = (size_t)(KH - 1) * TASKS * 2 * WT * 16 * WAVE * 4;
   return stage > fold ? stage : fold;
 }
 
-template <typename E, int WT, int DENSE_TASKS, class Epi>
-__global__ __launch_bounds__(DENSE_TASKS * DENSE_KH * WAVE) void gemm_dense_kernel(const E* __restrict__ W, int ksteps,
-                                                                                  const E* __restrict__ B, int T,
-                                                                                  int n_tasks, Epi epi, const int32_t* __restrict__ live) {
+// The token tiles are dealt evenly to the gridDim.y token groups, at most WT each.
+template <typename E, int WT, int TASKS, int KH, class Epi>
+__global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* __restrict__ W, int ksteps,
+                                                                       const E* __restrict__ B, int T, int n_tasks,
+                                                                       Epi epi, const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   typedef typename ET<E>::vec vec;
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
   constexpr int G = ET<E>::G, KS = ET<E>::KS, NP = Planes<E>::N, PER = 4;
   constexpr int KID = Epi::ROWSUM ? 13 : 12;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-  const int team = wave / DENSE_TASKS, rank = wave % DENSE_TASKS;
-  const int slot = blockIdx.x * DENSE_TASKS + rank, task = min(slot, n_tasks - 1);
-  const int tok0 = blockIdx.y * WT * TILE;
-  const int nt = min(WT, (T - tok0 + TILE - 1) / TILE);
-  const int chunks = ksteps / WKC / DENSE_KH;          // per team
-  const int ks0 = team * chunks * WKC;
+  const int team = wave / TASKS, rank = wave % TASKS;
+  const int slot = blockIdx.x * TASKS + rank, task = min(slot, n_tasks - 1);
+  const int tiles = (T + TILE - 1) / TILE, tile0 = (int)((int64_t)tiles * blockIdx.y / gridDim.y);
+  const int nt = (int)((int64_t)tiles * (blockIdx.y + 1) / gridDim.y) - tile0, tok0 = tile0 * TILE;
+  const int ks_team = ksteps / (WKC * KH) * WKC, ks0 = team * ks_team;
   vec* sb = reinterpret_cast<vec*>(lds_raw + team * wide_lds<E, KID, WT>());
   auto row_of = [&](int r) { return min(tok0 + (rank % WT) * TILE + r, T - 1); };
   f32x16 acc0[WT], acc1[WT];
   zero_acc<WT>(acc0);
   zero_acc<WT>(acc1);
-  wide_stream<E, WT, DENSE_TASKS, KID>(
-      W + (int64_t)task * task_stride_elems<E>(ksteps) + (int64_t)ks0 * (2 * WAVE * G), chunks * WKC, B + (int64_t)ks0 * T * (NP * KS), row_of,
+  wide_stream<E, WT, TASKS, KID>(
+      W + (int64_t)task * task_stride_elems<E>(ksteps) + (int64_t)ks0 * (2 * WAVE * G), ks_team, B + (int64_t)ks0 * T * (NP * KS), row_of,
       (int64_t)T * (NP * KS), sb, nt, acc0, acc1, rank);
-  if (DENSE_KH > 1) {
+  if constexpr (KH > 1) {
     // fold: team h > 0 leaves its sums at red[h-1][rank][t*32 + tile*16 + v][lane], team 0 adds them up
     float* red = reinterpret_cast<float*>(lds_raw);
     __syncthreads();   // the staging areas are done with
     if (team > 0) {
-      float* r = red + ((int64_t)((team - 1) * DENSE_TASKS + rank) * (2 * WT * 16)) * WAVE + lane;
+      float* r = red + ((int64_t)((team - 1) * TASKS + rank) * (2 * WT * 16)) * WAVE + lane;
 #pragma unroll
       for (int t = 0; t < WT; ++t)
 #pragma unroll
@@ -658,8 +658,8 @@ __global__ __launch_bounds__(DENSE_TASKS * DENSE_KH * WAVE) void gemm_dense_kern
     }
     __syncthreads();
     if (team > 0) return;
-    for (int h = 1; h < DENSE_KH; ++h) {
-      const float* r = red + ((int64_t)((h - 1) * DENSE_TASKS + rank) * (2 * WT * 16)) * WAVE + lane;
+    for (int h = 1; h < KH; ++h) {
+      const float* r = red + ((int64_t)((h - 1) * TASKS + rank) * (2 * WT * 16)) * WAVE + lane;
 #pragma unroll
       for (int t = 0; t < WT; ++t)
 #pragma unroll
@@ -671,39 +671,68 @@ __global__ __launch_bounds__(DENSE_TASKS * DENSE_KH * WAVE) void gemm_dense_kern
   }
   if (slot >= n_tasks) return;
   // Epilogue in three sweeps over the (tile, register group) pairs, so that the loads of one sweep are all in flight
-  // together: what is addressed by the token, what is addressed by what those loads return, then the arithmetic.
+  // together: what is addressed by the token, what is addressed by what those loads return, then the arithmetic.  Four
+  // tiles, whose accumulators leave no room for that, go one by one.
   constexpr int NG = 16 / PER;
-  typename Epi::template Pre<PER> pre[WT][NG];
+  if constexpr (WT < 4) {
+    typename Epi::template Pre<PER> pre[WT][NG];
 #pragma unroll
-  for (int t = 0; t < WT; ++t)
+    for (int t = 0; t < WT; ++t)
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const int tok = tok0 + t * TILE + col;
-      pre[t][g] = epi.template prefetch<PER>(task, tok, t < nt && tok < T, half, g * PER);
-    }
-#pragma unroll
-  for (int t = 0; t < WT; ++t)
-#pragma unroll
-    for (int g = 0; g < NG; ++g) epi.template prefetch2<PER>(pre[t][g], task, half, g * PER);
-#pragma unroll
-  for (int t = 0; t < WT; ++t) {
-    const int tok = tok0 + t * TILE + col;
-    const bool valid = t < nt && tok < T;
-    float ss = 0.f;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      float a0[PER], a1[PER];
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        a0[i] = acc0[t][g * PER + i];
-        a1[i] = acc1[t][g * PER + i];
+      for (int g = 0; g < NG; ++g) {
+        const int tok = tok0 + t * TILE + col;
+        pre[t][g] = epi.template prefetch<PER>(task, tok, t < nt && tok < T, half, g * PER);
       }
-      ss += epi.template apply<PER>(pre[t][g], task, tok, valid, half, g * PER, a0, a1);
+#pragma unroll
+    for (int t = 0; t < WT; ++t)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) epi.template prefetch2<PER>(pre[t][g], task, half, g * PER);
+#pragma unroll
+    for (int t = 0; t < WT; ++t) {
+      const int tok = tok0 + t * TILE + col;
+      const bool valid = t < nt && tok < T;
+      float ss = 0.f;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        float a0[PER], a1[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          a0[i] = acc0[t][g * PER + i];
+          a1[i] = acc1[t][g * PER + i];
+        }
+        ss += epi.template apply<PER>(pre[t][g], task, tok, valid, half, g * PER, a0, a1);
+      }
+      if (Epi::ROWSUM) {   // the wave holds the whole task: the row statistic is the sum over its two half-waves
+        ss += __shfl_xor(ss, 32, WAVE);
+        if (half == 0 && valid) epi.row_sum(task, tok, ss);
+      }
     }
-    if (Epi::ROWSUM) {   // the wave holds the whole task: the row statistic is the sum over its two half-waves
-      ss += __shfl_xor(ss, 32, WAVE);
-      if (half == 0 && valid) epi.row_sum(task, tok, ss);
-    }
+  } else {
+    static_for<WT>([&](auto I) {
+      constexpr int t = decltype(I)::value;
+      const int tok = tok0 + t * TILE + col;
+      const bool valid = t < nt && tok < T;
+      typename Epi::template Pre<PER> pre[NG];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) pre[g] = epi.template prefetch<PER>(task, tok, valid, half, g * PER);
+#pragma unroll
+      for (int g = 0; g < NG; ++g) epi.template prefetch2<PER>(pre[g], task, half, g * PER);
+      float ss = 0.f;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        float a0[PER], a1[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          a0[i] = acc0[t][g * PER + i];
+          a1[i] = acc1[t][g * PER + i];
+        }
+        ss += epi.template apply<PER>(pre[g], task, tok, valid, half, g * PER, a0, a1);
+      }
+      if (Epi::ROWSUM) {
+        ss += __shfl_xor(ss, 32, WAVE);
+        if (half == 0 && valid) epi.row_sum(task, tok, ss);
+      }
+    });
   }
   TRACE_MARK(KID, 7);
 }
@@ -715,25 +744,29 @@ __global__ __launch_bounds__(DENSE_TASKS * DENSE_KH * WAVE) void gemm_dense_kern
 // of the weights, split-K was ahead all along, 11.5 against 17.1.)
 static bool dense_applies(int T, int ksteps) { return T > 2 * TILE && ksteps % (WKC * DENSE_KH) == 0; }
 
-template <typename E, int WT, int TASKS, class Epi>
-static void launch_dense_as(const E* W, int ksteps, const E* B, int T, int n_tasks, const Epi& epi, hipStream_t st) {
+template <typename E, int WT, int TASKS, int KH, class Epi>
+static void launch_dense_as(const E* W, int ksteps, const E* B, int T, int n_tasks, int groups, const Epi& epi, hipStream_t st) {
   constexpr int KID = Epi::ROWSUM ? 13 : 12;
-  gemm_dense_kernel<E, WT, TASKS, Epi><<<dim3((n_tasks + TASKS - 1) / TASKS, (T + WT * TILE - 1) / (WT * TILE)),
-                                        TASKS * DENSE_KH * WAVE, dense_lds<E, KID, WT, TASKS>(), st>>>(W, ksteps, B, T,
-                                                                                                    n_tasks, epi, live_word());
+  gemm_dense_kernel<E, WT, TASKS, KH, Epi><<<dim3((n_tasks + TASKS - 1) / TASKS, groups),
+                                            TASKS * KH * WAVE, dense_lds<E, KID, WT, TASKS, KH>(), st>>>(W, ksteps, B, T, n_tasks,
+                                                                                                       epi, live_word());
 }
 // More tasks and token tiles per workgroup cut the operand traffic, but only while the launch still fills the chip.
 template <typename E, class Epi>
 static void launch_dense(const E* W, int ksteps, const E* B, int T, int n_tasks, const Epi& epi, hipStream_t st) {
   const DenseForm f = dense_form(sizeof(E) == 2, n_tasks, T);
-  if (f.tiles == DENSE_WT) launch_dense_as<E, DENSE_WT, 4, Epi>(W, ksteps, B, T, n_tasks, epi, st);
-  else if (f.tasks == 4) launch_dense_as<E, 1, 4, Epi>(W, ksteps, B, T, n_tasks, epi, st);
-  else launch_dense_as<E, 1, 2, Epi>(W, ksteps, B, T, n_tasks, epi, st);
+  if (f.tasks == DENSE_WIDE_TASKS) {
+    if constexpr (sizeof(E) == 2) launch_dense_as<E, DENSE_WIDE_TILES, DENSE_WIDE_TASKS, 1, Epi>(W, ksteps, B, T, n_tasks, f.groups, epi, st);
+  } else if (f.tiles == 2) launch_dense_as<E, 2, 4, DENSE_KH, Epi>(W, ksteps, B, T, n_tasks, f.groups, epi, st);
+  else if (f.tasks == 4) launch_dense_as<E, 1, 4, DENSE_KH, Epi>(W, ksteps, B, T, n_tasks, f.groups, epi, st);
+  else launch_dense_as<E, 1, 2, DENSE_KH, Epi>(W, ksteps, B, T, n_tasks, f.groups, epi, st);
 }
 
 template <typename E, class Epi> static bool configure_dense() {
-  return opt_in_lds((const void*)gemm_dense_kernel<E, DENSE_WT, 4, Epi>) && opt_in_lds((const void*)gemm_dense_kernel<E, 1, 4, Epi>) &&
-         opt_in_lds((const void*)gemm_dense_kernel<E, 1, 2, Epi>);
+  if constexpr (sizeof(E) == 2)
+    if (!opt_in_lds((const void*)gemm_dense_kernel<E, DENSE_WIDE_TILES, DENSE_WIDE_TASKS, 1, Epi>)) return false;
+  return opt_in_lds((const void*)gemm_dense_kernel<E, 2, 4, DENSE_KH, Epi>) && opt_in_lds((const void*)gemm_dense_kernel<E, 1, 4, DENSE_KH, Epi>) &&
+         opt_in_lds((const void*)gemm_dense_kernel<E, 1, 2, DENSE_KH, Epi>);
 }
 
 template <typename E> static void launch_qkv_t(bool bf16, const QkvArgs& a, hipStream_t st) {

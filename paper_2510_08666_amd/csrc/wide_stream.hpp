@@ -26,6 +26,8 @@ struct WideShape4x8 {
 template <> struct WideShape<9, 4> : WideShape4x8 {};
 template <> struct WideShape<10, 4> : WideShape4x8 {};
 template <> struct WideShape<11, 4> : WideShape4x8 {};
+template <> struct WideShape<12, 4> : WideShape4x8 {};
+template <> struct WideShape<13, 4> : WideShape4x8 {};
 constexpr int WKC = 4;     // K is cut in units of this many k-steps
 
 // Planes of the activations a kernel (by its trace id) feeds to the matrix cores.  The LM head with hundreds of

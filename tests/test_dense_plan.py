@@ -11,6 +11,7 @@ extern "C" int form(int bf16, int n_tasks, int T) {
   const dinfer::DenseForm f = dinfer::dense_form(bf16 != 0, n_tasks, T);
   return 10 * f.tasks + f.tiles;
 }
+extern "C" int groups(int bf16, int n_tasks, int T) { return dinfer::dense_form(bf16 != 0, n_tasks, T).groups; }
 """
 
 
@@ -31,3 +32,25 @@ def test_two_tiles_follow_the_type(form):
 def test_two_tasks_where_four_leave_the_chip_idle(form, dtype):
     assert form(dtype, 96, 96) == (2, 1) and form(dtype, 96, 160) == (2, 1) and form(dtype, 96, 192) == (4, 1)
     assert form(dtype, 32, 512) == (2, 1) and form(dtype, 32, 560) == (4, 1)
+
+
+@pytest.fixture(scope="module")
+def groups(tmp_path_factory):
+    lib = host_shim.load(tmp_path_factory.mktemp("dense_groups"), SHIM)
+    return lambda dtype, n_tasks, T: lib.groups(int(dtype == "bf16"), n_tasks, T)
+
+
+def test_eight_tasks_from_the_second_round_of_four(form):
+    assert form("bf16", 96, 640) == (4, 2) and form("bf16", 96, 641) == (8, 4)        # 24 x 10 and 24 x 11 workgroups
+    assert form("bf16", 32, 2048) == (4, 2) and form("bf16", 32, 2049) == (8, 4)
+    assert form("bf16", 36, 4000) == (8, 4) and form("bf16", 33, 4000) == (4, 2) and form("f32", 96, 4000) == (4, 2)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_token_groups_cover_every_tile(form, groups, dtype):
+    """Group g takes tiles tiles*g/n .. tiles*(g+1)/n: at least one and no more than its form holds."""
+    for n_tasks in (1, 2, 6, 8, 16, 32, 33, 48, 64, 96, 144, 192):
+        for T in list(range(65, 2200, 31)) + [4287, 8192, 30001]:
+            tiles, n = (T + 31) // 32, groups(dtype, n_tasks, T)
+            size = {tiles * (g + 1) // n - tiles * g // n for g in range(n)}
+            assert min(size) >= 1 and max(size) <= form(dtype, n_tasks, T)[1], (n_tasks, T)

@@ -12,11 +12,13 @@ from harness import GpuRun, OracleRun, bars_for, kv_close, make_case
 pytestmark = pytest.mark.gpu
 
 
+# The last one takes attention in its other form and the output projection (hidden 4096) over eight tasks and four token
+# tiles at once, as the others do the QKV projection.
 @pytest.mark.parametrize("n_heads,head_dim,lens", [(32, 64, [385, 416, 447, 97]), (32, 128, [384, 353, 129, 200]),
-                                                   (64, 64, [512, 97]), (64, 64, [500, 40])])
+                                                   (64, 64, [512, 97]), (64, 64, [500, 40]), (1, 128, [1057])])
 def test_prefill_rows_form(n_heads, head_dim, lens):
     tiny = di.model_preset("tiny")
-    cfg = di.configs.scaled(tiny, hidden=128, n_heads=n_heads, head_dim=head_dim, n_experts=8, moe_inter=64, vocab=500,
+    cfg = di.configs.scaled(tiny, hidden=4096 if n_heads == 1 else 128, n_heads=n_heads, head_dim=head_dim, n_experts=8, moe_inter=64, vocab=500,
                             dtype="bf16", logit_scale=1.0)
     wl = di.Workload("prompts", cfg, len(lens), 1, 0, 0, threshold=0.9, seed_index=70)
     cfg, w, inp = make_case(wl, room=max(lens))
