@@ -7,6 +7,7 @@
 namespace dinfer {
 
 constexpr int EXPERT_TILE = 32;   // rows of a token tile
+constexpr int EXPERT_DIES = 8;     // workgroup i of a launch runs on die i % 8
 constexpr int EXPERT_CUS = 256;   // compute units; eight waves of these kernels fill one
 // An item is a run of an expert's sorted rows, up to expert_group_tiles tiles; a workgroup takes it with EXPERT_WW tasks (one
 // per wave) and four tiles, or, up to MID_ROWS rows per expert on average, with MID_WW tasks and two tiles, so that two
@@ -43,5 +44,22 @@ inline int expert_most_piece_items(int E, int n_pairs, int H, int I) {
   const int beyond = expert_work_items(E, n_pairs, expert_group_tiles(E, n_pairs)) - round;
   return beyond <= 0 ? 0 : beyond < few ? beyond : few;
 }
+
+// From two full items per expert on average (prompts), the items of an expert run on one die, and each with its task groups
+// one after the other, so that the expert's weights and the item's rows come to that die's L2 once: the work list is dealt out
+// over the dies (item i to die i % 8), its full items lie EXPERT_DIES places apart, and the weights are loaded as ordinary
+// lines (non-temporal ones do not stay in the L2: 32 workgroups of a die that read 16 MB side by side get 11 to 14 TB/s over
+// all dies, with ordinary loads 23 to 33).  4287 tokens, about five items per expert: L2 misses of gate/up + down 20.8 + 12.7 ->
+// 13.0 + 7.5 million lines, 546 + 319 -> 535 + 299 us.  With fewer items nothing is shared, and ordinary loads only push
+// other data out of the caches (gate/up at 160 tokens 93 -> 103 us).
+inline bool expert_shared(int E, int n_pairs) { return n_pairs >= 2 * EXPERT_WT * EXPERT_TILE * E; }
+inline int expert_item_stride(int E, int n_pairs) { return expert_shared(E, n_pairs) ? EXPERT_DIES : 1; }
+// Place of item i of n: items 0, 1, ... take the places 0, stride, 2 * stride, ... below n, then 1, 1 + stride, ...
+DINFER_HOST_DEVICE inline int expert_item_place(int i, int n, int stride) {
+  const int q = n / stride, r = n % stride, front = r * (q + 1);   // r classes of q + 1 places, then classes of q
+  return i < front ? i % (q + 1) * stride + i / (q + 1) : (i - front) % (q > 0 ? q : 1) * stride + r + (i - front) / (q > 0 ? q : 1);
+}
+// The place behind place p.
+DINFER_HOST_DEVICE inline int expert_next_place(int p, int n, int stride) { return p + stride < n ? p + stride : p % stride + 1; }
 
 }  // namespace dinfer

@@ -618,7 +618,7 @@ template <typename E, int KID, int WT, int TASKS, int KH> constexpr size_t dense
   return stage > fold ? stage : fold;
 }
 
-// The token tiles are dealt evenly to the gridDim.y token groups, at most WT each.
+// The token tiles go to the gridDim.y token groups WT by WT, with four tiles evenly (at most four each).
 template <typename E, int WT, int TASKS, int KH, class Epi>
 __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* __restrict__ W, int ksteps,
                                                                        const E* __restrict__ B, int T, int n_tasks,
@@ -631,8 +631,11 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int team = wave / TASKS, rank = wave % TASKS;
   const int slot = blockIdx.x * TASKS + rank, task = min(slot, n_tasks - 1);
-  const int tiles = (T + TILE - 1) / TILE, tile0 = (int)((int64_t)tiles * blockIdx.y / gridDim.y);
-  const int nt = (int)((int64_t)tiles * (blockIdx.y + 1) / gridDim.y) - tile0, tok0 = tile0 * TILE;
+  // (divisions only where the groups are unequal: they cost the small forms 0.6 us a launch; tiles * groups fits 32 bits)
+  const uint32_t tiles = (T + TILE - 1) / TILE;
+  const int tile0 = WT < 4 ? blockIdx.y * WT : tiles * blockIdx.y / gridDim.y;
+  const int nt = WT < 4 ? min(WT, (int)tiles - tile0) : (int)(tiles * (blockIdx.y + 1) / gridDim.y) - tile0;
+  const int tok0 = tile0 * TILE;
   const int ks_team = ksteps / (WKC * KH) * WKC, ks0 = team * ks_team;
   vec* sb = reinterpret_cast<vec*>(lds_raw + team * wide_lds<E, KID, WT>());
   auto row_of = [&](int r) { return min(tok0 + (rank % WT) * TILE + r, T - 1); };
@@ -1261,7 +1264,8 @@ template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a
         W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
         a.topk_w, 0, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
     launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work,
-                   expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
+                   expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I),
+                   expert_item_stride(a.E, a.T * a.top_k), st);
   }
 }
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {

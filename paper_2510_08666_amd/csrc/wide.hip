@@ -195,11 +195,24 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
   const int4* items = reinterpret_cast<const int4*>(work + WORK_ITEMS);
   const int n_big = work[WORK_BIG];
-  if ((int)blockIdx.y < n_big) {
-    expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
-    return;
+  int piece;
+  if constexpr (KID == 25 || KID == 26) {
+    // all task groups of an item on one die, one after the other; its expert's other items follow there (expert_plan.hpp)
+    const int wg = blockIdx.y * gridDim.x + blockIdx.x, turn = wg / XCDS, item = turn / (int)gridDim.x * XCDS + wg % XCDS;
+    const int whole = (n_big + XCDS - 1) / XCDS * XCDS * gridDim.x;
+    if (wg < whole) {
+      if (item < n_big) expert_tasks<E, WT, WW, KID, Op>(op, items[item], turn % (int)gridDim.x, lds_raw);
+      return;
+    }
+    piece = wg - whole;
+  } else {
+    if ((int)blockIdx.y < n_big) {
+      expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+      return;
+    }
+    piece = ((int)blockIdx.y - n_big) * gridDim.x + blockIdx.x;
   }
-  const int piece = ((int)blockIdx.y - n_big) * gridDim.x + blockIdx.x, n_tasks = op.n_tasks();
+  const int n_tasks = op.n_tasks();
   if (piece >= (work[WORK_ALL] - n_big) * n_tasks) return;   // uniform over the block
   const int4 it = items[n_big + piece / n_tasks];
   if (it.z <= TILE) expert_piece<E, 1, WW, Op>(op, it, piece % n_tasks, lds_raw);
@@ -222,10 +235,10 @@ constexpr int GU1_WW = 1;
 // LDS of expert_many_kernel: staged fragments, or two tiles of WW waves' partial sums
 template <int WW> constexpr size_t many_lds() { return (size_t)WW * 2 * 2 * 16 * WAVE * 4; }
 
-// KID: trace ids of the forms for up to 32, up to 64, few rows per expert, many rows per expert
+// KID: trace ids of the forms for up to 32, up to 64, few rows per expert, many rows per expert, several items per expert
 // (Up to 32 tokens the down projection takes its first form, ids 18 and the pieces of one tile, only under the single-slice
 // test switch: expert_down_fused_kernel has it otherwise.)
-template <typename E, int WW1, int K1, int K2, int K3, int K4, class Op>
+template <typename E, int WW1, int K1, int K2, int K3, int K4, int K5, class Op>
 static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hipStream_t st) {
   const int n_pairs = a.T * a.top_k;
   auto grid = [&](int ww, int items) { return dim3((n_tasks + ww - 1) / ww, items); };
@@ -244,12 +257,13 @@ static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hip
     else
       expert_kernel<E, 2, SMALL_WW, K2, Op><<<grid(SMALL_WW, a.E), SMALL_WW * WAVE, wide_lds<E, K2, 2>(), st>>>(op, n_items, records, live_word());
   } else {
-    auto many = [&](auto kernel, int wt, int ww, size_t lds) {
-      const dim3 whole = grid(ww, expert_work_items(a.E, n_pairs, wt));
+    auto many = [&](auto kernel, int wt, int ww, size_t lds, int more = 0) {   // more: rows of the grid for the whole multiple of dies
+      const dim3 whole = grid(ww, expert_work_items(a.E, n_pairs, wt) + more);
       const int pieces = expert_most_piece_items(a.E, n_pairs, a.H, a.I) * n_tasks;
       kernel<<<dim3(whole.x, whole.y + (pieces + whole.x - 1) / whole.x), ww * WAVE, lds, st>>>(op, a.work, live_word());
     };
     if (expert_group_tiles(a.E, n_pairs) == MID_WT) many(expert_many_kernel<E, MID_WT, MID_WW, K3, Op>, MID_WT, MID_WW, many_lds<MID_WW>());
+    else if (expert_shared(a.E, n_pairs)) many(expert_many_kernel<E, WT, EXPERT_WW, K5, Op>, WT, EXPERT_WW, many_lds<EXPERT_WW>(), XCDS - 1);
     else many(expert_many_kernel<E, WT, EXPERT_WW, K4, Op>, WT, EXPERT_WW, many_lds<EXPERT_WW>());
   }
 }
@@ -257,11 +271,11 @@ template <typename E> static GateUp<E> gate_up_op(const ExpertArgs& a) {
   return GateUp<E>{(const E*)a.w_gate_up, (const E*)a.xn, a.rinv, (E*)a.y, a.perm, a.T, a.H, a.I, a.top_k, a.topk_w};
 }
 template <typename E> static void launch_gate_up_wide_t(const ExpertArgs& a, hipStream_t st) {
-  launch_expert_op<E, GU1_WW, 16, 17, 20, 10>(gate_up_op<E>(a), a, a.I / TILE, st);
+  launch_expert_op<E, GU1_WW, 16, 17, 20, 10, 25>(gate_up_op<E>(a), a, a.I / TILE, st);
 }
 template <typename E> static void launch_down_wide_t(const ExpertArgs& a, hipStream_t st) {
   const Down<E> op{(const E*)a.w_down, (const E*)a.y, a.o, a.perm, a.T * a.top_k, a.H, a.I};
-  launch_expert_op<E, SMALL_WW, 18, 19, 21, 11>(op, a, a.H / (2 * TILE), st);
+  launch_expert_op<E, SMALL_WW, 18, 19, 21, 11, 26>(op, a, a.H / (2 * TILE), st);
 }
 void launch_expert_gate_up_wide(bool bf16, const ExpertArgs& a, hipStream_t st) {
   if (bf16) launch_gate_up_wide_t<bf16_t>(a, st);
@@ -477,7 +491,11 @@ void launch_lm_head_wide(bool bf16, const LmArgs& a, hipStream_t st) {
 
 bool configure_wide() {
   auto opt_in = [](const void* f, int bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; };
-  const void* many[8] = {(const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 10, GateUp<bf16_t>>,
+  const void* many[12] = {(const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 25, GateUp<bf16_t>>,
+                         (const void*)expert_many_kernel<float, WT, EXPERT_WW, 25, GateUp<float>>,
+                         (const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 26, Down<bf16_t>>,
+                         (const void*)expert_many_kernel<float, WT, EXPERT_WW, 26, Down<float>>,
+                         (const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 10, GateUp<bf16_t>>,
                          (const void*)expert_many_kernel<float, WT, EXPERT_WW, 10, GateUp<float>>,
                          (const void*)expert_many_kernel<bf16_t, WT, EXPERT_WW, 11, Down<bf16_t>>,
                          (const void*)expert_many_kernel<float, WT, EXPERT_WW, 11, Down<float>>,

@@ -12,22 +12,25 @@ namespace dinfer {
 // How a kernel (by its trace id) with WT token tiles moves its operands.  KC: k-steps per chunk; PRE: chunks of weights in
 // the registers of a wave; BD: chunks of activation fragments in its registers on their way to LDS; NB: chunks of fragments
 // in LDS.
-// The forms of four tiles and eight waves (LM head, expert GEMMs) have one workgroup per compute unit and 128 accumulator
-// registers per lane: short chunks with one barrier each let four of them be under way in the registers that two of four
-// k-steps took, and a third LDS buffer carries a wave over the barrier (see the ring below).  Bit for bit the sums of the
-// longer chunks (KC 4, PRE 2, NB 2); LM head at 512 / 160 tokens 366 -> 342 / 220 -> 195 us, gate/up + down at 4287 tokens
-// 534 + 312 -> 526 + 308, no spills (2 registers before).  With chunks of four k-steps and three buffers 539 + 318.  Two workgroups of four waves per compute unit stage the fragments twice: LM head 404.
+// The forms of four tiles and eight waves have one workgroup per compute unit and 128 accumulator registers per lane.  Where
+// the matrix cores are the bound (LM head, prompts), short chunks with one barrier each let four of them be under way in the
+// registers that two of four k-steps took, and a third LDS buffer carries a wave over the barrier (see the ring below).  Bit
+// for bit the sums of the longer chunks; LM head at 512 / 160 tokens 366 -> 342 / 220 -> 195 us, gate/up + down at 4287
+// tokens 534 + 312 -> 526 + 308, no spills (2 registers before); with chunks of four k-steps and three buffers 539 + 318.  The
+// expert GEMMs with an item or less per expert (ids 10, 11) are bound by their weights and keep four k-steps and two buffers
+// (12 sequences of 32, whole refresh: 569 us, 573 with short chunks).  Two workgroups of four waves per compute unit stage
+// the fragments twice: LM head 404.
 template <int KID, int WT> struct WideShape {
-  static constexpr int KC = 4, PRE = 2, BD = KID == 24 ? 1 : 2, NB = 2;
+  static constexpr int KC = 4, PRE = 2, BD = KID == 24 || KID == 10 || KID == 11 ? 1 : 2, NB = 2;
 };
 struct WideShape4x8 {
   static constexpr int KC = 2, PRE = 4, BD = 1, NB = 3;
 };
 template <> struct WideShape<9, 4> : WideShape4x8 {};
-template <> struct WideShape<10, 4> : WideShape4x8 {};
-template <> struct WideShape<11, 4> : WideShape4x8 {};
 template <> struct WideShape<12, 4> : WideShape4x8 {};
 template <> struct WideShape<13, 4> : WideShape4x8 {};
+template <> struct WideShape<25, 4> : WideShape4x8 {};
+template <> struct WideShape<26, 4> : WideShape4x8 {};
 constexpr int WKC = 4;     // K is cut in units of this many k-steps
 
 // Planes of the activations a kernel (by its trace id) feeds to the matrix cores.  The LM head with hundreds of
@@ -84,7 +87,7 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
   const uint32_t wlane = lane * 16;
   auto wload = [&](int c, int ks, int tile) {
     const char* base = (const char*)w + (int64_t)(min(c, last) * KC + ks) * STEP + tile * (WAVE * 16);
-        return (KID == 12 || KID == 13) ? load16<E>((const E*)(base + wlane)) : load16_stream<E>((const E*)(base + wlane));
+        return (KID == 12 || KID == 13 || KID == 25 || KID == 26) ? load16<E>((const E*)(base + wlane)) : load16_stream<E>((const E*)(base + wlane));
   };
   vec wa0[PRE][KC], wa1[PRE][KC];
   vec bset[BD][SKS][NP];                           // fragments of later chunks, on their way to LDS

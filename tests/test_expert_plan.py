@@ -14,6 +14,8 @@ extern "C" void plan(int E, int n_pairs, int H, int I, int* o) {
   o[0] = expert_group_tiles(E, n_pairs), o[1] = expert_round_items(E, n_pairs, H, I);
   o[2] = expert_work_items(E, n_pairs, o[0]), o[3] = expert_most_piece_items(E, n_pairs, H, I);
 }
+extern "C" int item_place(int i, int n, int stride) { return expert_item_place(i, n, stride); }
+extern "C" int next_place(int p, int n, int stride) { return expert_next_place(p, n, stride); }
 extern "C" int piece_items(int items, int light, int round) { return expert_piece_items(items, light, round); }
 """
 
@@ -75,3 +77,13 @@ def test_pieces_are_few(lib):
     # a forward whose routing cannot exceed a round asks for no workgroups of pieces
     assert _plan(lib, 48, 1298, 128, 192)[3] == 0
     assert _plan(lib, 64, 8 * 256, 2048, 1024)[3] == 64 + 2048 // 128 - 64
+
+
+@pytest.mark.parametrize("stride", [1, 8])
+def test_items_have_places_of_their_own(lib, stride):
+    """Consecutive items lie a stride apart but where the list wraps, so that an expert's items run on one die."""
+    for n in list(range(1, 40)) + [63, 64, 65, 331, 509]:
+        places = [lib.item_place(i, n, stride) for i in range(n)]
+        assert sorted(places) == list(range(n))
+        assert places[1:] == [lib.next_place(p, n, stride) for p in places[:-1]]
+        assert sum(b != a + stride for a, b in zip(places, places[1:])) < stride
