@@ -1002,82 +1002,45 @@ template <int L> __device__ inline void group_argmax(float& bv, int& bi) {
   bv = mx;
 }
 
-// Token->expert permutation of at most 8*64 pairs whose expert ids sit in LDS (s_idx): a stable counting sort.
-// A wave takes 64 consecutive pairs (a chunk).  The chunk's 64 ballots "which lanes go to expert e" are formed all
-// at once by OR-ing lane bits into s_ballot[chunk][e]; a pair's rank inside its chunk is the number of set bits
-// below its lane in its expert's ballot, the chunk's count for expert e the population of ballot e.  Lane e of
-// wave 0 then turns the per-chunk counts into offsets.  s_ballot: [8][MAX_EXPERTS] 64-bit words, s_cc:
-// [8][MAX_EXPERTS] ints.  A wave owns chunks wave and wave + n_waves (at least 4 waves, at most 8 chunks).
-__device__ inline void ballot_permute_small(const int32_t* s_idx, int n_pairs, int n_exp, int32_t* __restrict__ cnt,
-                                            int32_t* __restrict__ off, int32_t* __restrict__ perm,
-                                            int32_t* __restrict__ pos_of_pair, unsigned long long* s_ballot,
-                                            int32_t* s_cc) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n_waves = blockDim.x >> 6;
-  const int n_chunks = (n_pairs + WAVE - 1) / WAVE;
+// Token->expert permutation of at most 64 tokens, a stable counting sort of the pairs: s_mask[e] has a bit per token that
+// goes to expert e, so a pair's rank within its expert is the number of set bits below its token, and every wave scans the
+// experts' counts for itself (lane = expert): nothing waits behind another wave.  s_pair[p]: expert + 256 * token of pair p.
+__device__ inline void mask_permute(const int32_t* s_pair, const unsigned long long* s_mask, int n_pairs, int n_exp, int32_t* __restrict__ cnt,
+                                    int32_t* __restrict__ off, int32_t* __restrict__ perm, int32_t* __restrict__ pos_of_pair) {
+  const int lane = threadIdx.x & 63;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int i = threadIdx.x; i < n_chunks * MAX_EXPERTS; i += blockDim.x) s_ballot[i] = 0ull;
-  __syncthreads();
-  int my_e[2];
+  const int tot = lane < n_exp ? __popcll(s_mask[lane]) : 0;
+  int incl = tot;   // inclusive scan over the lanes (experts)
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = wave + i * n_waves;
-    const int p = c * WAVE + lane;
-    my_e[i] = (c < n_chunks && p < n_pairs) ? s_idx[p] : -1;
-    if (my_e[i] >= 0) atomicOr(&s_ballot[c * MAX_EXPERTS + my_e[i]], 1ull << lane);
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const int up = __shfl_up(incl, o, WAVE);
+    if (lane >= o) incl += up;
   }
-  __syncthreads();
-  int my_rank[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = wave + i * n_waves;
-    my_rank[i] = my_e[i] >= 0 ? __popcll(s_ballot[c * MAX_EXPERTS + my_e[i]] & below) : 0;
-    if (c < n_chunks) s_cc[c * MAX_EXPERTS + lane] = __popcll(s_ballot[c * MAX_EXPERTS + lane]);   // lane = expert id
-  }
-  __syncthreads();
-  if (wave == 0) {
-    int tot = 0;
-    for (int c = 0; c < n_chunks; ++c) tot += s_cc[c * MAX_EXPERTS + lane];
-    if (lane >= n_exp) tot = 0;
-    int incl = tot;   // inclusive scan over the lanes (experts)
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-      const int up = __shfl_up(incl, o, WAVE);
-      if (lane >= o) incl += up;
-    }
-    const int start = incl - tot;
-    if (lane < n_exp) {
-      cnt[lane] = tot;
-      off[lane] = start;
-      if (lane == n_exp - 1) off[n_exp] = incl;
-    }
-    const uint64_t has_rows = __ballot(tot > 0);          // dense list of the experts with rows (ACTIVE_LIST)
-    if (tot > 0) {
-      const int at = __popcll(has_rows & below);
-      off[ACTIVE_LIST + at] = lane;
-      *reinterpret_cast<int4*>(off + ACTIVE_RECORDS + 4 * at) = make_int4(lane, start, tot, 0);
-    }
-    if (lane == 0) {
-      off[ACTIVE_LIST + MAX_EXPERTS] = __popcll(has_rows);
-      off[STAT_ACTIVE_SUM] += __popcll(has_rows);
-      off[STAT_PERMUTATIONS] += 1;
-    }
-    int run = start;                                      // chunk c of expert `lane` starts at run
-    for (int c = 0; c < n_chunks; ++c) {
-      const int n = s_cc[c * MAX_EXPERTS + lane];
-      s_cc[c * MAX_EXPERTS + lane] = run;
-      run += n;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = wave + i * n_waves;
-    if (c < n_chunks && my_e[i] >= 0) {
-      const int p = c * WAVE + lane;
-      const int r = s_cc[c * MAX_EXPERTS + my_e[i]] + my_rank[i];
+  const int start = incl - tot;
+  for (int p0 = 0; p0 < n_pairs; p0 += blockDim.x) {   // uniform over the wave: every lane takes part in the shuffle
+    const int p = p0 + threadIdx.x, pair = s_pair[min(p, n_pairs - 1)], e = pair & 255, tok = pair >> 8;
+    const int r = __shfl(start, e, WAVE) + __popcll(s_mask[e] & ((1ull << tok) - 1));
+    if (p < n_pairs) {
       perm[r] = p;
       pos_of_pair[p] = r;
     }
+  }
+  if (threadIdx.x >= WAVE) return;
+  if (lane < n_exp) {
+    cnt[lane] = tot;
+    off[lane] = start;
+    if (lane == n_exp - 1) off[n_exp] = incl;
+  }
+  const uint64_t has_rows = __ballot(tot > 0);          // dense list of the experts with rows (ACTIVE_LIST)
+  if (tot > 0) {
+    const int at = __popcll(has_rows & below);
+    off[ACTIVE_LIST + at] = lane;
+    *reinterpret_cast<int4*>(off + ACTIVE_RECORDS + 4 * at) = make_int4(lane, start, tot, 0);
+  }
+  if (lane == 0) {
+    off[ACTIVE_LIST + MAX_EXPERTS] = __popcll(has_rows);
+    off[STAT_ACTIVE_SUM] += __popcll(has_rows);
+    off[STAT_PERMUTATIONS] += 1;
   }
 }
 
@@ -1101,9 +1064,9 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
   __shared__ float s_logit[NTOK * LOGIT_STRIDE];
   __shared__ float s_ssp[SS_PARTS * NTOK];
   __shared__ float s_rinv[NTOK];
-  __shared__ int32_t s_idx[NTOK * MAX_TOPK];
-  __shared__ unsigned long long s_ballot[8 * MAX_EXPERTS];
-  __shared__ int32_t s_cc[8 * MAX_EXPERTS];
+  __shared__ int32_t s_pair[NTOK * MAX_TOPK];                // expert + 256 * token
+  __shared__ unsigned long long s_mask[MAX_EXPERTS];         // bit per token that goes to the expert
+  static_assert(NTOK <= 64 && NTHREADS >= MAX_EXPERTS, "a token is a bit of the mask");
   __shared__ int32_t s_flag;
   const int slice = blockIdx.x, n_slices = gridDim.x, group = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
@@ -1147,6 +1110,7 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
     if (!last_arrival(tickets + group, n_slices, &s_flag)) return;
     sum_slices<TT, PER>(part, group, n_slices, lane, v0, a0, a1);
   }
+  if (threadIdx.x < MAX_EXPERTS) s_mask[threadIdx.x] = 0ull;
   if (threadIdx.x < NTOK) {
     float row_ss = 0.f;
     for (int q = 0; q < SS_PARTS; ++q) row_ss += s_ssp[q * NTOK + threadIdx.x];
@@ -1215,27 +1179,19 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
       }
       sel_sum += bv;
     }
-    if (sub < top_k) {
+    if (sub < top_k && tok0 + tl < T) {
       const int tok = tok0 + tl;
-      if (tok < T) {
-        topk_idx[tok * top_k + sub] = isel;
-        topk_w[tok * top_k + sub] = norm_topk ? wsel / sel_sum : wsel;
-      }
-      s_idx[tl * top_k + sub] = tok < T ? isel : -1;
+      topk_idx[tok * top_k + sub] = isel;
+      topk_w[tok * top_k + sub] = norm_topk ? wsel / sel_sum : wsel;
+      s_pair[tl * top_k + sub] = isel | (tl << 8);
+      atomicOr(&s_mask[isel], 1ull << tl);
     }
   }
   TRACE_MARK(3, 4);
-  if (!fuse_permute) {   // many tokens: the permutation kernel takes the group's pairs per expert
-    if (threadIdx.x < MAX_EXPERTS) s_cc[threadIdx.x] = 0;
-    __syncthreads();
-    for (int i = threadIdx.x; i < NTOK * top_k; i += NTHREADS)
-      if (s_idx[i] >= 0) atomicAdd(&s_cc[s_idx[i]], 1);
-    __syncthreads();
-    if (threadIdx.x < MAX_EXPERTS) hist[group * MAX_EXPERTS + threadIdx.x] = s_cc[threadIdx.x];
-    return;
-  }
   __syncthreads();
-  ballot_permute_small(s_idx, T * top_k, n_exp, cnt, off, perm, pos_of_pair, s_ballot, s_cc);
+  if (fuse_permute) mask_permute(s_pair, s_mask, T * top_k, n_exp, cnt, off, perm, pos_of_pair);
+  else if (threadIdx.x < MAX_EXPERTS)    // many tokens: the permutation kernel takes the group's pairs per expert
+    hist[group * MAX_EXPERTS + threadIdx.x] = __popcll(s_mask[threadIdx.x]);
   TRACE_MARK(3, 5);
 }
 
