@@ -388,9 +388,16 @@ __global__ __launch_bounds__(256) void lm_merge_kernel(const f32x4* __restrict__
   const int t = blockIdx.x;
   if (mask && !((mask[t / block_len] >> (t % block_len)) & 1ull)) return;   // a decided position: nothing was computed
   LmStat a{-INFINITY, 0.f, 0x7fffffff};
-  for (int w = threadIdx.x; w < n_parts; w += 256) {
-    const f32x4 p = part[(int64_t)t * n_parts + w];
-    a = lm_combine(a, LmStat{p[0], p[1], __float_as_int(p[2])});
+  // the loads of ten rounds are issued together (157184 ids leave 2456 partials above 64 tokens); round by round, each behind
+  // a memory round trip, 7.2 us at 160 tokens, now 5.6
+  constexpr int U = 10;
+  for (int w0 = threadIdx.x; w0 < n_parts; w0 += U * 256) {
+    f32x4 p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) p[u] = part[(int64_t)t * n_parts + min(w0 + u * 256, n_parts - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (w0 + u * 256 < n_parts) a = lm_combine(a, LmStat{p[u][0], p[u][1], __float_as_int(p[u][2])});
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
