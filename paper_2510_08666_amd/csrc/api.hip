@@ -137,7 +137,7 @@ int attn_splits(int n_qtiles, int n_heads, int key_bound) {
 }
 
 struct Workspace {
-  size_t cos_tab, sin_tab, tok_seq, tok_pos, seq_nkeys, qtile, x, xn, ssq, ssq_a, tk_part, tickets, tickets_bytes, attn_tickets, attn_tickets_bytes, rinv_f, q, a, attn_part, topk_idx, topk_w, cnt, off,
+  size_t cos_tab, sin_tab, tok_seq, tok_pos, seq_nkeys, qtile, x, xn, xn_hi, ssq, ssq_a, tk_part, tickets, tickets_bytes, attn_tickets, attn_tickets_bytes, rinv_f, q, a, attn_part, topk_idx, topk_w, cnt, off,
       perm, pos_of_pair, work, hist, run_tokens, run_base, n_finished, loop_flags, loop_steps, lm_rows, y, o, lm_part, smooth_part, lm_stats, conf, argmax, total;
 };
 
@@ -158,6 +158,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.rinv_f = cv.take(T * 4);   // 1/rms of the residual rows entering the expert half
   const size_t planes = c.dtype == DINFER_BF16 ? 2 : 1;   // stored bf16 activations are hi + lo planes
   w.xn = cv.take(planes * T * H * es);   // normalised-input planes of the residual rows
+  w.xn_hi = cv.take(planes > 1 ? T * H * es : 0);   // their high plane alone, for the LM head of many tokens
   w.ssq = cv.take((size_t)(H / 64) * T * 4);     // sums of squares of the rows entering the expert half, per task
   w.ssq_a = cv.take((size_t)(H / 64) * T * 4);   // ... of the rows entering the attention half / the LM head
   {
@@ -376,7 +377,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
   // many tokens: the last layer's expert outputs are folded into the residual here, with the final norm's gain
   if (!fused_down)
     launch_combine(bf, x, at<float>(ws, w.o), at<float>(ws, w.topk_w) + (size_t)(f.n_layers - 1) * T * f.top_k, f.top_k,
-                   T, H, ssq_a, at<float>(c->weights, c->wm.final_gain), ws + w.xn, st);
+                   T, H, ssq_a, at<float>(c->weights, c->wm.final_gain), ws + w.xn, st, T > 2 * TILE ? ws + w.xn_hi : nullptr);
   c->last_n_ssq = n_ssq_a;
   (void)with_head;
   c->last_T = T;
@@ -603,7 +604,7 @@ static int step_impl(dinfer_ctx* c, int32_t n_seq, int32_t block_len, int32_t* d
   if (rc != DINFER_OK) return rc;
   const dinfer_config& f = c->cfg;
   const int T = n_seq * block_len;
-  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn,
+  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn, c->ws + c->wsm.xn_hi,
             RowNorm{at<float>(c->ws, c->wsm.ssq_a), c->last_n_ssq, f.rms_eps}, T, f.hidden, f.vocab, f.logit_scale,
             at<float>(c->ws, c->wsm.lm_part), nullptr};
   const bool skip = decode->skip_decided != 0;
@@ -664,7 +665,7 @@ static int smooth_impl(dinfer_ctx* c, int32_t n_seq, int32_t block_len, int32_t*
   float* stats = at<float>(c->ws, c->wsm.lm_stats);
   // this variant keeps the logits of the block (T x vocab float32): the second contraction over the vocabulary
   // needs the normalised probabilities, which exist only once the row's maximum and sum are known
-  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn,
+  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn, c->ws + c->wsm.xn_hi,
             RowNorm{at<float>(c->ws, c->wsm.ssq_a), c->last_n_ssq, f.rms_eps}, T, f.hidden, f.vocab, f.logit_scale,
             at<float>(c->ws, c->wsm.lm_part), logits};
   {
@@ -730,7 +731,7 @@ int dinfer_step_credit(dinfer_ctx* c, int32_t n_seq, int32_t block_len, int32_t*
   const dinfer_config& f = c->cfg;
   const int T = n_seq * block_len;
   float* stats = at<float>(c->ws, c->wsm.lm_stats);
-  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn,
+  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn, c->ws + c->wsm.xn_hi,
             RowNorm{at<float>(c->ws, c->wsm.ssq_a), c->last_n_ssq, f.rms_eps}, T, f.hidden, f.vocab, f.logit_scale,
             at<float>(c->ws, c->wsm.lm_part), nullptr};
   {
@@ -773,7 +774,7 @@ int dinfer_step_vicinity(dinfer_ctx* c, int32_t n_seq, int32_t block_len, int32_
   const int T = n_seq * run;
   float* conf_rows = at<float>(c->ws, c->wsm.conf);
   int32_t* argmax_rows = at<int32_t>(c->ws, c->wsm.argmax);
-  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn,
+  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn, c->ws + c->wsm.xn_hi,
             RowNorm{at<float>(c->ws, c->wsm.ssq_a), c->last_n_ssq, f.rms_eps}, T, f.hidden, f.vocab, f.logit_scale,
             at<float>(c->ws, c->wsm.lm_part), nullptr};
   {
@@ -1025,7 +1026,7 @@ int dinfer_debug_logits(dinfer_ctx* c, int32_t n_rows, float* d_out, void* strea
   // the normalised-input planes are laid out for last_T rows: the kernel must be run over exactly those
   if (n_rows != c->last_T) return fail(DINFER_EINVAL, "n_rows %d is not the last forward's %d rows", n_rows, c->last_T);
   const dinfer_config& f = c->cfg;
-  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn,
+  LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn, c->ws + c->wsm.xn_hi,
             RowNorm{at<float>(c->ws, c->wsm.ssq_a), c->last_n_ssq, f.rms_eps}, n_rows, f.hidden, f.vocab, f.logit_scale,
             at<float>(c->ws, c->wsm.lm_part), d_out};
   launch_lm_head(c->bf16, la, (hipStream_t)stream);

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(MAX_HIDDEN / 4) void combine_kernel(float* __restri
                                                                  const float* __restrict__ topk_w, int top_k,
                                                                  int H, float* __restrict__ ssq,
                                                                  const float* __restrict__ gain, E* __restrict__ xn,
-                                                                 int T, const int32_t* __restrict__ live) {
+                                                                 E* __restrict__ xn_hi, int T, const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   __shared__ float sh[4];
   __shared__ f32x4 s_acc[MAX_HIDDEN / 4 - NORM_THREADS];
@@ -229,6 +229,8 @@ __global__ __launch_bounds__(MAX_HIDDEN / 4) void combine_kernel(float* __restri
     }
     *reinterpret_cast<f32x4*>(x + (int64_t)t * H + col) = acc;
     store_actk4<E>(xn, T, t, col, n);
+    if constexpr (Planes<E>::N > 1)
+      if (xn_hi) store_elems4<E>(xn_hi + ((int64_t)(col / ET<E>::KS) * T + t) * ET<E>::KS + col % ET<E>::KS, n);
     if (threadIdx.x >= NORM_THREADS) s_acc[threadIdx.x - NORM_THREADS] = acc;
   }
   __syncthreads();
@@ -248,12 +250,12 @@ __global__ __launch_bounds__(MAX_HIDDEN / 4) void combine_kernel(float* __restri
   if (threadIdx.x == 0) ssq[t] = sh[0] + sh[1] + sh[2] + sh[3];
 }
 void launch_combine(bool bf16, float* x, const float* O, const float* topk_w, int top_k,
-                    int T, int H, float* ssq, const float* gain, void* xn, hipStream_t st) {
+                    int T, int H, float* ssq, const float* gain, void* xn, hipStream_t st, void* xn_hi) {
   const int threads = H / 4 <= NORM_THREADS ? NORM_THREADS : (H / 4 + WAVE - 1) / WAVE * WAVE;
   if (bf16)
-    combine_kernel<bf16_t><<<T, threads, 0, st>>>(x, O, topk_w, top_k, H, ssq, gain, (bf16_t*)xn, T, live_word());
+    combine_kernel<bf16_t><<<T, threads, 0, st>>>(x, O, topk_w, top_k, H, ssq, gain, (bf16_t*)xn, (bf16_t*)xn_hi, T, live_word());
   else
-    combine_kernel<float><<<T, threads, 0, st>>>(x, O, topk_w, top_k, H, ssq, gain, (float*)xn, T, live_word());
+    combine_kernel<float><<<T, threads, 0, st>>>(x, O, topk_w, top_k, H, ssq, gain, (float*)xn, nullptr, T, live_word());
 }
 
 // ---------------------------------------------------------------- token -> expert permutation

@@ -404,7 +404,7 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
   zero_acc<WT>(acc0);
   zero_acc<WT>(acc1);
   wide_stream<E, WT, WW, KID>(W + (int64_t)task * task_stride_elems<E>(ksteps), ksteps, xn,
-                                      [&](int r) { return row_of(tok0 + (wave % WT) * TILE + r); }, (int64_t)T * (NP * KS), sb, nt, acc0, acc1, wave);
+                                      [&](int r) { return row_of(tok0 + (wave % WT) * TILE + r); }, (int64_t)T * (WidePlanes<E, KID>::N * KS), sb, nt, acc0, acc1, wave);
 #pragma unroll
   for (int t = 0; t < WT; ++t) {
     const bool listed = tok0 + t * TILE + col < n_rows;
@@ -482,8 +482,11 @@ template <typename E> static void launch_lm_wide_t(const LmArgs& a, hipStream_t 
   const LmPlan p = lm_plan(a.V, a.T);
   const int groups = a.T <= 2 * TILE ? 1 : (a.T + WT * TILE - 1) / (WT * TILE);
   const int wgs = (p.whole + p.tasks - p.first_piece + XCDS - 1) / XCDS * XCDS * groups;
+  // the high plane alone as a matrix of its own: out of the interleaved planes every fetched cache line is half of no use (TCC
+  // reads of the launch 31.7 million lines for 26; 512 / 160 tokens 315 -> 308 / 187 -> 175 us, the combine that writes it +0.3)
+  const void* xn = a.T > 2 * TILE && Planes<E>::N > 1 ? a.xn_hi : a.xn;
   auto go = [&](auto kernel, int ww, size_t lds) {
-    kernel<<<wgs, ww * WAVE, lds, st>>>((const E*)a.w, (const E*)a.xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows,
+    kernel<<<wgs, ww * WAVE, lds, st>>>((const E*)a.w, (const E*)xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows,
                                         p, live_word());
   };
   if (a.T <= TILE) {

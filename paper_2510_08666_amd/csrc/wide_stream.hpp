@@ -72,7 +72,7 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
   typedef WidePieces<E, KID> Pc;
   typedef WideShape<KID, WT> Sh;
   constexpr int KC = Sh::KC, PRE = Sh::PRE, BD = Sh::BD, NB = Sh::NB;
-  constexpr int NP = WidePlanes<E, KID>::N, ROW_BYTES = Planes<E>::N * ET<E>::KS * (int)sizeof(E);   // planes used; a row's k-step
+  constexpr int NP = WidePlanes<E, KID>::N, ROW_BYTES = NP * ET<E>::KS * (int)sizeof(E);   // planes; a row's k-step
   constexpr int STEP = 2 * WAVE * 16;              // bytes of a task's k-step
   static_assert(PRE % BD == 0 && (NB == 2 || NB == 3), "register sets are taken from the unrolled index");
   static_assert(WW % WT == 0 && (KC * WT) % WW == 0, "every wave stages whole k-steps of one token tile");
