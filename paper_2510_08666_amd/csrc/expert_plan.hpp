@@ -7,7 +7,7 @@
 namespace dinfer {
 
 constexpr int EXPERT_TILE = 32;   // rows of a token tile
-constexpr int EXPERT_DIES = 8;     // workgroup i of a launch runs on die i % 8
+constexpr int EXPERT_DIES = 8;    // workgroup i of a launch runs on die i % 8
 constexpr int EXPERT_CUS = 256;   // compute units; eight waves of these kernels fill one
 // An item is a run of an expert's sorted rows, up to expert_group_tiles tiles; a workgroup takes it with EXPERT_WW tasks (one
 // per wave) and four tiles, or, up to MID_ROWS rows per expert on average, with MID_WW tasks and two tiles, so that two
@@ -45,21 +45,45 @@ inline int expert_most_piece_items(int E, int n_pairs, int H, int I) {
   return beyond <= 0 ? 0 : beyond < few ? beyond : few;
 }
 
-// From two full items per expert on average (prompts), the items of an expert run on one die, and each with its task groups
-// one after the other, so that the expert's weights and the item's rows come to that die's L2 once: the work list is dealt out
-// over the dies (item i to die i % 8), its full items lie EXPERT_DIES places apart, and the weights are loaded as ordinary
-// lines (non-temporal ones do not stay in the L2: 32 workgroups of a die that read 16 MB side by side get 11 to 14 TB/s over
-// all dies, with ordinary loads 23 to 33).  4287 tokens, about five items per expert: L2 misses of gate/up + down 20.8 + 12.7 ->
-// 13.0 + 7.5 million lines, 546 + 319 -> 535 + 299 us.  With fewer items nothing is shared, and ordinary loads only push
-// other data out of the caches (gate/up at 160 tokens 93 -> 103 us).
-inline bool expert_shared(int E, int n_pairs) { return n_pairs >= 2 * EXPERT_WT * EXPERT_TILE * E; }
-inline int expert_item_stride(int E, int n_pairs) { return expert_shared(E, n_pairs) ? EXPERT_DIES : 1; }
-// Place of item i of n: items 0, 1, ... take the places 0, stride, 2 * stride, ... below n, then 1, 1 + stride, ...
-DINFER_HOST_DEVICE inline int expert_item_place(int i, int n, int stride) {
-  const int q = n / stride, r = n % stride, front = r * (q + 1);   // r classes of q + 1 places, then classes of q
-  return i < front ? i % (q + 1) * stride + i / (q + 1) : (i - front) % (q > 0 ? q : 1) * stride + r + (i - front) / (q > 0 ? q : 1);
+// From two full items per expert on average (prompts), the shared form: an item's task groups run on one die one after the other,
+// then its expert's other items, so that the expert's weights and the item's rows come to that die's L2 once, and the weights
+// are loaded as ordinary lines (non-temporal ones do not stay in the L2: 32 workgroups of a die that read 16 MB side by side get
+// 11 to 14 TB/s over all dies, with ordinary loads 23 to 33).  64 experts of width 1024, hidden 2048, bf16, plain -> shared: 4287
+// tokens gate/up + down 544 + 323 -> 523 + 294 us (L2 misses 20.8 + 12.7 -> 13.0 + 7.5 million lines), 2048 tokens (the line) 311 +
+// 185 -> 290 + 162; float32, 8 experts of width 1408 at the line 506 + 350 -> 480 + 332.  Below the line these two launches
+// gain as well, but ordinary loads push other data out of the caches, and a whole layer gains or loses with the model (1500 tokens:
+// 64 experts of width 1024 453 -> 446, 32 of 768 at hidden 4096 424 -> 432; 1100 tokens 376 -> 379).
+// bf16 with 32 groups or more, a multiple of the dies: an item alone fills its die, so nothing runs beside it that could share its
+// weights, while in plain order every item's group g runs on die g % 8 (four experts of width 8192, 32 groups, 3000 tokens: 359 us
+// plain, 363 shared and a layer 807 -> 823; two experts of width 14336, 1500 tokens: 616 and 626).
+inline bool expert_shared(bool bf16, int E, int n_pairs, int groups) {
+  return n_pairs >= 2 * EXPERT_WT * EXPERT_TILE * E && !(bf16 && groups >= EXPERT_CUS / EXPERT_DIES && groups % EXPERT_DIES == 0);
 }
-// The place behind place p.
-DINFER_HOST_DEVICE inline int expert_next_place(int p, int n, int stride) { return p + stride < n ? p + stride : p % stride + 1; }
+// Which item and task group workgroup wg of the shared form takes.  The list's items lie by weight: `heavy` of four tiles (an
+// expert's one behind the other), then to `full` those of three, then the light ones.  Each kind's (item, task group) pairs go to
+// the dies in equal runs, so that every die has its share of the work within a workgroup, the heavy ones first.  Items dealt
+// whole, i to die i % 8, left some dies a round more than the others (8 experts of width 2816, gate/up of 1200 tokens, 23 or 24
+// items of 11 groups: 126 us in plain order, 156 with whole items, 109 with equal runs), and items dealt in one run a die some
+// dies without any lighter item (float32, 16 experts of width 2816, 3000 tokens: 675, 748, 639).
+struct ExpertUnit {
+  int item, group;   // item -1: nothing to do
+};
+DINFER_HOST_DEVICE inline int expert_unit_wgs(int n, int groups) { return (n * groups + EXPERT_DIES - 1) / EXPERT_DIES * EXPERT_DIES; }
+DINFER_HOST_DEVICE inline ExpertUnit expert_unit(int wg, int heavy, int full, int n, int groups) {
+  const int ends[3] = {heavy < n ? heavy : n, full < n ? full : n, n};
+  int turn = wg / EXPERT_DIES, start = 0, dealt = 0;   // turn of the die; items of the kinds before; runs with a pair more so far
+  for (int k = 0; k < 3; ++k) {
+    const int pairs = (ends[k] - start) * groups, each = pairs / EXPERT_DIES, more = pairs % EXPERT_DIES;
+    const int run = (wg - dealt) & (EXPERT_DIES - 1);  // the first `more` runs have a pair more, from where the last kind's ended
+    if (turn < each + (run < more ? 1 : 0)) {
+      const int pair = run * each + (run < more ? run : more) + turn;
+      return ExpertUnit{start + pair / groups, pair % groups};
+    }
+    turn -= each + (run < more ? 1 : 0);
+    start = ends[k];
+    dealt = (dealt + more) & (EXPERT_DIES - 1);
+  }
+  return ExpertUnit{-1, 0};
+}
 
 }  // namespace dinfer

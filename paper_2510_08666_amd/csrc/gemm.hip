@@ -1305,8 +1305,7 @@ template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a
         W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
         a.topk_w, 0, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
     launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work,
-                   expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I),
-                   expert_item_stride(a.E, a.T * a.top_k), st);
+                   expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
   }
 }
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {

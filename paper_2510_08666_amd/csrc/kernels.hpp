@@ -191,12 +191,13 @@ struct RouterArgs {
   int32_t* tickets;
 };
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st);
-// hist: the router's histograms, see RouterArgs; round: expert_round_items; stride: expert_item_stride.
+// hist: the router's histograms, see RouterArgs; round: expert_round_items.
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
-                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, int stride, hipStream_t st);
+                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, hipStream_t st);
 // Work list of the expert GEMMs above 64 tokens: number of items [WORK_BIG] taken by whole workgroups, of all items
-// [WORK_ALL] (the rest in pieces of one task), then 16-byte items {expert, first sorted row, rows, 0}.
-constexpr int WORK_BIG = 0, WORK_ALL = 1, WORK_ITEMS = 4;
+// [WORK_ALL] (the rest in pieces of one task), of those with the most tiles [WORK_HEAVY] and with one or two [WORK_LIGHT], then
+// 16-byte items {expert, first sorted row, rows, 0}, the ones with more tiles first.
+constexpr int WORK_BIG = 0, WORK_ALL = 1, WORK_HEAVY = 2, WORK_LIGHT = 3, WORK_ITEMS = 4;
 int permute_max_pairs();      // most (token, slot) pairs one forward may route
 
 struct ExpertArgs {

@@ -273,7 +273,7 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
                                                         const int32_t* __restrict__ hist, int n_exp,
                                                         int32_t* __restrict__ cnt, int32_t* __restrict__ off,
                                                         int32_t* __restrict__ perm, int32_t* __restrict__ pos_of_pair,
-                                                        int32_t* __restrict__ work, int group_tiles, int round, int stride,
+                                                        int32_t* __restrict__ work, int group_tiles, int round,
                                                         const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   __shared__ unsigned long long s_ballot[PERMUTE_WAVES * MAX_EXPERTS];
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
       const int rows_per = group_tiles * TILE, full = tot / rows_per, rem = tot % rows_per, rem_tiles = (rem + TILE - 1) / TILE;
       int4* items = reinterpret_cast<int4*>(work + WORK_ITEMS);
       const int start = incl - tot;
-      int at = 0, light = 0;                                // items so far; of them those with one or two tiles
+      int at = 0, light = 0, heavy = 0;                     // items so far; of them with one or two tiles, with the most
       for (int k = group_tiles; k >= 1; --k) {
         const int mine_k = (k == group_tiles ? full : 0) + (rem_tiles == k ? 1 : 0);
         int incl_k = mine_k;
@@ -343,19 +343,18 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
           if (lane >= o) incl_k += up;
         }
         const int first = at + incl_k - mine_k, n_k = __shfl(incl_k, WAVE - 1, WAVE);
-        if (k == group_tiles) {
-          int place = stride == 1 ? first : expert_item_place(first, n_k, stride);   // (two integer divisions)
-          for (int g = 0; g < mine_k; ++g, place = stride == 1 ? place + 1 : expert_next_place(place, n_k, stride))
-            items[place] = make_int4(lane, start + g * rows_per, g < full ? rows_per : rem, 0);
-        } else if (mine_k) {
-          items[first] = make_int4(lane, start + full * rows_per, rem, 0);
-        }
+        if (k == group_tiles)
+          for (int g = 0; g < full; ++g) items[first + g] = make_int4(lane, start + g * rows_per, rows_per, 0);
+        if (rem_tiles == k) items[first + mine_k - 1] = make_int4(lane, start + full * rows_per, rem, 0);
         at += n_k;
         if (k <= 2) light += n_k;
+        if (k == group_tiles) heavy = n_k;
       }
       if (lane == 0) {
         work[WORK_BIG] = at - expert_piece_items(at, light, round);
         work[WORK_ALL] = at;
+        work[WORK_HEAVY] = heavy;
+        work[WORK_LIGHT] = light;
       }
     }
   }
@@ -372,10 +371,10 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
 constexpr int PERMUTE_MAX_PAIRS = 65535;
 int permute_max_pairs() { return PERMUTE_MAX_PAIRS; }
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
-                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, int stride, hipStream_t st) {
+                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, hipStream_t st) {
   const int per_group = TILE * top_k;
   permute_kernel<<<(n_pairs + per_group - 1) / per_group, PERMUTE_WAVES * WAVE, 0, st>>>(
-      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, pos_of_pair, work, group_tiles, round, stride, live_word());
+      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, pos_of_pair, work, group_tiles, round, live_word());
 }
 
 // ---------------------------------------------------------------- LM-head partial merge

@@ -197,11 +197,11 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
   const int n_big = work[WORK_BIG];
   int piece;
   if constexpr (KID == 25 || KID == 26) {
-    // all task groups of an item on one die, one after the other; its expert's other items follow there (expert_plan.hpp)
-    const int wg = blockIdx.y * gridDim.x + blockIdx.x, turn = wg / XCDS, item = turn / (int)gridDim.x * XCDS + wg % XCDS;
-    const int whole = (n_big + XCDS - 1) / XCDS * XCDS * gridDim.x;
+    // an item's task groups on one die, one after the other, and behind them its expert's other items (expert_plan.hpp)
+    const int wg = blockIdx.y * gridDim.x + blockIdx.x, whole = expert_unit_wgs(n_big, gridDim.x);
     if (wg < whole) {
-      if (item < n_big) expert_tasks<E, WT, WW, KID, Op>(op, items[item], turn % (int)gridDim.x, lds_raw);
+      const ExpertUnit u = expert_unit(wg, work[WORK_HEAVY], work[WORK_ALL] - work[WORK_LIGHT], n_big, gridDim.x);
+      if (u.item >= 0) expert_tasks<E, WT, WW, KID, Op>(op, items[u.item], u.group, lds_raw);
       return;
     }
     piece = wg - whole;
@@ -263,7 +263,7 @@ static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hip
       kernel<<<dim3(whole.x, whole.y + (pieces + whole.x - 1) / whole.x), ww * WAVE, lds, st>>>(op, a.work, live_word());
     };
     if (expert_group_tiles(a.E, n_pairs) == MID_WT) many(expert_many_kernel<E, MID_WT, MID_WW, K3, Op>, MID_WT, MID_WW, many_lds<MID_WW>());
-    else if (expert_shared(a.E, n_pairs)) many(expert_many_kernel<E, WT, EXPERT_WW, K5, Op>, WT, EXPERT_WW, many_lds<EXPERT_WW>(), XCDS - 1);
+    else if (expert_shared(sizeof(E) == 2, a.E, n_pairs, grid(EXPERT_WW, 1).x)) many(expert_many_kernel<E, WT, EXPERT_WW, K5, Op>, WT, EXPERT_WW, many_lds<EXPERT_WW>(), XCDS - 1);
     else many(expert_many_kernel<E, WT, EXPERT_WW, K4, Op>, WT, EXPERT_WW, many_lds<EXPERT_WW>());
   }
 }

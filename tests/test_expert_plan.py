@@ -14,8 +14,14 @@ extern "C" void plan(int E, int n_pairs, int H, int I, int* o) {
   o[0] = expert_group_tiles(E, n_pairs), o[1] = expert_round_items(E, n_pairs, H, I);
   o[2] = expert_work_items(E, n_pairs, o[0]), o[3] = expert_most_piece_items(E, n_pairs, H, I);
 }
-extern "C" int item_place(int i, int n, int stride) { return expert_item_place(i, n, stride); }
-extern "C" int next_place(int p, int n, int stride) { return expert_next_place(p, n, stride); }
+extern "C" int unit_wgs(int n, int groups) { return expert_unit_wgs(n, groups); }
+extern "C" void units(int n_wgs, int heavy, int full, int n, int groups, int* o) {
+  for (int i = 0; i < n_wgs; ++i) {
+    const ExpertUnit u = expert_unit(i, heavy, full, n, groups);
+    o[2 * i] = u.item, o[2 * i + 1] = u.group;
+  }
+}
+extern "C" int shared_form(int bf16, int E, int n_pairs, int groups) { return expert_shared(bf16 != 0, E, n_pairs, groups); }
 extern "C" int piece_items(int items, int light, int round) { return expert_piece_items(items, light, round); }
 """
 
@@ -79,11 +85,36 @@ def test_pieces_are_few(lib):
     assert _plan(lib, 64, 8 * 256, 2048, 1024)[3] == 64 + 2048 // 128 - 64
 
 
-@pytest.mark.parametrize("stride", [1, 8])
-def test_items_have_places_of_their_own(lib, stride):
-    """Consecutive items lie a stride apart but where the list wraps, so that an expert's items run on one die."""
-    for n in list(range(1, 40)) + [63, 64, 65, 331, 509]:
-        places = [lib.item_place(i, n, stride) for i in range(n)]
-        assert sorted(places) == list(range(n))
-        assert places[1:] == [lib.next_place(p, n, stride) for p in places[:-1]]
-        assert sum(b != a + stride for a, b in zip(places, places[1:])) < stride
+@pytest.mark.parametrize("groups", [1, 2, 3, 4, 11, 22, 31, 43])
+def test_shared_items_go_to_the_dies_in_equal_runs(lib, groups):
+    """Workgroup i runs on die i % 8.  Every (item, task group) pair is taken once; of the items of each weight, and of all, no
+    die has more than one pair more than another, so that none runs a round of workgroups longer; a die takes the heavy
+    ones first and has a run of consecutive pairs of each kind, so that the task groups of an item meet on it."""
+    rng = np.random.default_rng(groups)
+    for trial in range(200):
+        n = [1, 2, 7, 8, 9, 23, 24, 48, 331][trial] if trial < 9 else int(rng.integers(1, 400))
+        heavy = int(rng.integers(0, n + 10))     # the list may go on behind the n items (with the ones handed out in pieces)
+        full = heavy + int(rng.integers(0, n + 10))
+        n_wgs = lib.unit_wgs(n, groups)
+        assert n_wgs <= (n + 7) * groups         # the rows that the launch adds to the grid
+        o = (ctypes.c_int * (2 * n_wgs))()
+        lib.units(n_wgs, heavy, full, n, groups, o)
+        u = np.array(o).reshape(-1, 2)
+        pair = np.where(u[:, 0] >= 0, u[:, 0] * groups + u[:, 1], -1)
+        assert np.array_equal(np.sort(pair[pair >= 0]), np.arange(n * groups))
+        assert np.all((u[:, 1] >= 0) & (u[:, 1] < groups))
+        kind = (u[:, 0] >= heavy).astype(int) + (u[:, 0] >= full)
+        dies = [[(kind[i], pair[i]) for i in range(d, n_wgs, 8) if pair[i] >= 0] for d in range(8)]
+        assert max(map(len, dies)) - min(map(len, dies)) <= 1
+        for k in range(3):
+            runs = [[p for kk, p in die if kk == k] for die in dies]
+            assert max(map(len, runs)) - min(map(len, runs)) <= 1
+            assert all(r == list(range(r[0], r[0] + len(r))) for r in runs if r)
+        assert all([k for k, _ in die] == sorted(k for k, _ in die) for die in dies)
+
+
+def test_shared_form_where_items_meet_on_a_die(lib):
+    assert lib.shared_form(1, 64, 64 * 256, 4) and not lib.shared_form(1, 64, 64 * 256 - 1, 4)
+    assert lib.shared_form(1, 8, 8 * 300, 31) and not lib.shared_form(1, 8, 8 * 300, 32)    # 32 groups fill a die ...
+    assert lib.shared_form(1, 8, 8 * 300, 33) and not lib.shared_form(1, 8, 8 * 300, 40)
+    assert lib.shared_form(0, 8, 8 * 300, 32) and not lib.shared_form(0, 8, 8 * 255, 4)      # ... in bf16
