@@ -158,7 +158,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.rinv_f = cv.take(T * 4);   // 1/rms of the residual rows entering the expert half
   const size_t planes = c.dtype == DINFER_BF16 ? 2 : 1;   // stored bf16 activations are hi + lo planes
   w.xn = cv.take(planes * T * H * es);   // normalised-input planes of the residual rows
-  w.xn_hi = cv.take(planes > 1 ? T * H * es : 0);   // their high plane alone, for the LM head of many tokens
+  w.xn_hi = cv.take(lm_compact(planes > 1, max_tokens) ? T * H * es : 0);   // their high plane alone, for the LM head
   w.ssq = cv.take((size_t)(H / 64) * T * 4);     // sums of squares of the rows entering the expert half, per task
   w.ssq_a = cv.take((size_t)(H / 64) * T * 4);   // ... of the rows entering the attention half / the LM head
   {
@@ -280,7 +280,7 @@ struct StageTimer {
   }
 };
 
-// One forward over the packed tokens of `span`.  with_head: final norm into h (ready for the LM head).
+// One forward over the packed tokens of `span`.  with_head: an LM head follows (LmArgs::xn_hi is wanted).
 int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const int32_t* d_base,
             const int32_t* d_page_table, int pt_stride, bool with_head, hipStream_t st,
             const SmoothIn* smooth = nullptr) {
@@ -377,9 +377,9 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
   // many tokens: the last layer's expert outputs are folded into the residual here, with the final norm's gain
   if (!fused_down)
     launch_combine(bf, x, at<float>(ws, w.o), at<float>(ws, w.topk_w) + (size_t)(f.n_layers - 1) * T * f.top_k, f.top_k,
-                   T, H, ssq_a, at<float>(c->weights, c->wm.final_gain), ws + w.xn, st, T > 2 * TILE ? ws + w.xn_hi : nullptr);
+                   T, H, ssq_a, at<float>(c->weights, c->wm.final_gain), ws + w.xn, st,
+                   with_head && lm_compact(bf, T) ? ws + w.xn_hi : nullptr);
   c->last_n_ssq = n_ssq_a;
-  (void)with_head;
   c->last_T = T;
   HIP_TRY(hipGetLastError());
   return DINFER_OK;
@@ -1029,6 +1029,8 @@ int dinfer_debug_logits(dinfer_ctx* c, int32_t n_rows, float* d_out, void* strea
   LmArgs la{c->weights + c->wm.lm_head, c->ws + c->wsm.xn, c->ws + c->wsm.xn_hi,
             RowNorm{at<float>(c->ws, c->wsm.ssq_a), c->last_n_ssq, f.rms_eps}, n_rows, f.hidden, f.vocab, f.logit_scale,
             at<float>(c->ws, c->wsm.lm_part), d_out};
+  // from the planes themselves: the last forward may have been one without a head
+  if (lm_compact(c->bf16, n_rows)) launch_high_plane(c->ws + c->wsm.xn, n_rows, f.hidden, c->ws + c->wsm.xn_hi, (hipStream_t)stream);
   launch_lm_head(c->bf16, la, (hipStream_t)stream);
   HIP_TRY(hipGetLastError());
   return DINFER_OK;

@@ -69,6 +69,8 @@ void launch_embed(bool bf16, const int32_t* tokens, const void* emb, int T, int 
 // x[t] += sum_j topk_w[t][j] * O[t*k+j];  ssq[t] and xn[t] as above, of the updated row; xn_hi (may be null): LmArgs::xn_hi
 void launch_combine(bool bf16, float* x, const float* O, const float* topk_w, int top_k,
                     int T, int H, float* ssq, const float* gain, void* xn, hipStream_t st, void* xn_hi = nullptr);
+// xn_hi = the high plane of bf16 planes xn (LmArgs::xn_hi)
+void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st);
 
 // Cross-workgroup split-K scratch shared by the projections and the router (see gemm.hip): `part` holds the
 // workgroup sums, `tickets` one arrival counter per (task, token group), all zero between launches.
@@ -229,7 +231,7 @@ void launch_expert_down_wide(bool bf16, const ExpertArgs& a, hipStream_t st);
 struct LmArgs {
   const void* w;            // packed LM head
   const void* xn;           // [T][H] normalised-input planes (final gain)
-  const void* xn_hi;        // bf16, more than 64 tokens: their high plane alone, [H / 16][T][16]
+  const void* xn_hi;        // where lm_compact (lm_plan.hpp): their high plane alone, [H / 16][T][16]
   RowNorm norm;             // statistics of the residual rows
   int T, H, V;
   float scale;

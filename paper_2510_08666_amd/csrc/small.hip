@@ -258,6 +258,18 @@ void launch_combine(bool bf16, float* x, const float* O, const float* topk_w, in
     combine_kernel<float><<<T, threads, 0, st>>>(x, O, topk_w, top_k, H, ssq, gain, (float*)xn, nullptr, T, live_word());
 }
 
+// Half a row's k-step (eight elements, 16 bytes) per thread; a test hook's kernel.
+__global__ __launch_bounds__(256) void high_plane_kernel(const bf16_t* __restrict__ xn, int64_t n, bf16_t* __restrict__ xn_hi) {
+  constexpr int KS = ET<bf16_t>::KS, NP = Planes<bf16_t>::N;
+  static_assert(KS == 16, "two threads per k-step of a row");
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) *reinterpret_cast<bf16x8*>(xn_hi + i * 8) = *reinterpret_cast<const bf16x8*>(xn + (i >> 1) * (NP * KS) + (i & 1) * 8);
+}
+void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st) {
+  const int64_t n = (int64_t)T * (H / 8);
+  high_plane_kernel<<<(int)((n + 255) / 256), 256, 0, st>>>((const bf16_t*)xn, n, (bf16_t*)xn_hi);
+}
+
 // ---------------------------------------------------------------- token -> expert permutation
 // Stand-alone form (many tokens); small forwards run the same idea inside the router kernel.  Stable counting sort of
 // the (token, slot) pairs by expert.  The router's workgroups have left the histogram of their 32 tokens,

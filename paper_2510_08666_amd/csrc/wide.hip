@@ -482,9 +482,7 @@ template <typename E> static void launch_lm_wide_t(const LmArgs& a, hipStream_t 
   const LmPlan p = lm_plan(a.V, a.T);
   const int groups = a.T <= 2 * TILE ? 1 : (a.T + WT * TILE - 1) / (WT * TILE);
   const int wgs = (p.whole + p.tasks - p.first_piece + XCDS - 1) / XCDS * XCDS * groups;
-  // the high plane alone as a matrix of its own: out of the interleaved planes every fetched cache line is half of no use (TCC
-  // reads of the launch 31.7 million lines for 26; 512 / 160 tokens 315 -> 308 / 187 -> 175 us, the combine that writes it +0.3)
-  const void* xn = a.T > 2 * TILE && Planes<E>::N > 1 ? a.xn_hi : a.xn;
+  const void* xn = lm_compact(Planes<E>::N > 1, a.T) ? a.xn_hi : a.xn;
   auto go = [&](auto kernel, int ww, size_t lds) {
     kernel<<<wgs, ww * WAVE, lds, st>>>((const E*)a.w, (const E*)xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out, a.rows,
                                         p, live_word());

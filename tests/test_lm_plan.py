@@ -17,6 +17,7 @@ extern "C" void plans(int T, int v0, int n, int* out) {
     o[0] = p.tasks, o[1] = p.ww, o[2] = p.whole, o[3] = p.first_piece, o[4] = p.parts, o[5] = dinfer::lm_head_most_parts(v0 + i);
   }
 }
+extern "C" int compact(int bf16, int T) { return dinfer::lm_compact(bf16 != 0, T); }
 """
 
 
@@ -54,3 +55,9 @@ def test_pieces_are_few(plans):
         for over, in_pieces in ((0, 0), (1, 1), (102, 102), (103, 0), (187, 0), (255, 0), (511, 0)):
             tasks, ww, whole, first, parts, _ = plans(48, (512 * rounds + over) * 256, 1)[:, 0]
             assert ww == 4 and whole == 512 * rounds + over - in_pieces and tasks - first == 4 * in_pieces, (rounds, over)
+
+
+def test_high_plane_of_many_bf16_tokens(tmp_path):
+    lib = host_shim.load(tmp_path, SHIM)
+    assert [lib.compact(1, T) for T in (1, 64, 65, 4096)] == [0, 0, 1, 1]
+    assert [lib.compact(0, T) for T in (64, 65, 4096)] == [0, 0, 0]
