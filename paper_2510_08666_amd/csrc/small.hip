@@ -401,13 +401,14 @@ __global__ __launch_bounds__(256) void lm_merge_kernel(const f32x4* __restrict__
   const int t = blockIdx.x;
   if (mask && !((mask[t / block_len] >> (t % block_len)) & 1ull)) return;   // a decided position: nothing was computed
   LmStat a{-INFINITY, 0.f, 0x7fffffff};
-  // the loads of ten rounds are issued together (157184 ids leave 2456 partials above 64 tokens); round by round, each behind
-  // a memory round trip, 7.2 us at 160 tokens, now 5.6
-  constexpr int U = 10;
+  // the loads of up to U rounds (64 registers) are issued together, those past the end of the row not at all: round by round,
+  // each behind a memory round trip, 2456 partials took 7.2 us at 160 tokens, now 5.6
+  constexpr int U = 16;
   for (int w0 = threadIdx.x; w0 < n_parts; w0 += U * 256) {
     f32x4 p[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) p[u] = part[(int64_t)t * n_parts + min(w0 + u * 256, n_parts - 1)];
+    for (int u = 0; u < U; ++u)
+      if (w0 + u * 256 < n_parts) p[u] = part[(int64_t)t * n_parts + w0 + u * 256];
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (w0 + u * 256 < n_parts) a = lm_combine(a, LmStat{p[u][0], p[u][1], __float_as_int(p[u][2])});
