@@ -1,4 +1,4 @@
-// Which form the dense projections (QKV and output) of more than 64 tokens take.  Plain host C++.
+// Which form the dense projections (QKV and output) take.  Plain host C++.
 #pragma once
 
 namespace dinfer {
@@ -36,6 +36,37 @@ inline DenseForm dense_form(bool bf16, int n_tasks, int T) {
   }
   const bool two = bf16 ? groups * tiles > DENSE_CUS : groups * ((tiles + 1) / 2) >= 160;
   return two ? DenseForm{4, 2, (tiles + 1) / 2} : groups * tiles >= DENSE_FILL ? DenseForm{4, 1, tiles} : DenseForm{2, 1, tiles};
+}
+
+// Up to 64 tokens: split-K.  K slices (workgroups) per task: as many as leave every wave exactly one burst of k-steps (8 with
+// one token tile, 4 with two), when K divides that way; one otherwise and whenever there are several token groups.
+inline int gemm_slices(bool bf16, int K, int T) {
+  if (T > 2 * DENSE_TILE) return 1;
+  const int ksteps = K / (bf16 ? 16 : 8);
+  const int burst = 4 * (T <= DENSE_TILE ? 8 : 4);   // of a workgroup's four waves
+  return ksteps % burst == 0 ? ksteps / burst : 1;
+}
+// Slices a launch uses of those gemm_slices() allows (the workspace is sized for the latter): a hand-off among
+// fewer workgroups is cheaper, so a projection with many tasks takes only as many slices as bring the launch to
+// about half a workgroup per compute unit (measured at 32 tokens, K = 2048: the QKV projection, 96 tasks, 12.3 us
+// with 2 slices against 13.1 with 4 and 14.9 with 1; the output projection, 32 tasks, 8.1 us with 4 slices, 10.0
+// with 2, 13.4 with 1).
+inline int ksplit_slices(bool bf16, int K, int T, int n_tasks) {
+  const int most = gemm_slices(bf16, K, T);
+  int s = 1;
+  while (s < most && s * n_tasks < DENSE_CUS / 2) s *= 2;
+  return most % s == 0 ? s : most;
+}
+// bf16, up to 32 tokens: half a task per workgroup of HALF_KW waves instead of two slices of a task, where two slices are what
+// split-K would take (the order of the sums is theirs), half tasks are half a round of the chip to a whole one, and a wave's
+// share of K fits its registers (HALF_PF k-steps, or half as many: K of 2048 or 1024; 1536 takes three slices, and other
+// multiples of 128 below 2048 one).  QKV projection, split-K -> half tasks in us at 1 / 11 / 32 tokens (with the events around a
+// launch): 66 tasks of K = 1024 11.7 -> 9.3 / 10.8 -> 9.2 / 11.1 -> 9.7, 126 tasks 13.2 -> 10.4 / 12.3 -> 9.9 / 12.7 -> 10.7; 66 tasks of K = 2048
+// 13.4 -> 11.9 / 12.9 -> 11.8 / 13.6 -> 13.0, 96 tasks 14.4 -> 13.1 / 13.7 -> 12.9 / 14.8 -> 14.1, 126 tasks 15.8 -> 14.1 / 14.9 -> 13.9 / 15.8 -> 15.2.
+constexpr int HALF_KW = 8, HALF_PF = 16;   // waves; most k-steps of a wave
+inline bool half_applies(bool bf16, int K, int T, int n_tasks) {
+  if (!bf16 || T > DENSE_TILE || 4 * n_tasks < DENSE_CUS || 2 * n_tasks > DENSE_CUS) return false;
+  return ksplit_slices(bf16, K, T, n_tasks) == 2 && K / 16 <= HALF_KW * HALF_PF;
 }
 
 }  // namespace dinfer

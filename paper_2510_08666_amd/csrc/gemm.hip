@@ -350,27 +350,6 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
 
 template <int TT, int KW> constexpr size_t ksplit_lds() { return (size_t)KW * 2 * TT * 16 * WAVE * 4; }
 
-// K slices (workgroups) per task: as many as leave every wave exactly one burst of k-steps (8 with one token
-// tile, 4 with two), when K divides that way; one otherwise and whenever there are several token groups.
-int gemm_slices(bool bf16, int K, int T) {
-  if (T > 2 * TILE) return 1;
-  const int ksteps = K / (bf16 ? 16 : 8);
-  const int burst = 4 * (T <= TILE ? 8 : 4);   // KW = 4 waves
-  return ksteps % burst == 0 ? ksteps / burst : 1;
-}
-
-// Slices a launch uses of those gemm_slices() allows (the workspace is sized for the latter): a hand-off among
-// fewer workgroups is cheaper, so a projection with many tasks takes only as many slices as bring the launch to
-// about half a workgroup per compute unit (measured at 32 tokens, K = 2048: the QKV projection, 96 tasks, 12.3 us
-// with 2 slices against 13.1 with 4 and 14.9 with 1; the output projection, 32 tasks, 8.1 us with 4 slices, 10.0
-// with 2, 13.4 with 1).
-static int ksplit_slices(bool bf16, int K, int T, int n_tasks) {
-  const int most = gemm_slices(bf16, K, T);
-  int s = 1;
-  while (s < most && s * n_tasks < 128) s *= 2;
-  return most % s == 0 ? s : most;
-}
-
 template <typename E, class Epi>
 static void launch_ksplit(bool bf16, const E* W, int ksteps, const E* B, int T, int K, int n_tasks,
                           float* part, int32_t* tickets, const Epi& epi, hipStream_t st) {
@@ -386,15 +365,13 @@ static void launch_ksplit(bool bf16, const E* W, int ksteps, const E* B, int T, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// QKV projection of up to 32 tokens where 32 features (half a task) per workgroup fill the chip: HALF_KW waves cut the whole K
-// range, every wave has its share in flight at once, and the sums meet in LDS.  Bound by memory latency like the split-K
-// kernel, whose two slices per task needed a hand-off between workgroups (about 3 us) to get as many bytes under way.  The
-// matrix instruction's 32 rows are 16 of each of the task's two tiles, so that an epilogue still finds its pairs (feature
+// QKV projection of up to 32 tokens with 32 features (half a task) per workgroup (rule and figures: half_applies): HALF_KW waves
+// cut the whole K range, every wave has its share in flight at once, and the sums meet in LDS.  Bound by memory latency like the
+// split-K kernel, whose two slices per task need a hand-off between workgroups (about 3 us) to get as many bytes under way.
+// The matrix instruction's 32 rows are 16 of each of the task's two tiles, so that an epilogue still finds its pairs (feature
 // j and its rotary partner, rows r and r + 16) in one lane: registers v and v + 8.  Sums in the order of the split-K kernel
-// with two slices, bit for bit.  32 tokens, 96 tasks of K = 2048: 11.8 -> 11.0 us;
-// 11 tokens 10.9 -> 9.9.
+// with two slices, bit for bit.
 // ------------------------------------------------------------------------------------------------
-constexpr int HALF_KW = 8, HALF_PF = 16;   // waves; most k-steps of a wave
 template <typename E, class Epi>
 __global__ __launch_bounds__(HALF_KW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void gemm_half_kernel(const E* __restrict__ W, int ksteps, const E* __restrict__ B, int T,
                                                                    Epi epi, const int32_t* __restrict__ live) {
@@ -405,8 +382,9 @@ __global__ __launch_bounds__(HALF_KW * WAVE) __attribute__((amdgpu_waves_per_eu(
   const int task = blockIdx.x >> 1, sub = blockIdx.x & 1;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int v0 = (wave < EW ? wave : 0) * PER, tok = col;
+  TRACE_MARK(1, 0);
   auto pre = epi.template prefetch<PER>(task, tok, tok < T, half, 8 * sub + v0);
-  const int per = ksteps / HALF_KW, ks0 = wave * per;    // per: a multiple of 8, at most HALF_PF
+  const int per = ksteps / HALF_KW, ks0 = wave * per;    // per: HALF_PF or half of it
   // lane l of the operand: row l % 16 of this half, tile (l / 16) % 2, k half l / 32
   const E* wp = W + (int64_t)task * task_stride_elems<E>(ksteps) + (int64_t)ks0 * (2 * WAVE * G) +
                 ((lane >> 4 & 1) * WAVE + half * TILE + sub * 16 + (lane & 15)) * G;
@@ -430,10 +408,12 @@ __global__ __launch_bounds__(HALF_KW * WAVE) __attribute__((amdgpu_waves_per_eu(
   };
   if (per == HALF_PF) stream(std::integral_constant<int, HALF_PF>{});
   else stream(std::integral_constant<int, HALF_PF / 2>{});
+  TRACE_MARK(1, 1);
   if (wave < EW) epi.template prefetch2<PER>(pre, task, half, 8 * sub + v0);
 #pragma unroll
   for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * WAVE + lane] = acc[0][v];
   __syncthreads();
+  TRACE_MARK(1, 2);
   if (wave >= EW) return;
   float a0[PER], a1[PER];
 #pragma unroll
@@ -459,12 +439,7 @@ __global__ __launch_bounds__(HALF_KW * WAVE) __attribute__((amdgpu_waves_per_eu(
     }
   }
   epi.template apply<PER>(pre, task, tok, tok < T, half, 8 * sub + v0, a0, a1);
-}
-// bf16, up to 32 tokens, one workgroup per compute unit or a little less, K in whole shares that fit a wave's registers.
-static bool half_applies(bool bf16, int K, int T, int n_tasks) {
-  const int per = K / 16 / HALF_KW;
-  return bf16 && T <= TILE && !single_slice() && 2 * n_tasks >= 128 && 2 * n_tasks <= 256 && K % (16 * HALF_KW) == 0 &&
-         (per == HALF_PF || per == HALF_PF / 2);
+  TRACE_MARK(1, 4);
 }
 
 // Static + dynamic LDS of these kernels can pass the 64 KiB default: opt in to the 160 KiB LDS of gfx950
@@ -860,7 +835,7 @@ template <typename E> static void launch_qkv_t(bool bf16, const QkvArgs& a, hipS
                 a.pt_stride, a.cos_tab, a.sin_tab, a.norm, a.T, a.H, D};
   if (dense_applies(a.T, a.H / ET<E>::KS))
     launch_dense<E>((const E*)a.w, a.H / ET<E>::KS, (const E*)a.xn, a.T, 3 * D / 64, epi, st);
-  else if (half_applies(bf16, a.H, a.T, 3 * D / 64)) {
+  else if (!single_slice() && half_applies(bf16, a.H, a.T, 3 * D / 64)) {
     if constexpr (sizeof(E) == 2)
       gemm_half_kernel<E, QkvEpi<E>><<<2 * (3 * D / 64), HALF_KW * WAVE, 0, st>>>((const E*)a.w, a.H / ET<E>::KS, (const E*)a.xn, a.T, epi, live_word());
   } else

@@ -74,7 +74,6 @@ void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st
 
 // Cross-workgroup split-K scratch shared by the projections and the router (see gemm.hip): `part` holds the
 // workgroup sums, `tickets` one arrival counter per (task, token group), all zero between launches.
-int gemm_slices(bool bf16, int K, int T);   // workgroups that share one task's K range for T tokens
 
 struct QkvArgs {
   const void* w;            // packed fused QKV

@@ -58,3 +58,25 @@ def test_token_groups_cover_every_tile(form, groups, dtype):
                 continue
             size = {tiles * (g + 1) // n - tiles * g // n for g in range(n)}
             assert min(size) >= 1 and max(size) <= 4 and tiles * n < 2 ** 32, (n_tasks, T)
+
+
+HALF_SHIM = """
+#include "dense_plan.hpp"
+extern "C" int half(int bf16, int K, int T, int n_tasks) { return dinfer::half_applies(bf16 != 0, K, T, n_tasks); }
+extern "C" int slices(int bf16, int K, int T, int n_tasks) { return dinfer::ksplit_slices(bf16 != 0, K, T, n_tasks); }
+"""
+
+
+def test_half_tasks_replace_two_slices(tmp_path):
+    """Every width, token and task count that takes half tasks would have taken two slices (the order of the sums), in whole
+    shares of 8 or 16 k-steps for the eight waves; float32, more than 32 tokens, and fewer than 64 tasks do not."""
+    lib = host_shim.load(tmp_path, HALF_SHIM)
+    taken = set()
+    for K in range(64, 4097, 64):
+        for n_tasks in range(1, 260):
+            for T in (1, 11, 32, 33, 64, 65):
+                assert not lib.half(0, K, T, n_tasks)
+                if lib.half(1, K, T, n_tasks):
+                    assert lib.slices(1, K, T, n_tasks) == 2 and K // 16 in (8 * 8, 8 * 16) and T <= 32
+                    taken.add((K, n_tasks))
+    assert taken == {(K, n) for K in (1024, 2048) for n in range(64, 128)}
