@@ -303,7 +303,7 @@ __host__ __device__ inline int attn_splits_for(int n_keys) {
 }
 
 // Optional in-kernel phase timestamps (builds with -DDINFER_TRACE=<kernel id> only): thread 0 of every workgroup
-// of the chosen kernel stores the 100 MHz wall clock at each mark.  Kernel ids: 1 QKV, 2 O-proj, 3 router,
+// of the chosen kernel stores the 100 MHz wall clock at each mark.  Kernel ids: 1 QKV (both forms of up to 64 tokens), 2 O-proj, 3 router,
 // 4 expert GEMM 1, 5 expert GEMM 2, 6 LM head, 7 attention, 8 combine, 9 / 10 / 11 many-token LM head / expert GEMM 1 /
 // expert GEMM 2 (25 / 26 with several items per expert), 12 / 13 many-token QKV / output projection, 14 LM head of 33 to
 // 64 tokens.

@@ -22,9 +22,11 @@ struct DenseForm {
 // with one wave for a task's whole K range.  A workgroup of the smaller forms multiplies for a third of its time (QKV at 4287
 // tokens: 17 of 44 us, the rest prologue, fold and epilogue) and every task group fetches the rows again.  A round of it
 // takes about 25 us and 24 a tile, so the tiles are dealt evenly to the token groups that fill its rounds.  QKV projection
-// (96 tasks), before -> now: 800 tokens 74 -> 73 us, 1300 82 -> 75, 1811 122 -> 101, 2500 157 -> 128, 3072 191 -> 181, 4000
-// 234 -> 195; output projection (32 tasks): 2500 79 -> 73, 4000 95 -> 90, 4287 121 -> 103, but up to 2048, one round of the
-// smaller form, 32 -> 48 to 52 -> 66.  Task groups with more than a tenth of their waves idle stay with the smaller forms.
+// (96 tasks, K = 2048), smaller forms -> this one: 641 tokens (the line) 64 -> 46 us, 704 67 -> 61, 1024 68 -> 63, 1300 75 -> 66, 1811
+// 107 -> 87, 2048 112 -> 108, 2500 143 -> 113, 3072 174 -> 165, 4000 211 -> 178; output projection (32 tasks): 2049 66 -> 64, 2500 76 ->
+// 69, 3072 80 -> 82, 4000 93 -> 85, but up to 2048, one round of the smaller form, 32 -> 48 to 52 -> 66.  Over 48 to 384 tasks, K of
+// 256 to 4096 and 129 to 4000 tokens it gains 3 to 30 % but where the smaller form just fills its rounds: 192 tasks of K = 4096 352
+// tokens 97 -> 100, 1024 tokens 184 -> 185.  Task groups with more than a tenth of their waves idle stay with the smaller forms.
 constexpr int DENSE_WIDE_TASKS = 8, DENSE_WIDE_TILES = 4;
 inline DenseForm dense_form(bool bf16, int n_tasks, int T) {
   const int groups = (n_tasks + 3) / 4, tiles = (T + DENSE_TILE - 1) / DENSE_TILE;

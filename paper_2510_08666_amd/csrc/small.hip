@@ -193,11 +193,11 @@ void launch_prob_planes(bool bf16, const float* logits, const float* stats, int 
 }
 
 // x[t] += sum_j w[t][j] * O[t*k+j]  (j ascending: a fixed summation order);  ssq[t] = sum of squares and the
-// normalised-input planes of the new row.  (Forwards of more than 64 tokens; smaller ones fold this into the down
+// normalised-input planes of the new row.  (Forwards of more than 32 tokens; smaller ones fold this into the down
 // projection.)
 // A thread takes four columns, so that all loads of a row are under way at once (with 256 threads that took the 1024-column
-// chunks one after the other 8.4 us at 64 tokens and 10.7 at 512, now 5.4 and 9.0).  The sum of squares keeps the order of those chunks: the
-// threads past 256 hand their columns down.
+// chunks one after the other 8.4 us at 64 tokens and 10.7 at 512, now 5.4 and 9.0).  The sum of squares keeps the order of those
+// chunks: the threads past 256 hand their columns down.
 template <typename E>
 __global__ __launch_bounds__(MAX_HIDDEN / 4) void combine_kernel(float* __restrict__ x, const float* __restrict__ O,
                                                                  const float* __restrict__ topk_w, int top_k,
@@ -271,8 +271,8 @@ void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st
 }
 
 // ---------------------------------------------------------------- token -> expert permutation
-// Stand-alone form (many tokens); small forwards run the same idea inside the router kernel.  Stable counting sort of
-// the (token, slot) pairs by expert.  The router's workgroups have left the histogram of their 32 tokens,
+// Stand-alone form (more than 64 tokens; below, the router kernel sorts its pairs by a token mask per expert).  Stable counting
+// sort of the (token, slot) pairs by expert.  The router's workgroups have left the histogram of their 32 tokens,
 // hist[group][MAX_EXPERTS]; workgroup g of this launch adds up the groups before its own and all of them, which
 // gives the place of its first pair of every expert, and places its group's pairs: a wave takes 64 consecutive pairs
 // (a chunk) and forms the ballots "which lanes go to expert e" for all experts at once by OR-ing lane bits into its own

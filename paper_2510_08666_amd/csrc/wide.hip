@@ -196,7 +196,7 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
   const int4* items = reinterpret_cast<const int4*>(work + WORK_ITEMS);
   const int n_big = work[WORK_BIG];
   int piece;
-  if constexpr (KID == 25 || KID == 26) {
+  if constexpr (wide_expert_shared(KID)) {
     // an item's task groups on one die, one after the other, and behind them its expert's other items (expert_plan.hpp)
     const int wg = blockIdx.y * gridDim.x + blockIdx.x, whole = expert_unit_wgs(n_big, gridDim.x);
     if (wg < whole) {

@@ -9,28 +9,38 @@
 
 namespace dinfer {
 
+// Kinds of kernels by trace id (the ids: common.hpp).
+constexpr bool wide_dense(int kid) { return kid == 12 || kid == 13; }                // dense projections
+constexpr bool wide_expert(int kid) { return kid == 10 || kid == 11; }               // expert GEMMs of four tiles: an item for itself,
+constexpr bool wide_expert_shared(int kid) { return kid == 25 || kid == 26; }        // or beside its expert's others (expert_plan.hpp)
+constexpr bool wide_smooth(int kid) { return kid == 24; }                            // smoothing contraction of four tiles
+
 // How a kernel (by its trace id) with WT token tiles moves its operands.  KC: k-steps per chunk; PRE: chunks of weights in
 // the registers of a wave; BD: chunks of activation fragments in its registers on their way to LDS; NB: chunks of fragments
-// in LDS.
+// in LDS; AGAIN: other workgroups read the weights again soon.  Those are loaded as ordinary lines, which stay in the L2 (the
+// dense projections' few MB, an expert's between its items); what is streamed once goes by non-temporal loads, which push
+// nothing else out of the caches.
 // The forms of four tiles and eight waves have one workgroup per compute unit and 128 accumulator registers per lane.  Where
 // the matrix cores are the bound (LM head, prompts), short chunks with one barrier each let four of them be under way in the
 // registers that two of four k-steps took, and a third LDS buffer carries a wave over the barrier (see the ring below).  Bit
 // for bit the sums of the longer chunks; LM head at 512 / 160 tokens 366 -> 342 / 220 -> 195 us, gate/up + down at 4287
 // tokens 534 + 312 -> 526 + 308, no spills (2 registers before); with chunks of four k-steps and three buffers 539 + 318.  The
-// expert GEMMs with an item or less per expert (ids 10, 11) are bound by their weights and keep four k-steps and two buffers
-// (12 sequences of 32, whole refresh: 569 us, 573 with short chunks).  Two workgroups of four waves per compute unit stage
-// the fragments twice: LM head 404.
+// expert GEMMs of up to two items per expert on average (wide_expert) keep four k-steps and two buffers: they are bound by
+// their weights (12 sequences of 32, whole refresh: 569 us, 573 with short chunks).  Two workgroups of four waves per compute
+// unit stage the fragments twice: LM head 404.
 template <int KID, int WT> struct WideShape {
-  static constexpr int KC = 4, PRE = 2, BD = KID == 24 || KID == 10 || KID == 11 ? 1 : 2, NB = 2;
+  static constexpr int KC = 4, PRE = 2, BD = wide_smooth(KID) || wide_expert(KID) ? 1 : 2, NB = 2;
+  static constexpr bool AGAIN = wide_dense(KID);
 };
-struct WideShape4x8 {
+template <int KID> struct WideShape4x8 {
   static constexpr int KC = 2, PRE = 4, BD = 1, NB = 3;
+  static constexpr bool AGAIN = wide_dense(KID) || wide_expert_shared(KID);
 };
-template <> struct WideShape<9, 4> : WideShape4x8 {};
-template <> struct WideShape<12, 4> : WideShape4x8 {};
-template <> struct WideShape<13, 4> : WideShape4x8 {};
-template <> struct WideShape<25, 4> : WideShape4x8 {};
-template <> struct WideShape<26, 4> : WideShape4x8 {};
+template <> struct WideShape<9, 4> : WideShape4x8<9> {};
+template <> struct WideShape<12, 4> : WideShape4x8<12> {};
+template <> struct WideShape<13, 4> : WideShape4x8<13> {};
+template <> struct WideShape<25, 4> : WideShape4x8<25> {};
+template <> struct WideShape<26, 4> : WideShape4x8<26> {};
 constexpr int WKC = 4;     // K is cut in units of this many k-steps
 
 // Planes of the activations a kernel (by its trace id) feeds to the matrix cores.  The LM head with hundreds of
@@ -82,12 +92,10 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
   constexpr int SKS = KC * WT / WW;                // k-steps of a chunk this wave stages (of token tile wave % WT)
   const int st = wave % WT, sk0 = (wave / WT) * SKS;
   constexpr int BUF = KC * WT * Pc::TILE_VECS;
-  // Weights that are streamed once (experts, LM head) are loaded non-temporally; those of the dense projections
-  // (kernel ids 12, 13: a few MB that every token group reads again) must stay in the L2.
   const uint32_t wlane = lane * 16;
   auto wload = [&](int c, int ks, int tile) {
     const char* base = (const char*)w + (int64_t)(min(c, last) * KC + ks) * STEP + tile * (WAVE * 16);
-        return (KID == 12 || KID == 13 || KID == 25 || KID == 26) ? load16<E>((const E*)(base + wlane)) : load16_stream<E>((const E*)(base + wlane));
+    return Sh::AGAIN ? load16<E>((const E*)(base + wlane)) : load16_stream<E>((const E*)(base + wlane));
   };
   vec wa0[PRE][KC], wa1[PRE][KC];
   vec bset[BD][SKS][NP];                           // fragments of later chunks, on their way to LDS
