@@ -92,10 +92,14 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
   constexpr int SKS = KC * WT / WW;                // k-steps of a chunk this wave stages (of token tile wave % WT)
   const int st = wave % WT, sk0 = (wave / WT) * SKS;
   constexpr int BUF = KC * WT * Pc::TILE_VECS;
-  const uint32_t wlane = lane * 16;
+  // A pointer per lane, not a scalar base per k-step: the scalar arithmetic stood in front of every chunk's loads, and the
+  // float32 projections, whose matrix instructions leave no slack, took 10 to 18 % longer (QKV of 1500 tokens, hidden 1024: 276
+  // us with scalar bases, 249 with a pointer per lane for the weights, 239 for the rows as well; LM head of 32 tokens, hidden 3584,
+  // 476, 463 and 452).  bf16 rows keep the scalar base: two planes of pointers cost registers (384 tokens 260 -> 264 us a layer).
+  const char* wl = (const char*)w + lane * 16;
   auto wload = [&](int c, int ks, int tile) {
-    const char* base = (const char*)w + (int64_t)(min(c, last) * KC + ks) * STEP + tile * (WAVE * 16);
-    return Sh::AGAIN ? load16<E>((const E*)(base + wlane)) : load16_stream<E>((const E*)(base + wlane));
+    const E* p = (const E*)(wl + (int64_t)(min(c, last) * KC + ks) * STEP + tile * (WAVE * 16));
+    return Sh::AGAIN ? load16<E>(p) : load16_stream<E>(p);
   };
   vec wa0[PRE][KC], wa1[PRE][KC];
   vec bset[BD][SKS][NP];                           // fragments of later chunks, on their way to LDS
@@ -118,12 +122,18 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
     src[j] = src[j] * (uint32_t)ROW_BYTES + (lane % Pc::N) * 16;
     dst[j] = (sk0 * WT + st) * Pc::TILE_VECS + Pc::slot(r, lane % Pc::N);
   }
+  constexpr bool LANE_ROWS = sizeof(E) == 4;
+  const int64_t step = bkstride * (int64_t)sizeof(E);
+  const char* row[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) row[j] = (const char*)act + sk0 * step + src[j];
   auto fetch = [&](int c, vec (&b)[SKS][NP]) {
+    const int64_t at = (int64_t)(min(c, last) * KC) * step;
     const char* base = (const char*)(act + (int64_t)(min(c, last) * KC + sk0) * bkstride);
 #pragma unroll
     for (int ks = 0; ks < SKS; ++ks)
 #pragma unroll
-      for (int j = 0; j < NP; ++j) b[ks][j] = load16<E>((const E*)(base + ks * bkstride * (int64_t)sizeof(E) + src[j]));
+      for (int j = 0; j < NP; ++j) b[ks][j] = load16<E>((const E*)(LANE_ROWS ? row[j] + at + ks * step : base + ks * step + src[j]));
   };
   auto put = [&](int buf, const vec (&b)[SKS][NP]) {
 #pragma unroll
