@@ -92,13 +92,16 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
   constexpr int SKS = KC * WT / WW;                // k-steps of a chunk this wave stages (of token tile wave % WT)
   const int st = wave % WT, sk0 = (wave / WT) * SKS;
   constexpr int BUF = KC * WT * Pc::TILE_VECS;
-  // A pointer per lane, not a scalar base per k-step: the scalar arithmetic stood in front of every chunk's loads, and the
-  // float32 projections, whose matrix instructions leave no slack, took 10 to 18 % longer (QKV of 1500 tokens, hidden 1024: 276
-  // us with scalar bases, 249 with a pointer per lane for the weights, 239 for the rows as well; LM head of 32 tokens, hidden 3584,
-  // 476, 463 and 452).  bf16 rows keep the scalar base: two planes of pointers cost registers (384 tokens 260 -> 264 us a layer).
-  const char* wl = (const char*)w + lane * 16;
+  // bf16 operands are addressed by a scalar base per k-step, float32 ones by a pointer per lane: there the scalar arithmetic in
+  // front of every chunk's loads cost the matrix instructions 6 to 18 % (QKV of 1500 tokens, hidden 1024: 276 us with scalar bases,
+  // 249 with a pointer per lane for the weights, 239 for the rows as well; LM head of 32 tokens, hidden 3584, 476, 463 and 452).
+  // bf16 gains nothing, and two planes of row pointers cost registers (384 tokens 260 -> 264 us a layer).
+  constexpr bool LANES = sizeof(E) == 4;
+  const uint32_t wlane = lane * 16;
+  const char* wl = (const char*)w + wlane;
   auto wload = [&](int c, int ks, int tile) {
-    const E* p = (const E*)(wl + (int64_t)(min(c, last) * KC + ks) * STEP + tile * (WAVE * 16));
+    const int64_t at = (int64_t)(min(c, last) * KC + ks) * STEP + tile * (WAVE * 16);
+    const E* p = (const E*)(LANES ? wl + at : (const char*)w + at + wlane);
     return Sh::AGAIN ? load16<E>(p) : load16_stream<E>(p);
   };
   vec wa0[PRE][KC], wa1[PRE][KC];
@@ -122,7 +125,6 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
     src[j] = src[j] * (uint32_t)ROW_BYTES + (lane % Pc::N) * 16;
     dst[j] = (sk0 * WT + st) * Pc::TILE_VECS + Pc::slot(r, lane % Pc::N);
   }
-  constexpr bool LANE_ROWS = sizeof(E) == 4;
   const int64_t step = bkstride * (int64_t)sizeof(E);
   const char* row[NP];
 #pragma unroll
@@ -133,7 +135,7 @@ __device__ inline void wide_stream_nt(const E* __restrict__ w, int ksteps, const
 #pragma unroll
     for (int ks = 0; ks < SKS; ++ks)
 #pragma unroll
-      for (int j = 0; j < NP; ++j) b[ks][j] = load16<E>((const E*)(LANE_ROWS ? row[j] + at + ks * step : base + ks * step + src[j]));
+      for (int j = 0; j < NP; ++j) b[ks][j] = load16<E>((const E*)(LANES ? row[j] + at + ks * step : base + ks * step + src[j]));
   };
   auto put = [&](int buf, const vec (&b)[SKS][NP]) {
 #pragma unroll
