@@ -12,6 +12,8 @@
 // MFMA mapping (32x32 tiles):  S^T[key][query] = K_tile . Q^T   (A = K rows, B = Q columns), so a lane owns
 // one query column and softmax statistics are per lane;  O^T[d][query] += V^T_tile . P^T  (A = V^T rows read
 // from the transposed V page, B = P^T taken from the S^T accumulator registers without any shuffle).
+#include <type_traits>
+
 #include "gemm.hpp"
 #include "kernels.hpp"
 
@@ -306,47 +308,67 @@ __global__ __launch_bounds__(ATTN_WAVES * WAVE) void attention_kernel(const E* _
       coherent_store_n<4>(pr, pb + (col * HD + (g / 16) * TILE + acc_row(g % 16, half)) * 4, v4);
     }
     if (wave == 0 && half == 0) {
-      const float mv[1] = {M}, lv[1] = {L};
-      coherent_store_n<1>(pr, pb + (TILE * HD + col) * 4, mv);
-      coherent_store_n<1>(pr, pb + (TILE * HD + TILE + col) * 4, lv);
+      const float ml[2] = {M, L};
+      coherent_store_n<2>(pr, pb + (TILE * HD + 2 * col) * 4, ml);
     }
   }
   __shared__ int32_t s_flag;
   if (!last_arrival(tickets + pair, my_splits, &s_flag)) return;
-  // Last to arrive: fold the partials in split order.  A thread takes a (query, 4 consecutive features) item.
-  for (int item = threadIdx.x; item < TILE * HD / 4; item += ATTN_WAVES * WAVE) {
-    const int q = item / (HD / 4), d = (item % (HD / 4)) * 4;
-    if (q >= nvalid) continue;
-    float mp[ATTN_MAX_SPLITS], lp[ATTN_MAX_SPLITS], op[ATTN_MAX_SPLITS][4];
+  // Last to arrive: fold the partials in split order.  A thread takes ITEMS (query, 4 consecutive features) items.  The loads
+  // of N splits are under way together; they bypass the L2, so that one compute unit's fetch is the bound, and none is issued for a
+  // count of splits that is not there (sixteen clamped loads for every count -> this: two splits, 64 tokens behind 768 keys 19.0 ->
+  // 16.0 us for the launch, 12 sequences of 32 40.0 -> 36.8; eight splits of 4096 keys 22.4 -> 21.0).
+  constexpr int ITEMS = TILE * HD / 4 / (ATTN_WAVES * WAVE);
+  static_assert(ITEMS * ATTN_WAVES * WAVE == TILE * HD / 4, "whole items per thread");
+  float Mx[ITEMS], Ls[ITEMS];
+  f32x4 acc[ITEMS];
 #pragma unroll
-    for (int p = 0; p < ATTN_MAX_SPLITS; ++p) {   // all loads first (clamped: the unused ones repeat the last part)
-      const uint32_t pb = pair_bytes + min(p, my_splits - 1) * part_bytes;
-      float t1[1], t2[1];
-      coherent_load_n<1>(pr, pb + (TILE * HD + q) * 4, t1);
-      coherent_load_n<1>(pr, pb + (TILE * HD + TILE + q) * 4, t2);
-      coherent_load_n<4>(pr, pb + (q * HD + d) * 4, op[p]);
-      mp[p] = t1[0];
-      lp[p] = t2[0];
-    }
-    float Mx = -INFINITY;
+  for (int i = 0; i < ITEMS; ++i) {
+    Mx[i] = -INFINITY;
+    Ls[i] = 0.f;
+    acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto item_q = [&](int i) { return (int)(threadIdx.x + i * ATTN_WAVES * WAVE) / (HD / 4); };
+  auto item_d = [&](int i) { return (int)(threadIdx.x + i * ATTN_WAVES * WAVE) % (HD / 4) * 4; };
+  auto fold = [&](auto C, int p0) {
+    constexpr int N = decltype(C)::value;
+    float ml[ITEMS][N][2], op[ITEMS][N][4];
 #pragma unroll
-    for (int p = 0; p < ATTN_MAX_SPLITS; ++p) Mx = p < my_splits ? fmaxf(Mx, mp[p]) : Mx;
-    float Ls = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < ITEMS; ++i)
 #pragma unroll
-    for (int p = 0; p < ATTN_MAX_SPLITS; ++p) {
-      if (p < my_splits && mp[p] > -INFINITY) {   // (a split whose waves saw no key tile contributes nothing)
-        const float w = __builtin_amdgcn_exp2f(mp[p] - Mx);
-        Ls += w * lp[p];
+      for (int p = 0; p < N; ++p) {
+        const uint32_t pb = pair_bytes + min(p0 + p, my_splits - 1) * part_bytes;
+        coherent_load_n<2>(pr, pb + (TILE * HD + 2 * item_q(i)) * 4, ml[i][p]);
+        coherent_load_n<4>(pr, pb + (item_q(i) * HD + item_d(i)) * 4, op[i][p]);
+      }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] += w * op[p][i];
+    for (int i = 0; i < ITEMS; ++i) {
+      float m_new = Mx[i];
+#pragma unroll
+      for (int p = 0; p < N; ++p) m_new = p0 + p < my_splits ? fmaxf(m_new, ml[i][p][0]) : m_new;
+      const float alpha = Mx[i] > -INFINITY ? __builtin_amdgcn_exp2f(Mx[i] - m_new) : 0.f;
+      Mx[i] = m_new;
+      Ls[i] *= alpha;
+      acc[i] *= alpha;
+#pragma unroll
+      for (int p = 0; p < N; ++p) {
+        if (p0 + p < my_splits && ml[i][p][0] > -INFINITY) {   // (a split whose waves saw no key tile contributes nothing)
+          const float w = __builtin_amdgcn_exp2f(ml[i][p][0] - m_new);
+          Ls[i] += w * ml[i][p][1];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[i][k] += w * op[i][p][k];
+        }
       }
     }
-    const float inv = 1.f / Ls;
-    f32x4 res;
+  };
+  if (my_splits == 2) fold(std::integral_constant<int, 2>{}, 0);
+  else if (my_splits <= 4) fold(std::integral_constant<int, 4>{}, 0);
+  else for (int p0 = 0; p0 < my_splits; p0 += 8) fold(std::integral_constant<int, 8>{}, p0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) res[i] = acc[i] * inv;
-    store_actk4<E>(out, T_out, tok0 + q, head * HD + d, res);
+  for (int i = 0; i < ITEMS; ++i) {
+    if (item_q(i) >= nvalid) continue;
+    const float inv = 1.f / Ls[i];
+    store_actk4<E>(out, T_out, tok0 + item_q(i), head * HD + item_d(i), acc[i] * inv);
   }
 }
 
