@@ -138,7 +138,7 @@ int attn_splits(int n_qtiles, int n_heads, int key_bound) {
 
 struct Workspace {
   size_t cos_tab, sin_tab, tok_seq, tok_pos, seq_nkeys, qtile, x, xn, xn_hi, ssq, ssq_a, tk_part, tickets, tickets_bytes, attn_tickets, attn_tickets_bytes, rinv_f, q, a, attn_part, topk_idx, topk_w, cnt, off,
-      perm, pos_of_pair, work, hist, run_tokens, run_base, n_finished, loop_flags, loop_steps, lm_rows, y, o, lm_part, smooth_part, lm_stats, conf, argmax, total;
+      perm, shares, work, hist, run_tokens, run_base, n_finished, loop_flags, loop_steps, lm_rows, y, o, lm_part, smooth_part, lm_stats, conf, argmax, total;
 };
 
 Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
@@ -163,7 +163,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.ssq_a = cv.take((size_t)(H / 64) * T * 4);   // ... of the rows entering the attention half / the LM head
   {
     // cross-workgroup split-K scratch: units (tasks) x slices x [2 * token tiles * 16][64] floats, for one and
-    // two token tiles, over the QKV projection (K = H), the output projection (K = D) and the router
+    // two token tiles, over the QKV projection (K = H) and the output projection (K = D)
     const bool bf = c.dtype == DINFER_BF16;
     size_t most = 0;
     for (int tt = 1; tt <= 2; ++tt) {
@@ -193,9 +193,9 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.topk_idx = cv.take((size_t)c.n_layers * T * K * 4);   // kept per layer (tests read the routing back)
   w.topk_w = cv.take((size_t)c.n_layers * T * K * 4);
   w.cnt = cv.take((size_t)MAX_EXPERTS * 4);
-  w.off = cv.take((size_t)OFF_INTS * 4);   // offsets, then the lists of experts with rows (gemm.hpp)
+  w.off = cv.take((size_t)OFF_INTS * 4);   // offsets, then running totals (gemm.hpp)
   w.perm = cv.take(T * K * 4);
-  w.pos_of_pair = cv.take(T * K * 4);
+  w.shares = cv.take((size_t)(H / 64) * (max_tokens < ROUTER_SHARES_T ? max_tokens : ROUTER_SHARES_T) * MAX_EXPERTS * 4);   // of the router's logits
   w.run_tokens = cv.take(T * 4);                 // token run and start positions of a vicinity-refresh forward
   w.run_base = cv.take((size_t)max_seqs * 4);
   w.n_finished = cv.take(4);                     // generation loop: sequences that have produced the end-of-sequence id
@@ -340,14 +340,14 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
       launch_attention(bf, aa, st);
     }
     OprojArgs oa{c->weights + lw.wo, ws + w.a, x, at<float>(c->weights, lw.ffn_gain), xn,
-                 at<float>(ws, w.ssq), T, D, H, tk_part, tickets};
+                 at<float>(ws, w.ssq), T, D, H, tk_part, tickets, T <= ROUTER_SHARES_T ? c->weights + lw.router : nullptr, at<float>(ws, w.shares)};
     {
       StageTimer tm(c, DINFER_STAGE_OPROJ, st);
       launch_oproj(bf, oa, st);
     }
     RouterArgs ra{c->weights + lw.router, xn, at<float>(ws, w.ssq), f.rms_eps, T, H, f.n_experts, f.top_k,
                   f.norm_topk, f.moe_inter, rinv_f, topk_idx, topk_w, at<int32_t>(ws, w.cnt), at<int32_t>(ws, w.off),
-                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.pos_of_pair), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), tk_part, tickets};
+                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), at<float>(ws, w.shares)};
     {
       StageTimer tm(c, DINFER_STAGE_ROUTER, st);
       launch_router(bf, ra, st);
@@ -355,7 +355,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
     ExpertArgs ea{c->weights + lw.gate_up, c->weights + lw.down, xn, rinv_f,
                   ws + w.y, at<float>(ws, w.o), at<int32_t>(ws, w.off),
                   at<int32_t>(ws, w.perm), at<int32_t>(ws, w.work), T, H, f.moe_inter, f.n_experts, f.top_k,
-                  fused_down ? topk_w : nullptr, topk_idx, at<int32_t>(ws, w.pos_of_pair)};
+                  fused_down ? topk_w : nullptr, topk_idx};
     {
       StageTimer tm(c, DINFER_STAGE_EXPERT_GATE_UP, st);
       launch_expert_gate_up(bf, ea, st);
@@ -366,7 +366,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
         // the gain of the norm that reads the new rows: the next layer's attention norm, or the final norm
         const float* next_gain = l + 1 < f.n_layers ? at<float>(c->weights, c->wm.layers[l + 1].attn_gain)
                                                     : at<float>(c->weights, c->wm.final_gain);
-        OprojArgs res{nullptr, nullptr, x, next_gain, xn, ssq_a, T, 0, H, tk_part, tickets};
+        OprojArgs res{nullptr, nullptr, x, next_gain, xn, ssq_a, T, 0, H, tk_part, tickets, nullptr, nullptr};
         launch_expert_down_fused(bf, ea, res, st);
         n_ssq_a = H / 64;
       } else {
@@ -1052,6 +1052,10 @@ int dinfer_debug_get(dinfer_ctx* c, int32_t what, void* d_out, size_t bytes, voi
     default: return fail(DINFER_EINVAL, "what %d", what);
   }
   if (bytes != want || want == 0) return fail(DINFER_EINVAL, "%zu bytes given, %zu expected", bytes, want);
+  // the tables of the last layer's permutation: up to 64 tokens no kernel of a forward writes them
+  if (what >= 3 && what <= 5 && T <= 2 * TILE)
+    launch_pair_tables(at<int32_t>(c->ws, c->wsm.topk_idx) + (size_t)(f.n_layers - 1) * T * f.top_k, (int)T * f.top_k, f.n_experts,
+                       at<int32_t>(c->ws, c->wsm.cnt), at<int32_t>(c->ws, c->wsm.off), at<int32_t>(c->ws, c->wsm.perm), (hipStream_t)stream);
   HIP_TRY(hipMemcpyAsync(d_out, c->ws + off, want, hipMemcpyDeviceToDevice, (hipStream_t)stream));
   return DINFER_OK;
 }

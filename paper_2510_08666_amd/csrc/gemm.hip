@@ -7,6 +7,7 @@
 // feed those planes to the matrix cores and scale their accumulators by the row's 1/rms in the epilogue.
 #include "gemm.hpp"
 #include "kernels.hpp"
+#include "routing.hpp"
 #include "wide_stream.hpp"
 
 namespace dinfer {
@@ -145,6 +146,36 @@ template <typename E> struct QkvEpi {
   __device__ void row_sum(int, int, float) const {}
 };
 
+// Eight features' contribution to the router's logits, straight from the registers of an epilogue: a lane holds four of them
+// for its token, rows 8 * step + 4 * half .. +3 of weight tile `tile` of the 64-feature task, which is the B operand of a
+// matrix instruction of depth eight as it stands (bf16: both planes of the values).  Result as for mfma32: experts along the rows.
+template <typename E> struct RouterStep;
+template <> struct RouterStep<bf16_t> {
+  typedef bf16x4 frag;
+  // packed router weights: the lane's expert (of 32 from 32 * et on), the four features above
+  __device__ static frag load(const bf16_t* w, int task, int tile, int step, int et, int lane) {
+    return *reinterpret_cast<const frag*>(w + (((int64_t)task * 4 + tile * 2 + (step >> 1)) * 2 + et) * (WAVE * 8) + ((step & 1) * TILE + (lane & 31)) * 8 + (lane >> 5) * 4);
+  }
+  __device__ static void add(f32x16& acc, const frag& a, const f32x4& v) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    bf16x4 hi, lo;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      hi[i] = (bf16_t)v[i];
+      lo[i] = (bf16_t)(v[i] - (float)hi[i]);
+    }
+    acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, hi), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, lo), acc, 0, 0, 0);
+  }
+};
+template <> struct RouterStep<float> {
+  typedef f32x4 frag;
+  __device__ static frag load(const float* w, int task, int tile, int step, int et, int lane) {
+    return *reinterpret_cast<const frag*>(w + (((int64_t)task * 8 + tile * 4 + step) * 2 + et) * (WAVE * 4) + lane * 4);
+  }
+  __device__ static void add(f32x16& acc, const frag& a, const f32x4& v) { mfma32(acc, a, v); }
+};
+
 // x += result; the new row also goes out as normalised-input planes for the expert half (times its norm's gain),
 // and the task's share of the row's sum of squares to ssq[task][token].
 template <typename E> struct ResidualEpi {
@@ -155,6 +186,8 @@ template <typename E> struct ResidualEpi {
   E* xn;               // [T][H] k-major planes
   float* ssq;          // [H/64][T]
   int T;
+  const E* w_router;   // null: no shares of the router's logits
+  float* shares;       // [H/64][T][MAX_EXPERTS]
 
   template <int PER> struct Pre {
     float x0[PER], x1[PER], g0[PER], g1[PER];
@@ -221,6 +254,17 @@ template <typename E> struct ResidualEpi {
     return ss;
   }
   __device__ void row_sum(int task, int tok, float s) const { ssq[(int64_t)task * T + tok] = s; }
+  // the values that apply() stores as planes, four features of each tile
+  __device__ static void normed(const Pre<4>& pre, const float (&a0)[4], const float (&a1)[4], f32x4 (&m)[2]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      m[0][i] = (pre.x0[i] + a0[i]) * pre.g0[i];
+      m[1][i] = (pre.x1[i] + a1[i]) * pre.g1[i];
+    }
+  }
+  __device__ void store_share(int task, int tok, int expert, const f32x4& v) const {
+    *reinterpret_cast<f32x4*>(shares + ((int64_t)task * T + tok) * MAX_EXPERTS + expert) = v;
+  }
 };
 
 // The workgroup's sums leave for / come back from the cross-workgroup buffer.  A thread holds PER consecutive
@@ -286,6 +330,7 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
   if (step_is_dead(live)) return;
   extern __shared__ float red[];   // [KW][2*TT*16][64]
   __shared__ int32_t s_flag;
+  __shared__ float s_ss[Epi::ROWSUM ? KW * TT * TILE : 1];
   constexpr int ROWS = 2 * TT * 16, PER = 16 / KW;
   [[maybe_unused]] constexpr int KID = Epi::ROWSUM ? 2 : 1;
   const int slice = blockIdx.x, n_slices = gridDim.x, task = blockIdx.y, group = blockIdx.z;
@@ -311,6 +356,15 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
   TRACE_MARK(KID, 1);
 #pragma unroll
   for (int t = 0; t < TT; ++t) epi.template prefetch2<PER>(pre[t], task, half, v0);
+  [[maybe_unused]] typename RouterStep<E>::frag rw[2][2];   // [tile][experts from 0, from 32]
+  if constexpr (Epi::ROWSUM) {
+    if (epi.w_router) {
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int et = 0; et < 2; ++et) rw[f][et] = RouterStep<E>::load(epi.w_router, task, f, wave, et, lane);
+    }
+  }
   spill_partials<TT, ROWS>(red, wave, lane, acc0, acc1);
   __syncthreads();
   TRACE_MARK(KID, 2);
@@ -329,18 +383,49 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
     const int tok = tok0 + t * TILE + (lane & 31);
     ss[t] = epi.template apply<PER>(pre[t], task, tok, tok < T, half, v0, a0[t], a1[t]);
   }
-  if (Epi::ROWSUM) {
+  if constexpr (Epi::ROWSUM) {
     // the task's row statistic: both half-waves of a column, then the KW waves in order
-    __syncthreads();   // the partials in `red` are consumed
+    const bool routed = epi.w_router != nullptr;   // with it the task's share of the router's logits, summed over the waves likewise
+    if (routed) {
+      // wave w holds features 8w .. 8w + 7 of both tiles, eight of a matrix instruction's depth each
+      static_assert(PER == 4, "RouterStep");
+      f32x16 r0[TT], r1[TT];
+      zero_acc<TT>(r0);
+      zero_acc<TT>(r1);
+#pragma unroll
+      for (int t = 0; t < TT; ++t) {
+        f32x4 m[2];
+        Epi::normed(pre[t], a0[t], a1[t], m);
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+          RouterStep<E>::add(r0[t], rw[f][0], m[f]);
+          RouterStep<E>::add(r1[t], rw[f][1], m[f]);
+        }
+      }
+      __syncthreads();   // the partials in `red` are consumed
+      spill_partials<TT, ROWS>(red, wave, lane, r0, r1);
+    }
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
       const float s2 = ss[t] + __shfl_xor(ss[t], 32, WAVE);
-      if (half == 0) red[(wave * TT + t) * TILE + lane] = s2;
+      if (half == 0) s_ss[(wave * TT + t) * TILE + lane] = s2;
     }
     __syncthreads();
+    if (routed) {
+      float b0[TT][PER], b1[TT][PER];
+      fold_partials<TT, KW, PER>(red, lane, v0, b0, b1);
+#pragma unroll
+      for (int t = 0; t < TT; ++t) {
+        const int tok = tok0 + t * TILE + (lane & 31);
+        if (tok < T) {
+          epi.store_share(task, tok, acc_row(v0, half), f32x4{b0[t][0], b0[t][1], b0[t][2], b0[t][3]});
+          epi.store_share(task, tok, TILE + acc_row(v0, half), f32x4{b1[t][0], b1[t][1], b1[t][2], b1[t][3]});
+        }
+      }
+    }
     for (int i = threadIdx.x; i < TT * TILE; i += KW * WAVE) {
       float s = 0.f;
-      for (int w = 0; w < KW; ++w) s += red[w * TT * TILE + i];
+      for (int w = 0; w < KW; ++w) s += s_ss[w * TT * TILE + i];
       const int tok = tok0 + i;
       if (tok < T) epi.row_sum(task, tok, s);
     }
@@ -470,9 +555,7 @@ template <typename E, class Epi> static bool configure_ksplit() {
 // ------------------------------------------------------------------------------------------------
 template <typename E, int TT, int KW, int PF>
 __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* __restrict__ W, const E* __restrict__ Y,
-                                                                       int64_t y_rows, const int32_t* __restrict__ off,
-                                                                       const int32_t* __restrict__ topk_idx,
-                                                                       const int32_t* __restrict__ pos_of_pair, int T,
+                                                                       int64_t y_rows, const int32_t* __restrict__ topk_idx, int T,
                                                                        int I, int top_k, int n_tasks,
                                                                        float* __restrict__ part,
                                                                        int32_t* __restrict__ tickets, ResidualEpi<E> epi, const int32_t* __restrict__ live) {
@@ -488,30 +571,37 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   TRACE_MARK(5, 0);
   TRACE_MARK_WAVE(55, 0, KW);
-  // Everything the first loads hang on is requested at once, so that a workgroup is two memory round trips away
-  // from its first weights however busy the memory system already is: the list of experts with rows (one per
-  // lane) and their number, and this lane's tokens -- which experts they were routed to, where those rows sit in Y.
-  const int listed = off[ACTIVE_LIST + lane];
-  const int n_act = __builtin_amdgcn_readfirstlane(off[ACTIVE_LIST + MAX_EXPERTS]);
-  int my_e[TT][MAX_TOPK], my_row[TT][MAX_TOPK];
+  // The first loads hang on the routing alone: this lane's tokens' experts, from which the wave reads off the list of
+  // experts with rows and, for the two of them it meets, where its tokens' rows sit in Y (sorted by expert, then token).
+  static_assert(TT == 1, "a token is a bit of a half-wave's ballot");
+  int my_e[MAX_TOPK];
+  const bool is_tok = col < T;
 #pragma unroll
-  for (int t = 0; t < TT; ++t) {
-    const int tok = min(t * TILE + col, T - 1);
+  for (int j = 0; j < MAX_TOPK; ++j) my_e[j] = topk_idx[min(col, T - 1) * top_k + min(j, top_k - 1)];
+  uint64_t experts = 0;
+#pragma unroll
+  for (int j = 0; j < MAX_TOPK; ++j) experts |= 1ull << my_e[j];
+  experts = wave_all_or(experts);
+  const int n_act = __popcll(experts);
+  auto row_in_y = [&](int e) {      // -1: the lane's token was not routed to e
+    int before = 0;
+    bool here = false;
 #pragma unroll
     for (int j = 0; j < MAX_TOPK; ++j) {
-      const int jj = min(j, top_k - 1);
-      my_e[t][j] = topk_idx[tok * top_k + jj];
-      my_row[t][j] = pos_of_pair[tok * top_k + jj];
+      const bool pair = is_tok && half == 0 && j < top_k;
+      before += __popcll(__ballot(pair && my_e[j] < e));
+      here |= my_e[j] == e;
     }
-  }
+    const uint32_t toks = (uint32_t)__ballot(is_tok && here);   // bit per token, from the lower half-wave
+    return is_tok && here ? before + __popc(toks & ((1u << col) - 1)) : -1;
+  };
   // The long K: experts with rows in list order, ksteps_e k-steps each, in groups of PF k-steps; this wave's
   // contiguous share [g0, g1).  A share is never longer than one expert's groups, so it meets at most two experts.
   const int ksteps_e = I / KS, groups_e = ksteps_e / PF, total = n_act * groups_e;
   const int units = n_slices * KW, per = (total + units - 1) / units;
   const int g0 = min(total, (slice * KW + wave) * per), g1 = min(total, g0 + per);
   const int i0 = g0 / groups_e;
-  const int e_first = __builtin_amdgcn_readlane(listed, min(i0, MAX_EXPERTS - 1));
-  const int e_second = __builtin_amdgcn_readlane(listed, min(i0 + 1, MAX_EXPERTS - 1));
+  const int e_first = nth_bit(experts, min(i0, n_act - 1)), e_second = nth_bit(experts, min(i0 + 1, n_act - 1));
   const E* wbase = W + (int64_t)task * task_stride_elems<E>(ksteps_e) + lane * G;
   const int64_t wexpert = (int64_t)n_tasks * task_stride_elems<E>(ksteps_e);
   auto weights_of = [&](int g) { return wbase + (g / groups_e == i0 ? e_first : e_second) * wexpert + (g % groups_e) * PF * STEP; };
@@ -523,13 +613,11 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
       const_cast<E*>(Y), 0, (uint32_t)(y_rows * I * NP * sizeof(E)), 0x00020000);
   constexpr uint32_t ROW_BYTES = NP * KS * sizeof(E), PAST_END = 0x80000000u;
   const uint32_t ykstride = (uint32_t)y_rows * ROW_BYTES;
+  int row_first = 0, row_second = 0;   // set behind the first weights
   auto rows_of = [&](int g, uint32_t (&yoff)[TT], uint32_t (&ystep)[TT]) {
-    const int e = g / groups_e == i0 ? e_first : e_second, kk = (g % groups_e) * PF;
+    const int kk = (g % groups_e) * PF, row = g / groups_e == i0 ? row_first : row_second;
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
-      int row = -1;
-#pragma unroll
-      for (int j = 0; j < MAX_TOPK; ++j) row = (j < top_k && my_e[t][j] == e) ? my_row[t][j] : row;
       yoff[t] = row >= 0 ? ((uint32_t)kk * (uint32_t)y_rows + row) * ROW_BYTES + half * 16 : PAST_END;
       ystep[t] = row >= 0 ? ykstride : 0;
     }
@@ -565,6 +653,8 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
       TRACE_MARK_WAVE(55, 1, KW);
 #pragma unroll
       for (int i = 0; i < PF; ++i) issue_w(i, wp);
+      row_first = row_in_y(e_first);
+      row_second = row_in_y(e_second);
       uint32_t yoff[TT], ystep[TT];
       rows_of(g0, yoff, ystep);
 #pragma unroll
@@ -848,7 +938,7 @@ void launch_qkv(bool bf16, const QkvArgs& a, hipStream_t st) {
 }
 
 template <typename E> static void launch_oproj_t(bool bf16, const OprojArgs& a, hipStream_t st) {
-  ResidualEpi<E> epi{a.x, a.H, a.gain, (E*)a.xn, a.ssq, a.T};
+  ResidualEpi<E> epi{a.x, a.H, a.gain, (E*)a.xn, a.ssq, a.T, (const E*)a.w_router, a.shares};
   if (dense_applies(a.T, a.D / ET<E>::KS))
     launch_dense<E>((const E*)a.w, a.D / ET<E>::KS, (const E*)a.a, a.T, a.H / 64, epi, st);
   else
@@ -1018,117 +1108,110 @@ template <typename E> static bool configure_smooth() {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Router.  The single weight task holds experts 0-31 (tile 0) and 32-63 (tile 1); per token group its K range is
-// shared by `slices` workgroups of KW waves exactly as in the split-K kernel above.  The workgroup that holds the
-// complete sums turns them into logits[token][expert] (times the row's 1/rms, which it derives from the per-task
-// sums of squares the output projection left), then groups of 16 or 8 lanes take one token each
-// through softmax and the k selection rounds (ties to the lower expert id).  With a single token group the same
-// workgroup goes on to build the token->expert permutation.
+// Router of at most ROUTER_SHARES_T tokens: a wave per token, a lane per expert.  The logits are the sum of the shares that the
+// tasks of the output projection left (in task order), times the row's 1/rms, which comes from their sums of squares; then
+// softmax and the k selection rounds (ties to the lower expert id).  No sum between workgroups is left, and the pairs are sorted by
+// whoever needs them (PairIds).  Bound by one dependent round trip and the rounds' cross-lane steps.  Until the output projection left
+// shares, one or two token tiles were contracted with the whole of K here by up to eight workgroups, with a hand-off between them, and
+// the last one selected and sorted: with events around the launch 14.3 -> 6.8 us at 32 tokens, 16.3 -> 6.8 at 64 (hidden 2048), the float32
+// test model 11.3 -> 6.7; the output projection takes 1.2 to 1.6 longer, the expert kernels up to 0.8.
 // ------------------------------------------------------------------------------------------------
-// Cross-lane moves inside rows of 16 lanes on the data-parallel-primitive path (no LDS round trip).  The four
-// controls below form a butterfly: after them (the first three) every lane of a 16-lane (8-lane) group holds the group's
-// result, provided the combining step is symmetric.
-template <int CTRL> __device__ inline int dpp_i(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
-template <int CTRL> __device__ inline float dpp_f(float v) { return __int_as_float(dpp_i<CTRL>(__float_as_int(v))); }
-constexpr int DPP_SWAP1 = 0xB1;         // quad_perm [1,0,3,2]
-constexpr int DPP_SWAP2 = 0x4E;         // quad_perm [2,3,0,1]
-constexpr int DPP_HALF_MIRROR = 0x141;  // lane i <- lane 7-i of its group of 8
-constexpr int DPP_MIRROR = 0x140;       // lane i <- lane 15-i of its row
-// L (8 or 16) lanes form a group; every lane ends with the same bits.
-template <int L> __device__ inline float group_max(float v) {
+constexpr int SELECT_WAVES = 4;
+__global__ __launch_bounds__(SELECT_WAVES * WAVE) void router_select_kernel(const float* __restrict__ shares, const float* __restrict__ ssq, int n_tasks,
+                                                                            float eps, int T, int H, int n_exp, int top_k, int norm_topk,
+                                                                            float* __restrict__ rinv, int32_t* __restrict__ topk_idx,
+                                                                            float* __restrict__ topk_w, const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  const int tok = blockIdx.x * SELECT_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (tok >= T) return;                 // uniform over the wave; nothing below meets the others
+  static_assert(MAX_EXPERTS == WAVE && MAX_HIDDEN / 64 <= WAVE, "a lane per expert, and per task for the sums of squares");
+  const float ss = lane < n_tasks ? ssq[(int64_t)lane * T + tok] : 0.f;
+  float z = 0.f;
+  for (int j0 = 0; j0 < n_tasks; j0 += 32) {   // 32 independent loads at a time
+    float v[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = shares[((int64_t)min(j0 + i, n_tasks - 1) * T + tok) * MAX_EXPERTS + lane];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) z += j0 + i < n_tasks ? v[i] : 0.f;
+  }
+  const float r = rsqrtf(wave_all_sum(ss) / H + eps);
+  const bool on = lane < n_exp;
+  z = on ? z * r : -INFINITY;
+  const float m = wave_all_max(z);
+  const float ez = on ? expf(z - m) : 0.f;
+  const float inv = 1.f / wave_all_sum(ez);
+  // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its expert ids
+  // would be no ids, and the expert kernels would index with them
+  float p = on ? fmaxf(ez * inv, 0.f) : -1.f;
+  float wsel = 0.f, sel_sum = 0.f;      // lane j keeps the j-th selection
+  int isel = 0;
+  for (int j = 0; j < top_k; ++j) {
+    const float best = wave_all_max(p);
+    const int e = __builtin_ctzll(__ballot(p == best) | 1ull << 63);
+    if (lane == e) p = -1.f;
+    if (lane == j) {
+      wsel = best;
+      isel = e;
+    }
+    sel_sum += best;
+  }
+  if (lane < top_k) {
+    topk_idx[tok * top_k + lane] = isel;
+    topk_w[tok * top_k + lane] = norm_topk ? wsel / sel_sum : wsel;
+  }
+  if (lane == 0) rinv[tok] = r;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Router of more tokens.  The single weight task holds experts 0-31 (tile 0) and 32-63 (tile 1); a workgroup takes a token
+// tile, its KW waves the K range, and the partial tiles meet in LDS.  It turns the sums into logits[token][expert] (times the
+// row's 1/rms, which it derives from the per-task sums of squares the output projection left), then groups of 16 lanes take one
+// token each through softmax and the k selection rounds (ties to the lower expert id).
+// ------------------------------------------------------------------------------------------------
+// A row of 16 lanes forms a group; every lane ends with the same bits (each step combines the same two values on both sides).
+__device__ inline float group_max(float v) {
   v = fmaxf(v, dpp_f<DPP_SWAP1>(v));
   v = fmaxf(v, dpp_f<DPP_SWAP2>(v));
   v = fmaxf(v, dpp_f<DPP_HALF_MIRROR>(v));
-  return L == 16 ? fmaxf(v, dpp_f<DPP_MIRROR>(v)) : v;
+  return fmaxf(v, dpp_f<DPP_MIRROR>(v));
 }
-// Sum over the group in a fixed tree (each step adds the same two values on both sides, and float addition commutes).
-template <int L> __device__ inline float group_sum(float v) {
+__device__ inline float group_sum(float v) {
   v += dpp_f<DPP_SWAP1>(v);
   v += dpp_f<DPP_SWAP2>(v);
   v += dpp_f<DPP_HALF_MIRROR>(v);
-  return L == 16 ? v + dpp_f<DPP_MIRROR>(v) : v;
+  return v + dpp_f<DPP_MIRROR>(v);
 }
-template <int L> __device__ inline int group_min(int v) {
+__device__ inline int group_min(int v) {
   v = min(v, dpp_i<DPP_SWAP1>(v));
   v = min(v, dpp_i<DPP_SWAP2>(v));
   v = min(v, dpp_i<DPP_HALF_MIRROR>(v));
-  return L == 16 ? min(v, dpp_i<DPP_MIRROR>(v)) : v;
+  return min(v, dpp_i<DPP_MIRROR>(v));
 }
 // Largest value of the group and the lowest id that holds it: the largest value first, then the lowest id among
 // the lanes whose own best equals it (two plain butterflies instead of one with a compound comparison).
-template <int L> __device__ inline void group_argmax(float& bv, int& bi) {
-  const float mx = group_max<L>(bv);
-  bi = group_min<L>(bv == mx ? bi : 0x7fffffff);
+__device__ inline void group_argmax(float& bv, int& bi) {
+  const float mx = group_max(bv);
+  bi = group_min(bv == mx ? bi : 0x7fffffff);
   bv = mx;
 }
 
-// Token->expert permutation of at most 64 tokens, a stable counting sort of the pairs: s_mask[e] has a bit per token that
-// goes to expert e, so a pair's rank within its expert is the number of set bits below its token, and every wave scans the
-// experts' counts for itself (lane = expert): nothing waits behind another wave.  s_pair[p]: expert + 256 * token of pair p.
-__device__ inline void mask_permute(const int32_t* s_pair, const unsigned long long* s_mask, int n_pairs, int n_exp, int32_t* __restrict__ cnt,
-                                    int32_t* __restrict__ off, int32_t* __restrict__ perm, int32_t* __restrict__ pos_of_pair) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  const int tot = lane < n_exp ? __popcll(s_mask[lane]) : 0;
-  int incl = tot;   // inclusive scan over the lanes (experts)
-#pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const int up = __shfl_up(incl, o, WAVE);
-    if (lane >= o) incl += up;
-  }
-  const int start = incl - tot;
-  for (int p0 = 0; p0 < n_pairs; p0 += blockDim.x) {   // uniform over the wave: every lane takes part in the shuffle
-    const int p = p0 + threadIdx.x, pair = s_pair[min(p, n_pairs - 1)], e = pair & 255, tok = pair >> 8;
-    const int r = __shfl(start, e, WAVE) + __popcll(s_mask[e] & ((1ull << tok) - 1));
-    if (p < n_pairs) {
-      perm[r] = p;
-      pos_of_pair[p] = r;
-    }
-  }
-  if (threadIdx.x >= WAVE) return;
-  if (lane < n_exp) {
-    cnt[lane] = tot;
-    off[lane] = start;
-    if (lane == n_exp - 1) off[n_exp] = incl;
-  }
-  const uint64_t has_rows = __ballot(tot > 0);          // dense list of the experts with rows (ACTIVE_LIST)
-  if (tot > 0) {
-    const int at = __popcll(has_rows & below);
-    off[ACTIVE_LIST + at] = lane;
-    *reinterpret_cast<int4*>(off + ACTIVE_RECORDS + 4 * at) = make_int4(lane, start, tot, 0);
-  }
-  if (lane == 0) {
-    off[ACTIVE_LIST + MAX_EXPERTS] = __popcll(has_rows);
-    off[STAT_ACTIVE_SUM] += __popcll(has_rows);
-    off[STAT_PERMUTATIONS] += 1;
-  }
-}
-
-template <typename E, int TT, int KW>
+template <typename E, int KW>
 __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__ W, const E* __restrict__ xn,
                                                             const float* __restrict__ ssq, int n_ssq,
                                                             float eps, int T, int H, int n_exp, int top_k, int norm_topk,
                                                             float* __restrict__ rinv, int32_t* __restrict__ topk_idx,
-                                                            float* __restrict__ topk_w, int fuse_permute,
-                                                            int32_t* __restrict__ cnt, int32_t* __restrict__ off,
-                                                            int32_t* __restrict__ perm,
-                                                            int32_t* __restrict__ pos_of_pair, int32_t* __restrict__ hist,
-                                                            float* __restrict__ part,
-                                                            int32_t* __restrict__ tickets, const int32_t* __restrict__ live) {
+                                                            float* __restrict__ topk_w, int32_t* __restrict__ hist, const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   extern __shared__ float red[];   // [KW][2*TT*16][64] partials
-  constexpr int ROWS = 2 * TT * 16, NTOK = TT * TILE, NTHREADS = KW * WAVE, PER = 16 / KW;
+  constexpr int TT = 1, ROWS = 2 * TT * 16, NTOK = TT * TILE, NTHREADS = KW * WAVE, PER = 16 / KW;
   constexpr int SS_PARTS = NTHREADS / NTOK;                       // threads per token for the sums of squares
   constexpr int SS_PER = (MAX_HIDDEN / 64 + SS_PARTS - 1) / SS_PARTS;
   constexpr int LOGIT_STRIDE = MAX_EXPERTS + 1;   // padded: the transposed writes spread over the banks
   __shared__ float s_logit[NTOK * LOGIT_STRIDE];
   __shared__ float s_ssp[SS_PARTS * NTOK];
   __shared__ float s_rinv[NTOK];
-  __shared__ int32_t s_pair[NTOK * MAX_TOPK];                // expert + 256 * token
-  __shared__ unsigned long long s_mask[MAX_EXPERTS];         // bit per token that goes to the expert
-  static_assert(NTOK <= 64 && NTHREADS >= MAX_EXPERTS, "a token is a bit of the mask");
-  __shared__ int32_t s_flag;
-  const int slice = blockIdx.x, n_slices = gridDim.x, group = blockIdx.y;
+  __shared__ int32_t s_cnt[MAX_EXPERTS];                     // pairs per expert
+  const int group = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
   const int tok0 = group * NTOK;
   const int ksteps = H / ET<E>::KS;
@@ -1149,8 +1232,8 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
   PlaneLoader<E, TT> ld;
 #pragma unroll
   for (int t = 0; t < TT; ++t) ld.set(t, xn, T, min(tok0 + t * TILE + (lane & 31), T - 1), half);
-  const int per = (ksteps + n_slices * KW - 1) / (n_slices * KW);
-  const int ks0 = min(ksteps, (slice * KW + wave) * per), ks1 = min(ksteps, ks0 + per);
+  const int per = (ksteps + KW - 1) / KW;
+  const int ks0 = min(ksteps, wave * per), ks1 = min(ksteps, ks0 + per);
   stream_task<E, TT, (TT == 1 ? 8 : 4), false>(W, ks0, ks1, ld, acc0, acc1);
   TRACE_MARK(3, 1);
   spill_partials<TT, ROWS>(red, wave, lane, acc0, acc1);
@@ -1165,12 +1248,7 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
   const int v0 = wave * PER;
   float a0[TT][PER], a1[TT][PER];
   fold_partials<TT, KW, PER>(red, lane, v0, a0, a1);
-  if (n_slices > 1) {
-    put_slice<TT, PER>(part, (int64_t)group * n_slices + slice, lane, v0, a0, a1);
-    if (!last_arrival(tickets + group, n_slices, &s_flag)) return;
-    sum_slices<TT, PER>(part, group, n_slices, lane, v0, a0, a1);
-  }
-  if (threadIdx.x < MAX_EXPERTS) s_mask[threadIdx.x] = 0ull;
+  if (threadIdx.x < MAX_EXPERTS) s_cnt[threadIdx.x] = 0;
   if (threadIdx.x < NTOK) {
     float row_ss = 0.f;
     for (int q = 0; q < SS_PARTS; ++q) row_ss += s_ssp[q * NTOK + threadIdx.x];
@@ -1191,10 +1269,9 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
   }
   __syncthreads();
   TRACE_MARK(3, 3);
-  // 16 lanes per token with 4 consecutive experts each; with 64 tokens 8 lanes and 8 experts, so that one pass does
-  // (two passes of 32 tokens: 3.3 us).  A lane can keep one of the at most eight selections either way.
-  constexpr int LPT = NTHREADS / NTOK >= 16 ? 16 : 8, EPL = MAX_EXPERTS / LPT;
-  static_assert(LPT >= MAX_TOPK, "lane j keeps the j-th selection");
+  // 16 lanes per token with 4 consecutive experts each
+  constexpr int LPT = NTHREADS / NTOK, EPL = MAX_EXPERTS / LPT;
+  static_assert(LPT == 16 && LPT >= MAX_TOPK, "lane j keeps the j-th selection");
   const int grp = threadIdx.x / LPT, sub = threadIdx.x % LPT;
   for (int tl = grp; tl < NTOK; tl += NTHREADS / LPT) {
     float p[EPL];
@@ -1204,14 +1281,14 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
       p[i] = EPL * sub + i < n_exp ? s_logit[tl * LOGIT_STRIDE + EPL * sub + i] : -INFINITY;
       m = fmaxf(m, p[i]);
     }
-    m = group_max<LPT>(m);
+    m = group_max(m);
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
       p[i] = EPL * sub + i < n_exp ? expf(p[i] - m) : 0.f;
       sum += p[i];
     }
-    const float inv = 1.f / group_sum<LPT>(sum);
+    const float inv = 1.f / group_sum(sum);
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
       // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its
@@ -1229,7 +1306,7 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
           bv = p[i];
           bi = EPL * sub + i;
         }
-      group_argmax<LPT>(bv, bi);
+      group_argmax(bv, bi);
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
         if (EPL * sub + i == bi) p[i] = -1.f;
@@ -1243,45 +1320,26 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
       const int tok = tok0 + tl;
       topk_idx[tok * top_k + sub] = isel;
       topk_w[tok * top_k + sub] = norm_topk ? wsel / sel_sum : wsel;
-      s_pair[tl * top_k + sub] = isel | (tl << 8);
-      atomicOr(&s_mask[isel], 1ull << tl);
+      atomicAdd(&s_cnt[isel], 1);
     }
   }
   TRACE_MARK(3, 4);
   __syncthreads();
-  if (fuse_permute) mask_permute(s_pair, s_mask, T * top_k, n_exp, cnt, off, perm, pos_of_pair);
-  else if (threadIdx.x < MAX_EXPERTS)    // many tokens: the permutation kernel takes the group's pairs per expert
-    hist[group * MAX_EXPERTS + threadIdx.x] = __popcll(s_mask[threadIdx.x]);
+  if (threadIdx.x < MAX_EXPERTS) hist[group * MAX_EXPERTS + threadIdx.x] = s_cnt[threadIdx.x];   // for the permutation
   TRACE_MARK(3, 5);
 }
 
-// Workgroups that share the router's K range: as for the projections, with 8 waves per workgroup.
-static int router_slices(bool bf16, int K, int T) {
-  if (T > 2 * TILE || single_slice()) return 1;
-  const int ksteps = K / (bf16 ? 16 : 8);
-  const int burst = 8 * (T <= TILE ? 8 : 4);
-  return ksteps % burst == 0 ? ksteps / burst : 1;
-}
-
 template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a, hipStream_t st) {
-  const E* W = (const E*)a.w;
-  const int slices = router_slices(bf16, a.H, a.T);
-  if (a.T <= 32) {
-    router_kernel<E, 1, 8><<<dim3(slices, 1), 8 * WAVE, ksplit_lds<1, 8>(), st>>>(
-        W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
-        a.topk_w, 1, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
-  } else if (a.T <= 64) {
-    router_kernel<E, 2, 8><<<dim3(slices, 1), 8 * WAVE, ksplit_lds<2, 8>(), st>>>(
-        W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
-        a.topk_w, 1, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
-  } else {
-    const int groups = (a.T + TILE - 1) / TILE;   // 32 tokens per workgroup: one round of the top-k lanes, more workgroups
-    router_kernel<E, 1, 8><<<dim3(1, groups), 8 * WAVE, ksplit_lds<1, 8>(), st>>>(
-        W, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx,
-        a.topk_w, 0, a.cnt, a.off, a.perm, a.pos_of_pair, a.hist, a.part, a.tickets, live_word());
-    launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.E, a.cnt, a.off, a.perm, a.pos_of_pair, a.work,
-                   expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
+  if (a.T <= ROUTER_SHARES_T) {
+    router_select_kernel<<<(a.T + SELECT_WAVES - 1) / SELECT_WAVES, SELECT_WAVES * WAVE, 0, st>>>(
+        a.shares, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx, a.topk_w, live_word());
+    return;
   }
+  const int groups = (a.T + TILE - 1) / TILE;   // 32 tokens per workgroup: one round of the top-k lanes, more workgroups
+  router_kernel<E, 8><<<groups, 8 * WAVE, ksplit_lds<1, 8>(), st>>>((const E*)a.w, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k,
+                                                                    a.norm_topk, a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
+  launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.E, a.cnt, a.off, a.perm, a.work,
+                 expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
 }
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {
   if (bf16) launch_router_t<bf16_t>(true, a, st);
@@ -1292,17 +1350,17 @@ void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {
 constexpr int DOWN_SLICES = 8, DOWN_KW = 8;
 int down_fused_slices() { return DOWN_SLICES; }
 template <typename E> static void launch_down_fused_t(const ExpertArgs& a, const OprojArgs& r, hipStream_t st) {
-  ResidualEpi<E> epi{r.x, r.H, r.gain, (E*)r.xn, r.ssq, r.T};
+  ResidualEpi<E> epi{r.x, r.H, r.gain, (E*)r.xn, r.ssq, r.T, nullptr, nullptr};
   const int n_tasks = a.H / 64, ksteps_e = a.I / ET<E>::KS;
   const dim3 grid(DOWN_SLICES, n_tasks);
   const E *w = (const E*)a.w_down, *y = (const E*)a.y;
   const int64_t y_rows = (int64_t)a.T * a.top_k;
   if (ksteps_e % 8 == 0)
     expert_down_fused_kernel<E, 1, DOWN_KW, 8><<<grid, DOWN_KW * WAVE, ksplit_lds<1, DOWN_KW>(), st>>>(
-        w, y, y_rows, a.off, a.topk_idx, a.pos_of_pair, a.T, a.I, a.top_k, n_tasks, r.part, r.tickets, epi, live_word());
+        w, y, y_rows, a.topk_idx, a.T, a.I, a.top_k, n_tasks, r.part, r.tickets, epi, live_word());
   else
     expert_down_fused_kernel<E, 1, DOWN_KW, 4><<<grid, DOWN_KW * WAVE, ksplit_lds<1, DOWN_KW>(), st>>>(
-        w, y, y_rows, a.off, a.topk_idx, a.pos_of_pair, a.T, a.I, a.top_k, n_tasks, r.part, r.tickets, epi, live_word());
+        w, y, y_rows, a.topk_idx, a.T, a.I, a.top_k, n_tasks, r.part, r.tickets, epi, live_word());
 }
 void launch_expert_down_fused(bool bf16, const ExpertArgs& a, const OprojArgs& res, hipStream_t st) {
   if (bf16) launch_down_fused_t<bf16_t>(a, res, st);
@@ -1324,8 +1382,7 @@ bool configure_kernels() {
        opt_in_lds((const void*)expert_down_fused_kernel<bf16_t, 1, DOWN_KW, 4>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<float, 1, DOWN_KW, 8>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<float, 1, DOWN_KW, 4>);
-  ok = ok && opt_in_lds((const void*)router_kernel<bf16_t, 1, 8>) && opt_in_lds((const void*)router_kernel<float, 1, 8>) &&
-       opt_in_lds((const void*)router_kernel<bf16_t, 2, 8>) && opt_in_lds((const void*)router_kernel<float, 2, 8>);
+  ok = ok && opt_in_lds((const void*)router_kernel<bf16_t, 8>) && opt_in_lds((const void*)router_kernel<float, 8>);
   (void)hipGetLastError();
   return ok;
 }

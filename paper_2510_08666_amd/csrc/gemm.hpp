@@ -168,17 +168,9 @@ __device__ inline void fold_partials(const float* red, int lane, int v0, float (
   }
 }
 
-// The offset array is followed by the list of experts that received at least one row: off[ACTIVE_LIST + i] is
-// the i-th such expert (ascending), off[ACTIVE_LIST + MAX_EXPERTS] their number.  The grouped GEMMs index their
-// grid through it, so that workgroups of experts without rows sit at the end of the grid instead of leaving
-// holes in the dispatch order.
-constexpr int ACTIVE_LIST = MAX_EXPERTS + 1;
-// ... and by one 16-byte record per listed expert, {expert, first sorted row, rows, 0}, at off[ACTIVE_RECORDS + 4*i]:
-// everything a grouped-GEMM workgroup needs to know about its expert in a single load.
-constexpr int ACTIVE_RECORDS = 2 * MAX_EXPERTS + 4;
-// ... and by two running totals for benchmarks: experts with rows summed over the permutations built so far, and the
-// number of permutations (one per layer and forward); dinfer_profile_start clears them.
-constexpr int STAT_ACTIVE_SUM = ACTIVE_RECORDS + 4 * MAX_EXPERTS;
+// The offset array (off[0 .. E]) is followed by two running totals for benchmarks: experts with rows summed over the layers run
+// so far, and the number of those (one per layer and forward); dinfer_profile_start clears them.
+constexpr int STAT_ACTIVE_SUM = MAX_EXPERTS + 1;
 constexpr int STAT_PERMUTATIONS = STAT_ACTIVE_SUM + 1;
 constexpr int OFF_INTS = STAT_PERMUTATIONS + 1;   // size of the offset array with everything behind it
 

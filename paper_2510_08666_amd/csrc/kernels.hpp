@@ -72,7 +72,7 @@ void launch_combine(bool bf16, float* x, const float* O, const float* topk_w, in
 // xn_hi = the high plane of bf16 planes xn (LmArgs::xn_hi)
 void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st);
 
-// Cross-workgroup split-K scratch shared by the projections and the router (see gemm.hip): `part` holds the
+// Cross-workgroup split-K scratch of the projections (see gemm.hip): `part` holds the
 // workgroup sums, `tickets` one arrival counter per (task, token group), all zero between launches.
 
 struct QkvArgs {
@@ -146,7 +146,12 @@ struct OprojArgs {
   int T, D, H;
   float* part;
   int32_t* tickets;
+  // with at most ROUTER_SHARES_T tokens: each 64-feature task also leaves its share of the router's logits (packed router
+  // weights, times the planes of its features, without 1/rms): shares[H/64][T][MAX_EXPERTS].  Null: not wanted
+  const void* w_router;
+  float* shares;
 };
+constexpr int ROUTER_SHARES_T = 64;
 void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st);
 
 // Iteration smoothing: delta[t] = softmax(logits[t]) . W_emb for the rows of positions that are still masked.
@@ -168,9 +173,9 @@ struct SmoothArgs {
 void launch_expected_embedding(bool bf16, const SmoothArgs& a, hipStream_t st);
 void launch_prob_planes(bool bf16, const float* logits, const float* stats, int T, int V, int Kpad, void* probs,
                         hipStream_t st);
-// Router logits on the matrix cores + softmax + top-k (ties to the lower expert id, weights renormalised when
-// norm_topk); rinv[t] from the sums of squares above; for T <= 64 also the token->expert permutation
-// (otherwise launch_permute is issued behind it).
+// Router: softmax + top-k (ties to the lower expert id, weights renormalised when norm_topk); rinv[t] from the sums of squares
+// above.  Up to ROUTER_SHARES_T tokens the logits are the sum of the shares the output projection left, and the expert kernels
+// sort the pairs; beyond, the logits are contracted here and launch_permute is issued behind.
 struct RouterArgs {
   const void* w;            // packed router weights (one task)
   const void* xn;           // [T][H] normalised-input planes (FFN gain)
@@ -181,20 +186,20 @@ struct RouterArgs {
   float* rinv;              // [T] out: 1/rms of the residual rows
   int32_t* topk_idx;        // [T][top_k] out
   float* topk_w;            // [T][top_k] out
-  int32_t* cnt;             // [E], off [E+1], perm [T*top_k], pos_of_pair [T*top_k]: out
+  int32_t* cnt;             // [E], off [E+1], perm [T*top_k]: out (T > 64)
   int32_t* off;
   int32_t* perm;
-  int32_t* pos_of_pair;
   int32_t* work;            // [WORK_ITEMS + 4 * expert_work_items at two tiles per group]: work list of the many-token
                             // expert GEMMs (T > 64 only), 16-byte aligned
   int32_t* hist;            // [ceil(T / 32)][MAX_EXPERTS]: pairs per expert of every 32 tokens (T > 64 only)
-  float* part;
-  int32_t* tickets;
+  const float* shares;      // OprojArgs::shares
 };
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st);
 // hist: the router's histograms, see RouterArgs; round: expert_round_items.
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
-                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, hipStream_t st);
+                    int32_t* perm, int32_t* work, int group_tiles, int round, hipStream_t st);
+// cnt, off and perm of at most 64 tokens (a test hook).
+void launch_pair_tables(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm, hipStream_t st);
 // Work list of the expert GEMMs above 64 tokens: number of items [WORK_BIG] taken by whole workgroups, of all items
 // [WORK_ALL] (the rest in pieces of one task), of those with the most tiles [WORK_HEAVY] and with one or two [WORK_LIGHT], then
 // 16-byte items {expert, first sorted row, rows, 0}, the ones with more tiles first.
@@ -208,15 +213,14 @@ struct ExpertArgs {
   const float* rinv;        // [T]
   void* y;                  // [T*k][I] k-major
   float* o;                 // [T*k][H], row = token*top_k + slot (many-token form only)
-  const int32_t* off;
-  const int32_t* perm;
-  const int32_t* work;      // see RouterArgs
+  int32_t* off;             // its running totals (up to 64 tokens; beyond, the permutation keeps them)
+  const int32_t* perm;      // T > 64
+  const int32_t* work;      // T > 64, see RouterArgs
   int T, H, I, E, top_k;
   // at most 32 tokens: the down projection is fused with the combine (launch_expert_down_fused); the expert
   // intermediate then carries the routing weight, taken from topk_w [T][top_k] (null: not applied)
   const float* topk_w;
   const int32_t* topk_idx;  // [T][top_k]
-  const int32_t* pos_of_pair;
 };
 void launch_expert_gate_up(bool bf16, const ExpertArgs& a, hipStream_t st);   // picks the form by a.T
 void launch_expert_down(bool bf16, const ExpertArgs& a, hipStream_t st);

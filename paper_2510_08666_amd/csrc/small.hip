@@ -271,7 +271,7 @@ void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st
 }
 
 // ---------------------------------------------------------------- token -> expert permutation
-// Stand-alone form (more than 64 tokens; below, the router kernel sorts its pairs by a token mask per expert).  Stable counting
+// More than 64 tokens (below, the expert kernels sort the pairs for themselves: routing.hpp).  Stable counting
 // sort of the (token, slot) pairs by expert.  The router's workgroups have left the histogram of their 32 tokens,
 // hist[group][MAX_EXPERTS]; workgroup g of this launch adds up the groups before its own and all of them, which
 // gives the place of its first pair of every expert, and places its group's pairs: a wave takes 64 consecutive pairs
@@ -284,7 +284,7 @@ static_assert(TILE * MAX_TOPK <= PERMUTE_WAVES * WAVE, "a group's pairs are at m
 __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int32_t* __restrict__ expert_of_pair, int n_pairs, int pairs_per_group,
                                                         const int32_t* __restrict__ hist, int n_exp,
                                                         int32_t* __restrict__ cnt, int32_t* __restrict__ off,
-                                                        int32_t* __restrict__ perm, int32_t* __restrict__ pos_of_pair,
+                                                        int32_t* __restrict__ perm,
                                                         int32_t* __restrict__ work, int group_tiles, int round,
                                                         const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
@@ -329,14 +329,8 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
         off[lane] = incl - tot;
         if (lane == n_exp - 1) off[n_exp] = incl;
       }
-      const uint64_t has_rows = __ballot(tot > 0);          // dense list of the experts that received rows
-      if (tot > 0) {
-        const int at = __popcll(has_rows & below);
-        off[ACTIVE_LIST + at] = lane;
-        *reinterpret_cast<int4*>(off + ACTIVE_RECORDS + 4 * at) = make_int4(lane, incl - tot, tot, 0);
-      }
+      const uint64_t has_rows = __ballot(tot > 0);
       if (lane == 0) {
-        off[ACTIVE_LIST + MAX_EXPERTS] = __popcll(has_rows);
         off[STAT_ACTIVE_SUM] += __popcll(has_rows);
         off[STAT_PERMUTATIONS] += 1;
       }
@@ -375,7 +369,6 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
     int r = s_first[e] + __popcll(s_ballot[wave * MAX_EXPERTS + e] & below);
     for (int w = 0; w < wave; ++w) r += __popcll(s_ballot[w * MAX_EXPERTS + e]);
     perm[r] = p;
-    pos_of_pair[p] = r;
   }
 }
 // The bound that the interface states for a context (dinfer_workspace_bytes); counts and positions are 32-bit and the grid of
@@ -383,10 +376,33 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
 constexpr int PERMUTE_MAX_PAIRS = 65535;
 int permute_max_pairs() { return PERMUTE_MAX_PAIRS; }
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
-                    int32_t* perm, int32_t* pos_of_pair, int32_t* work, int group_tiles, int round, hipStream_t st) {
+                    int32_t* perm, int32_t* work, int group_tiles, int round, hipStream_t st) {
   const int per_group = TILE * top_k;
   permute_kernel<<<(n_pairs + per_group - 1) / per_group, PERMUTE_WAVES * WAVE, 0, st>>>(
-      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, pos_of_pair, work, group_tiles, round, live_word());
+      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, work, group_tiles, round, live_word());
+}
+
+// The tables of permute_kernel for at most 64 tokens, where no kernel of a forward needs them; a test hook's kernel.
+__global__ __launch_bounds__(WAVE) void pair_tables_kernel(const int32_t* __restrict__ expert_of_pair, int n_pairs, int n_exp,
+                                                           int32_t* __restrict__ cnt, int32_t* __restrict__ off, int32_t* __restrict__ perm) {
+  __shared__ int32_t s_cnt[MAX_EXPERTS];
+  const int e = threadIdx.x;
+  int n = 0;
+  for (int p = 0; p < n_pairs; ++p) n += expert_of_pair[p] == e;
+  s_cnt[e] = n;
+  __syncthreads();
+  int at = 0;
+  for (int i = 0; i < e; ++i) at += s_cnt[i];
+  if (e < n_exp) {
+    cnt[e] = n;
+    off[e] = at;
+    if (e == n_exp - 1) off[n_exp] = at + n;
+  }
+  for (int p = 0; p < n_pairs; ++p)
+    if (expert_of_pair[p] == e) perm[at++] = p;
+}
+void launch_pair_tables(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm, hipStream_t st) {
+  pair_tables_kernel<<<1, WAVE, 0, st>>>(topk_idx, n_pairs, E, cnt, off, perm);
 }
 
 // ---------------------------------------------------------------- LM-head partial merge

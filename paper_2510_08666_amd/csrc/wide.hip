@@ -7,6 +7,7 @@
 // unit's address path busy with 64 separate rows per load.  Work that would leave most of the chip idle (a few items
 // beyond a full round, small models) goes out in pieces instead: one task per workgroup, K cut over its waves.
 #include "kernels.hpp"
+#include "routing.hpp"
 #include "wide_stream.hpp"
 
 namespace dinfer {
@@ -23,31 +24,32 @@ constexpr int XCDS = 8;      // accelerator dies, each with its own L2; workgrou
 
 // ------------------------------------------------------------------------------------------------
 // Routed experts.  An item is a run of an expert's sorted rows, {expert, first sorted row, rows, 0}: up to 64 tokens all
-// rows of an expert (the records the router's fused permutation leaves), beyond groups of up to 64 or 128 rows, heaviest
-// first (the work list of the permutation kernel).  Pair of sorted row r: perm[r].
+// rows of an expert (the i-th expert with rows: PairIds in routing.hpp), beyond groups of up to 64 or 128 rows, heaviest
+// first (the work list of the permutation kernel).  pair(): the (token, slot) pair of sorted row r.
 //   GEMM 1: task = 32 gate features + the same 32 up features;  y = silu(gate) * up  -> Y[sorted row][I]
 //   GEMM 2: task = 64 adjacent output features of the down projection                -> O[token*top_k + slot][H]
 // ------------------------------------------------------------------------------------------------
 template <typename E> struct GateUp {
+  static constexpr bool COUNTS = true;     // keeps the running totals of experts with rows
   const E* W;
   const E* xn;
   const float* rinv;
   E* Y;
-  const int32_t* perm;
+  const int32_t* perm;   // more than 64 tokens
   int T, H, I, top_k;
   const float* topk_w;   // the routing weight, when the down projection sums the experts itself; else null
   __device__ int ksteps() const { return H / ET<E>::KS; }
   __device__ int n_tasks() const { return I / TILE; }
   __device__ const E* act() const { return xn; }
   __device__ int64_t act_rows() const { return T; }
-  __device__ int act_row(int r) const { return perm[r] / top_k; }
+  template <class P> __device__ int act_row(int, P&& pair) const { return pair() / top_k; }
   // what the lane needs to know about sorted row r
   struct Row {
     int act;         // its row among the activations
     float r, wgt;
   };
-  __device__ Row row(int r) const {
-    const int pair = perm[r], tok = pair / top_k;
+  __device__ Row row(int, int pair) const {
+    const int tok = pair / top_k;
     return Row{tok, rinv[tok], topk_w ? topk_w[pair] : 1.f};
   }
   __device__ static float silu(float x) { return x / (1.f + __expf(-x)); }
@@ -60,6 +62,7 @@ template <typename E> struct GateUp {
   }
 };
 template <typename E> struct Down {
+  static constexpr bool COUNTS = false;
   const E* W;
   const E* Y;
   float* O;
@@ -69,11 +72,11 @@ template <typename E> struct Down {
   __device__ int n_tasks() const { return H / (2 * TILE); }
   __device__ const E* act() const { return Y; }
   __device__ int64_t act_rows() const { return n_pairs; }
-  __device__ int act_row(int r) const { return r; }
+  template <class P> __device__ int act_row(int r, P&&) const { return r; }
   struct Row {
     int act, pair;
   };
-  __device__ Row row(int r) const { return Row{r, perm[r]}; }
+  __device__ Row row(int r, int pair) const { return Row{r, pair}; }
   __device__ void store(const Row& w, int, int task, int g, int half, const f32x4& a, const f32x4& b) const {
     float* o = O + (int64_t)w.pair * H + (2 * task) * TILE + acc_row(4 * g, half);
     *reinterpret_cast<f32x4*>(o) = a;
@@ -81,9 +84,10 @@ template <typename E> struct Down {
   }
 };
 
-// One item and WW tasks (task group tg) by a workgroup: every wave streams its task's whole K range.
-template <typename E, int WT, int WW, int KID, class Op>
-__device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* lds) {
+// One item and WW tasks (task group tg) by a workgroup: every wave streams its task's whole K range.  pair_of(i): the pair of
+// the item's row i.
+template <typename E, int WT, int WW, int KID, class Op, class PairOf>
+__device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* lds, PairOf&& pair_of) {
   typedef typename ET<E>::vec vec;
   constexpr int KS = ET<E>::KS, NP = Planes<E>::N;
   TRACE_MARK(KID, 3);
@@ -95,8 +99,14 @@ __device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* 
   // needs of them waits in registers; where the accumulators of four tiles leave too few, it is asked for again there.
   constexpr bool AGAIN = WT >= 4;
   typename Op::Row rows[WT];
-  auto row_of = [&](int t) { return op.row(base + min(t * TILE + col, n_rows - 1)); };
-  auto staged = [&](int r) { return op.act_row(base + min((wave % WT) * TILE + r, n_rows - 1)); };
+  auto row_of = [&](int t) {
+    const int i = min(t * TILE + col, n_rows - 1);
+    return op.row(base + i, pair_of(i));
+  };
+  auto staged = [&](int r) {
+    const int i = min((wave % WT) * TILE + r, n_rows - 1);
+    return op.act_row(base + i, [&] { return pair_of(i); });
+  };
   if constexpr (!AGAIN) {
 #pragma unroll
     for (int t = 0; t < WT; ++t) rows[t] = row_of(t);
@@ -129,8 +139,8 @@ __device__ inline void expert_tasks(const Op& op, const int4& it, int tg, char* 
 }
 
 // One item of up to TT tiles and ONE task by a workgroup of KW waves, which cut the task's K range and meet in LDS.
-template <typename E, int TT, int KW, class Op>
-__device__ inline void expert_piece(const Op& op, const int4& it, int task, char* lds) {
+template <typename E, int TT, int KW, class Op, class PairOf>
+__device__ inline void expert_piece(const Op& op, const int4& it, int task, char* lds, PairOf&& pair_of) {
   constexpr int PER = 4, EW = 16 / PER;
   static_assert(KW >= EW, "the first EW waves run the epilogue");
   const int e = it.x, base = it.y, n_rows = it.z;
@@ -140,7 +150,8 @@ __device__ inline void expert_piece(const Op& op, const int4& it, int task, char
   PlaneLoader<E, TT> ld;
 #pragma unroll
   for (int t = 0; t < TT; ++t) {
-    rows[t] = op.row(base + min(t * TILE + col, n_rows - 1));
+    const int i = min(t * TILE + col, n_rows - 1);
+    rows[t] = op.row(base + i, pair_of(i));
     ld.set(t, op.act(), op.act_rows(), rows[t].act, half);
   }
   f32x16 acc0[TT], acc1[TT];
@@ -160,26 +171,46 @@ __device__ inline void expert_piece(const Op& op, const int4& it, int task, char
                f32x4{a1[t][0], a1[t][1], a1[t][2], a1[t][3]});
 }
 
-// Grid (task groups, items): one workgroup each.
+// Up to 64 tokens: the workgroup's item, the i-th expert with rows, from the routing; false where there is none.
+template <int TT> __device__ inline bool routed_item(const int32_t* __restrict__ topk_idx, int n_pairs, int i, int32_t* s_pair, int32_t* totals, int4& it) {
+  PairIds<TT * TILE * MAX_TOPK / WAVE> ids;
+  ids.load(topk_idx, n_pairs);
+  const uint64_t experts = ids.experts();
+  const int n = __popcll(experts);
+  if (totals && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    totals[0] += n;
+    totals[1] += 1;
+  }
+  if (i >= n) return false;                         // uniform over the block
+  it = ids.rows_of(nth_bit(experts, i), s_pair);
+  __syncthreads();
+  return true;
+}
+
+// Grid (task groups, experts): one workgroup each, those beyond the experts with rows at the end.
 template <typename E, int WT, int WW, int KID, class Op>
-__global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_kernel(Op op, const int32_t* __restrict__ n_items,
-                                                                                                 const int4* __restrict__ items,
+__global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_kernel(Op op, const int32_t* __restrict__ topk_idx, int n_pairs,
+                                                                                                 int32_t* __restrict__ totals,
                                                                                                  const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
-  if ((int)blockIdx.y >= *n_items) return;          // uniform over the block
-  expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+  __shared__ __align__(16) int32_t s_pair[WAVE];
+  int4 it;
+  if (!routed_item<WT>(topk_idx, n_pairs, blockIdx.y, s_pair, totals, it)) return;
+  expert_tasks<E, WT, WW, KID, Op>(op, it, blockIdx.x, lds_raw, [&](int i) { return s_pair[i]; });
 }
 
-// Grid (tasks, items): every task in pieces (up to 64 tokens, few tasks: see launch_expert_op).
+// Grid (tasks, experts): every task in pieces (up to 64 tokens, few tasks: see launch_expert_op).
 template <typename E, int TT, class Op>
-__global__ __launch_bounds__(EXPERT_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_pieces_kernel(Op op, const int32_t* __restrict__ n_items,
-                                                                                                              const int4* __restrict__ items,
+__global__ __launch_bounds__(EXPERT_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void expert_pieces_kernel(Op op, const int32_t* __restrict__ topk_idx, int n_pairs,
+                                                                                                              int32_t* __restrict__ totals,
                                                                                                               const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   extern __shared__ __align__(16) char lds_raw[];
-  if ((int)blockIdx.y >= *n_items) return;          // uniform over the block
-  expert_piece<E, TT, EXPERT_WW, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+  __shared__ __align__(16) int32_t s_pair[WAVE];
+  int4 it;
+  if (!routed_item<TT>(topk_idx, n_pairs, blockIdx.y, s_pair, totals, it)) return;
+  expert_piece<E, TT, EXPERT_WW, Op>(op, it, blockIdx.x, lds_raw, [&](int i) { return s_pair[i]; });
 }
 
 // More than 64 tokens.  Grid (task groups, rows): the first rows are items in whole task groups (WW tasks, one per
@@ -195,19 +226,24 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
   extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
   const int4* items = reinterpret_cast<const int4*>(work + WORK_ITEMS);
   const int n_big = work[WORK_BIG];
+  auto pairs_at = [&](int base) { return [&op, base](int i) { return op.perm[base + i]; }; };
   int piece;
   if constexpr (wide_expert_shared(KID)) {
     // an item's task groups on one die, one after the other, and behind them its expert's other items (expert_plan.hpp)
     const int wg = blockIdx.y * gridDim.x + blockIdx.x, whole = expert_unit_wgs(n_big, gridDim.x);
     if (wg < whole) {
       const ExpertUnit u = expert_unit(wg, work[WORK_HEAVY], work[WORK_ALL] - work[WORK_LIGHT], n_big, gridDim.x);
-      if (u.item >= 0) expert_tasks<E, WT, WW, KID, Op>(op, items[u.item], u.group, lds_raw);
+      if (u.item >= 0) {
+        const int4 it = items[u.item];
+        expert_tasks<E, WT, WW, KID, Op>(op, it, u.group, lds_raw, pairs_at(it.y));
+      }
       return;
     }
     piece = wg - whole;
   } else {
     if ((int)blockIdx.y < n_big) {
-      expert_tasks<E, WT, WW, KID, Op>(op, items[blockIdx.y], blockIdx.x, lds_raw);
+      const int4 it = items[blockIdx.y];
+      expert_tasks<E, WT, WW, KID, Op>(op, it, blockIdx.x, lds_raw, pairs_at(it.y));
       return;
     }
     piece = ((int)blockIdx.y - n_big) * gridDim.x + blockIdx.x;
@@ -215,11 +251,11 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) 
   const int n_tasks = op.n_tasks();
   if (piece >= (work[WORK_ALL] - n_big) * n_tasks) return;   // uniform over the block
   const int4 it = items[n_big + piece / n_tasks];
-  if (it.z <= TILE) expert_piece<E, 1, WW, Op>(op, it, piece % n_tasks, lds_raw);
-  else expert_piece<E, 2, WW, Op>(op, it, piece % n_tasks, lds_raw);
+  if (it.z <= TILE) expert_piece<E, 1, WW, Op>(op, it, piece % n_tasks, lds_raw, pairs_at(it.y));
+  else expert_piece<E, 2, WW, Op>(op, it, piece % n_tasks, lds_raw, pairs_at(it.y));
 }
 
-// Up to 32 / 64 tokens: one / two token tiles and SMALL_WW tasks per workgroup, experts from the router's records
+// Up to 32 / 64 tokens: one / two token tiles and SMALL_WW tasks per workgroup
 // (trace ids 16 .. 19); more: four tiles, eight tasks, the work list of the permutation kernel (ids 10, 11).
 // (Measured, gate/up + down in microseconds: two tasks 69.8 + 37.6 at 32 tokens and 86.6 + 49.2 at 64; four tasks
 // 68.9 + 38.9 and 88.1 + 50.7; the earlier per-wave-operand kernels, whose four waves split K, 72.9 + 38.6 and
@@ -243,19 +279,18 @@ static void launch_expert_op(const Op& op, const ExpertArgs& a, int n_tasks, hip
   const int n_pairs = a.T * a.top_k;
   auto grid = [&](int ww, int items) { return dim3((n_tasks + ww - 1) / ww, items); };
   if (a.T <= 2 * TILE) {
-    const int32_t* n_items = a.off + ACTIVE_LIST + MAX_EXPERTS;
-    const int4* records = reinterpret_cast<const int4*>(a.off + ACTIVE_RECORDS);
+    int32_t* totals = Op::COUNTS ? a.off + STAT_ACTIVE_SUM : nullptr;
     // Few tasks over all experts (one per compute unit or less): a workgroup of eight waves each, since a wave alone with
     // a task is bound by its chain of loads and matrix instructions (8 experts of 512, hidden 256, float32: gate/up 14.6
     // -> 9.6 us at 32 tokens, 23 -> 13 at 64, down at 64 tokens 37 -> 17.5).
     if (a.E * n_tasks <= EXPERT_CUS && a.T <= TILE)
-      expert_pieces_kernel<E, 1, Op><<<dim3(n_tasks, a.E), EXPERT_WW * WAVE, many_lds<EXPERT_WW>() / 2, st>>>(op, n_items, records, live_word());
+      expert_pieces_kernel<E, 1, Op><<<dim3(n_tasks, a.E), EXPERT_WW * WAVE, many_lds<EXPERT_WW>() / 2, st>>>(op, a.topk_idx, n_pairs, totals, live_word());
     else if (a.E * n_tasks <= EXPERT_CUS)
-      expert_pieces_kernel<E, 2, Op><<<dim3(n_tasks, a.E), EXPERT_WW * WAVE, many_lds<EXPERT_WW>(), st>>>(op, n_items, records, live_word());
+      expert_pieces_kernel<E, 2, Op><<<dim3(n_tasks, a.E), EXPERT_WW * WAVE, many_lds<EXPERT_WW>(), st>>>(op, a.topk_idx, n_pairs, totals, live_word());
     else if (a.T <= TILE)
-      expert_kernel<E, 1, WW1, K1, Op><<<grid(WW1, a.E), WW1 * WAVE, wide_lds<E, K1, 1>(), st>>>(op, n_items, records, live_word());
+      expert_kernel<E, 1, WW1, K1, Op><<<grid(WW1, a.E), WW1 * WAVE, wide_lds<E, K1, 1>(), st>>>(op, a.topk_idx, n_pairs, totals, live_word());
     else
-      expert_kernel<E, 2, SMALL_WW, K2, Op><<<grid(SMALL_WW, a.E), SMALL_WW * WAVE, wide_lds<E, K2, 2>(), st>>>(op, n_items, records, live_word());
+      expert_kernel<E, 2, SMALL_WW, K2, Op><<<grid(SMALL_WW, a.E), SMALL_WW * WAVE, wide_lds<E, K2, 2>(), st>>>(op, a.topk_idx, n_pairs, totals, live_word());
   } else {
     auto many = [&](auto kernel, int wt, int ww, size_t lds, int more = 0) {   // more: rows of the grid for the whole multiple of dies
       const dim3 whole = grid(ww, expert_work_items(a.E, n_pairs, wt) + more);
