@@ -203,7 +203,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.loop_steps = cv.take(4);                     // inner loop: steps that ran
   w.lm_rows = cv.take((size_t)(1 + T) * 4);      // LM head: rows of the undecided positions
   w.work = cv.take((size_t)(WORK_ITEMS + 4 * expert_work_items(MAX_EXPERTS, (int)(T * K), 2)) * 4);
-  w.hist = cv.take((T + TILE - 1) / TILE * MAX_EXPERTS * 4);   // pairs per expert of every 32 tokens
+  w.hist = cv.take((T + HIST_TOKENS - 1) / HIST_TOKENS * MAX_EXPERTS * 4);   // pairs per expert of every 8 or 32 tokens
   w.y = cv.take(planes * T * K * I * es);
   w.o = cv.take(T * K * H * 4);
   w.lm_part = cv.take((size_t)lm_head_most_parts(c.vocab) * T * 4 * 4);
@@ -306,6 +306,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
   // (the fused kernel needs its 64 wave shares, each within two experts; under the single-slice test switch the
   // down projection takes the unfused route, which has no sum across workgroups)
   const bool fused_down = T <= TILE && !single_slice();
+  const bool shares = router_shares(bf, D, H, T);
   int n_ssq_a = 1;
   const int64_t q_plane = (int64_t)c->max_tokens * D;
   for (int l = 0; l < f.n_layers; ++l) {
@@ -340,14 +341,14 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
       launch_attention(bf, aa, st);
     }
     OprojArgs oa{c->weights + lw.wo, ws + w.a, x, at<float>(c->weights, lw.ffn_gain), xn,
-                 at<float>(ws, w.ssq), T, D, H, tk_part, tickets, T <= ROUTER_SHARES_T ? c->weights + lw.router : nullptr, at<float>(ws, w.shares)};
+                 at<float>(ws, w.ssq), T, D, H, tk_part, tickets, shares ? c->weights + lw.router : nullptr, at<float>(ws, w.shares)};
     {
       StageTimer tm(c, DINFER_STAGE_OPROJ, st);
       launch_oproj(bf, oa, st);
     }
     RouterArgs ra{c->weights + lw.router, xn, at<float>(ws, w.ssq), f.rms_eps, T, H, f.n_experts, f.top_k,
                   f.norm_topk, f.moe_inter, rinv_f, topk_idx, topk_w, at<int32_t>(ws, w.cnt), at<int32_t>(ws, w.off),
-                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), at<float>(ws, w.shares)};
+                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), shares ? at<float>(ws, w.shares) : nullptr};
     {
       StageTimer tm(c, DINFER_STAGE_ROUTER, st);
       launch_router(bf, ra, st);

@@ -837,11 +837,30 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
     for (int t = 0; t < WT; ++t)
 #pragma unroll
       for (int g = 0; g < NG; ++g) epi.template prefetch2<PER>(pre[t][g], task, half, g * PER);
+    [[maybe_unused]] typename RouterStep<E>::frag rw[2][NG][2];   // [tile][eight features][experts from 0, from 32]
+    constexpr bool SHARES = Epi::ROWSUM && WT == 1;   // (with two tiles they do not fit the registers)
+    bool routed = false;
+    if constexpr (SHARES) {
+      routed = epi.w_router != nullptr;
+      if (routed) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int et = 0; et < 2; ++et) rw[f][g][et] = RouterStep<E>::load(epi.w_router, task, f, g, et, lane);
+      }
+    }
 #pragma unroll
     for (int t = 0; t < WT; ++t) {
       const int tok = tok0 + t * TILE + col;
       const bool valid = t < nt && tok < T;
       float ss = 0.f;
+      [[maybe_unused]] f32x16 r0[1], r1[1];
+      if constexpr (SHARES) {
+        zero_acc<1>(r0);
+        zero_acc<1>(r1);
+      }
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         float a0[PER], a1[PER];
@@ -851,6 +870,26 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
           a1[i] = acc1[t][g * PER + i];
         }
         ss += epi.template apply<PER>(pre[t][g], task, tok, valid, half, g * PER, a0, a1);
+        if constexpr (SHARES) {
+          if (routed) {
+            f32x4 m[2];
+            Epi::normed(pre[t][g], a0, a1, m);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              RouterStep<E>::add(r0[0], rw[f][g][0], m[f]);
+              RouterStep<E>::add(r1[0], rw[f][g][1], m[f]);
+            }
+          }
+        }
+      }
+      if constexpr (SHARES) {
+        if (routed && valid) {
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            epi.store_share(task, tok, acc_row(g * PER, half), f32x4{r0[0][4 * g], r0[0][4 * g + 1], r0[0][4 * g + 2], r0[0][4 * g + 3]});
+            epi.store_share(task, tok, TILE + acc_row(g * PER, half), f32x4{r1[0][4 * g], r1[0][4 * g + 1], r1[0][4 * g + 2], r1[0][4 * g + 3]});
+          }
+        }
       }
       if (Epi::ROWSUM) {   // the wave holds the whole task: the row statistic is the sum over its two half-waves
         ss += __shfl_xor(ss, 32, WAVE);
@@ -893,6 +932,10 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
 // slices that ksplit_slices() now gives a launch of 96 tasks it takes 14.9 us.  For the output projection, a third
 // of the weights, split-K was ahead all along, 11.5 against 17.1.)
 static bool dense_applies(int T, int ksteps) { return T > 2 * TILE && ksteps % (WKC * DENSE_KH) == 0; }
+bool router_shares(bool bf16, int D, int H, int T) {
+  if (T <= 2 * TILE) return true;
+  return T <= ROUTER_SHARES_T && dense_applies(T, D / (bf16 ? 16 : 8)) && dense_form(bf16, H / 64, T).tiles == 1;
+}
 
 template <typename E, int WT, int TASKS, int KH, class Epi>
 static void launch_dense_as(const E* W, int ksteps, const E* B, int T, int n_tasks, int groups, const Epi& epi, hipStream_t st) {
@@ -1108,62 +1151,79 @@ template <typename E> static bool configure_smooth() {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Router of at most ROUTER_SHARES_T tokens: a wave per token, a lane per expert.  The logits are the sum of the shares that the
+// Router where the output projection leaves shares of the logits (router_shares): a wave per token, a lane per expert.  The logits are the sum of the shares that the
 // tasks of the output projection left (in task order), times the row's 1/rms, which comes from their sums of squares; then
-// softmax and the k selection rounds (ties to the lower expert id).  No sum between workgroups is left, and the pairs are sorted by
-// whoever needs them (PairIds).  Bound by one dependent round trip and the rounds' cross-lane steps.  Until the output projection left
+// softmax and the k selection rounds (ties to the lower expert id).  No sum between workgroups is left; up to 64 tokens the pairs
+// are sorted by whoever needs them (PairIds).  Bound by one dependent round trip and the rounds' cross-lane steps.  Until the output projection left
 // shares, one or two token tiles were contracted with the whole of K here by up to eight workgroups, with a hand-off between them, and
 // the last one selected and sorted: with events around the launch 14.3 -> 6.8 us at 32 tokens, 16.3 -> 6.8 at 64 (hidden 2048), the float32
 // test model 11.3 -> 6.7; the output projection takes 1.2 to 1.6 longer, the expert kernels up to 0.8.
+// More tokens: as the router kernel below and the permutation take it 18.9 us at 160 tokens and 21.5 at 512, with this kernel 13.1 and 13.1
+// (the output projection +1.3 to 1.6), as long as the projection takes its forms of one token tile (1024 tokens at hidden 2048; beyond, shares
+// of 8 KB a token would cost more than the contraction).  Eight tokens a workgroup: with 32, one compute unit fetches 256 KB, 17.2 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int SELECT_WAVES = 4;
-__global__ __launch_bounds__(SELECT_WAVES * WAVE) void router_select_kernel(const float* __restrict__ shares, const float* __restrict__ ssq, int n_tasks,
-                                                                            float eps, int T, int H, int n_exp, int top_k, int norm_topk,
-                                                                            float* __restrict__ rinv, int32_t* __restrict__ topk_idx,
-                                                                            float* __restrict__ topk_w, const int32_t* __restrict__ live) {
+// HIST (more than 64 tokens): the workgroup leaves its tokens' pairs per expert for the permutation.
+template <int WAVES, bool HIST>
+__global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float* __restrict__ shares, const float* __restrict__ ssq, int n_tasks,
+                                                                     float eps, int T, int H, int n_exp, int top_k, int norm_topk,
+                                                                     float* __restrict__ rinv, int32_t* __restrict__ topk_idx,
+                                                                     float* __restrict__ topk_w, int32_t* __restrict__ hist, const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
-  const int tok = blockIdx.x * SELECT_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (tok >= T) return;                 // uniform over the wave; nothing below meets the others
   static_assert(MAX_EXPERTS == WAVE && MAX_HIDDEN / 64 <= WAVE, "a lane per expert, and per task for the sums of squares");
-  const float ss = lane < n_tasks ? ssq[(int64_t)lane * T + tok] : 0.f;
-  float z = 0.f;
-  for (int j0 = 0; j0 < n_tasks; j0 += 32) {   // 32 independent loads at a time
-    float v[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = shares[((int64_t)min(j0 + i, n_tasks - 1) * T + tok) * MAX_EXPERTS + lane];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) z += j0 + i < n_tasks ? v[i] : 0.f;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tok = blockIdx.x * WAVES + wave;
+  __shared__ int32_t s_cnt[HIST ? MAX_EXPERTS : 1];
+  if constexpr (HIST) {
+    if (wave == 0) s_cnt[lane] = 0;
+    __syncthreads();
   }
-  const float r = rsqrtf(wave_all_sum(ss) / H + eps);
-  const bool on = lane < n_exp;
-  z = on ? z * r : -INFINITY;
-  const float m = wave_all_max(z);
-  const float ez = on ? expf(z - m) : 0.f;
-  const float inv = 1.f / wave_all_sum(ez);
-  // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its expert ids
-  // would be no ids, and the expert kernels would index with them
-  float p = on ? fmaxf(ez * inv, 0.f) : -1.f;
-  float wsel = 0.f, sel_sum = 0.f;      // lane j keeps the j-th selection
-  int isel = 0;
-  for (int j = 0; j < top_k; ++j) {
-    const float best = wave_all_max(p);
-    const int e = __builtin_ctzll(__ballot(p == best) | 1ull << 63);
-    if (lane == e) p = -1.f;
-    if (lane == j) {
-      wsel = best;
-      isel = e;
+  if (tok < T) {                        // uniform over the wave
+    const float ss = lane < n_tasks ? ssq[(int64_t)lane * T + tok] : 0.f;
+    float z = 0.f;
+    for (int j0 = 0; j0 < n_tasks; j0 += 32) {   // 32 independent loads at a time
+      float v[32];
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = shares[((int64_t)min(j0 + i, n_tasks - 1) * T + tok) * MAX_EXPERTS + lane];
+#pragma unroll
+      for (int i = 0; i < 32; ++i) z += j0 + i < n_tasks ? v[i] : 0.f;
     }
-    sel_sum += best;
+    const float r = rsqrtf(wave_all_sum(ss) / H + eps);
+    const bool on = lane < n_exp;
+    z = on ? z * r : -INFINITY;
+    const float m = wave_all_max(z);
+    const float ez = on ? expf(z - m) : 0.f;
+    const float inv = 1.f / wave_all_sum(ez);
+    // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its expert ids
+    // would be no ids, and the expert kernels would index with them
+    float p = on ? fmaxf(ez * inv, 0.f) : -1.f;
+    float wsel = 0.f, sel_sum = 0.f;    // lane j keeps the j-th selection
+    int isel = 0;
+    for (int j = 0; j < top_k; ++j) {
+      const float best = wave_all_max(p);
+      const int e = __builtin_ctzll(__ballot(p == best) | 1ull << 63);
+      if (lane == e) p = -1.f;
+      if (lane == j) {
+        wsel = best;
+        isel = e;
+      }
+      sel_sum += best;
+    }
+    if (lane < top_k) {
+      topk_idx[tok * top_k + lane] = isel;
+      topk_w[tok * top_k + lane] = norm_topk ? wsel / sel_sum : wsel;
+      if constexpr (HIST) atomicAdd(&s_cnt[isel], 1);
+    }
+    if (lane == 0) rinv[tok] = r;
   }
-  if (lane < top_k) {
-    topk_idx[tok * top_k + lane] = isel;
-    topk_w[tok * top_k + lane] = norm_topk ? wsel / sel_sum : wsel;
+  if constexpr (HIST) {
+    __syncthreads();
+    if (wave == 0) hist[blockIdx.x * MAX_EXPERTS + lane] = s_cnt[lane];
   }
-  if (lane == 0) rinv[tok] = r;
 }
 
 // ------------------------------------------------------------------------------------------------
-// Router of more tokens.  The single weight task holds experts 0-31 (tile 0) and 32-63 (tile 1); a workgroup takes a token
+// Router without shares.  The single weight task holds experts 0-31 (tile 0) and 32-63 (tile 1); a workgroup takes a token
 // tile, its KW waves the K range, and the partial tiles meet in LDS.  It turns the sums into logits[token][expert] (times the
 // row's 1/rms, which it derives from the per-task sums of squares the output projection left), then groups of 16 lanes take one
 // token each through softmax and the k selection rounds (ties to the lower expert id).
@@ -1330,15 +1390,16 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
 }
 
 template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a, hipStream_t st) {
-  if (a.T <= ROUTER_SHARES_T) {
-    router_select_kernel<<<(a.T + SELECT_WAVES - 1) / SELECT_WAVES, SELECT_WAVES * WAVE, 0, st>>>(
-        a.shares, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx, a.topk_w, live_word());
-    return;
-  }
-  const int groups = (a.T + TILE - 1) / TILE;   // 32 tokens per workgroup: one round of the top-k lanes, more workgroups
-  router_kernel<E, 8><<<groups, 8 * WAVE, ksplit_lds<1, 8>(), st>>>((const E*)a.w, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k,
-                                                                    a.norm_topk, a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
-  launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.E, a.cnt, a.off, a.perm, a.work,
+  auto select = [&](auto kernel, int waves) {
+    kernel<<<(a.T + waves - 1) / waves, waves * WAVE, 0, st>>>(a.shares, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv,
+                                                               a.topk_idx, a.topk_w, a.hist, live_word());
+  };
+  if (a.T <= 2 * TILE) return select(router_select_kernel<SELECT_WAVES, false>, SELECT_WAVES);
+  if (a.shares) select(router_select_kernel<HIST_TOKENS, true>, HIST_TOKENS);
+  else
+    router_kernel<E, 8><<<(a.T + TILE - 1) / TILE, 8 * WAVE, ksplit_lds<1, 8>(), st>>>((const E*)a.w, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E,
+                                                                                       a.top_k, a.norm_topk, a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
+  launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.shares ? HIST_TOKENS : TILE, a.E, a.cnt, a.off, a.perm, a.work,
                  expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
 }
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {

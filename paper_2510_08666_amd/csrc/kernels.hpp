@@ -146,12 +146,15 @@ struct OprojArgs {
   int T, D, H;
   float* part;
   int32_t* tickets;
-  // with at most ROUTER_SHARES_T tokens: each 64-feature task also leaves its share of the router's logits (packed router
+  // where router_shares() says so: each 64-feature task also leaves its share of the router's logits (packed router
   // weights, times the planes of its features, without 1/rms): shares[H/64][T][MAX_EXPERTS].  Null: not wanted
   const void* w_router;
   float* shares;
 };
-constexpr int ROUTER_SHARES_T = 64;
+// Whether the output projection leaves the router's shares: all its forms of up to 64 tokens, and of more tokens the
+// dense ones of one token tile, up to ROUTER_SHARES_T.
+constexpr int ROUTER_SHARES_T = 1024;
+bool router_shares(bool bf16, int D, int H, int T);
 void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st);
 
 // Iteration smoothing: delta[t] = softmax(logits[t]) . W_emb for the rows of positions that are still masked.
@@ -174,8 +177,9 @@ void launch_expected_embedding(bool bf16, const SmoothArgs& a, hipStream_t st);
 void launch_prob_planes(bool bf16, const float* logits, const float* stats, int T, int V, int Kpad, void* probs,
                         hipStream_t st);
 // Router: softmax + top-k (ties to the lower expert id, weights renormalised when norm_topk); rinv[t] from the sums of squares
-// above.  Up to ROUTER_SHARES_T tokens the logits are the sum of the shares the output projection left, and the expert kernels
-// sort the pairs; beyond, the logits are contracted here and launch_permute is issued behind.
+// above.  The logits are the sum of the shares the output projection left, or without those contracted here.  Up to 64 tokens
+// the expert kernels sort the pairs; beyond, launch_permute is issued behind.
+constexpr int HIST_TOKENS = 8;
 struct RouterArgs {
   const void* w;            // packed router weights (one task)
   const void* xn;           // [T][H] normalised-input planes (FFN gain)
@@ -191,12 +195,12 @@ struct RouterArgs {
   int32_t* perm;
   int32_t* work;            // [WORK_ITEMS + 4 * expert_work_items at two tiles per group]: work list of the many-token
                             // expert GEMMs (T > 64 only), 16-byte aligned
-  int32_t* hist;            // [ceil(T / 32)][MAX_EXPERTS]: pairs per expert of every 32 tokens (T > 64 only)
-  const float* shares;      // OprojArgs::shares
+  int32_t* hist;            // [ceil(T / HIST_TOKENS)][MAX_EXPERTS]: pairs per expert of every HIST_TOKENS or 32 tokens (T > 64 only)
+  const float* shares;      // OprojArgs::shares, or null
 };
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st);
-// hist: the router's histograms, see RouterArgs; round: expert_round_items.
-void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
+// hist: the router's histograms, see RouterArgs, one per hist_tokens tokens (a divisor of 32); round: expert_round_items.
+void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int hist_tokens, int E, int32_t* cnt, int32_t* off,
                     int32_t* perm, int32_t* work, int group_tiles, int round, hipStream_t st);
 // cnt, off and perm of at most 64 tokens (a test hook).
 void launch_pair_tables(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm, hipStream_t st);

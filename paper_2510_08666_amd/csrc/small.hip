@@ -272,8 +272,8 @@ void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st
 
 // ---------------------------------------------------------------- token -> expert permutation
 // More than 64 tokens (below, the expert kernels sort the pairs for themselves: routing.hpp).  Stable counting
-// sort of the (token, slot) pairs by expert.  The router's workgroups have left the histogram of their 32 tokens,
-// hist[group][MAX_EXPERTS]; workgroup g of this launch adds up the groups before its own and all of them, which
+// sort of the (token, slot) pairs by expert.  The router's workgroups have left the histogram of their tokens,
+// hist[n_hist][MAX_EXPERTS], `hists` of them for 32 tokens; workgroup g of this launch, which takes 32 tokens, adds up those before its own and all of them, which
 // gives the place of its first pair of every expert, and places its group's pairs: a wave takes 64 consecutive pairs
 // (a chunk) and forms the ballots "which lanes go to expert e" for all experts at once by OR-ing lane bits into its own
 // 64 LDS words; the population of ballot e is the chunk's count for e, the bits below a lane in its expert's ballot
@@ -282,7 +282,7 @@ void launch_high_plane(const void* xn, int T, int H, void* xn_hi, hipStream_t st
 constexpr int PERMUTE_WAVES = 4;
 static_assert(TILE * MAX_TOPK <= PERMUTE_WAVES * WAVE, "a group's pairs are at most one chunk per wave");
 __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int32_t* __restrict__ expert_of_pair, int n_pairs, int pairs_per_group,
-                                                        const int32_t* __restrict__ hist, int n_exp,
+                                                        const int32_t* __restrict__ hist, int n_hist, int hists, int n_exp,
                                                         int32_t* __restrict__ cnt, int32_t* __restrict__ off,
                                                         int32_t* __restrict__ perm,
                                                         int32_t* __restrict__ work, int group_tiles, int round,
@@ -290,17 +290,17 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
   if (step_is_dead(live)) return;
   __shared__ unsigned long long s_ballot[PERMUTE_WAVES * MAX_EXPERTS];
   __shared__ int32_t s_before[PERMUTE_WAVES * MAX_EXPERTS], s_total[PERMUTE_WAVES * MAX_EXPERTS], s_first[MAX_EXPERTS];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, group = blockIdx.x, n_groups = gridDim.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, group = blockIdx.x;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   const int in_group = wave * WAVE + lane, p = group * pairs_per_group + in_group;
   const int e = in_group < pairs_per_group && p < n_pairs ? expert_of_pair[p] : -1;
   {
     int before = 0, total = 0;                              // lane = expert
 #pragma unroll 8
-    for (int g = wave; g < n_groups; g += PERMUTE_WAVES) {
+    for (int g = wave; g < n_hist; g += PERMUTE_WAVES) {
       const int n = hist[g * MAX_EXPERTS + lane];
       total += n;
-      before += g < group ? n : 0;
+      before += g < group * hists ? n : 0;
     }
     s_before[wave * MAX_EXPERTS + lane] = before;
     s_total[wave * MAX_EXPERTS + lane] = total;
@@ -375,11 +375,11 @@ __global__ __launch_bounds__(PERMUTE_WAVES * WAVE) void permute_kernel(const int
 // the expert GEMMs grows with a 128th of the pairs, so the kernels themselves do not need it.
 constexpr int PERMUTE_MAX_PAIRS = 65535;
 int permute_max_pairs() { return PERMUTE_MAX_PAIRS; }
-void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int E, int32_t* cnt, int32_t* off,
-                    int32_t* perm, int32_t* work, int group_tiles, int round, hipStream_t st) {
+void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int hist_tokens, int E, int32_t* cnt,
+                    int32_t* off, int32_t* perm, int32_t* work, int group_tiles, int round, hipStream_t st) {
   const int per_group = TILE * top_k;
   permute_kernel<<<(n_pairs + per_group - 1) / per_group, PERMUTE_WAVES * WAVE, 0, st>>>(
-      topk_idx, n_pairs, per_group, hist, E, cnt, off, perm, work, group_tiles, round, live_word());
+      topk_idx, n_pairs, per_group, hist, (n_pairs / top_k + hist_tokens - 1) / hist_tokens, TILE / hist_tokens, E, cnt, off, perm, work, group_tiles, round, live_word());
 }
 
 // The tables of permute_kernel for at most 64 tokens, where no kernel of a forward needs them; a test hook's kernel.
