@@ -50,6 +50,17 @@ inline LmPlan lm_plan(int V, int T) {
 // 175 us).  The last combine of a forward with a head writes it (+0.3 us at 512 tokens; a prompt of 4287 tokens, which has no
 // head, would store 17.6 MB for nothing).
 inline bool lm_compact(bool bf16, int T) { return bf16 && T > LM_MID_T; }
+// bf16 rows of 129 to 192 and of 289 to 320 tokens: half a task per wave, so that five or six token tiles fit a workgroup's
+// registers and the vocabulary's weights go to one workgroup where four tiles at most (or two, beyond 256 tokens, where they are three)
+// would take two of them.  A compute unit takes in about 27 GB/s whatever the cache it comes from, and at 160 tokens
+// two thirds of that was the second delivery.  LM head in us, four tiles and whole tasks -> this: 130 tokens 163 -> 137, 160 168 -> 142,
+// 192 172 -> 150, 288 219 -> 214 (the call is no faster), 320 223 -> 212, 352 230 -> 234, 384 238 -> 238, 480 286 -> 322, 512 288 -> 317 (with
+// eight tiles in a workgroup: every fragment read from LDS feeds one matrix instruction instead of two, and LDS is the bound); 320
+// tokens of which half are decided 189 -> 156, 160 with 16 undecided ones 136 -> 126.
+inline bool lm_half(bool bf16, int T) {
+  const int tiles = (T + 31) / 32;
+  return bf16 && (tiles == 5 || tiles == 6 || tiles == 10);
+}
 // Upper bound of the partials per token row, whatever the token count (workspace sizing): one per task, rounded up.
 inline int lm_head_most_parts(int V) { return ((V + LM_TASK_IDS - 1) / LM_TASK_IDS + LM_WW - 1) / LM_WW * LM_WW; }
 inline int lm_head_parts(int V, int T) { return lm_plan(V, T).parts; }

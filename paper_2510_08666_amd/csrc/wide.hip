@@ -509,6 +509,182 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// LM head, form of five and six token tiles (where: lm_half): half a task (32 vocabulary ids, one weight tile) per wave, four tasks
+// per workgroup, the high plane as in the form above, statistics of a task's two halves folded at the end.  Bound by what a compute unit
+// takes in (1 MB of weights and as much as 0.75 MB of rows per workgroup) and the last, partial round of workgroups (2.4 rounds of them at
+// 157184 ids).  Twelve k-steps of weights in flight per wave: 16, 24 or 32 were slower at 160 tokens (140.8 us, 144.5, 150, 211: loads return
+// in order, so that the rows on their way to LDS wait behind them), 8 as fast (141.1); rows requested two chunks ahead 160 against 155.
+// ------------------------------------------------------------------------------------------------
+constexpr int LMH_WW = 8, LMH_WT = 6, LMH_TASKS = LMH_WW / 2;      // waves, token tiles and tasks of a workgroup
+constexpr int LMH_KC = 4, LMH_PRE = 3, LMH_NB = 3;                 // as WideShape's KC, PRE, NB
+template <typename E> constexpr size_t lm_half_lds() { return (size_t)LMH_NB * LMH_KC * LMH_WT * WidePieces<E, 9>::TILE_VECS * 16; }
+
+// acc[t] += the wave's tile times token tile t, NT tiles, over ksteps k-steps (a multiple of LMH_KC).  w: the tile's k-step 0;
+// row_of(tile, r): activation row; SN tiles are staged, an even number of at least NT: wave w stages half of them for k-step w / 2 of
+// every chunk.
+template <typename E, int NT, int SN, class RowOf>
+__device__ inline void lm_half_stream(const E* __restrict__ w, int ksteps, const E* __restrict__ act, RowOf&& row_of, int64_t bkstride,
+                                      typename ET<E>::vec* sb, f32x16 (&acc)[NT], int wave) {
+  typedef typename ET<E>::vec vec;
+  typedef WidePieces<E, 9> Pc;
+  static_assert(Pc::N == 2 && Pc::ROWS == TILE && LMH_KC * 2 == LMH_WW && SN % 2 == 0 && SN >= NT, "a load is a k-step of a whole tile");
+  constexpr int KC = LMH_KC, PRE = LMH_PRE, NB = LMH_NB, PP = SN / 2;
+  constexpr int STEP = 2 * WAVE * 16, ROW_BYTES = 32, BUF = KC * SN * Pc::TILE_VECS;
+  const int lane = threadIdx.x & 63, n_chunks = ksteps / KC, last = n_chunks - 1;
+  const uint32_t wlane = lane * 16;
+  auto wload = [&](int c, int ks) { return load16_stream<E>((const E*)((const char*)w + (int64_t)(min(c, last) * KC + ks) * STEP + wlane)); };
+  vec wa[PRE][KC], bset[PP];
+  const int pks = wave >> 1, ptile = (wave & 1) * PP;
+  uint32_t src[PP];
+#pragma unroll
+  for (int j = 0; j < PP; ++j) src[j] = (uint32_t)row_of(ptile + j, lane >> 1) * ROW_BYTES + (lane & 1) * 16;
+#pragma unroll
+  for (int i = 0; i < PRE; ++i)
+#pragma unroll
+    for (int ks = 0; ks < KC; ++ks) wa[i][ks] = wload(i, ks);
+  const int dst = (pks * SN + ptile) * Pc::TILE_VECS + Pc::slot(lane >> 1, lane & 1);
+  auto fetch = [&](int c, vec (&b)[PP]) {
+    const char* base = (const char*)(act + (int64_t)(min(c, last) * KC + pks) * bkstride);
+#pragma unroll
+    for (int j = 0; j < PP; ++j) b[j] = load16<E>((const E*)(base + src[j]));
+  };
+  auto put = [&](int buf, const vec (&b)[PP]) {
+#pragma unroll
+    for (int j = 0; j < PP; ++j) sb[buf + dst + j * Pc::TILE_VECS] = b[j];
+  };
+  {
+    vec b0[NB - 1][PP];
+#pragma unroll
+    for (int i = 0; i < NB - 1; ++i) fetch(i, b0[i]);
+    fetch(NB - 1, bset);
+#pragma unroll
+    for (int i = 0; i < NB - 1; ++i) put(i * BUF, b0[i]);
+  }
+  const int rd = Pc::slot(lane & 31, lane >> 5);
+  constexpr int F = KC * NT, FD = 4;
+  vec ring[FD];
+  auto frag = [&](int buf, int f) { return sb[buf + ((f / NT) * SN + f % NT) * Pc::TILE_VECS + rd]; };
+  int cur = 0;
+  __syncthreads();
+  static_for<FD>([&](auto J) { ring[decltype(J)::value] = frag(0, decltype(J)::value); });
+  auto chunk = [&](auto I, int c) {
+    constexpr int i = decltype(I)::value;
+    __syncthreads();
+    const int nxt = cur + BUF < NB * BUF ? cur + BUF : 0;
+    put(nxt + BUF < NB * BUF ? nxt + BUF : 0, bset);
+    fetch(c + NB, bset);
+    static_for<F>([&](auto Fi) {
+      constexpr int f = decltype(Fi)::value, ks = f / NT, t = f % NT;
+      const vec b = ring[f % FD];
+      if constexpr (f + FD < F) ring[f % FD] = frag(cur, f + FD);
+      else ring[f % FD] = frag(nxt, f + FD - F);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma32(acc[t], wa[i][ks], b);
+    });
+#pragma unroll
+    for (int ks = 0; ks < KC; ++ks) wa[i][ks] = wload(c + PRE, ks);
+    cur = nxt;
+  };
+  int c0 = 0;       // whole rounds without a test between the chunks, the first one in front of the loop: see wide_stream_nt
+  if (n_chunks >= PRE) {
+    static_for<PRE>([&](auto I) { chunk(I, decltype(I)::value); });
+    for (c0 = PRE; c0 + PRE <= n_chunks; c0 += PRE) static_for<PRE>([&](auto I) { chunk(I, c0 + decltype(I)::value); });
+  }
+  static_for<PRE - 1>([&](auto I) {
+    if (c0 + decltype(I)::value < n_chunks) chunk(I, c0 + decltype(I)::value);   // uniform over the workgroup
+  });
+}
+
+template <typename E>
+__global__ __launch_bounds__(LMH_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2))) void lm_head_half_kernel(const E* __restrict__ W, const E* __restrict__ xn,
+                                                                  RowNorm norm, int T, int H, int V, float scale, float* __restrict__ part,
+                                                                  float* __restrict__ logits_out, const int32_t* __restrict__ rows, int n_tasks,
+                                                                  int n_parts, const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  typedef typename ET<E>::vec vec;
+  extern __shared__ __align__(16) char lds_raw[];   // 16-byte aligned: staged fragments move as 128-bit LDS accesses
+  __shared__ __align__(16) float s_scale[LMH_WT * TILE];
+  __shared__ __align__(16) int32_t s_row[LMH_WT * TILE];
+  constexpr int KS = ET<E>::KS;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int n_rows = rows ? min(rows[0], T) : T;
+  if (n_rows == 0) return;              // uniform over the workgroup
+  const int tiles = (n_rows + TILE - 1) / TILE, groups = (tiles + LMH_WT - 1) / LMH_WT, per_group = (tiles + groups - 1) / groups;
+  const int turn = blockIdx.x / XCDS, tgroup = (turn / groups) * XCDS + blockIdx.x % XCDS, tile0 = (turn % groups) * per_group;
+  if (tgroup * LMH_TASKS >= n_parts) return;
+  const int nt = min(per_group, tiles - tile0);
+  if (nt <= 0) return;                  // uniform: fewer tiles than groups * per_group
+  const int slot = tgroup * LMH_TASKS + (wave >> 1), task = min(slot, n_tasks - 1), ksteps = H / KS, tok0 = tile0 * TILE;
+  auto row_of = [&](int i) { return rows ? min(max(rows[1 + min(i, n_rows - 1)], 0), T - 1) : min(i, T - 1); };
+  if (threadIdx.x < LMH_WT * TILE) {    // read behind the stream's barriers
+    const int row = row_of(tok0 + threadIdx.x);
+    s_row[threadIdx.x] = row;
+    s_scale[threadIdx.x] = row_rinv(norm.ssq, norm.n_ssq, T, row, H, norm.eps) * scale;
+  }
+  const bool quads = V % 4 == 0 && ((uintptr_t)logits_out & 15) == 0;   // rows of logits start on 16-byte boundaries
+  LmStat* s_stat = reinterpret_cast<LmStat*>(lds_raw);   // [wave][token], once the fragments are done with
+  static_assert(LMH_WW * LMH_WT * TILE * sizeof(LmStat) <= lm_half_lds<E>(), "the statistics fit the staging area");
+  auto run = [&](auto N, auto S) {
+    constexpr int NT = decltype(N)::value, SN = decltype(S)::value;
+    f32x16 acc[NT];
+    zero_acc<NT>(acc);
+    lm_half_stream<E, NT, SN>(W + (int64_t)task * task_stride_elems<E>(ksteps) + (wave & 1) * (WAVE * ET<E>::G), ksteps, xn,
+                              [&](int t, int r) { return row_of(tok0 + t * TILE + r); }, (int64_t)T * KS, reinterpret_cast<vec*>(lds_raw), acc, wave);
+    __syncthreads();                    // the staged fragments have been read by every wave
+    const int id0 = (2 * task + (wave & 1)) * TILE + 4 * half;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const float zs = s_scale[t * TILE + col];
+      float m = -INFINITY, sum = 0.f, z[16];
+      int best = 0x7fffffff;
+      if (slot < n_tasks) {             // the maximum first, then the lowest id that has it: see lm_head_wide_kernel
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = acc[t][i] * zs;
+        if ((2 * task + (wave & 1) + 1) * TILE > V) {   // uniform
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (id0 + acc_row(i, 0) >= V) z[i] = -INFINITY;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m = fmaxf(m, z[i]);   // passes over NaN
+        int at = 0;
+#pragma unroll
+        for (int i = 15; i >= 0; --i) at = z[i] == m ? acc_row(i, 0) : at;
+        if (m > -INFINITY) best = id0 + at;
+        if (logits_out && tok0 + t * TILE + col < n_rows) {
+          float* out = logits_out + (int64_t)s_row[t * TILE + col] * V + id0;
+          if (quads) {
+#pragma unroll
+            for (int i = 0; i < 16; i += 4)
+              if (id0 + acc_row(i, 0) < V) *reinterpret_cast<f32x4*>(out + acc_row(i, 0)) = f32x4{z[i], z[i + 1], z[i + 2], z[i + 3]};
+          } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+              if (id0 + acc_row(i, 0) < V) out[acc_row(i, 0)] = z[i];
+          }
+        }
+        if (m > -INFINITY) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum += __expf(z[i] - m);
+        }
+      }
+      const LmStat w = lm_combine(LmStat{m, sum, best}, LmStat{__shfl_xor(m, 32, WAVE), __shfl_xor(sum, 32, WAVE), __shfl_xor(best, 32, WAVE)});
+      if (half == 0) s_stat[wave * LMH_WT * TILE + t * TILE + col] = w;
+    }
+  };
+  if (nt > 5) run(std::integral_constant<int, 6>{}, std::integral_constant<int, 6>{});
+  else if (nt == 5) run(std::integral_constant<int, 5>{}, std::integral_constant<int, 6>{});
+  else run(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+  __syncthreads();
+  // the two halves of a task, one partial per task as in the other form
+  for (int i = threadIdx.x; i < min(nt * TILE, n_rows - tok0) * LMH_TASKS; i += LMH_WW * WAVE) {
+    const int k = i % LMH_TASKS, r = i / LMH_TASKS;
+    const LmStat a = lm_combine(s_stat[(2 * k) * LMH_WT * TILE + r], s_stat[(2 * k + 1) * LMH_WT * TILE + r]);
+    *reinterpret_cast<f32x4*>(part + ((int64_t)s_row[r] * n_parts + tgroup * LMH_TASKS + k) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
+  }
+}
+
 // Up to 64 tokens: one or two token tiles per workgroup and both activation planes (trace ids 15, 14): there the weight
 // stream is the bound, and sharing the activation fragments relieves the address unit, which would otherwise take every
 // lane's own activation row one by one.  (33 to 64 tokens in workgroups of two tasks: 144 against 119 us, the fragments
@@ -530,6 +706,14 @@ template <typename E> static void launch_lm_wide_t(const LmArgs& a, hipStream_t 
     if (p.ww == LM_PIECE_WW) go(lm_head_wide_kernel<E, 2, 14, LM_PIECE_WW>, LM_PIECE_WW, lm_piece_lds<LM_PIECE_WW, 2>());
     else go(lm_head_wide_kernel<E, 2, 14, LM_MID_WW>, LM_MID_WW, lm_piece_lds<LM_MID_WW, 2>());
   } else {
+    if constexpr (sizeof(E) == 2) {
+      if (lm_half(true, a.T)) {
+        const int half_wgs = (p.parts / LMH_TASKS + XCDS - 1) / XCDS * XCDS * ((a.T + LMH_WT * TILE - 1) / (LMH_WT * TILE));
+        lm_head_half_kernel<E><<<half_wgs, LMH_WW * WAVE, lm_half_lds<E>(), st>>>((const E*)a.w, (const E*)xn, a.norm, a.T, a.H, a.V, a.scale, a.part, a.logits_out,
+                                                                                 a.rows, p.tasks, p.parts, live_word());
+        return;
+      }
+    }
     go(lm_head_wide_kernel<E, WT, 9, LM_WW>, LM_WW, wide_lds<E, 9, WT>());
   }
 }
@@ -556,7 +740,7 @@ bool configure_wide() {
                            (const void*)lm_head_wide_kernel<bf16_t, 2, 14, LM_PIECE_WW>, (const void*)lm_head_wide_kernel<float, 2, 14, LM_PIECE_WW>};
   for (const void* f : pieces)
     if (!opt_in(f, 128 * 1024)) return false;
-  return opt_in((const void*)lm_head_wide_kernel<bf16_t, WT, 9, LM_WW>, 128 * 1024) &&
+  return opt_in((const void*)lm_head_half_kernel<bf16_t>, (int)lm_half_lds<bf16_t>()) && opt_in((const void*)lm_head_wide_kernel<bf16_t, WT, 9, LM_WW>, 128 * 1024) &&
          opt_in((const void*)lm_head_wide_kernel<float, WT, 9, LM_WW>, 128 * 1024);
 }
 

@@ -1,0 +1,46 @@
+"""Steps at the token counts where the LM head takes half a task per wave (bf16, five, six and ten token tiles): the first and last
+count of each, one and two token groups, vocabularies whose last half task, task or group of four tasks is not full, logits that
+can be stored by four and that cannot, and row lists of undecided positions that fill fewer tiles than the step has."""
+import numpy as np
+import pytest
+
+import dinfer_inputs as di
+from harness import GpuRun, OracleRun, bars_for, compare_logits, compare_step, make_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("vocab", [300, 1090, 1102])      # 5, 18 and 18 tasks; half tasks of 12, 2 and 14 ids at the end
+@pytest.mark.parametrize("n_seq,block", [(3, 43), (5, 32), (7, 23), (3, 64), (17, 17), (5, 64)])
+def test_step_with_half_tasks_of_the_head(n_seq, block, vocab):
+    cfg = di.configs.scaled(di.model_preset("tiny"), hidden=320, n_heads=2, head_dim=64, n_experts=8, moe_inter=64, vocab=vocab, dtype="bf16",
+                            logit_scale=1.0)
+    wl = di.Workload("half_head", cfg, n_seq, block, 2, 30, precommit=True, threshold=0.9, seed_index=160 + n_seq)
+    cfg, w, inp = make_case(wl)
+    cap = int(inp.prefix_len.max()) + 2 * block + 16
+    ora = OracleRun(cfg, w, inp, cap)
+    T = n_seq * block
+    gpu = GpuRun(cfg, w, inp, T, cap)
+    bars = bars_for(cfg)
+    gpu.inject_prefix(ora.caches)
+    gpu.set_state(inp.block_tokens, inp.mask_bits, inp.prefix_len)
+    got = gpu.step(wl.threshold)
+    logits = gpu.logits(T).reshape(n_seq, block, vocab)
+    routing = gpu.routing().reshape(cfg.n_layers, n_seq, block, cfg.top_k)
+    for s in range(n_seq):
+        ref, _ = ora.step_following(s, inp.block_tokens[s], int(inp.mask_bits[s]), int(inp.prefix_len[s]), wl.threshold, 0, routing[:, s], bars)
+        compare_logits(ref["logits"], logits[s], bars)
+        compare_step(ref, got["tokens"][s], got["mask"][s], got["conf"][s], got["argmax"][s], got["n_committed"][s],
+                     inp.block_tokens[s], inp.mask_bits[s], wl.threshold, 0, bars, ref["logits"], logits[s])
+    # the same rows through a list: every sequence but the first keeps three undecided positions, the others' entries stay as they are
+    few = inp.mask_bits.copy()
+    few[1:] = [1 | 1 << (block // 2) | 1 << (block - 1)] * (n_seq - 1)
+    gpu.set_state(inp.block_tokens, few, inp.prefix_len)
+    gpu.conf.fill_(-7.0)
+    gpu.argmax.fill_(-7)
+    listed = gpu.step(gpu.binding.Decode(wl.threshold, 0, 0, 0.0, 1))
+    for s in range(n_seq):
+        on = np.array([(int(few[s]) >> i) & 1 for i in range(block)], dtype=bool)
+        assert np.array_equal(listed["conf"][s][on], got["conf"][s][on]) and np.array_equal(listed["argmax"][s][on], got["argmax"][s][on])
+        assert (listed["conf"][s][~on] == -7).all() and (listed["argmax"][s][~on] == -7).all()
+    gpu.close()
