@@ -748,8 +748,8 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
 // Dense projections over many token rows (more than 64).  A workgroup takes TASKS (eight, four or two) tasks and up to WT token
 // tiles; its TASKS * KH waves are KH teams, each team with its own share of the K range, its own LDS staging area for the
 // activation fragments (wide_stream.hpp) and one wave per task, which streams that task's weights once and keeps
-// the accumulators of 64 features x WT*32 rows.  The teams' sums are folded through LDS at the end and team 0
-// runs the epilogue (those of the split-K kernel, called for four accumulator registers at a time).  KH > 1 puts
+// the accumulators of 64 features x WT*32 rows.  The teams' sums are folded through LDS at the end, each
+// team taking a part of them through the epilogue (those of the split-K kernel, called for four accumulator registers at a time).  KH > 1 puts
 // several waves on every SIMD, so that one multiplies while another waits for LDS or memory, without asking the
 // launch for more workgroups than there are (task, token) tiles.
 // Grid (task groups, token groups): with a multiple of eight task groups the workgroups of one die always take the
@@ -764,7 +764,7 @@ static_assert(DENSE_TILE == TILE, "dense_plan.hpp counts in these units");
 
 template <typename E, int KID, int WT, int TASKS, int KH> constexpr size_t dense_lds() {
   const size_t stage = KH * wide_lds<E, KID, WT>();
-  const size_t fold = (size_t)(KH - 1) * TASKS * 2 * WT * 16 * WAVE * 4;
+  const size_t fold = KH > 1 ? (size_t)KH * TASKS * 32 * WAVE * 4 : 0;   // at most 32 registers a wave from either team
   return stage > fold ? stage : fold;
 }
 
@@ -795,136 +795,131 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
   wide_stream<E, WT, TASKS, KID>(
       W + (int64_t)task * task_stride_elems<E>(ksteps) + (int64_t)ks0 * (2 * WAVE * G), ks_team, B + (int64_t)ks0 * T * (NP * KS), row_of,
       (int64_t)T * (NP * KS), sb, nt, acc0, acc1, rank);
-  if constexpr (KH > 1) {
-    // fold: team h > 0 leaves its sums at red[h-1][rank][t*32 + tile*16 + v][lane], team 0 adds them up
-    float* red = reinterpret_cast<float*>(lds_raw);
-    __syncthreads();   // the staging areas are done with
-    if (team > 0) {
-      float* r = red + ((int64_t)((team - 1) * TASKS + rank) * (2 * WT * 16)) * WAVE + lane;
-#pragma unroll
-      for (int t = 0; t < WT; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          r[(t * 32 + v) * WAVE] = acc0[t][v];
-          r[(t * 32 + 16 + v) * WAVE] = acc1[t][v];
-        }
-    }
-    __syncthreads();
-    if (team > 0) return;
-    for (int h = 1; h < KH; ++h) {
-      const float* r = red + ((int64_t)((h - 1) * TASKS + rank) * (2 * WT * 16)) * WAVE + lane;
-#pragma unroll
-      for (int t = 0; t < WT; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          acc0[t][v] += r[(t * 32 + v) * WAVE];
-          acc1[t][v] += r[(t * 32 + 16 + v) * WAVE];
-        }
-    }
-  }
-  if (slot >= n_tasks) return;
-  // Epilogue in three sweeps over the (tile, register group) pairs, so that the loads of one sweep are all in flight
-  // together: what is addressed by the token, what is addressed by what those loads return, then the arithmetic.  Four
-  // tiles, whose accumulators leave no room for that, go one by one.
   constexpr int NG = 16 / PER;
-  if constexpr (WT < 4) {
-    typename Epi::template Pre<PER> pre[WT][NG];
+  // Epilogue of register groups G0 .. G0 + GN - 1 of token tile t, in three sweeps over them, so that the loads of one sweep are
+  // all in flight together: what is addressed by the token, what is addressed by what those loads return, then the arithmetic.
+  auto finish = [&](auto Tile, auto First, auto Count) {
+    constexpr int t = decltype(Tile)::value, G0 = decltype(First)::value, GN = decltype(Count)::value;
+    const int tok = tok0 + t * TILE + col;
+    const bool valid = t < nt && tok < T;
+    typename Epi::template Pre<PER> pre[GN];
 #pragma unroll
-    for (int t = 0; t < WT; ++t)
+    for (int g = 0; g < GN; ++g) pre[g] = epi.template prefetch<PER>(task, tok, valid, half, (G0 + g) * PER);
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const int tok = tok0 + t * TILE + col;
-        pre[t][g] = epi.template prefetch<PER>(task, tok, t < nt && tok < T, half, g * PER);
-      }
-#pragma unroll
-    for (int t = 0; t < WT; ++t)
-#pragma unroll
-      for (int g = 0; g < NG; ++g) epi.template prefetch2<PER>(pre[t][g], task, half, g * PER);
-    [[maybe_unused]] typename RouterStep<E>::frag rw[2][NG][2];   // [tile][eight features][experts from 0, from 32]
-    constexpr bool SHARES = Epi::ROWSUM && WT == 1;   // (with two tiles they do not fit the registers)
+    for (int g = 0; g < GN; ++g) epi.template prefetch2<PER>(pre[g], task, half, (G0 + g) * PER);
+    constexpr bool SHARES = Epi::ROWSUM && WT == 1;   // (with more tiles they do not fit the registers)
+    [[maybe_unused]] typename RouterStep<E>::frag rw[2][GN][2];   // [tile][eight features][experts from 0, from 32]
+    [[maybe_unused]] f32x16 r0[1], r1[1];
     bool routed = false;
     if constexpr (SHARES) {
+      zero_acc<1>(r0);
+      zero_acc<1>(r1);
       routed = epi.w_router != nullptr;
       if (routed) {
 #pragma unroll
         for (int f = 0; f < 2; ++f)
 #pragma unroll
-          for (int g = 0; g < NG; ++g)
+          for (int g = 0; g < GN; ++g)
 #pragma unroll
-            for (int et = 0; et < 2; ++et) rw[f][g][et] = RouterStep<E>::load(epi.w_router, task, f, g, et, lane);
+            for (int et = 0; et < 2; ++et) rw[f][g][et] = RouterStep<E>::load(epi.w_router, task, f, G0 + g, et, lane);
       }
     }
+    float ss = 0.f;
 #pragma unroll
-    for (int t = 0; t < WT; ++t) {
-      const int tok = tok0 + t * TILE + col;
-      const bool valid = t < nt && tok < T;
-      float ss = 0.f;
-      [[maybe_unused]] f32x16 r0[1], r1[1];
-      if constexpr (SHARES) {
-        zero_acc<1>(r0);
-        zero_acc<1>(r1);
+    for (int g = 0; g < GN; ++g) {
+      float a0[PER], a1[PER];
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        a0[i] = acc0[t][(G0 + g) * PER + i];
+        a1[i] = acc1[t][(G0 + g) * PER + i];
       }
+      ss += epi.template apply<PER>(pre[g], task, tok, valid, half, (G0 + g) * PER, a0, a1);
+      if constexpr (SHARES) {
+        if (routed) {
+          f32x4 m[2];
+          Epi::normed(pre[g], a0, a1, m);
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        float a0[PER], a1[PER];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-          a0[i] = acc0[t][g * PER + i];
-          a1[i] = acc1[t][g * PER + i];
-        }
-        ss += epi.template apply<PER>(pre[t][g], task, tok, valid, half, g * PER, a0, a1);
-        if constexpr (SHARES) {
-          if (routed) {
-            f32x4 m[2];
-            Epi::normed(pre[t][g], a0, a1, m);
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-              RouterStep<E>::add(r0[0], rw[f][g][0], m[f]);
-              RouterStep<E>::add(r1[0], rw[f][g][1], m[f]);
-            }
+          for (int f = 0; f < 2; ++f) {
+            RouterStep<E>::add(r0[0], rw[f][g][0], m[f]);
+            RouterStep<E>::add(r1[0], rw[f][g][1], m[f]);
           }
         }
       }
-      if constexpr (SHARES) {
-        if (routed && valid) {
+    }
+    if constexpr (SHARES) {
+      if (routed && valid) {
 #pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            epi.store_share(task, tok, acc_row(g * PER, half), f32x4{r0[0][4 * g], r0[0][4 * g + 1], r0[0][4 * g + 2], r0[0][4 * g + 3]});
-            epi.store_share(task, tok, TILE + acc_row(g * PER, half), f32x4{r1[0][4 * g], r1[0][4 * g + 1], r1[0][4 * g + 2], r1[0][4 * g + 3]});
-          }
+        for (int g = 0; g < 4; ++g) {
+          epi.store_share(task, tok, acc_row(4 * g, half), f32x4{r0[0][4 * g], r0[0][4 * g + 1], r0[0][4 * g + 2], r0[0][4 * g + 3]});
+          epi.store_share(task, tok, TILE + acc_row(4 * g, half), f32x4{r1[0][4 * g], r1[0][4 * g + 1], r1[0][4 * g + 2], r1[0][4 * g + 3]});
         }
       }
-      if (Epi::ROWSUM) {   // the wave holds the whole task: the row statistic is the sum over its two half-waves
-        ss += __shfl_xor(ss, 32, WAVE);
-        if (half == 0 && valid) epi.row_sum(task, tok, ss);
+    }
+    if (Epi::ROWSUM) {   // the wave holds the whole task: the row statistic is the sum over its two half-waves
+      static_assert(!Epi::ROWSUM || GN == NG, "all features of the task");
+      ss += __shfl_xor(ss, 32, WAVE);
+      if (half == 0 && valid) epi.row_sum(task, tok, ss);
+    }
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, NG> All;
+  if constexpr (KH > 1) {
+    // fold through red[sender][rank][register][lane].  The teams share the epilogue where it can be cut: each takes a token tile, or
+    // half of the registers of the only one, gets the other's sums of those and adds them to its own.  (Team 0 alone: QKV at 512 tokens
+    // 44.1 us, 42.9 with both; 384 41.5 and 40.8; 160 21.0 and 19.7; 256 26.1 and 25.7; asking for the epilogue's operands in front of the
+    // fold gains nothing more.)
+    static_assert(KH == 2 && WT <= 2, "two teams, a tile each");
+    constexpr bool CUT = WT == 2 || !Epi::ROWSUM;                  // (a row statistic needs all features of the tile)
+    constexpr int REGS = WT == 2 || !CUT ? 32 : 16, HG = NG / 2;   // registers a team sends
+    float* red = reinterpret_cast<float*>(lds_raw) + (int64_t)rank * REGS * WAVE + lane;
+    constexpr int SENDER = TASKS * REGS * WAVE;
+    auto send = [&](auto Tile, auto First) {
+      constexpr int t = decltype(Tile)::value, v = decltype(First)::value;
+      float* r = red + team * SENDER;
+#pragma unroll
+      for (int i = 0; i < REGS / 2; ++i) {
+        r[i * WAVE] = acc0[t][v + i];
+        r[(REGS / 2 + i) * WAVE] = acc1[t][v + i];
       }
+    };
+    auto receive = [&](auto Tile, auto First) {
+      constexpr int t = decltype(Tile)::value, v = decltype(First)::value;
+      const float* r = red + (1 - team) * SENDER;
+#pragma unroll
+      for (int i = 0; i < REGS / 2; ++i) {
+        acc0[t][v + i] += r[i * WAVE];
+        acc1[t][v + i] += r[(REGS / 2 + i) * WAVE];
+      }
+    };
+    typedef std::integral_constant<int, 8> I8;
+    typedef std::integral_constant<int, HG> IH;
+    __syncthreads();   // the staging areas are done with
+    if constexpr (!CUT) {
+      if (team > 0) send(I0{}, I0{});
+    } else if constexpr (WT == 2) {
+      if (team == 0) send(I1{}, I0{});
+      else send(I0{}, I0{});
+    } else {
+      if (team == 0) send(I0{}, I8{});
+      else send(I0{}, I0{});
+    }
+    __syncthreads();
+    if (slot >= n_tasks) return;
+    if (team == 0) {
+      receive(I0{}, I0{});
+      if constexpr (CUT && WT == 1) finish(I0{}, I0{}, IH{});
+      else finish(I0{}, I0{}, All{});
+    } else if constexpr (CUT && WT == 2) {
+      receive(I1{}, I0{});
+      finish(I1{}, I0{}, All{});
+    } else if constexpr (CUT) {
+      receive(I0{}, I8{});
+      finish(I0{}, IH{}, IH{});
     }
   } else {
-    static_for<WT>([&](auto I) {
-      constexpr int t = decltype(I)::value;
-      const int tok = tok0 + t * TILE + col;
-      const bool valid = t < nt && tok < T;
-      typename Epi::template Pre<PER> pre[NG];
-#pragma unroll
-      for (int g = 0; g < NG; ++g) pre[g] = epi.template prefetch<PER>(task, tok, valid, half, g * PER);
-#pragma unroll
-      for (int g = 0; g < NG; ++g) epi.template prefetch2<PER>(pre[g], task, half, g * PER);
-      float ss = 0.f;
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        float a0[PER], a1[PER];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-          a0[i] = acc0[t][g * PER + i];
-          a1[i] = acc1[t][g * PER + i];
-        }
-        ss += epi.template apply<PER>(pre[g], task, tok, valid, half, g * PER, a0, a1);
-      }
-      if (Epi::ROWSUM) {
-        ss += __shfl_xor(ss, 32, WAVE);
-        if (half == 0 && valid) epi.row_sum(task, tok, ss);
-      }
-    });
+    if (slot >= n_tasks) return;
+    static_for<WT>([&](auto I) { finish(I, I0{}, All{}); });   // (the accumulators of four tiles leave no room for all at once)
   }
   TRACE_MARK(KID, 7);
 }

@@ -52,7 +52,7 @@ inline LmPlan lm_plan(int V, int T) {
 inline bool lm_compact(bool bf16, int T) { return bf16 && T > LM_MID_T; }
 // bf16 rows of 129 to 192 and of 289 to 320 tokens: half a task per wave, so that five or six token tiles fit a workgroup's
 // registers and the vocabulary's weights go to one workgroup where four tiles at most (or two, beyond 256 tokens, where they are three)
-// would take two of them.  A compute unit takes in about 27 GB/s whatever the cache it comes from, and at 160 tokens
+// would take two of them.  While all compute units stream, each takes in about 27 GB/s, from its L2 as well, and at 160 tokens
 // two thirds of that was the second delivery.  LM head in us, four tiles and whole tasks -> this: 130 tokens 163 -> 137, 160 168 -> 142,
 // 192 172 -> 150, 288 219 -> 214 (the call is no faster), 320 223 -> 212, 352 230 -> 234, 384 238 -> 238, 480 286 -> 322, 512 288 -> 317 (with
 // eight tiles in a workgroup: every fragment read from LDS feeds one matrix instruction instead of two, and LDS is the bound); 320
