@@ -21,10 +21,13 @@ constexpr bool wide_smooth(int kid) { return kid == 24; }                       
 // dense projections' few MB, an expert's between its items); what is streamed once goes by non-temporal loads, which push
 // nothing else out of the caches.
 // The forms of four tiles and eight waves have one workgroup per compute unit and 128 accumulator registers per lane.  Where
-// the matrix cores are the bound (LM head, prompts), short chunks with one barrier each let four of them be under way in the
+// the matrix cores are the bound (LM head, prompts), short chunks with one barrier each let several of them be under way in the
 // registers that two of four k-steps took, and a third LDS buffer carries a wave over the barrier (see the ring below).  Bit
 // for bit the sums of the longer chunks; LM head at 512 / 160 tokens 366 -> 342 / 220 -> 195 us, gate/up + down at 4287
-// tokens 534 + 312 -> 526 + 308, no spills (2 registers before); with chunks of four k-steps and three buffers 539 + 318.  The
+// tokens 534 + 312 -> 526 + 308, no spills (2 registers before); with chunks of four k-steps and three buffers 539 + 318.
+// Three chunks of weights, not more: loads return in order, so the rows on their way to LDS wait for the weights asked for before
+// them (4287 tokens, QKV / gate/up / down 229.7 / 537.8 / 300.6 us with four, 226.9 / 531.3 / 296.0 with three, 228.7 / 535.5 / 300.3 with two,
+// 305.7 / 739 / 408 with six; LM head at 512 tokens 300.4 with four, 296.7 with three).  The
 // expert GEMMs of up to two items per expert on average (wide_expert) keep four k-steps and two buffers: they are bound by
 // their weights (12 sequences of 32, whole refresh: 569 us, 573 with short chunks).  Two workgroups of four waves per compute
 // unit stage the fragments twice: LM head 404.
@@ -33,9 +36,25 @@ template <int KID, int WT> struct WideShape {
   static constexpr bool AGAIN = wide_dense(KID);
 };
 template <int KID> struct WideShape4x8 {
-  static constexpr int KC = 2, PRE = 4, BD = 1, NB = 3;
+  static constexpr int KC = 2, PRE = 3, BD = 1, NB = 3;
   static constexpr bool AGAIN = wide_dense(KID) || wide_expert_shared(KID);
 };
+// Two token tiles, likewise in short chunks over three buffers (chunks of four k-steps over two -> this): dense projections, QKV at 512
+// tokens 43.1 -> 40.5 us, 384 41.3 -> 38.8; the forms of 33 to 64 tokens and of few rows per expert, with rows asked for three chunks ahead,
+// gate/up + down at 64 tokens 82.4 + 47.9 -> 81.4 + 46.4, LM head 118.8 -> 117.8, gate/up + down at 160 tokens 96.3 + 59.7 -> 95.1 + 58.7
+// (with four chunks of weights and rows two ahead 82.1 + 47.5, 118.2, 97.6 + 59.2).  Where a launch is a few workgroups, the
+// shorter queue shows: 32 experts of width 128 at 320 tokens, 36.6 -> 37.5 + 11.6.
+template <int KID, int P, int B> struct WideShape2 {
+  static constexpr int KC = 2, PRE = P, BD = B, NB = 3;
+  static constexpr bool AGAIN = wide_dense(KID);
+};
+template <> struct WideShape<12, 2> : WideShape2<12, 4, 2> {};
+template <> struct WideShape<13, 2> : WideShape2<13, 4, 2> {};
+template <> struct WideShape<14, 2> : WideShape2<14, 3, 3> {};
+template <> struct WideShape<17, 2> : WideShape2<17, 3, 3> {};
+template <> struct WideShape<19, 2> : WideShape2<19, 3, 3> {};
+template <> struct WideShape<20, 2> : WideShape2<20, 3, 3> {};
+template <> struct WideShape<21, 2> : WideShape2<21, 3, 3> {};
 template <> struct WideShape<9, 4> : WideShape4x8<9> {};
 template <> struct WideShape<12, 4> : WideShape4x8<12> {};
 template <> struct WideShape<13, 4> : WideShape4x8<13> {};
