@@ -1,7 +1,7 @@
 // The dense contractions of the step as weight-streaming MFMA kernels (core in gemm.hpp):
 //   QKV projection + rotary embedding + KV-page write, output projection + residual,
-//   router + top-k (+ token->expert permutation), routed-expert grouped GEMMs (gate/up + SwiGLU, down),
-//   LM head + streaming max / arg max / sum-exp.
+//   router + top-k, the fused down projection of the routed experts, iteration smoothing's contraction.
+// (The other expert GEMMs and the LM head: wide.hip.)
 // RMSNorm is never materialised.  Whoever produces a residual row also stores it multiplied by the gain of the
 // norm that follows, as MFMA-ready planes ("normalised-input planes", without the 1/rms factor); the consumers
 // feed those planes to the matrix cores and scale their accumulators by the row's 1/rms in the epilogue.
