@@ -40,10 +40,10 @@ template <int KID> struct WideShape4x8 {
   static constexpr bool AGAIN = wide_dense(KID) || wide_expert_shared(KID);
 };
 // Two token tiles, likewise in short chunks over three buffers (chunks of four k-steps over two -> this): dense projections, QKV at 512
-// tokens 43.1 -> 40.5 us, 384 41.3 -> 38.8; the forms of 33 to 64 tokens and of few rows per expert, with rows asked for three chunks ahead,
-// gate/up + down at 64 tokens 82.4 + 47.9 -> 81.4 + 46.4, LM head 118.8 -> 117.8, gate/up + down at 160 tokens 96.3 + 59.7 -> 95.1 + 58.7
-// (with four chunks of weights and rows two ahead 82.1 + 47.5, 118.2, 97.6 + 59.2).  Where a launch is a few workgroups, the
-// shorter queue shows: 32 experts of width 128 at 320 tokens, 36.6 -> 37.5 + 11.6.
+// tokens 43.1 -> 40.5 us, 384 41.3 -> 38.8; the forms of 33 to 64 tokens, with rows asked for three chunks ahead, gate/up + down at 64 tokens
+// 82.4 + 47.9 -> 81.4 + 46.4, LM head 118.8 -> 117.8 (with four chunks of weights and rows two ahead 82.1 + 47.5, 118.2).  The expert GEMMs of
+// few rows per expert, whose weights stream at the chip's rate, keep chunks of four: 64 experts of width 1024 at 160 tokens gain 1 us
+// (96.3 + 59.7 -> 95.1 + 58.7), but with two rounds of workgroups (width 1536, 290 tokens) gate/up goes from 139 to 149.
 template <int KID, int P, int B> struct WideShape2 {
   static constexpr int KC = 2, PRE = P, BD = B, NB = 3;
   static constexpr bool AGAIN = wide_dense(KID);
@@ -53,8 +53,6 @@ template <> struct WideShape<13, 2> : WideShape2<13, 4, 2> {};
 template <> struct WideShape<14, 2> : WideShape2<14, 3, 3> {};
 template <> struct WideShape<17, 2> : WideShape2<17, 3, 3> {};
 template <> struct WideShape<19, 2> : WideShape2<19, 3, 3> {};
-template <> struct WideShape<20, 2> : WideShape2<20, 3, 3> {};
-template <> struct WideShape<21, 2> : WideShape2<21, 3, 3> {};
 template <> struct WideShape<9, 4> : WideShape4x8<9> {};
 template <> struct WideShape<12, 4> : WideShape4x8<12> {};
 template <> struct WideShape<13, 4> : WideShape4x8<13> {};
