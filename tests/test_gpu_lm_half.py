@@ -13,7 +13,17 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("vocab", [300, 1090, 1102])      # 5, 18 and 18 tasks; half tasks of 12, 2 and 14 ids at the end
 @pytest.mark.parametrize("n_seq,block", [(3, 43), (5, 32), (7, 23), (3, 64), (17, 17), (5, 64)])
 def test_step_with_half_tasks_of_the_head(n_seq, block, vocab):
-    cfg = di.configs.scaled(di.model_preset("tiny"), hidden=320, n_heads=2, head_dim=64, n_experts=8, moe_inter=64, vocab=vocab, dtype="bf16",
+    check(n_seq, block, vocab, 320)
+
+
+@pytest.mark.parametrize("hidden", [64, 128, 192, 256])       # fewer chunks of K than the loop keeps under way, as many, one more
+@pytest.mark.parametrize("n_seq,block", [(5, 32), (5, 64)])
+def test_half_tasks_of_a_short_contraction(n_seq, block, hidden):
+    check(n_seq, block, 300, hidden)
+
+
+def check(n_seq, block, vocab, hidden):
+    cfg = di.configs.scaled(di.model_preset("tiny"), hidden=hidden, n_heads=2, head_dim=64, n_experts=8, moe_inter=64, vocab=vocab, dtype="bf16",
                             logit_scale=1.0)
     wl = di.Workload("half_head", cfg, n_seq, block, 2, 30, precommit=True, threshold=0.9, seed_index=160 + n_seq)
     cfg, w, inp = make_case(wl)
