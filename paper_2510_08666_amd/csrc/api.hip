@@ -306,7 +306,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
   // (the fused kernel needs its 64 wave shares, each within two experts; under the single-slice test switch the
   // down projection takes the unfused route, which has no sum across workgroups)
   const bool fused_down = T <= TILE && !single_slice();
-  const bool shares = router_shares(bf, D, H, T);
+  const int share_features = router_share_features(bf, D, H, T);
   int n_ssq_a = 1;
   const int64_t q_plane = (int64_t)c->max_tokens * D;
   for (int l = 0; l < f.n_layers; ++l) {
@@ -341,14 +341,14 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
       launch_attention(bf, aa, st);
     }
     OprojArgs oa{c->weights + lw.wo, ws + w.a, x, at<float>(c->weights, lw.ffn_gain), xn,
-                 at<float>(ws, w.ssq), T, D, H, tk_part, tickets, shares ? c->weights + lw.router : nullptr, at<float>(ws, w.shares)};
+                 at<float>(ws, w.ssq), T, D, H, tk_part, tickets, share_features ? c->weights + lw.router : nullptr, at<float>(ws, w.shares), share_features};
     {
       StageTimer tm(c, DINFER_STAGE_OPROJ, st);
       launch_oproj(bf, oa, st);
     }
     RouterArgs ra{c->weights + lw.router, xn, at<float>(ws, w.ssq), f.rms_eps, T, H, f.n_experts, f.top_k,
                   f.norm_topk, f.moe_inter, rinv_f, topk_idx, topk_w, at<int32_t>(ws, w.cnt), at<int32_t>(ws, w.off),
-                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), shares ? at<float>(ws, w.shares) : nullptr};
+                  at<int32_t>(ws, w.perm), at<int32_t>(ws, w.work), at<int32_t>(ws, w.hist), at<float>(ws, w.shares), share_features};
     {
       StageTimer tm(c, DINFER_STAGE_ROUTER, st);
       launch_router(bf, ra, st);
@@ -367,7 +367,7 @@ int forward(dinfer_ctx* c, const SeqSpan& span, const int32_t* d_tokens, const i
         // the gain of the norm that reads the new rows: the next layer's attention norm, or the final norm
         const float* next_gain = l + 1 < f.n_layers ? at<float>(c->weights, c->wm.layers[l + 1].attn_gain)
                                                     : at<float>(c->weights, c->wm.final_gain);
-        OprojArgs res{nullptr, nullptr, x, next_gain, xn, ssq_a, T, 0, H, tk_part, tickets, nullptr, nullptr};
+        OprojArgs res{nullptr, nullptr, x, next_gain, xn, ssq_a, T, 0, H, tk_part, tickets, nullptr, nullptr, 0};
         launch_expert_down_fused(bf, ea, res, st);
         n_ssq_a = H / 64;
       } else {

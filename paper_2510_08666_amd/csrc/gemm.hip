@@ -450,6 +450,106 @@ static void launch_ksplit(bool bf16, const E* W, int ksteps, const E* B, int T, 
 }
 
 // ------------------------------------------------------------------------------------------------
+// Output projection of up to 32 tokens in bfloat16 that leaves the router's shares of 128 features (router_share_features).  The
+// contraction of the router adds in chains of eight k-steps, two tasks, and a sum that runs on from the first task's into the second's
+// cannot be put together from two.  So the slices of two tasks meet in one workgroup, which runs the epilogue of both and then the
+// chain: the planes of the 128 features as operands in LDS, a wave per 32 experts.  Everything else, and every sum, as in the split-K kernel.
+// The operands of the epilogues are asked for with the slices, behind the hand-off (in front of the stream: 0.4 us more).  Bound by the
+// hand-off and by what one compute unit fetches behind it; with the events around the launches, hidden 2048 and 32 tokens: output projection
+// 13.2 us and selection 6.7; with a task's shares 11.2 and 6.7, in another order; without shares 10.1, and 13.3 for the router's contraction.
+// ------------------------------------------------------------------------------------------------
+template <typename E, int KW>
+__global__ __launch_bounds__(KW * WAVE) void oproj_pair_kernel(const E* __restrict__ W, int ksteps, const E* __restrict__ B, int T,
+                                                               float* __restrict__ part, int32_t* __restrict__ tickets, ResidualEpi<E> epi,
+                                                               const int32_t* __restrict__ live) {
+  if (step_is_dead(live)) return;
+  typedef typename ET<E>::vec vec;
+  constexpr int ROWS = 32, PER = 16 / KW, KS = ET<E>::KS, G = ET<E>::G, CHAIN = ROUTER_CHAIN;
+  static_assert(Planes<E>::N == 2 && KS == 16 && KW == 4 && CHAIN * KS == 128, "a wave's registers are half a k-step of each tile");
+  extern __shared__ __align__(16) float red[];   // [KW][ROWS][64], then the chain's operands
+  __shared__ int32_t s_flag;
+  __shared__ float s_ss[KW * 2 * TILE];
+  const int slice = blockIdx.x, n_slices = gridDim.x, task = blockIdx.y, pair = task >> 1;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int v0 = wave * PER;
+  const bool valid = col < T;
+  TRACE_MARK(2, 0);
+  float a0[1][PER], a1[1][PER];
+  {
+    f32x16 acc0[1], acc1[1];
+    zero_acc<1>(acc0);
+    zero_acc<1>(acc1);
+    const int per = (ksteps + n_slices * KW - 1) / (n_slices * KW);
+    const int ks0 = min(ksteps, (slice * KW + wave) * per), ks1 = min(ksteps, ks0 + per);
+    PlaneLoader<E, 1> ld;
+    ld.set(0, B, T, min(col, T - 1), half);
+    stream_task<E, 1, 8>(W + (int64_t)task * task_stride_elems<E>(ksteps), ks0, ks1, ld, acc0, acc1);
+    TRACE_MARK(2, 1);
+    spill_partials<1, ROWS>(red, wave, lane, acc0, acc1);
+    __syncthreads();
+    TRACE_MARK(2, 2);
+    fold_partials<1, KW, PER>(red, lane, v0, a0, a1);
+  }
+  // the slices of two token tiles of one task (sum_slices) are here those of one tile of two tasks
+  const buf_rsrc out = coherent_buffer(part);
+  const int64_t piece = (int64_t)pair * n_slices + slice;
+  coherent_store_n<PER>(out, slice_piece<2, PER>(piece, task & 1, 0, v0, lane), a0[0]);
+  coherent_store_n<PER>(out, slice_piece<2, PER>(piece, task & 1, 1, v0, lane), a1[0]);
+  if (!last_arrival(tickets + pair, 2 * n_slices, &s_flag)) return;
+  TRACE_MARK(2, 3);
+  vec rw[CHAIN];   // router weights of the wave's 32 experts
+  if (wave < 2) {
+#pragma unroll
+    for (int i = 0; i < CHAIN; ++i) rw[i] = load16<E>(epi.w_router + ((int64_t)(pair * CHAIN + i) * 2 + wave) * (WAVE * G) + lane * G);
+  }
+  typename ResidualEpi<E>::template Pre<PER> pre[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) pre[p] = epi.template prefetch<PER>(2 * pair + p, col, valid, half, v0);
+  float s0[2][PER], s1[2][PER];
+  sum_slices<2, PER>(part, pair, n_slices, lane, v0, s0, s1);
+  E* planes = reinterpret_cast<E*>(red);   // [k-step][plane][half-lane][token][8], an operand fragment each
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    epi.template apply<PER>(pre[p], 2 * pair + p, col, valid, half, v0, s0[p], s1[p]);
+    float ss = 0.f;                        // rounded as the split-K kernel's is, whichever square the compiler would add last
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const float n0 = pre[p].x0[i] + s0[p][i], n1 = pre[p].x1[i] + s1[p][i];
+      ss += __builtin_fmaf(n1, n1, n0 * n0);
+    }
+    const float s2 = ss + __shfl_xor(ss, 32, WAVE);
+    if (half == 0) s_ss[(wave * 2 + p) * TILE + col] = s2;
+    f32x4 m[2];
+    ResidualEpi<E>::normed(pre[p], s0[p], s1[p], m);
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {          // features 64 p + 32 f + 8 wave + 4 half ..
+      const int ks = 4 * p + 2 * f + (wave >> 1);
+      store_act4<E>(planes, (((ks * 2) * 2 + (wave & 1)) * TILE + col) * 8 + 4 * half, 2 * TILE * 8, m[f]);
+    }
+  }
+  __syncthreads();
+  if (wave < 2) {
+    f32x16 z;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) z[v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < CHAIN; ++i)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) mfma32(z, rw[i], *reinterpret_cast<const vec*>(planes + (((i * 2 + q) * 2 + half) * TILE + col) * 8));
+    if (valid) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        epi.store_share(pair, col, wave * TILE + acc_row(4 * g, half), f32x4{z[4 * g], z[4 * g + 1], z[4 * g + 2], z[4 * g + 3]});
+    }
+  } else if (wave == 2 && valid) {         // the tasks' row statistics: the KW waves in order
+    float s = 0.f;
+    for (int w = 0; w < KW; ++w) s += s_ss[(w * 2 + half) * TILE + col];
+    epi.row_sum(2 * pair + half, col, s);
+  }
+  TRACE_MARK(2, 4);
+}
+
+// ------------------------------------------------------------------------------------------------
 // QKV projection of up to 32 tokens with 32 features (half a task) per workgroup (rule and figures: half_applies): HALF_KW waves
 // cut the whole K range, every wave has its share in flight at once, and the sums meet in LDS.  Bound by memory latency like the
 // split-K kernel, whose two slices per task need a hand-off between workgroups (about 3 us) to get as many bytes under way.
@@ -540,6 +640,7 @@ template <typename E, class Epi> static bool configure_ksplit() {
          opt_in_lds((const void*)gemm_ksplit_kernel<E, 2, 4, Epi>) &&
          opt_in_lds((const void*)gemm_ksplit_kernel<E, 4, 4, Epi>);
 }
+static_assert(ksplit_lds<1, 4>() >= ROUTER_CHAIN * 2 * 2 * TILE * 16, "the chain's operands take the place of the partial sums");
 
 // ------------------------------------------------------------------------------------------------
 // Down projection of the routed experts fused with the weighted combine, the residual add and the statistics of
@@ -930,9 +1031,10 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
 // slices that ksplit_slices() now gives a launch of 96 tasks it takes 14.9 us.  For the output projection, a third
 // of the weights, split-K was ahead all along, 11.5 against 17.1.)
 static bool dense_applies(int T, int ksteps) { return T > 2 * TILE && ksteps % (WKC * DENSE_KH) == 0; }
-bool router_shares(bool bf16, int D, int H, int T) {
-  if (T <= 2 * TILE) return true;
-  return T <= ROUTER_SHARES_T && dense_applies(T, D / (bf16 ? 16 : 8)) && dense_form(bf16, H / 64, T).tiles == 1;
+int router_share_features(bool bf16, int D, int H, int T) {
+  if (T <= TILE && bf16) return single_slice() || H % (ROUTER_WAVES * ROUTER_CHAIN * 16) != 0 ? 0 : ROUTER_CHAIN * 16;
+  if (T <= 2 * TILE) return 64;
+  return T <= ROUTER_SHARES_T && dense_applies(T, D / (bf16 ? 16 : 8)) && dense_form(bf16, H / 64, T).tiles == 1 ? 64 : 0;
 }
 
 template <typename E, int WT, int TASKS, int KH, class Epi>
@@ -982,9 +1084,17 @@ template <typename E> static void launch_oproj_t(bool bf16, const OprojArgs& a, 
   ResidualEpi<E> epi{a.x, a.H, a.gain, (E*)a.xn, a.ssq, a.T, (const E*)a.w_router, a.shares};
   if (dense_applies(a.T, a.D / ET<E>::KS))
     launch_dense<E>((const E*)a.w, a.D / ET<E>::KS, (const E*)a.a, a.T, a.H / 64, epi, st);
-  else
+  else {
+    if constexpr (sizeof(E) == 2) {
+      if (a.w_router && a.share_features == 2 * 64) {
+        oproj_pair_kernel<E, 4><<<dim3(ksplit_slices(true, a.D, a.T, a.H / 64), a.H / 64), 4 * WAVE, ksplit_lds<1, 4>(), st>>>(
+            (const E*)a.w, a.D / ET<E>::KS, (const E*)a.a, a.T, a.part, a.tickets, epi, live_word());
+        return;
+      }
+    }
     launch_ksplit<E>(bf16, (const E*)a.w, a.D / ET<E>::KS, (const E*)a.a, a.T, a.D, a.H / 64, a.part, a.tickets,
                      epi, st);
+  }
 }
 // What the workgroups of the split-K launch stream: workgroup (slice, task) has index task * slices + slice and takes
 // the slice's share of the task's k-steps, 2 KB of packed weights each, so region i starts at i * region_bytes.
@@ -1149,21 +1259,24 @@ template <typename E> static bool configure_smooth() {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Router where the output projection leaves shares of the logits (router_shares): a wave per token, a lane per expert.  The logits are the sum of the shares that the
-// tasks of the output projection left (in task order), times the row's 1/rms, which comes from their sums of squares; then
-// softmax and the k selection rounds (ties to the lower expert id).  No sum between workgroups is left; up to 64 tokens the pairs
-// are sorted by whoever needs them (PairIds).  Bound by one dependent round trip and the rounds' cross-lane steps.  Until the output projection left
-// shares, one or two token tiles were contracted with the whole of K here by up to eight workgroups, with a hand-off between them, and
-// the last one selected and sorted: with events around the launch 14.3 -> 6.8 us at 32 tokens, 16.3 -> 6.8 at 64 (hidden 2048), the float32
-// test model 11.3 -> 6.7; the output projection takes 1.2 to 1.6 longer, the expert kernels up to 0.8.
+// Router where the output projection leaves shares of the logits (router_share_features): a wave per token, a lane per expert.  The
+// logits are the sum of the shares (in the order of their features), times the row's 1/rms, which comes from the sums of squares of the
+// output projection's tasks; then softmax and the k selection rounds (ties to the lower expert id).  No sum between workgroups is left; up to 64
+// tokens the pairs are sorted by whoever needs them (PairIds).  Bound by one dependent round trip and the rounds' cross-lane steps.
+// Until the output projection left shares, one or two token tiles were contracted with the whole of K here by up to eight workgroups, with
+// a hand-off between them, and the last one selected and sorted: with events around the launch 14.3 -> 6.8 us at 32 tokens, 16.3 -> 6.8
+// at 64 (hidden 2048), the float32 test model 11.3 -> 6.7; the output projection takes 1.2 to 1.6 longer (3.1 with shares of 128 features),
+// the expert kernels up to 0.8.
 // More tokens: as the router kernel below and the permutation take it 18.9 us at 160 tokens and 21.5 at 512, with this kernel 13.1 and 13.1
 // (the output projection +1.3 to 1.6), as long as the projection takes its forms of one token tile (1024 tokens at hidden 2048; beyond, shares
 // of 8 KB a token would cost more than the contraction).  Eight tokens a workgroup: with 32, one compute unit fetches 256 KB, 17.2 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int SELECT_WAVES = 4;
-// HIST (more than 64 tokens): the workgroup leaves its tokens' pairs per expert for the permutation.
-template <int WAVES, bool HIST>
-__global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float* __restrict__ shares, const float* __restrict__ ssq, int n_tasks,
+// HIST (more than 64 tokens): the workgroup leaves its tokens' pairs per expert for the permutation.  CHAINS (n_shares of 128 features
+// each): every sum in the order of the router kernel below, whose waves, workgroups and lanes these are: eight chains to a
+// workgroup, sums of squares in sixteen parts, four experts to a lane.
+template <int WAVES, bool HIST, bool CHAINS>
+__global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float* __restrict__ shares, const float* __restrict__ ssq, int n_tasks, int n_shares,
                                                                      float eps, int T, int H, int n_exp, int top_k, int norm_topk,
                                                                      float* __restrict__ rinv, int32_t* __restrict__ topk_idx,
                                                                      float* __restrict__ topk_w, int32_t* __restrict__ hist, const int32_t* __restrict__ live) {
@@ -1177,21 +1290,45 @@ __global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float
     __syncthreads();
   }
   if (tok < T) {                        // uniform over the wave
-    const float ss = lane < n_tasks ? ssq[(int64_t)lane * T + tok] : 0.f;
+    float ss[CHAINS ? 4 : 1];
+#pragma unroll
+    for (int i = 0; i < (CHAINS ? 4 : 1); ++i) {
+      const int j = CHAINS ? lane % 16 + 16 * i : lane;
+      ss[i] = j < n_tasks ? ssq[(int64_t)j * T + tok] : 0.f;
+    }
     float z = 0.f;
-    for (int j0 = 0; j0 < n_tasks; j0 += 32) {   // 32 independent loads at a time
+    for (int j0 = 0; j0 < n_shares; j0 += 32) {   // 32 independent loads at a time
       float v[32];
 #pragma unroll
-      for (int i = 0; i < 32; ++i) v[i] = shares[((int64_t)min(j0 + i, n_tasks - 1) * T + tok) * MAX_EXPERTS + lane];
+      for (int i = 0; i < 32; ++i) v[i] = shares[((int64_t)min(j0 + i, n_shares - 1) * T + tok) * MAX_EXPERTS + lane];
+      if constexpr (CHAINS) {                     // (at most 32, a multiple of eight)
 #pragma unroll
-      for (int i = 0; i < 32; ++i) z += j0 + i < n_tasks ? v[i] : 0.f;
+        for (int i = 0; i < 32; i += ROUTER_WAVES) {
+          float part = 0.f;
+#pragma unroll
+          for (int k = 0; k < ROUTER_WAVES; ++k) part += v[i + k];
+          z += i < n_shares ? part : 0.f;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) z += j0 + i < n_shares ? v[i] : 0.f;
+      }
     }
-    const float r = rsqrtf(wave_all_sum(ss) / H + eps);
+    float row_ss = 0.f;
+    if constexpr (CHAINS) {
+      const float part = ((ss[0] + ss[1]) + ss[2]) + ss[3];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) row_ss += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(part), q));
+    } else
+      row_ss = wave_all_sum(ss[0]);
+    const float r = rsqrtf(row_ss / H + eps);
     const bool on = lane < n_exp;
-    z = on ? z * r : -INFINITY;
+    z *= r;
+    asm("" : "+v"(z));                            // rounded here, not in a sum with the maximum
+    z = on ? z : -INFINITY;
     const float m = wave_all_max(z);
     const float ez = on ? expf(z - m) : 0.f;
-    const float inv = 1.f / wave_all_sum(ez);
+    const float inv = 1.f / (CHAINS ? wave_all_sum_by_fours(ez) : wave_all_sum(ez));
     // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its expert ids
     // would be no ids, and the expert kernels would index with them
     float p = on ? fmaxf(ez * inv, 0.f) : -1.f;
@@ -1387,22 +1524,25 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
   TRACE_MARK(3, 5);
 }
 
-template <typename E> static void launch_router_t(bool bf16, const RouterArgs& a, hipStream_t st) {
+template <typename E> static void launch_router_t(const RouterArgs& a, hipStream_t st) {
   auto select = [&](auto kernel, int waves) {
-    kernel<<<(a.T + waves - 1) / waves, waves * WAVE, 0, st>>>(a.shares, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv,
-                                                               a.topk_idx, a.topk_w, a.hist, live_word());
+    kernel<<<(a.T + waves - 1) / waves, waves * WAVE, 0, st>>>(a.shares, a.ssq, a.H / 64, a.H / a.share_features, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk,
+                                                               a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
   };
-  if (a.T <= 2 * TILE) return select(router_select_kernel<SELECT_WAVES, false>, SELECT_WAVES);
-  if (a.shares) select(router_select_kernel<HIST_TOKENS, true>, HIST_TOKENS);
+  const bool few = a.T <= 2 * TILE;   // the expert kernels sort the pairs
+  if (a.share_features == 2 * 64) select(router_select_kernel<SELECT_WAVES, false, true>, SELECT_WAVES);
+  else if (a.share_features && few) select(router_select_kernel<SELECT_WAVES, false, false>, SELECT_WAVES);
+  else if (a.share_features) select(router_select_kernel<HIST_TOKENS, true, false>, HIST_TOKENS);
   else
-    router_kernel<E, 8><<<(a.T + TILE - 1) / TILE, 8 * WAVE, ksplit_lds<1, 8>(), st>>>((const E*)a.w, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E,
-                                                                                       a.top_k, a.norm_topk, a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
-  launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.shares ? HIST_TOKENS : TILE, a.E, a.cnt, a.off, a.perm, a.work,
+    router_kernel<E, ROUTER_WAVES><<<(a.T + TILE - 1) / TILE, ROUTER_WAVES * WAVE, ksplit_lds<1, ROUTER_WAVES>(), st>>>(
+        (const E*)a.w, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
+  if (few) return;
+  launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.share_features ? HIST_TOKENS : TILE, a.E, a.cnt, a.off, a.perm, a.work,
                  expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
 }
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st) {
-  if (bf16) launch_router_t<bf16_t>(true, a, st);
-  else launch_router_t<float>(false, a, st);
+  if (bf16) launch_router_t<bf16_t>(a, st);
+  else launch_router_t<float>(a, st);
 }
 
 // Fused down projection: DOWN_SLICES workgroups of DOWN_KW waves share a task's long K.
@@ -1441,7 +1581,7 @@ bool configure_kernels() {
        opt_in_lds((const void*)expert_down_fused_kernel<bf16_t, 1, DOWN_KW, 4>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<float, 1, DOWN_KW, 8>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<float, 1, DOWN_KW, 4>);
-  ok = ok && opt_in_lds((const void*)router_kernel<bf16_t, 8>) && opt_in_lds((const void*)router_kernel<float, 8>);
+  ok = ok && opt_in_lds((const void*)router_kernel<bf16_t, ROUTER_WAVES>) && opt_in_lds((const void*)router_kernel<float, ROUTER_WAVES>);
   (void)hipGetLastError();
   return ok;
 }

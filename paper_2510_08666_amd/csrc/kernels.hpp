@@ -146,15 +146,21 @@ struct OprojArgs {
   int T, D, H;
   float* part;
   int32_t* tickets;
-  // where router_shares() says so: each 64-feature task also leaves its share of the router's logits (packed router
-  // weights, times the planes of its features, without 1/rms): shares[H/64][T][MAX_EXPERTS].  Null: not wanted
+  // with share_features: each task of 64 features, or pair of tasks, also leaves its share of the router's logits (packed router
+  // weights, times the planes of its features, without 1/rms): shares[H / share_features][T][MAX_EXPERTS]
   const void* w_router;
   float* shares;
+  int share_features;
 };
-// Whether the output projection leaves the router's shares: all its forms of up to 64 tokens, and of more tokens the
-// dense ones of one token tile, up to ROUTER_SHARES_T.
-constexpr int ROUTER_SHARES_T = 1024;
-bool router_shares(bool bf16, int D, int H, int T);
+// Features per share of the router's logits that the output projection leaves, or 0: a task's in its forms of up to 64 tokens
+// and, of more tokens up to ROUTER_SHARES_T, in the dense ones of one token tile.
+// Up to 32 tokens in bfloat16, two tasks': a chain of the contraction as the router itself sums it, with eight waves in every
+// workgroup of the K range and ROUTER_CHAIN k-steps in every wave (where hidden sizes divide so; others are left to it).  Sums in
+// another order differ by 1e-7, cached keys and values then round to other neighbours, and in 45 of 160 steps of
+// sixteen layers one row's eighth expert, a tie, was another one, with outputs up to 4e-2 apart (2-norm; the median 4e-4).
+// A float32 model rounds nothing to sixteen bits on the way: its outputs move by 1e-6.
+constexpr int ROUTER_SHARES_T = 1024, ROUTER_WAVES = 8, ROUTER_CHAIN = 8;
+int router_share_features(bool bf16, int D, int H, int T);
 void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st);
 
 // Iteration smoothing: delta[t] = softmax(logits[t]) . W_emb for the rows of positions that are still masked.
@@ -196,7 +202,8 @@ struct RouterArgs {
   int32_t* work;            // [WORK_ITEMS + 4 * expert_work_items at two tiles per group]: work list of the many-token
                             // expert GEMMs (T > 64 only), 16-byte aligned
   int32_t* hist;            // [ceil(T / HIST_TOKENS)][MAX_EXPERTS]: pairs per expert of every HIST_TOKENS or 32 tokens (T > 64 only)
-  const float* shares;      // OprojArgs::shares, or null
+  const float* shares;      // OprojArgs::shares
+  int share_features;       // OprojArgs::share_features
 };
 void launch_router(bool bf16, const RouterArgs& a, hipStream_t st);
 // hist: the router's histograms, see RouterArgs, one per hist_tokens tokens (a divisor of 32); round: expert_round_items.

@@ -33,6 +33,20 @@ __device__ inline float wave_all_max(float v) {
 __device__ inline float wave_all_sum(float v) {
   return __int_as_float(wave_all(__float_as_int(v), [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }));
 }
+// The sum as lanes with four consecutive values each would form it: those in order, then a butterfly over the sixteen sums.
+__device__ inline float wave_all_sum_by_fours(float v) {
+  float s = dpp_f<0x00>(v) + dpp_f<0x55>(v);      // quad_perm: the same lane of four to all of them
+  s += dpp_f<0xAA>(v);
+  s += dpp_f<0xFF>(v);
+  s += dpp_f<DPP_HALF_MIRROR>(s);
+  s += dpp_f<DPP_MIRROR>(s);
+  const int i = __float_as_int(s);
+  const auto r = __builtin_amdgcn_permlane16_swap(i, i, false, false);
+  s = __int_as_float(r[0]) + __int_as_float(r[1]);
+  const int k = __float_as_int(s);
+  const auto h = __builtin_amdgcn_permlane32_swap(k, k, false, false);
+  return __int_as_float(h[0]) + __int_as_float(h[1]);
+}
 // OR over the wave, as a scalar
 __device__ inline uint64_t wave_all_or(uint64_t v) {
   auto all = [](int x) { return (uint32_t)__builtin_amdgcn_readfirstlane(wave_all(x, [](int a, int b) { return a | b; })); };
