@@ -697,13 +697,15 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
     return is_tok && here ? before + __popc(toks & ((1u << col) - 1)) : -1;
   };
   // The long K: experts with rows in list order, ksteps_e k-steps each, in groups of PF k-steps; this wave's
-  // contiguous share [g0, g1).  A share is never longer than one expert's groups, so it meets at most two experts.  Shares of
-  // equal length rounded down or up: each workgroup then has the same number of groups within one, where shares all rounded
-  // up left the last ones short (50 experts: 57 of 64 waves had all of the 6.25 groups each; batch-1 layers of 21 to 58 experts 42.0 ->
-  // 40.1 us on average with events around the launch, the float32 test model 14.5 -> 12.3).
+  // contiguous share [g0, g1).  A share is never longer than one expert's groups, so it meets at most two experts.  Float32: shares of
+  // equal length rounded down or up, so that each workgroup has the same number of groups within one; shares all rounded up leave the
+  // last ones short (the float32 test model 14.5 against 12.3 us with events around the launch).  In bfloat16 they are all rounded up: the cut
+  // is the order of the sum, and in another order outputs of sixteen layers differ where an expert is a tie (router_share_features).
+  // It costs 42.0 against 40.1 us on average over batch-1 layers of 21 to 58 experts (50 experts: 57 of 64 waves have seven groups each).
+  constexpr bool EVEN = sizeof(E) == 4;
   const int ksteps_e = I / KS, groups_e = ksteps_e / PF, total = n_act * groups_e;
-  const int units = n_slices * KW, unit = slice * KW + wave;
-  const int g0 = total * unit / units, g1 = total * (unit + 1) / units;
+  const int units = n_slices * KW, unit = slice * KW + wave, per = (total + units - 1) / units;
+  const int g0 = EVEN ? total * unit / units : min(total, unit * per), g1 = EVEN ? total * (unit + 1) / units : min(total, g0 + per);
   const int i0 = g0 / groups_e;
   const int e_first = nth_bit(experts, min(i0, n_act - 1)), e_second = nth_bit(experts, min(i0 + 1, n_act - 1));
   const E* wbase = W + (int64_t)task * task_stride_elems<E>(ksteps_e) + lane * G;

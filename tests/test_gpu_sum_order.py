@@ -69,3 +69,26 @@ def router_case(dtype, n_seq, block, hidden, small, negative):
 def test_router_of_up_to_32_tokens_adds_along_its_chains(hidden, chain, n_seq, block):
     assert not router_case("bf16", n_seq, block, hidden, range(16, chain, 16), chain)
     assert router_case("bf16", n_seq, block, hidden, range(chain, 2 * chain, 16), 2 * chain)      # a chain of their own
+
+
+# 5 experts of 2048 are 80 groups of eight k-steps for 64 waves: two each in list order, the last 24 waves none
+@pytest.mark.parametrize("n_seq,block", [(1, 1), (1, 32)])
+def test_fused_down_projection_cuts_its_contraction_into_equal_shares(n_seq, block):
+    T, group = n_seq * block, 128
+    cfg, weights, inp = model("bf16", n_seq, block, 64, 5, 5, 2048)
+    layer = weights["layers"][0]
+    put("bf16", layer["w_gate"], (slice(None), slice(None), 0), 1.0)
+    put("bf16", layer["w_up"], (slice(None), slice(None), 0), 1.0)
+    # every element of the experts' intermediate rows is y = silu(1) / 5; BIG * y + 0.5 * y is BIG * y.  Features 0 and 1 of expert 0:
+    # the small terms in the group behind the large one's, which is the same wave's, and in the one after it, the next wave's
+    w = layer["w_down"]
+    for feature, small in ((0, 1), (1, 2)):
+        put("bf16", w, (0, feature, 0), BIG)
+        put("bf16", w, (0, feature, slice(small * group, (small + 1) * group, 16)), 0.5)
+        put("bf16", w, (0, feature, 4 * group), -BIG)
+    hidden, _ = step(cfg, weights, inp, T)
+    y = 1 / (1 + np.exp(-1)) / 5
+    ulp = np.spacing(np.float32(BIG * y))
+    assert (hidden[:, 0] == 1).all()
+    assert (np.abs(hidden[:, 1] - 1 - 8 * 0.5 * y) <= ulp).all()      # two sums with BIG * y in them, half an ulp each
+    assert (hidden[:, 2:] == 1).all()
