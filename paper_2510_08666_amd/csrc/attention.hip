@@ -295,7 +295,7 @@ __global__ __launch_bounds__(ATTN_WAVES * WAVE) void attention_kernel(const E* _
     TRACE_MARK(7, 4);
     return;
   }
-  // partial of this split: O [32 q][HD] (unnormalised), m [32], l [32], handed over with device-coherent stores
+  // partial of this split: O [32 q][HD] (unnormalised), (m, l) [32], handed over with device-coherent stores
   const int pair = qt * geom.n_heads + head;
   const buf_rsrc pr = coherent_buffer(part);
   const uint32_t pair_bytes = (uint32_t)pair * n_splits * TILE * (HD + 2) * 4, part_bytes = TILE * (HD + 2) * 4;
@@ -315,9 +315,10 @@ __global__ __launch_bounds__(ATTN_WAVES * WAVE) void attention_kernel(const E* _
   __shared__ int32_t s_flag;
   if (!last_arrival(tickets + pair, my_splits, &s_flag)) return;
   // Last to arrive: fold the partials in split order.  A thread takes ITEMS (query, 4 consecutive features) items.  The loads
-  // of N splits are under way together; they bypass the L2, so that one compute unit's fetch is the bound, and none is issued for a
-  // count of splits that is not there (sixteen clamped loads for every count -> this: two splits, 64 tokens behind 768 keys 19.0 ->
-  // 16.0 us for the launch, 12 sequences of 32 40.0 -> 36.8; eight splits of 4096 keys 22.4 -> 21.0).
+  // of N splits are under way together; they bypass the L2, so that one compute unit's fetch is the bound, and no more are issued than
+  // for two, four, eight or sixteen splits (sixteen clamped loads for every count -> this: two splits, 64 tokens behind 768 keys 19.0 ->
+  // 16.0 us for the launch, 12 sequences of 32 40.0 -> 36.8; eight splits of 4096 keys 22.4 -> 21.0).  Beyond eight there are two
+  // rounds, with all maxima in front of the first: every weight is relative to the row's own maximum then, and nothing is scaled twice.
   constexpr int ITEMS = TILE * HD / 4 / (ATTN_WAVES * WAVE);
   static_assert(ITEMS * ATTN_WAVES * WAVE == TILE * HD / 4, "whole items per thread");
   float Mx[ITEMS], Ls[ITEMS];
@@ -361,6 +362,18 @@ __global__ __launch_bounds__(ATTN_WAVES * WAVE) void attention_kernel(const E* _
       }
     }
   };
+  if (my_splits > 8) {
+    float m[ITEMS][ATTN_MAX_SPLITS][1];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+#pragma unroll
+      for (int p = 0; p < ATTN_MAX_SPLITS; ++p)
+        coherent_load_n<1>(pr, pair_bytes + min(p, my_splits - 1) * part_bytes + (TILE * HD + 2 * item_q(i)) * 4, m[i][p]);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+#pragma unroll
+      for (int p = 0; p < ATTN_MAX_SPLITS; ++p) Mx[i] = fmaxf(Mx[i], m[i][p][0]);
+  }
   if (my_splits == 2) fold(std::integral_constant<int, 2>{}, 0);
   else if (my_splits <= 4) fold(std::integral_constant<int, 4>{}, 0);
   else for (int p0 = 0; p0 < my_splits; p0 += 8) fold(std::integral_constant<int, 8>{}, p0);

@@ -21,12 +21,12 @@ def put(dtype, a, where, value):
     a[where] = np.float32(value) if dtype == "f32" else np.uint16(np.float32(value).view(np.uint32) >> 16)
 
 
-def model(dtype, n_seq, block, hidden, experts, top_k, width):
+def model(dtype, n_seq, block, hidden, experts, top_k, width, prefix=None, n_heads=1):
     """One layer whose attention adds nothing to rows of ones (1/rms is 1 but for epsilon); every other weight is zero."""
-    cfg = di.configs.scaled(di.model_preset("tiny"), n_layers=1, hidden=hidden, n_heads=1, head_dim=64, n_experts=experts, top_k=top_k,
+    cfg = di.configs.scaled(di.model_preset("tiny"), n_layers=1, hidden=hidden, n_heads=n_heads, head_dim=64, n_experts=experts, top_k=top_k,
                             moe_inter=width, vocab=64, dtype=dtype, logit_scale=1.0)
     weights = di.make_weights(cfg, di.BASE_SEED)
-    inp = di.make_workload_inputs(di.Workload("order", cfg, n_seq, block, 2, 10, threshold=2.0, seed_index=190))
+    inp = di.make_workload_inputs(di.Workload("order", cfg, n_seq, block, prefix or 2, prefix or 10, threshold=2.0, seed_index=190))
     for name, a in weights["layers"][0].items():
         if name.startswith("w"):
             zeros(a)
@@ -36,15 +36,18 @@ def model(dtype, n_seq, block, hidden, experts, top_k, width):
     return cfg, weights, inp
 
 
-def step(cfg, weights, inp, T):
-    gpu = GpuRun(cfg, weights, inp, T, 128)
+def step(cfg, weights, inp, T, max_pos=128, fill=None):
+    gpu = GpuRun(cfg, weights, inp, T, max_pos)
     gpu.ctx.kv.zero_()
+    if fill:
+        fill(gpu)
     gpu.set_state(inp.block_tokens, inp.mask_bits, inp.prefix_len)
     gpu.step(2.0)
     hidden = gpu.ctx.debug_get(0, (T, cfg.hidden), gpu.torch.float32).cpu().numpy()
     routing = gpu.routing(T)[0]
+    weights = gpu.ctx.debug_get(2, (cfg.n_layers, T, cfg.top_k), gpu.torch.float32).cpu().numpy()[0]
     gpu.close()
-    return hidden, routing
+    return hidden, routing, weights
 
 
 def router_case(dtype, n_seq, block, hidden, small, negative):
@@ -86,9 +89,32 @@ def test_fused_down_projection_cuts_its_contraction_into_equal_shares(n_seq, blo
         put("bf16", w, (0, feature, 0), BIG)
         put("bf16", w, (0, feature, slice(small * group, (small + 1) * group, 16)), 0.5)
         put("bf16", w, (0, feature, 4 * group), -BIG)
-    hidden, _ = step(cfg, weights, inp, T)
+    hidden, _, _ = step(cfg, weights, inp, T)
     y = 1 / (1 + np.exp(-1)) / 5
     ulp = np.spacing(np.float32(BIG * y))
     assert (hidden[:, 0] == 1).all()
     assert (np.abs(hidden[:, 1] - 1 - 8 * 0.5 * y) <= ulp).all()      # two sums with BIG * y in them, half an ulp each
     assert (hidden[:, 2:] == 1).all()
+
+
+# Sixteen splits of the keys, dealt by tiles of 32 to eight waves each: split p has keys 256 p on.  One key each in splits 0 to 7 has
+# all of the split's weight, and one in split 8 a little more.  Splits 0 and 1 have values that cancel: each multiplied by its weight
+# against the maximum of all, with a fused add, they leave the first one's rounding; added first and scaled then, nothing.
+def test_attention_folds_its_splits_against_one_maximum():
+    block, prefix, value = 5, 8187, 1.3984375 * 2.0 ** 20
+    cfg, weights, inp = model("bf16", 1, block, 64, 2, 1, 64, prefix)
+    layer = weights["layers"][0]
+    put("bf16", layer["wq"], (31, 0), 16.0)      # the pair of features that positions turn least
+    put("bf16", layer["wo"], (0, 0), 1.0)
+
+    def fill(gpu):
+        kv = gpu.torch.zeros((2, prefix, cfg.n_heads * cfg.head_dim), dtype=gpu.torch.float32, device=gpu.dev)
+        kv[0, 0:8 * 256:256, 31] = 100.0
+        kv[0, 8 * 256, 31] = 100.5
+        kv[1, 0, 0], kv[1, 256, 0] = value, -value
+        gpu.ctx.kv_write(0, gpu.page_table[0], 0, kv[0], kv[1])
+
+    hidden, _, _ = step(cfg, weights, inp, block, prefix + 2 * block, fill)
+    off = np.abs(hidden[:, 0] - 1)
+    assert off.any() and (off <= value * 2.0 ** -24).all()
+    assert (hidden[:, 1:] == 1).all()
