@@ -82,7 +82,7 @@ template <typename E> struct QkvEpi {
 
   template <int PER>
   __device__ float apply(const Pre<PER>& pre, int task, int tok, bool valid, int half, int v0, const float (&a0)[PER],
-                         const float (&a1)[PER]) const {
+                         const float (&a1)[PER], bool) const {
     if (!valid) return 0.f;
     const int hd = geom.head_dim;
     const int per_head = hd / 64;
@@ -219,9 +219,14 @@ template <typename E> struct ResidualEpi {
   }
   template <int PER> __device__ void prefetch2(Pre<PER>&, int, int, int) const {}
 
+  // Two squares, the first of which is rounded by itself.  Which of a tile pair's that is was the compiler's choice for each kernel, and
+  // another one is another 1/rms for every product that follows: so it is written down (first0; a constant for the callers).
+  __device__ static float two_squares(float n0, float n1, bool first0) {
+    return first0 ? __builtin_fmaf(n1, n1, n0 * n0) : __builtin_fmaf(n0, n0, n1 * n1);
+  }
   template <int PER>
   __device__ float apply(const Pre<PER>& pre, int task, int tok, bool valid, int half, int v0, const float (&a0)[PER],
-                         const float (&a1)[PER]) const {
+                         const float (&a1)[PER], bool first0) const {
     if (!valid) return 0.f;
     const int col = (2 * task) * TILE + acc_row(v0, half);
     float* p0 = x + (int64_t)tok * H + col;
@@ -234,7 +239,7 @@ template <typename E> struct ResidualEpi {
         n1[i] = pre.x1[i] + a1[i];
         m0[i] = n0[i] * pre.g0[i];
         m1[i] = n1[i] * pre.g1[i];
-        ss += n0[i] * n0[i] + n1[i] * n1[i];
+        ss += two_squares(n0[i], n1[i], first0);
       }
       *reinterpret_cast<f32x4*>(p0) = n0;
       *reinterpret_cast<f32x4*>(p0 + TILE) = n1;
@@ -249,7 +254,7 @@ template <typename E> struct ResidualEpi {
       p0[TILE + i] = n1;
       store_actk<E>(xn, T, tok, col + i, n0 * pre.g0[i]);
       store_actk<E>(xn, T, tok, col + TILE + i, n1 * pre.g1[i]);
-      ss += n0 * n0 + n1 * n1;
+      ss += two_squares(n0, n1, first0);
     }
     return ss;
   }
@@ -381,7 +386,7 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
 #pragma unroll
   for (int t = 0; t < TT; ++t) {
     const int tok = tok0 + t * TILE + (lane & 31);
-    ss[t] = epi.template apply<PER>(pre[t], task, tok, tok < T, half, v0, a0[t], a1[t]);
+    ss[t] = epi.template apply<PER>(pre[t], task, tok, tok < T, half, v0, a0[t], a1[t], TT == 1);
   }
   if constexpr (Epi::ROWSUM) {
     // the task's row statistic: both half-waves of a column, then the KW waves in order
@@ -510,13 +515,7 @@ __global__ __launch_bounds__(KW * WAVE) void oproj_pair_kernel(const E* __restri
   E* planes = reinterpret_cast<E*>(red);   // [k-step][plane][half-lane][token][8], an operand fragment each
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    epi.template apply<PER>(pre[p], 2 * pair + p, col, valid, half, v0, s0[p], s1[p]);
-    float ss = 0.f;                        // rounded as the split-K kernel's is, whichever square the compiler would add last
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const float n0 = pre[p].x0[i] + s0[p][i], n1 = pre[p].x1[i] + s1[p][i];
-      ss += __builtin_fmaf(n1, n1, n0 * n0);
-    }
+    const float ss = epi.template apply<PER>(pre[p], 2 * pair + p, col, valid, half, v0, s0[p], s1[p], true);
     const float s2 = ss + __shfl_xor(ss, 32, WAVE);
     if (half == 0) s_ss[(wave * 2 + p) * TILE + col] = s2;
     f32x4 m[2];
@@ -623,7 +622,7 @@ __global__ __launch_bounds__(HALF_KW * WAVE) __attribute__((amdgpu_waves_per_eu(
       a1[i] += b1[i];
     }
   }
-  epi.template apply<PER>(pre, task, tok, tok < T, half, 8 * sub + v0, a0, a1);
+  epi.template apply<PER>(pre, task, tok, tok < T, half, 8 * sub + v0, a0, a1, true);
   TRACE_MARK(1, 4);
 }
 
@@ -827,7 +826,7 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
       const int tok = t * TILE + col;
-      ss[t] = epi.template apply<PER>(pre[t], task, tok, tok < T, half, v0, s0[t], s1[t]);
+      ss[t] = epi.template apply<PER>(pre[t], task, tok, tok < T, half, v0, s0[t], s1[t], true);
     }
   }
   __syncthreads();   // the partials in `red` are consumed
@@ -936,7 +935,7 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
         a0[i] = acc0[t][(G0 + g) * PER + i];
         a1[i] = acc1[t][(G0 + g) * PER + i];
       }
-      ss += epi.template apply<PER>(pre[g], task, tok, valid, half, (G0 + g) * PER, a0, a1);
+      ss += epi.template apply<PER>(pre[g], task, tok, valid, half, (G0 + g) * PER, a0, a1, WT == 4 && G0 + g == 0);
       if constexpr (SHARES) {
         if (routed) {
           f32x4 m[2];

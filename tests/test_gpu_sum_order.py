@@ -118,3 +118,32 @@ def test_attention_folds_its_splits_against_one_maximum():
     off = np.abs(hidden[:, 0] - 1)
     assert off.any() and (off <= value * 2.0 ** -24).all()
     assert (hidden[:, 1:] == 1).all()
+
+
+# Rows whose squares have more than 24 bits, in features that a lane of the output projection holds together: which of a pair's two squares
+# is rounded by itself is the same in split-K (63 tokens) and in workgroups of one and of two token tiles (72, 522).
+@pytest.mark.parametrize("more", [8, 58])
+def test_row_statistics_round_alike_in_every_form(more):
+    got = []
+    for n_seq in (7, more):
+        cfg, weights, inp = model("bf16", n_seq, 9, 4096, 2, 2, 64, n_heads=2)
+        layer, on = weights["layers"][0], list(range(8)) + list(range(32, 40))
+        put("bf16", weights["emb"], ..., 0.0)
+        for f in on:
+            weights["emb"][:, f] = np.random.default_rng(f).standard_normal(cfg.vocab).astype(np.float32).view(np.uint32) >> 16
+        inp.block_tokens[...] = np.arange(n_seq * 9).reshape(n_seq, 9) % cfg.vocab
+        put("bf16", layer["wo"], (on, on), 1.3671875)
+        put("bf16", layer["w_router"], (0, 0), 0.5)
+
+        def fill(gpu):
+            values = np.random.default_rng(7).standard_normal((more, cfg.n_heads * cfg.head_dim))
+            for s in range(n_seq):
+                n = int(inp.prefix_len[s])
+                k = gpu.torch.zeros((n, values.shape[1]), dtype=gpu.torch.float32, device=gpu.dev)
+                v = gpu.torch.from_numpy(values[s]).to(gpu.torch.bfloat16).float().to(gpu.dev).expand(n, -1).contiguous()
+                gpu.ctx.kv_write(0, gpu.page_table[s], 0, k, v)
+
+        got.append([a[:63] for a in step(cfg, weights, inp, 9 * n_seq, fill=fill)])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+    assert len(np.unique(got[0][2])) > 63
