@@ -146,34 +146,15 @@ template <typename E> struct QkvEpi {
   __device__ void row_sum(int, int, float) const {}
 };
 
-// Eight features' contribution to the router's logits, straight from the registers of an epilogue: a lane holds four of them
-// for its token, rows 8 * step + 4 * half .. +3 of weight tile `tile` of the 64-feature task, which is the B operand of a
-// matrix instruction of depth eight as it stands (bf16: both planes of the values).  Result as for mfma32: experts along the rows.
-template <typename E> struct RouterStep;
-template <> struct RouterStep<bf16_t> {
-  typedef bf16x4 frag;
+// Eight features' contribution to the router's logits in float32, straight from the registers of an epilogue: a lane holds four of
+// them for its token, rows 8 * step + 4 * half .. +3 of weight tile `tile` of the 64-feature task, which is the B operand of
+// two matrix instructions as it stands.  Result as for mfma32: experts along the rows.
+struct RouterStep {
   // packed router weights: the lane's expert (of 32 from 32 * et on), the four features above
-  __device__ static frag load(const bf16_t* w, int task, int tile, int step, int et, int lane) {
-    return *reinterpret_cast<const frag*>(w + (((int64_t)task * 4 + tile * 2 + (step >> 1)) * 2 + et) * (WAVE * 8) + ((step & 1) * TILE + (lane & 31)) * 8 + (lane >> 5) * 4);
+  __device__ static f32x4 load(const float* w, int task, int tile, int step, int et, int lane) {
+    return *reinterpret_cast<const f32x4*>(w + (((int64_t)task * 8 + tile * 4 + step) * 2 + et) * (WAVE * 4) + lane * 4);
   }
-  __device__ static void add(f32x16& acc, const frag& a, const f32x4& v) {
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
-    bf16x4 hi, lo;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      hi[i] = (bf16_t)v[i];
-      lo[i] = (bf16_t)(v[i] - (float)hi[i]);
-    }
-    acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, hi), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, lo), acc, 0, 0, 0);
-  }
-};
-template <> struct RouterStep<float> {
-  typedef f32x4 frag;
-  __device__ static frag load(const float* w, int task, int tile, int step, int et, int lane) {
-    return *reinterpret_cast<const frag*>(w + (((int64_t)task * 8 + tile * 4 + step) * 2 + et) * (WAVE * 4) + lane * 4);
-  }
-  __device__ static void add(f32x16& acc, const frag& a, const f32x4& v) { mfma32(acc, a, v); }
+  __device__ static void add(f32x16& acc, const f32x4& a, const f32x4& v) { mfma32(acc, a, v); }
 };
 
 // x += result; the new row also goes out as normalised-input planes for the expert half (times its norm's gain),
@@ -361,13 +342,16 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
   TRACE_MARK(KID, 1);
 #pragma unroll
   for (int t = 0; t < TT; ++t) epi.template prefetch2<PER>(pre[t], task, half, v0);
-  [[maybe_unused]] typename RouterStep<E>::frag rw[2][2];   // [tile][experts from 0, from 32]
-  if constexpr (Epi::ROWSUM) {
+  // Shares of the router's logits: of up to 64 tokens, in float32 a wave's eight features of either tile straight from its registers; in
+  // bfloat16, two token tiles (one: oproj_pair_kernel), a chain of the task's four k-steps on the planes as they are stored.
+  constexpr bool STEPS = Epi::ROWSUM && sizeof(E) == 4 && TT <= 2, CHAIN = Epi::ROWSUM && sizeof(E) == 2 && TT == 2;
+  [[maybe_unused]] f32x4 rw[2][2];   // [tile][experts from 0, from 32]
+  if constexpr (STEPS) {
     if (epi.w_router) {
 #pragma unroll
       for (int f = 0; f < 2; ++f)
 #pragma unroll
-        for (int et = 0; et < 2; ++et) rw[f][et] = RouterStep<E>::load(epi.w_router, task, f, wave, et, lane);
+        for (int et = 0; et < 2; ++et) rw[f][et] = RouterStep::load(epi.w_router, task, f, wave, et, lane);
     }
   }
   spill_partials<TT, ROWS>(red, wave, lane, acc0, acc1);
@@ -382,6 +366,13 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
     TRACE_MARK(KID, 3);
     sum_slices<TT, PER>(part, unit, n_slices, lane, v0, a0, a1);
   }
+  [[maybe_unused]] typename ET<E>::vec rc[4];   // the chain's router weights: experts of half wave & 1, for token tile wave / 2
+  if constexpr (CHAIN) {
+    if (epi.w_router) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rc[i] = load16<E>(epi.w_router + (((int64_t)task * 4 + i) * 2 + (wave & 1)) * (WAVE * ET<E>::G) + lane * ET<E>::G);
+    }
+  }
   float ss[TT];
 #pragma unroll
   for (int t = 0; t < TT; ++t) {
@@ -390,25 +381,42 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
   }
   if constexpr (Epi::ROWSUM) {
     // the task's row statistic: both half-waves of a column, then the KW waves in order
-    const bool routed = epi.w_router != nullptr;   // with it the task's share of the router's logits, summed over the waves likewise
-    if (routed) {
-      // wave w holds features 8w .. 8w + 7 of both tiles, eight of a matrix instruction's depth each
-      static_assert(PER == 4, "RouterStep");
-      f32x16 r0[TT], r1[TT];
-      zero_acc<TT>(r0);
-      zero_acc<TT>(r1);
+    const bool routed = (STEPS || CHAIN) && epi.w_router != nullptr;
+    if constexpr (STEPS) {
+      if (routed) {
+        // wave w holds features 8w .. 8w + 7 of both tiles, the depth of two instructions each; summed over the waves like the statistic
+        static_assert(PER == 4, "RouterStep");
+        f32x16 r0[TT], r1[TT];
+        zero_acc<TT>(r0);
+        zero_acc<TT>(r1);
 #pragma unroll
-      for (int t = 0; t < TT; ++t) {
-        f32x4 m[2];
-        Epi::normed(pre[t], a0[t], a1[t], m);
+        for (int t = 0; t < TT; ++t) {
+          f32x4 m[2];
+          Epi::normed(pre[t], a0[t], a1[t], m);
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-          RouterStep<E>::add(r0[t], rw[f][0], m[f]);
-          RouterStep<E>::add(r1[t], rw[f][1], m[f]);
+          for (int f = 0; f < 2; ++f) {
+            RouterStep::add(r0[t], rw[f][0], m[f]);
+            RouterStep::add(r1[t], rw[f][1], m[f]);
+          }
+        }
+        __syncthreads();   // the partials in `red` are consumed
+        spill_partials<TT, ROWS>(red, wave, lane, r0, r1);
+      }
+    }
+    [[maybe_unused]] E* planes = reinterpret_cast<E*>(red);   // [token tile][k-step][plane][half-lane][token][8], an operand fragment each
+    if constexpr (CHAIN) {
+      if (routed) {
+        static_assert(Planes<E>::N == 2 && ET<E>::KS == 16 && KW == 4, "a wave's registers are half a k-step of each tile");
+        __syncthreads();   // the partials in `red` are consumed
+#pragma unroll
+        for (int t = 0; t < TT; ++t) {
+          f32x4 m[2];
+          Epi::normed(pre[t], a0[t], a1[t], m);
+#pragma unroll
+          for (int f = 0; f < 2; ++f)   // features 32 f + 8 wave + 4 half ..
+            store_act4<E>(planes, ((((t * 4 + 2 * f + (wave >> 1)) * 2) * 2 + (wave & 1)) * TILE + (lane & 31)) * 8 + 4 * half, 2 * TILE * 8, m[f]);
         }
       }
-      __syncthreads();   // the partials in `red` are consumed
-      spill_partials<TT, ROWS>(red, wave, lane, r0, r1);
     }
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
@@ -416,15 +424,36 @@ __global__ __launch_bounds__(KW * WAVE) void gemm_ksplit_kernel(const E* __restr
       if (half == 0) s_ss[(wave * TT + t) * TILE + lane] = s2;
     }
     __syncthreads();
-    if (routed) {
-      float b0[TT][PER], b1[TT][PER];
-      fold_partials<TT, KW, PER>(red, lane, v0, b0, b1);
+    if constexpr (STEPS) {
+      if (routed) {
+        float b0[TT][PER], b1[TT][PER];
+        fold_partials<TT, KW, PER>(red, lane, v0, b0, b1);
 #pragma unroll
-      for (int t = 0; t < TT; ++t) {
-        const int tok = tok0 + t * TILE + (lane & 31);
+        for (int t = 0; t < TT; ++t) {
+          const int tok = tok0 + t * TILE + (lane & 31);
+          if (tok < T) {
+            epi.store_share(task, tok, acc_row(v0, half), f32x4{b0[t][0], b0[t][1], b0[t][2], b0[t][3]});
+            epi.store_share(task, tok, TILE + acc_row(v0, half), f32x4{b1[t][0], b1[t][1], b1[t][2], b1[t][3]});
+          }
+        }
+      }
+    }
+    if constexpr (CHAIN) {
+      if (routed) {
+        typedef typename ET<E>::vec vec;
+        f32x16 z;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) z[v] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            mfma32(z, rc[i], *reinterpret_cast<const vec*>(planes + (((((wave >> 1) * 4 + i) * 2 + q) * 2 + half) * TILE + (lane & 31)) * 8));
+        const int tok = tok0 + (wave >> 1) * TILE + (lane & 31);
         if (tok < T) {
-          epi.store_share(task, tok, acc_row(v0, half), f32x4{b0[t][0], b0[t][1], b0[t][2], b0[t][3]});
-          epi.store_share(task, tok, TILE + acc_row(v0, half), f32x4{b1[t][0], b1[t][1], b1[t][2], b1[t][3]});
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            epi.store_share(task, tok, (wave & 1) * TILE + acc_row(4 * g, half), f32x4{z[4 * g], z[4 * g + 1], z[4 * g + 2], z[4 * g + 3]});
         }
       }
     }
@@ -909,8 +938,8 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
     for (int g = 0; g < GN; ++g) pre[g] = epi.template prefetch<PER>(task, tok, valid, half, (G0 + g) * PER);
 #pragma unroll
     for (int g = 0; g < GN; ++g) epi.template prefetch2<PER>(pre[g], task, half, (G0 + g) * PER);
-    constexpr bool SHARES = Epi::ROWSUM && WT == 1;   // (with more tiles they do not fit the registers)
-    [[maybe_unused]] typename RouterStep<E>::frag rw[2][GN][2];   // [tile][eight features][experts from 0, from 32]
+    constexpr bool SHARES = Epi::ROWSUM && WT == 1 && sizeof(E) == 4;   // (with more tiles they do not fit the registers)
+    [[maybe_unused]] f32x4 rw[2][GN][2];   // [tile][eight features][experts from 0, from 32]
     [[maybe_unused]] f32x16 r0[1], r1[1];
     bool routed = false;
     if constexpr (SHARES) {
@@ -923,7 +952,7 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
 #pragma unroll
           for (int g = 0; g < GN; ++g)
 #pragma unroll
-            for (int et = 0; et < 2; ++et) rw[f][g][et] = RouterStep<E>::load(epi.w_router, task, f, G0 + g, et, lane);
+            for (int et = 0; et < 2; ++et) rw[f][g][et] = RouterStep::load(epi.w_router, task, f, G0 + g, et, lane);
       }
     }
     float ss = 0.f;
@@ -942,8 +971,8 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
           Epi::normed(pre[g], a0, a1, m);
 #pragma unroll
           for (int f = 0; f < 2; ++f) {
-            RouterStep<E>::add(r0[0], rw[f][g][0], m[f]);
-            RouterStep<E>::add(r1[0], rw[f][g][1], m[f]);
+            RouterStep::add(r0[0], rw[f][g][0], m[f]);
+            RouterStep::add(r1[0], rw[f][g][1], m[f]);
           }
         }
       }
@@ -1033,9 +1062,12 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
 // of the weights, split-K was ahead all along, 11.5 against 17.1.)
 static bool dense_applies(int T, int ksteps) { return T > 2 * TILE && ksteps % (WKC * DENSE_KH) == 0; }
 int router_share_features(bool bf16, int D, int H, int T) {
-  if (T <= TILE && bf16) return single_slice() || H % (ROUTER_WAVES * ROUTER_CHAIN * 16) != 0 ? 0 : ROUTER_CHAIN * 16;
+  if (bf16) {
+    const int features = T <= TILE ? ROUTER_CHAIN * 16 : T <= 2 * TILE ? ROUTER_CHAIN * 8 : 0;
+    return !single_slice() && features && H % (ROUTER_WAVES * features) == 0 ? features : 0;
+  }
   if (T <= 2 * TILE) return 64;
-  return T <= ROUTER_SHARES_T && dense_applies(T, D / (bf16 ? 16 : 8)) && dense_form(bf16, H / 64, T).tiles == 1 ? 64 : 0;
+  return T <= ROUTER_SHARES_T && dense_applies(T, D / 8) && dense_form(false, H / 64, T).tiles == 1 ? 64 : 0;
 }
 
 template <typename E, int WT, int TASKS, int KH, class Epi>
@@ -1273,10 +1305,10 @@ template <typename E> static bool configure_smooth() {
 // of 8 KB a token would cost more than the contraction).  Eight tokens a workgroup: with 32, one compute unit fetches 256 KB, 17.2 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int SELECT_WAVES = 4;
-// HIST (more than 64 tokens): the workgroup leaves its tokens' pairs per expert for the permutation.  CHAINS (n_shares of 128 features
-// each): every sum in the order of the router kernel below, whose waves, workgroups and lanes these are: eight chains to a
-// workgroup, sums of squares in sixteen parts, four experts to a lane.
-template <int WAVES, bool HIST, bool CHAINS>
+// HIST (more than 64 tokens): the workgroup leaves its tokens' pairs per expert for the permutation.  PARTS (bfloat16, shares that are
+// chains): every sum in the order of the router kernel below, whose waves, workgroups and lanes these are: eight chains to a
+// workgroup, sums of squares in PARTS parts (16, or 8 with two token tiles), 64 / PARTS experts to a lane.  0: no order kept.
+template <int WAVES, bool HIST, int PARTS>
 __global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float* __restrict__ shares, const float* __restrict__ ssq, int n_tasks, int n_shares,
                                                                      float eps, int T, int H, int n_exp, int top_k, int norm_topk,
                                                                      float* __restrict__ rinv, int32_t* __restrict__ topk_idx,
@@ -1291,10 +1323,11 @@ __global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float
     __syncthreads();
   }
   if (tok < T) {                        // uniform over the wave
-    float ss[CHAINS ? 4 : 1];
+    constexpr int SS = PARTS ? WAVE / PARTS : 1;
+    float ss[SS];
 #pragma unroll
-    for (int i = 0; i < (CHAINS ? 4 : 1); ++i) {
-      const int j = CHAINS ? lane % 16 + 16 * i : lane;
+    for (int i = 0; i < SS; ++i) {
+      const int j = PARTS ? lane % PARTS + PARTS * i : lane;
       ss[i] = j < n_tasks ? ssq[(int64_t)j * T + tok] : 0.f;
     }
     float z = 0.f;
@@ -1302,13 +1335,13 @@ __global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float
       float v[32];
 #pragma unroll
       for (int i = 0; i < 32; ++i) v[i] = shares[((int64_t)min(j0 + i, n_shares - 1) * T + tok) * MAX_EXPERTS + lane];
-      if constexpr (CHAINS) {                     // (at most 32, a multiple of eight)
+      if constexpr (PARTS) {                      // (a multiple of eight)
 #pragma unroll
         for (int i = 0; i < 32; i += ROUTER_WAVES) {
           float part = 0.f;
 #pragma unroll
           for (int k = 0; k < ROUTER_WAVES; ++k) part += v[i + k];
-          z += i < n_shares ? part : 0.f;
+          z += j0 + i < n_shares ? part : 0.f;
         }
       } else {
 #pragma unroll
@@ -1316,10 +1349,12 @@ __global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float
       }
     }
     float row_ss = 0.f;
-    if constexpr (CHAINS) {
-      const float part = ((ss[0] + ss[1]) + ss[2]) + ss[3];
+    if constexpr (PARTS) {
+      float part = ss[0];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) row_ss += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(part), q));
+      for (int i = 1; i < SS; ++i) part += ss[i];
+#pragma unroll
+      for (int q = 0; q < PARTS; ++q) row_ss += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(part), q));
     } else
       row_ss = wave_all_sum(ss[0]);
     const float r = rsqrtf(row_ss / H + eps);
@@ -1329,7 +1364,11 @@ __global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float
     z = on ? z : -INFINITY;
     const float m = wave_all_max(z);
     const float ez = on ? expf(z - m) : 0.f;
-    const float inv = 1.f / (CHAINS ? wave_all_sum_by_fours(ez) : wave_all_sum(ez));
+    float sum;
+    if constexpr (PARTS == 16) sum = wave_all_sum_by_fours(ez);
+    else if constexpr (PARTS == 8) sum = wave_all_sum_by_eights(ez);
+    else sum = wave_all_sum(ez);
+    const float inv = 1.f / sum;
     // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its expert ids
     // would be no ids, and the expert kernels would index with them
     float p = on ? fmaxf(ez * inv, 0.f) : -1.f;
@@ -1361,37 +1400,38 @@ __global__ __launch_bounds__(WAVES * WAVE) void router_select_kernel(const float
 // ------------------------------------------------------------------------------------------------
 // Router without shares.  The single weight task holds experts 0-31 (tile 0) and 32-63 (tile 1); a workgroup takes a token
 // tile, its KW waves the K range, and the partial tiles meet in LDS.  It turns the sums into logits[token][expert] (times the
-// row's 1/rms, which it derives from the per-task sums of squares the output projection left), then groups of 16 lanes take one
+// row's 1/rms, which it derives from the per-task sums of squares the output projection left), then groups of 16 or 8 lanes take one
 // token each through softmax and the k selection rounds (ties to the lower expert id).
 // ------------------------------------------------------------------------------------------------
-// A row of 16 lanes forms a group; every lane ends with the same bits (each step combines the same two values on both sides).
-__device__ inline float group_max(float v) {
+// L (8 or 16) lanes form a group; every lane ends with the same bits (each step combines the same two values on both sides).
+template <int L> __device__ inline float group_max(float v) {
   v = fmaxf(v, dpp_f<DPP_SWAP1>(v));
   v = fmaxf(v, dpp_f<DPP_SWAP2>(v));
   v = fmaxf(v, dpp_f<DPP_HALF_MIRROR>(v));
-  return fmaxf(v, dpp_f<DPP_MIRROR>(v));
+  return L == 16 ? fmaxf(v, dpp_f<DPP_MIRROR>(v)) : v;
 }
-__device__ inline float group_sum(float v) {
+template <int L> __device__ inline float group_sum(float v) {
   v += dpp_f<DPP_SWAP1>(v);
   v += dpp_f<DPP_SWAP2>(v);
   v += dpp_f<DPP_HALF_MIRROR>(v);
-  return v + dpp_f<DPP_MIRROR>(v);
+  return L == 16 ? v + dpp_f<DPP_MIRROR>(v) : v;
 }
-__device__ inline int group_min(int v) {
+template <int L> __device__ inline int group_min(int v) {
   v = min(v, dpp_i<DPP_SWAP1>(v));
   v = min(v, dpp_i<DPP_SWAP2>(v));
   v = min(v, dpp_i<DPP_HALF_MIRROR>(v));
-  return min(v, dpp_i<DPP_MIRROR>(v));
+  return L == 16 ? min(v, dpp_i<DPP_MIRROR>(v)) : v;
 }
 // Largest value of the group and the lowest id that holds it: the largest value first, then the lowest id among
 // the lanes whose own best equals it (two plain butterflies instead of one with a compound comparison).
-__device__ inline void group_argmax(float& bv, int& bi) {
-  const float mx = group_max(bv);
-  bi = group_min(bv == mx ? bi : 0x7fffffff);
+template <int L> __device__ inline void group_argmax(float& bv, int& bi) {
+  const float mx = group_max<L>(bv);
+  bi = group_min<L>(bv == mx ? bi : 0x7fffffff);
   bv = mx;
 }
 
-template <typename E, int KW>
+// TT: one token tile per workgroup, or two (33 to 64 tokens).
+template <typename E, int TT, int KW>
 __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__ W, const E* __restrict__ xn,
                                                             const float* __restrict__ ssq, int n_ssq,
                                                             float eps, int T, int H, int n_exp, int top_k, int norm_topk,
@@ -1399,7 +1439,7 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
                                                             float* __restrict__ topk_w, int32_t* __restrict__ hist, const int32_t* __restrict__ live) {
   if (step_is_dead(live)) return;
   extern __shared__ float red[];   // [KW][2*TT*16][64] partials
-  constexpr int TT = 1, ROWS = 2 * TT * 16, NTOK = TT * TILE, NTHREADS = KW * WAVE, PER = 16 / KW;
+  constexpr int ROWS = 2 * TT * 16, NTOK = TT * TILE, NTHREADS = KW * WAVE, PER = 16 / KW;
   constexpr int SS_PARTS = NTHREADS / NTOK;                       // threads per token for the sums of squares
   constexpr int SS_PER = (MAX_HIDDEN / 64 + SS_PARTS - 1) / SS_PARTS;
   constexpr int LOGIT_STRIDE = MAX_EXPERTS + 1;   // padded: the transposed writes spread over the banks
@@ -1465,9 +1505,9 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
   }
   __syncthreads();
   TRACE_MARK(3, 3);
-  // 16 lanes per token with 4 consecutive experts each
+  // 16 lanes per token with 4 consecutive experts each; with 64 tokens 8 lanes and 8 experts
   constexpr int LPT = NTHREADS / NTOK, EPL = MAX_EXPERTS / LPT;
-  static_assert(LPT == 16 && LPT >= MAX_TOPK, "lane j keeps the j-th selection");
+  static_assert((LPT == 16 || LPT == 8) && LPT >= MAX_TOPK, "lane j keeps the j-th selection");
   const int grp = threadIdx.x / LPT, sub = threadIdx.x % LPT;
   for (int tl = grp; tl < NTOK; tl += NTHREADS / LPT) {
     float p[EPL];
@@ -1477,14 +1517,14 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
       p[i] = EPL * sub + i < n_exp ? s_logit[tl * LOGIT_STRIDE + EPL * sub + i] : -INFINITY;
       m = fmaxf(m, p[i]);
     }
-    m = group_max(m);
+    m = group_max<LPT>(m);
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
       p[i] = EPL * sub + i < n_exp ? expf(p[i] - m) : 0.f;
       sum += p[i];
     }
-    const float inv = 1.f / group_sum(sum);
+    const float inv = 1.f / group_sum<LPT>(sum);
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
       // a row of NaN (fmaxf takes the number) selects the first experts and gets NaN weights: without a selection its
@@ -1502,7 +1542,7 @@ __global__ __launch_bounds__(KW * WAVE) void router_kernel(const E* __restrict__
           bv = p[i];
           bi = EPL * sub + i;
         }
-      group_argmax(bv, bi);
+      group_argmax<LPT>(bv, bi);
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
         if (EPL * sub + i == bi) p[i] = -1.f;
@@ -1531,12 +1571,17 @@ template <typename E> static void launch_router_t(const RouterArgs& a, hipStream
                                                                a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
   };
   const bool few = a.T <= 2 * TILE;   // the expert kernels sort the pairs
-  if (a.share_features == 2 * 64) select(router_select_kernel<SELECT_WAVES, false, true>, SELECT_WAVES);
-  else if (a.share_features && few) select(router_select_kernel<SELECT_WAVES, false, false>, SELECT_WAVES);
-  else if (a.share_features) select(router_select_kernel<HIST_TOKENS, true, false>, HIST_TOKENS);
-  else
-    router_kernel<E, ROUTER_WAVES><<<(a.T + TILE - 1) / TILE, ROUTER_WAVES * WAVE, ksplit_lds<1, ROUTER_WAVES>(), st>>>(
-        (const E*)a.w, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E, a.top_k, a.norm_topk, a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
+  auto contract = [&](auto kernel, int tiles, size_t lds) {
+    kernel<<<(a.T + tiles * TILE - 1) / (tiles * TILE), ROUTER_WAVES * WAVE, lds, st>>>((const E*)a.w, (const E*)a.xn, a.ssq, a.H / 64, a.eps, a.T, a.H, a.E,
+                                                                                        a.top_k, a.norm_topk, a.rinv, a.topk_idx, a.topk_w, a.hist, live_word());
+  };
+  constexpr bool CHAINS = sizeof(E) == 2;
+  if (!a.share_features) {
+    if (few && a.T > TILE) contract(router_kernel<E, 2, ROUTER_WAVES>, 2, ksplit_lds<2, ROUTER_WAVES>());
+    else contract(router_kernel<E, 1, ROUTER_WAVES>, 1, ksplit_lds<1, ROUTER_WAVES>());
+  } else if (CHAINS && a.T <= TILE) select(router_select_kernel<SELECT_WAVES, false, CHAINS ? 16 : 0>, SELECT_WAVES);
+  else if (few) select(router_select_kernel<SELECT_WAVES, false, CHAINS ? 8 : 0>, SELECT_WAVES);
+  else select(router_select_kernel<HIST_TOKENS, true, 0>, HIST_TOKENS);
   if (few) return;
   launch_permute(a.topk_idx, a.T * a.top_k, a.top_k, a.hist, a.share_features ? HIST_TOKENS : TILE, a.E, a.cnt, a.off, a.perm, a.work,
                  expert_group_tiles(a.E, a.T * a.top_k), expert_round_items(a.E, a.T * a.top_k, a.H, a.I), st);
@@ -1582,7 +1627,8 @@ bool configure_kernels() {
        opt_in_lds((const void*)expert_down_fused_kernel<bf16_t, 1, DOWN_KW, 4>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<float, 1, DOWN_KW, 8>) &&
        opt_in_lds((const void*)expert_down_fused_kernel<float, 1, DOWN_KW, 4>);
-  ok = ok && opt_in_lds((const void*)router_kernel<bf16_t, ROUTER_WAVES>) && opt_in_lds((const void*)router_kernel<float, ROUTER_WAVES>);
+  ok = ok && opt_in_lds((const void*)router_kernel<bf16_t, 1, ROUTER_WAVES>) && opt_in_lds((const void*)router_kernel<float, 1, ROUTER_WAVES>) &&
+       opt_in_lds((const void*)router_kernel<bf16_t, 2, ROUTER_WAVES>) && opt_in_lds((const void*)router_kernel<float, 2, ROUTER_WAVES>);
   (void)hipGetLastError();
   return ok;
 }

@@ -47,6 +47,26 @@ __device__ inline float wave_all_sum_by_fours(float v) {
   const auto h = __builtin_amdgcn_permlane32_swap(k, k, false, false);
   return __int_as_float(h[0]) + __int_as_float(h[1]);
 }
+// ... as lanes with eight consecutive values each would form it.
+__device__ inline float wave_all_sum_by_eights(float v) {
+  float s = dpp_f<0x00>(v) + dpp_f<0x55>(v);      // the first four of the eight lanes
+  s += dpp_f<0xAA>(v);
+  s += dpp_f<0xFF>(v);
+  float t = dpp_f<DPP_HALF_MIRROR>(s);            // ... in the lanes of the other four, which go on from them
+  t += dpp_f<0x00>(v);
+  t += dpp_f<0x55>(v);
+  t += dpp_f<0xAA>(v);
+  t += dpp_f<0xFF>(v);
+  const float back = dpp_f<DPP_HALF_MIRROR>(t);
+  s = threadIdx.x & 4 ? t : back;
+  s += dpp_f<DPP_MIRROR>(s);
+  const int i = __float_as_int(s);
+  const auto r = __builtin_amdgcn_permlane16_swap(i, i, false, false);
+  s = __int_as_float(r[0]) + __int_as_float(r[1]);
+  const int k = __float_as_int(s);
+  const auto h = __builtin_amdgcn_permlane32_swap(k, k, false, false);
+  return __int_as_float(h[0]) + __int_as_float(h[1]);
+}
 // OR over the wave, as a scalar
 __device__ inline uint64_t wave_all_or(uint64_t v) {
   auto all = [](int x) { return (uint32_t)__builtin_amdgcn_readfirstlane(wave_all(x, [](int a, int b) { return a | b; })); };

@@ -50,10 +50,10 @@ def step(cfg, weights, inp, T, max_pos=128, fill=None):
     return hidden, routing, weights
 
 
-def router_case(dtype, n_seq, block, hidden, small, negative):
+def router_case(dtype, n_seq, block, hidden, small, negative, n_heads=1):
     """Expert 0's logit: BIG from feature 0, 0.75 from each of the features `small`, -BIG from feature `negative`; expert 1's is 1.
     Returns whether expert 0 was taken by every token, that is whether the small terms are left."""
-    cfg, weights, inp = model(dtype, n_seq, block, hidden, 2, 1, 64)
+    cfg, weights, inp = model(dtype, n_seq, block, hidden, 2, 1, 64, n_heads=n_heads)
     w = weights["layers"][0]["w_router"]
     put(dtype, w, (0, 0), BIG)
     for f in small:
@@ -65,13 +65,31 @@ def router_case(dtype, n_seq, block, hidden, small, negative):
     return taken[0] == 0
 
 
+def check_chains(hidden, chain, n_seq, block, n_heads=1):
+    assert not router_case("bf16", n_seq, block, hidden, range(16, chain, 16), chain, n_heads)
+    assert router_case("bf16", n_seq, block, hidden, range(chain, 2 * chain, 16), 2 * chain, n_heads)      # a chain of their own
+
+
 # features per chain of the contraction: eight waves of up to eight k-steps of sixteen features, the waves of several workgroups
 # where that divides K
 @pytest.mark.parametrize("n_seq,block", [(1, 1), (1, 11), (1, 32), (2, 16)])
 @pytest.mark.parametrize("hidden,chain", [(2048, 128), (4096, 128), (3072, 128), (1024, 128), (512, 64), (1536, 192)])
 def test_router_of_up_to_32_tokens_adds_along_its_chains(hidden, chain, n_seq, block):
-    assert not router_case("bf16", n_seq, block, hidden, range(16, chain, 16), chain)
-    assert router_case("bf16", n_seq, block, hidden, range(chain, 2 * chain, 16), 2 * chain)      # a chain of their own
+    check_chains(hidden, chain, n_seq, block)
+
+
+# ... of four k-steps, with two token tiles
+@pytest.mark.parametrize("n_seq,block", [(1, 33), (1, 64), (4, 16)])
+@pytest.mark.parametrize("hidden,chain", [(2048, 64), (4096, 64), (1536, 64), (512, 64), (768, 96), (320, 48)])
+def test_router_of_33_to_64_tokens_adds_along_its_chains(hidden, chain, n_seq, block):
+    check_chains(hidden, chain, n_seq, block)
+
+
+# ... an eighth of K (two heads: the output projection takes its dense form)
+@pytest.mark.parametrize("n_seq,block", [(5, 13), (5, 32), (16, 33)])
+@pytest.mark.parametrize("hidden,chain", [(2048, 256), (1024, 128), (768, 96), (320, 48)])
+def test_router_of_many_tokens_adds_along_its_chains(hidden, chain, n_seq, block):
+    check_chains(hidden, chain, n_seq, block, 2)
 
 
 # 5 experts of 2048 are 80 groups of eight k-steps for 64 waves: two each in list order, the last 24 waves none
