@@ -1062,9 +1062,10 @@ __global__ __launch_bounds__(TASKS * KH * WAVE) void gemm_dense_kernel(const E* 
 // of the weights, split-K was ahead all along, 11.5 against 17.1.)
 static bool dense_applies(int T, int ksteps) { return T > 2 * TILE && ksteps % (WKC * DENSE_KH) == 0; }
 int router_share_features(bool bf16, int D, int H, int T) {
+  if (single_slice()) return 0;
   if (bf16) {
     const int features = T <= TILE ? ROUTER_CHAIN * 16 : T <= 2 * TILE ? ROUTER_CHAIN * 8 : 0;
-    return !single_slice() && features && H % (ROUTER_WAVES * features) == 0 ? features : 0;
+    return features && H % (ROUTER_WAVES * features) == 0 ? features : 0;
   }
   if (T <= 2 * TILE) return 64;
   return T <= ROUTER_SHARES_T && dense_applies(T, D / 8) && dense_form(false, H / 64, T).tiles == 1 ? 64 : 0;

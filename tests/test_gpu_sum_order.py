@@ -92,6 +92,19 @@ def test_router_of_many_tokens_adds_along_its_chains(hidden, chain, n_seq, block
     check_chains(hidden, chain, n_seq, block, 2)
 
 
+# With the test switch on, no part of a logit comes from another workgroup: one workgroup contracts all of K, an eighth per wave.
+@pytest.mark.parametrize("n_seq,block", [(1, 1), (1, 32), (1, 33), (4, 16), (5, 13)])
+@pytest.mark.parametrize("dtype,hidden,chain,kstep", [("f32", 512, 64, 8), ("f32", 2048, 256, 8), ("bf16", 2048, 256, 16)])
+def test_single_slice_contracts_the_router_in_one_workgroup(dtype, hidden, chain, kstep, n_seq, block):
+    from paper_2510_08666_amd import binding
+    binding.debug_single_slice(True)
+    try:
+        assert not router_case(dtype, n_seq, block, hidden, range(kstep, chain, kstep), chain)
+        assert router_case(dtype, n_seq, block, hidden, range(chain, 2 * chain, kstep), 2 * chain)
+    finally:
+        binding.debug_single_slice(False)
+
+
 # 5 experts of 2048 are 80 groups of eight k-steps for 64 waves: two each in list order, the last 24 waves none
 @pytest.mark.parametrize("n_seq,block", [(1, 1), (1, 32)])
 def test_fused_down_projection_cuts_its_contraction_into_equal_shares(n_seq, block):
