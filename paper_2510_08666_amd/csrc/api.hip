@@ -1053,9 +1053,10 @@ int dinfer_debug_get(dinfer_ctx* c, int32_t what, void* d_out, size_t bytes, voi
     default: return fail(DINFER_EINVAL, "what %d", what);
   }
   if (bytes != want || want == 0) return fail(DINFER_EINVAL, "%zu bytes given, %zu expected", bytes, want);
-  // the tables of the last layer's permutation: up to 64 tokens no kernel of a forward writes them
+  // the tables of the last layer's permutation: up to 64 tokens no kernel of a forward writes them, and those that sort for themselves
+  // are made to say what they found
   if (what >= 3 && what <= 5 && T <= 2 * TILE)
-    launch_pair_tables(at<int32_t>(c->ws, c->wsm.topk_idx) + (size_t)(f.n_layers - 1) * T * f.top_k, (int)T * f.top_k, f.n_experts,
+    launch_pair_tables(at<int32_t>(c->ws, c->wsm.topk_idx) + (size_t)(f.n_layers - 1) * T * f.top_k, (int)T, f.top_k, f.n_experts,
                        at<int32_t>(c->ws, c->wsm.cnt), at<int32_t>(c->ws, c->wsm.off), at<int32_t>(c->ws, c->wsm.perm), (hipStream_t)stream);
   HIP_TRY(hipMemcpyAsync(d_out, c->ws + off, want, hipMemcpyDeviceToDevice, (hipStream_t)stream));
   return DINFER_OK;

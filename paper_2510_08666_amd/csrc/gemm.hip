@@ -702,28 +702,11 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
   TRACE_MARK_WAVE(55, 0, KW);
   // The first loads hang on the routing alone: this lane's tokens' experts, from which the wave reads off the list of
   // experts with rows and, for the two of them it meets, where its tokens' rows sit in Y (sorted by expert, then token).
-  static_assert(TT == 1, "a token is a bit of a half-wave's ballot");
-  int my_e[MAX_TOPK];
-  const bool is_tok = col < T;
-#pragma unroll
-  for (int j = 0; j < MAX_TOPK; ++j) my_e[j] = topk_idx[min(col, T - 1) * top_k + min(j, top_k - 1)];
-  uint64_t experts = 0;
-#pragma unroll
-  for (int j = 0; j < MAX_TOPK; ++j) experts |= 1ull << my_e[j];
-  experts = wave_all_or(experts);
+  static_assert(TT == 1, "TokenExperts");
+  TokenExperts tokens;
+  tokens.load(topk_idx, T, top_k);
+  const uint64_t experts = tokens.experts();
   const int n_act = __popcll(experts);
-  auto row_in_y = [&](int e) {      // -1: the lane's token was not routed to e
-    int before = 0;
-    bool here = false;
-#pragma unroll
-    for (int j = 0; j < MAX_TOPK; ++j) {
-      const bool pair = is_tok && half == 0 && j < top_k;
-      before += __popcll(__ballot(pair && my_e[j] < e));
-      here |= my_e[j] == e;
-    }
-    const uint32_t toks = (uint32_t)__ballot(is_tok && here);   // bit per token, from the lower half-wave
-    return is_tok && here ? before + __popc(toks & ((1u << col) - 1)) : -1;
-  };
   // The long K: experts with rows in list order, ksteps_e k-steps each, in groups of PF k-steps; this wave's
   // contiguous share [g0, g1).  A share is never longer than one expert's groups, so it meets at most two experts.  Float32: shares of
   // equal length rounded down or up, so that each workgroup has the same number of groups within one; shares all rounded up leave the
@@ -787,8 +770,8 @@ __global__ __launch_bounds__(KW * WAVE) void expert_down_fused_kernel(const E* _
       TRACE_MARK_WAVE(55, 1, KW);
 #pragma unroll
       for (int i = 0; i < PF; ++i) issue_w(i, wp);
-      row_first = row_in_y(e_first);
-      row_second = row_in_y(e_second);
+      row_first = tokens.row_of(e_first);
+      row_second = tokens.row_of(e_second);
       uint32_t yoff[TT], ystep[TT];
       rows_of(g0, yoff, ystep);
 #pragma unroll

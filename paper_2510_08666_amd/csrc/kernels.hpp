@@ -209,8 +209,8 @@ void launch_router(bool bf16, const RouterArgs& a, hipStream_t st);
 // hist: the router's histograms, see RouterArgs, one per hist_tokens tokens (a divisor of 32); round: expert_round_items.
 void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32_t* hist, int hist_tokens, int E, int32_t* cnt, int32_t* off,
                     int32_t* perm, int32_t* work, int group_tiles, int round, hipStream_t st);
-// cnt, off and perm of at most 64 tokens (a test hook).
-void launch_pair_tables(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm, hipStream_t st);
+// cnt, off and perm of at most 64 tokens, by the code with which the expert kernels sort their pairs (a test hook).
+void launch_pair_tables(const int32_t* topk_idx, int T, int top_k, int E, int32_t* cnt, int32_t* off, int32_t* perm, hipStream_t st);
 // Work list of the expert GEMMs above 64 tokens: number of items [WORK_BIG] taken by whole workgroups, of all items
 // [WORK_ALL] (the rest in pieces of one task), of those with the most tiles [WORK_HEAVY] and with one or two [WORK_LIGHT], then
 // 16-byte items {expert, first sorted row, rows, 0}, the ones with more tiles first.

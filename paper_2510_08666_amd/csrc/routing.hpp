@@ -116,4 +116,37 @@ template <int N> struct PairIds {
   }
 };
 
+// Up to 32 tokens, where a wave wants the rows of all tokens for a few experts: lane = token (both half-waves alike).
+struct TokenExperts {
+  int e[MAX_TOPK], top_k;       // (the last one again past top_k)
+  bool is_tok;
+  __device__ void load(const int32_t* __restrict__ topk_idx, int T, int k) {
+    const int col = threadIdx.x & 31;
+    top_k = k;
+    is_tok = col < T;
+#pragma unroll
+    for (int j = 0; j < MAX_TOPK; ++j) e[j] = topk_idx[min(col, T - 1) * k + min(j, k - 1)];
+  }
+  __device__ uint64_t experts() const {
+    uint64_t m = 0;
+#pragma unroll
+    for (int j = 0; j < MAX_TOPK; ++j) m |= 1ull << e[j];
+    return wave_all_or(m);
+  }
+  // Place of the lane's token for expert x among the pairs sorted by expert, then token; -1: not routed to it
+  __device__ int row_of(int x) const {
+    const int half = (threadIdx.x >> 5) & 1, col = threadIdx.x & 31;
+    int before = 0;
+    bool here = false;
+#pragma unroll
+    for (int j = 0; j < MAX_TOPK; ++j) {
+      const bool pair = is_tok && half == 0 && j < top_k;
+      before += __popcll(__ballot(pair && e[j] < x));
+      here |= e[j] == x;
+    }
+    const uint32_t toks = (uint32_t)__ballot(is_tok && here);   // bit per token, from the lower half-wave
+    return is_tok && here ? before + __popc(toks & ((1u << col) - 1)) : -1;
+  }
+};
+
 }  // namespace dinfer

@@ -3,6 +3,7 @@
 // and the KV import / export used by tests.
 #include "gemm.hpp"
 #include "kernels.hpp"
+#include "routing.hpp"
 
 namespace dinfer {
 
@@ -382,27 +383,56 @@ void launch_permute(const int32_t* topk_idx, int n_pairs, int top_k, const int32
       topk_idx, n_pairs, per_group, hist, (n_pairs / top_k + hist_tokens - 1) / hist_tokens, TILE / hist_tokens, E, cnt, off, perm, work, group_tiles, round, live_word());
 }
 
-// The tables of permute_kernel for at most 64 tokens, where no kernel of a forward needs them; a test hook's kernel.
-__global__ __launch_bounds__(WAVE) void pair_tables_kernel(const int32_t* __restrict__ expert_of_pair, int n_pairs, int n_exp,
-                                                           int32_t* __restrict__ cnt, int32_t* __restrict__ off, int32_t* __restrict__ perm) {
-  __shared__ int32_t s_cnt[MAX_EXPERTS];
-  const int e = threadIdx.x;
-  int n = 0;
-  for (int p = 0; p < n_pairs; ++p) n += expert_of_pair[p] == e;
-  s_cnt[e] = n;
-  __syncthreads();
-  int at = 0;
-  for (int i = 0; i < e; ++i) at += s_cnt[i];
-  if (e < n_exp) {
-    cnt[e] = n;
-    off[e] = at;
-    if (e == n_exp - 1) off[n_exp] = at + n;
+// The tables of permute_kernel for at most 64 tokens, where no kernel of a forward needs them; a test hook's kernel, one wave.  It
+// puts them together from what the expert kernels read off the routing: PairIds with N pairs in a lane, expert by expert, and up to 32
+// tokens also TokenExperts, from which a second permutation is made; an entry in which the two differ is -1.
+template <int N>
+__global__ __launch_bounds__(WAVE) void pair_tables_kernel(const int32_t* __restrict__ topk_idx, int T, int top_k, int n_exp, int32_t* __restrict__ cnt,
+                                                           int32_t* __restrict__ off, int32_t* __restrict__ perm) {
+  constexpr int PAIRS = N * WAVE;
+  __shared__ int32_t s_pair[WAVE], s_cnt[MAX_EXPERTS], s_perm[PAIRS], s_other[PAIRS];
+  const int lane = threadIdx.x, n_pairs = T * top_k;
+  for (int p = lane; p < PAIRS; p += WAVE) s_perm[p] = s_other[p] = -1;
+  s_cnt[lane] = 0;
+  PairIds<N> ids;
+  ids.load(topk_idx, n_pairs);
+  const uint64_t experts = ids.experts();
+  bool same = true;
+  for (int i = 0; i < __popcll(experts); ++i) {
+    __syncthreads();
+    const int4 it = ids.rows_of(nth_bit(experts, i), s_pair);
+    __syncthreads();
+    if (lane < it.z && it.y + lane < n_pairs) s_perm[it.y + lane] = s_pair[lane];
+    if (lane == 0 && it.x < n_exp) {
+      s_cnt[it.x] = it.z;
+      off[it.x] = it.y;
+    }
   }
-  for (int p = 0; p < n_pairs; ++p)
-    if (expert_of_pair[p] == e) perm[at++] = p;
+  if constexpr (N * WAVE == TILE * MAX_TOPK) {
+    TokenExperts tokens;
+    tokens.load(topk_idx, T, top_k);
+    same = tokens.experts() == experts;
+    for (int e = 0; e < n_exp; ++e) {
+      const int row = tokens.row_of(e);
+      for (int j = 0; j < top_k; ++j)
+        if (lane < TILE && row >= 0 && row < n_pairs && topk_idx[lane * top_k + j] == e) s_other[row] = lane * top_k + j;
+    }
+  }
+  __syncthreads();
+  if constexpr (N * WAVE != TILE * MAX_TOPK)
+    for (int p = lane; p < PAIRS; p += WAVE) s_other[p] = s_perm[p];
+  for (int p = lane; p < n_pairs; p += WAVE) perm[p] = same && s_perm[p] == s_other[p] ? s_perm[p] : -1;
+  int at = 0;
+  for (int i = 0; i < lane; ++i) at += s_cnt[i];
+  if (lane < n_exp) {
+    cnt[lane] = s_cnt[lane];
+    if (!(experts >> lane & 1)) off[lane] = at;               // without rows: nothing says where
+    if (lane == n_exp - 1) off[n_exp] = at + s_cnt[lane];
+  }
 }
-void launch_pair_tables(const int32_t* topk_idx, int n_pairs, int E, int32_t* cnt, int32_t* off, int32_t* perm, hipStream_t st) {
-  pair_tables_kernel<<<1, WAVE, 0, st>>>(topk_idx, n_pairs, E, cnt, off, perm);
+void launch_pair_tables(const int32_t* topk_idx, int T, int top_k, int E, int32_t* cnt, int32_t* off, int32_t* perm, hipStream_t st) {
+  if (T <= TILE) pair_tables_kernel<TILE * MAX_TOPK / WAVE><<<1, WAVE, 0, st>>>(topk_idx, T, top_k, E, cnt, off, perm);
+  else pair_tables_kernel<2 * TILE * MAX_TOPK / WAVE><<<1, WAVE, 0, st>>>(topk_idx, T, top_k, E, cnt, off, perm);
 }
 
 // ---------------------------------------------------------------- LM-head partial merge

@@ -10,7 +10,7 @@ from harness import GpuRun, bars_for, make_case
 pytestmark = pytest.mark.gpu
 
 
-# token counts of the router's forms: fused permutation with one and with two token tiles, permutation over groups
+# token counts of the router's forms: one and two token tiles, whose pairs the expert kernels sort, and the permutation over groups
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n_seq,block", [(2, 16), (2, 32), (3, 40)])
 def test_sequence_of_not_a_number(n_seq, block, dtype):

@@ -49,7 +49,7 @@ def _variant(name):
         # no prefix at all: the block attends to itself only
         "noprefix": W("noprefix", tiny, 2, 32, 0, 0, threshold=0.9, seed_index=10),
         # a skewed router (see _skew_router): three hot experts take most rows, eight more take the rest by the tie
-        # rule, 53 stay empty.  32 tokens (records of the fused permutation, fused down projection over few experts),
+        # rule, 53 stay empty.  32 tokens (pairs sorted in the expert kernels, fused down projection over few experts),
         # 64 tokens, and 288 tokens (work list: the hot experts have up to three row groups, most experts none)
         "skew": W("skew", sc(tiny, n_heads=2, head_dim=128, n_experts=64, top_k=8, moe_inter=128, vocab=1000),
                   1, 32, 5, 40, threshold=0.9, seed_index=41),
