@@ -314,69 +314,54 @@ __global__ __launch_bounds__(ATTN_WAVES * WAVE) void attention_kernel(const E* _
   }
   __shared__ int32_t s_flag;
   if (!last_arrival(tickets + pair, my_splits, &s_flag)) return;
-  // Last to arrive: fold the partials in split order.  A thread takes ITEMS (query, 4 consecutive features) items.  The loads
+  // Last to arrive: fold the partials in split order, each weighted against the maximum of all, by fused adds (as written: a product that
+  // the compiler rounds first is another last bit of every row).  A thread takes ITEMS (query, 4 consecutive features) items.  The loads
   // of N splits are under way together; they bypass the L2, so that one compute unit's fetch is the bound, and no more are issued than
   // for two, four, eight or sixteen splits (sixteen clamped loads for every count -> this: two splits, 64 tokens behind 768 keys 19.0 ->
-  // 16.0 us for the launch, 12 sequences of 32 40.0 -> 36.8; eight splits of 4096 keys 22.4 -> 21.0).  Beyond eight there are two
-  // rounds, with all maxima in front of the first: every weight is relative to the row's own maximum then, and nothing is scaled twice.
+  // 16.0 us for the launch, 12 sequences of 32 40.0 -> 36.8; eight splits of 4096 keys 22.4 -> 21.0;
+  // sixteen of 8000 25.6 -> 26.5, in two rounds of eight 26.7).
   constexpr int ITEMS = TILE * HD / 4 / (ATTN_WAVES * WAVE);
   static_assert(ITEMS * ATTN_WAVES * WAVE == TILE * HD / 4, "whole items per thread");
-  float Mx[ITEMS], Ls[ITEMS];
+  float Ls[ITEMS];
   f32x4 acc[ITEMS];
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
-    Mx[i] = -INFINITY;
     Ls[i] = 0.f;
     acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   auto item_q = [&](int i) { return (int)(threadIdx.x + i * ATTN_WAVES * WAVE) / (HD / 4); };
   auto item_d = [&](int i) { return (int)(threadIdx.x + i * ATTN_WAVES * WAVE) % (HD / 4) * 4; };
-  auto fold = [&](auto C, int p0) {
+  auto fold = [&](auto C) {
     constexpr int N = decltype(C)::value;
     float ml[ITEMS][N][2], op[ITEMS][N][4];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
 #pragma unroll
       for (int p = 0; p < N; ++p) {
-        const uint32_t pb = pair_bytes + min(p0 + p, my_splits - 1) * part_bytes;
+        const uint32_t pb = pair_bytes + min(p, my_splits - 1) * part_bytes;
         coherent_load_n<2>(pr, pb + (TILE * HD + 2 * item_q(i)) * 4, ml[i][p]);
         coherent_load_n<4>(pr, pb + (item_q(i) * HD + item_d(i)) * 4, op[i][p]);
       }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-      float m_new = Mx[i];
+      float Mx = -INFINITY;
 #pragma unroll
-      for (int p = 0; p < N; ++p) m_new = p0 + p < my_splits ? fmaxf(m_new, ml[i][p][0]) : m_new;
-      const float alpha = Mx[i] > -INFINITY ? __builtin_amdgcn_exp2f(Mx[i] - m_new) : 0.f;
-      Mx[i] = m_new;
-      Ls[i] *= alpha;
-      acc[i] *= alpha;
+      for (int p = 0; p < N; ++p) Mx = p < my_splits ? fmaxf(Mx, ml[i][p][0]) : Mx;
 #pragma unroll
       for (int p = 0; p < N; ++p) {
-        if (p0 + p < my_splits && ml[i][p][0] > -INFINITY) {   // (a split whose waves saw no key tile contributes nothing)
-          const float w = __builtin_amdgcn_exp2f(ml[i][p][0] - m_new);
-          Ls[i] += w * ml[i][p][1];
+        if (p < my_splits && ml[i][p][0] > -INFINITY) {   // (a split whose waves saw no key tile contributes nothing)
+          const float w = __builtin_amdgcn_exp2f(ml[i][p][0] - Mx);
+          Ls[i] = __builtin_fmaf(w, ml[i][p][1], Ls[i]);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) acc[i][k] += w * op[i][p][k];
+          for (int k = 0; k < 4; ++k) acc[i][k] = __builtin_fmaf(w, op[i][p][k], acc[i][k]);
         }
       }
     }
   };
-  if (my_splits > 8) {
-    float m[ITEMS][ATTN_MAX_SPLITS][1];
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-#pragma unroll
-      for (int p = 0; p < ATTN_MAX_SPLITS; ++p)
-        coherent_load_n<1>(pr, pair_bytes + min(p, my_splits - 1) * part_bytes + (TILE * HD + 2 * item_q(i)) * 4, m[i][p]);
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
-#pragma unroll
-      for (int p = 0; p < ATTN_MAX_SPLITS; ++p) Mx[i] = fmaxf(Mx[i], m[i][p][0]);
-  }
-  if (my_splits == 2) fold(std::integral_constant<int, 2>{}, 0);
-  else if (my_splits <= 4) fold(std::integral_constant<int, 4>{}, 0);
-  else for (int p0 = 0; p0 < my_splits; p0 += 8) fold(std::integral_constant<int, 8>{}, p0);
+  if (my_splits == 2) fold(std::integral_constant<int, 2>{});
+  else if (my_splits <= 4) fold(std::integral_constant<int, 4>{});
+  else if (my_splits <= 8) fold(std::integral_constant<int, 8>{});
+  else fold(std::integral_constant<int, ATTN_MAX_SPLITS>{});
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
     if (item_q(i) >= nvalid) continue;
