@@ -55,8 +55,11 @@ inline bool lm_compact(bool bf16, int T) { return bf16 && T > LM_MID_T; }
 // would take two of them.  While all compute units stream, each takes in about 27 GB/s, from its L2 as well, and at 160 tokens
 // two thirds of that was the second delivery.  LM head in us, four tiles and whole tasks -> this: 130 tokens 163 -> 137, 160 168 -> 142,
 // 192 172 -> 150, 288 219 -> 214 (the call is no faster), 320 223 -> 212, 352 230 -> 234, 384 238 -> 238, 480 286 -> 322, 512 288 -> 317 (with
-// eight tiles in a workgroup: every fragment read from LDS feeds one matrix instruction instead of two, and LDS is the bound); 320
-// tokens of which half are decided 189 -> 156, 160 with 16 undecided ones 136 -> 126.
+// eight tiles in a workgroup: every fragment read from LDS feeds one matrix instruction instead of two, and LDS is the bound).
+// The call's tokens choose, not its undecided ones, which only the device knows; the kernel deals the tiles of the list.  Lists that need no
+// second delivery either way gain too, since the head's last round of workgroups is shorter: of 160 tokens 16 undecided 135 -> 123, 97 to 128
+// 145 -> 133, 129 170 -> 140; of 320 tokens 97 149 -> 140, 128 150 -> 144, 160 183 -> 154, 192 185 -> 158, 193 to 256 184 to 188 -> 183 to 185, 257
+// 222 -> 211, all 223 -> 207 (events around the stage).  Confidences are 4e-8 off those of whole tasks, whose exponentials one lane adds up.
 inline bool lm_half(bool bf16, int T) {
   const int tiles = (T + 31) / 32;
   return bf16 && (tiles == 5 || tiles == 6 || tiles == 10);

@@ -54,3 +54,31 @@ def check(n_seq, block, vocab, hidden):
         assert np.array_equal(listed["conf"][s][on], got["conf"][s][on]) and np.array_equal(listed["argmax"][s][on], got["argmax"][s][on])
         assert (listed["conf"][s][~on] == -7).all() and (listed["argmax"][s][~on] == -7).all()
     gpu.close()
+
+
+# lists that fill three to ten tiles: one token group of four, five and six tiles; two groups of 4 + 3, 4 + 4, 5 + 4 and 5 + 5
+@pytest.mark.parametrize("n_seq,block,counts", [(5, 32, (96, 97, 100, 128, 129, 159)), (3, 64, (128, 129, 160, 161, 191)),
+                                                (5, 64, (96, 128, 129, 160, 161, 192, 193, 224, 225, 256, 257, 288, 289, 319))])
+def test_row_lists_of_every_number_of_tiles(n_seq, block, counts):
+    cfg = di.configs.scaled(di.model_preset("tiny"), hidden=320, n_heads=2, head_dim=64, n_experts=8, moe_inter=64, vocab=1102, dtype="bf16",
+                            logit_scale=1.0)
+    cfg, w, inp = make_case(di.Workload("half_list", cfg, n_seq, block, 2, 30, threshold=0.9, seed_index=170 + n_seq))
+    T, cap = n_seq * block, int(inp.prefix_len.max()) + 2 * block + 16
+    gpu = GpuRun(cfg, w, inp, T, cap)
+    gpu.ctx.kv.zero_()
+    rng = np.random.default_rng(T)
+    for n in counts:
+        on = np.zeros(T, dtype=bool)
+        on[::block] = True                                  # one position of every sequence, the others anywhere
+        on[rng.permutation(np.flatnonzero(~on))[:n - n_seq]] = True
+        on = on.reshape(n_seq, block)
+        masks = np.array([sum(1 << int(i) for i in np.flatnonzero(row)) for row in on], dtype=np.uint64)
+        gpu.set_state(inp.block_tokens, masks, inp.prefix_len)
+        full = gpu.step(0.9)
+        gpu.set_state(inp.block_tokens, masks, inp.prefix_len)
+        gpu.conf.fill_(-7.0)
+        gpu.argmax.fill_(-7)
+        listed = gpu.step(gpu.binding.Decode(0.9, 0, 0, 0.0, 1))
+        for key in ("conf", "argmax"):
+            assert np.array_equal(listed[key][on], full[key][on]) and (listed[key][~on] == -7).all(), (n, key)
+    gpu.close()

@@ -18,6 +18,7 @@ extern "C" void plans(int T, int v0, int n, int* out) {
   }
 }
 extern "C" int compact(int bf16, int T) { return dinfer::lm_compact(bf16 != 0, T); }
+extern "C" int half(int bf16, int T) { return dinfer::lm_half(bf16 != 0, T); }
 """
 
 
@@ -61,3 +62,9 @@ def test_high_plane_of_many_bf16_tokens(tmp_path):
     lib = host_shim.load(tmp_path, SHIM)
     assert [lib.compact(1, T) for T in (1, 64, 65, 4096)] == [0, 0, 1, 1]
     assert [lib.compact(0, T) for T in (64, 65, 4096)] == [0, 0, 0]
+
+
+def test_half_tasks_of_five_six_and_ten_token_tiles(tmp_path):
+    lib = host_shim.load(tmp_path, SHIM)
+    assert [T for T in range(1, 2000) if lib.half(1, T)] == list(range(129, 193)) + list(range(289, 321))
+    assert not any(lib.half(0, T) for T in range(1, 2000))
