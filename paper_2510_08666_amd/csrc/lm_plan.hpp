@@ -59,7 +59,7 @@ inline bool lm_compact(bool bf16, int T) { return bf16 && T > LM_MID_T; }
 // The call's tokens choose, not its undecided ones, which only the device knows; the kernel deals the tiles of the list.  Lists that need no
 // second delivery either way gain too, since the head's last round of workgroups is shorter: of 160 tokens 16 undecided 135 -> 123, 97 to 128
 // 145 -> 133, 129 170 -> 140; of 320 tokens 97 149 -> 140, 128 150 -> 144, 160 183 -> 154, 192 185 -> 158, 193 to 256 184 to 188 -> 183 to 185, 257
-// 222 -> 211, all 223 -> 207 (events around the stage).  Confidences are 4e-8 off those of whole tasks, whose exponentials one lane adds up.
+// 222 -> 211, all 223 -> 207 (events around the stage; 1 to 2 us more since the two halves' statistics are those of a whole task).
 inline bool lm_half(bool bf16, int T) {
   const int tiles = (T + 31) / 32;
   return bf16 && (tiles == 5 || tiles == 6 || tiles == 10);

@@ -511,7 +511,8 @@ __global__ __launch_bounds__(WW * WAVE) __attribute__((amdgpu_waves_per_eu(WT ==
 
 // ------------------------------------------------------------------------------------------------
 // LM head, form of five and six token tiles (where: lm_half): half a task (32 vocabulary ids, one weight tile) per wave, four tasks
-// per workgroup, the high plane as in the form above, statistics of a task's two halves folded at the end.  Bound by what a compute unit
+// per workgroup, the high plane as in the form above, statistics of a task's two halves put together at the end (with a fold of two
+// partials instead, 1 to 2 us less and confidences 4e-8 off the form above).  Bound by what a compute unit
 // takes in (1 MB of weights and as much as 0.75 MB of rows per workgroup) and the last, partial round of workgroups (2.4 rounds of them at
 // 157184 ids).  Twelve k-steps of weights in flight per wave: 16, 24 or 32 were slower at 160 tokens (140.8 us, 144.5, 150, 211: loads return
 // in order, so that the rows on their way to LDS wait behind them), 8 as fast (141.1); rows requested two chunks ahead 160 against 155.
@@ -623,8 +624,12 @@ __global__ __launch_bounds__(LMH_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2
     s_scale[threadIdx.x] = row_rinv(norm.ssq, norm.n_ssq, T, row, H, norm.eps) * scale;
   }
   const bool quads = V % 4 == 0 && ((uintptr_t)logits_out & 15) == 0;   // rows of logits start on 16-byte boundaries
-  LmStat* s_stat = reinterpret_cast<LmStat*>(lds_raw);   // [wave][token], once the fragments are done with
-  static_assert(LMH_WW * LMH_WT * TILE * sizeof(LmStat) <= lm_half_lds<E>(), "the statistics fit the staging area");
+  // Statistics of a task's two halves, once the fragments are done with, in the order of a lane that has both (lm_head_wide_kernel): the
+  // maximum of either half to the other's wave, exponentials against that of both, and the sum runs on from the first half's into the second's.
+  float* s_max = reinterpret_cast<float*>(lds_raw);                    // [wave][tile][lane]
+  float* s_sum = s_max + LMH_WW * LMH_WT * WAVE;                       // [task][tile][lane]
+  int32_t* s_id = reinterpret_cast<int32_t*>(s_sum + LMH_TASKS * LMH_WT * WAVE);
+  static_assert((LMH_WW + 2 * LMH_TASKS) * LMH_WT * WAVE * 4 <= lm_half_lds<E>(), "they fit the staging area");
   auto run = [&](auto N, auto S) {
     constexpr int NT = decltype(N)::value, SN = decltype(S)::value;
     f32x16 acc[NT];
@@ -632,26 +637,29 @@ __global__ __launch_bounds__(LMH_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2
     lm_half_stream<E, NT, SN>(W + (int64_t)task * task_stride_elems<E>(ksteps) + (wave & 1) * (WAVE * ET<E>::G), ksteps, xn,
                               [&](int t, int r) { return row_of(tok0 + t * TILE + r); }, (int64_t)T * KS, reinterpret_cast<vec*>(lds_raw), acc, wave);
     __syncthreads();                    // the staged fragments have been read by every wave
-    const int id0 = (2 * task + (wave & 1)) * TILE + 4 * half;
+    const int id0 = (2 * task + (wave & 1)) * TILE + 4 * half, pair = (wave >> 1) * LMH_WT;
+    float m[NT];
+    int best[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const float zs = s_scale[t * TILE + col];
-      float m = -INFINITY, sum = 0.f, z[16];
-      int best = 0x7fffffff;
+      f32x16& z = acc[t];
+      m[t] = -INFINITY;
+      best[t] = 0x7fffffff;
       if (slot < n_tasks) {             // the maximum first, then the lowest id that has it: see lm_head_wide_kernel
 #pragma unroll
-        for (int i = 0; i < 16; ++i) z[i] = acc[t][i] * zs;
+        for (int i = 0; i < 16; ++i) z[i] *= zs;
         if ((2 * task + (wave & 1) + 1) * TILE > V) {   // uniform
 #pragma unroll
           for (int i = 0; i < 16; ++i)
             if (id0 + acc_row(i, 0) >= V) z[i] = -INFINITY;
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) m = fmaxf(m, z[i]);   // passes over NaN
+        for (int i = 0; i < 16; ++i) m[t] = fmaxf(m[t], z[i]);   // passes over NaN
         int at = 0;
 #pragma unroll
-        for (int i = 15; i >= 0; --i) at = z[i] == m ? acc_row(i, 0) : at;
-        if (m > -INFINITY) best = id0 + at;
+        for (int i = 15; i >= 0; --i) at = z[i] == m[t] ? acc_row(i, 0) : at;
+        if (m[t] > -INFINITY) best[t] = id0 + at;
         if (logits_out && tok0 + t * TILE + col < n_rows) {
           float* out = logits_out + (int64_t)s_row[t * TILE + col] * V + id0;
           if (quads) {
@@ -664,25 +672,43 @@ __global__ __launch_bounds__(LMH_WW * WAVE) __attribute__((amdgpu_waves_per_eu(2
               if (id0 + acc_row(i, 0) < V) out[acc_row(i, 0)] = z[i];
           }
         }
-        if (m > -INFINITY) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) sum += __expf(z[i] - m);
-        }
       }
-      const LmStat w = lm_combine(LmStat{m, sum, best}, LmStat{__shfl_xor(m, 32, WAVE), __shfl_xor(sum, 32, WAVE), __shfl_xor(best, 32, WAVE)});
-      if (half == 0) s_stat[wave * LMH_WT * TILE + t * TILE + col] = w;
+      s_max[(wave * LMH_WT + t) * WAVE + lane] = m[t];
+    }
+    __syncthreads();
+    float sum[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const float other = s_max[((wave ^ 1) * LMH_WT + t) * WAVE + lane], both = fmaxf(m[t], other);
+      if (wave & 1 ? other == both : m[t] < both) best[t] = 0x7fffffff;   // of two halves that have it the first one's id is lower
+      m[t] = both;
+      sum[t] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][i] = both > -INFINITY ? __expf(acc[t][i] - both) : 0.f;
+      if (!(wave & 1)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum[t] += acc[t][i];
+        s_sum[(pair + t) * WAVE + lane] = sum[t];
+        s_id[(pair + t) * WAVE + lane] = best[t];
+      }
+    }
+    __syncthreads();
+    if (!(wave & 1)) return;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      sum[t] = s_sum[(pair + t) * WAVE + lane];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum[t] += acc[t][i];
+      best[t] = min(best[t], s_id[(pair + t) * WAVE + lane]);
+      const LmStat w = lm_combine(LmStat{m[t], sum[t], best[t]}, LmStat{__shfl_xor(m[t], 32, WAVE), __shfl_xor(sum[t], 32, WAVE), __shfl_xor(best[t], 32, WAVE)});
+      const int i = t * TILE + col;
+      if (half == 0 && t < nt && tok0 + i < n_rows)
+        *reinterpret_cast<f32x4*>(part + ((int64_t)s_row[i] * n_parts + slot) * 4) = f32x4{w.m, w.s, __int_as_float(w.id), 0.f};
     }
   };
   if (nt > 5) run(std::integral_constant<int, 6>{}, std::integral_constant<int, 6>{});
   else if (nt == 5) run(std::integral_constant<int, 5>{}, std::integral_constant<int, 6>{});
   else run(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
-  __syncthreads();
-  // the two halves of a task, one partial per task as in the other form
-  for (int i = threadIdx.x; i < min(nt * TILE, n_rows - tok0) * LMH_TASKS; i += LMH_WW * WAVE) {
-    const int k = i % LMH_TASKS, r = i / LMH_TASKS;
-    const LmStat a = lm_combine(s_stat[(2 * k) * LMH_WT * TILE + r], s_stat[(2 * k + 1) * LMH_WT * TILE + r]);
-    *reinterpret_cast<f32x4*>(part + ((int64_t)s_row[r] * n_parts + tgroup * LMH_TASKS + k) * 4) = f32x4{a.m, a.s, __int_as_float(a.id), 0.f};
-  }
 }
 
 // Up to 64 tokens: one or two token tiles per workgroup and both activation planes (trace ids 15, 14): there the weight

@@ -21,10 +21,10 @@ def put(dtype, a, where, value):
     a[where] = np.float32(value) if dtype == "f32" else np.uint16(np.float32(value).view(np.uint32) >> 16)
 
 
-def model(dtype, n_seq, block, hidden, experts, top_k, width, prefix=None, n_heads=1):
+def model(dtype, n_seq, block, hidden, experts, top_k, width, prefix=None, n_heads=1, vocab=64):
     """One layer whose attention adds nothing to rows of ones (1/rms is 1 but for epsilon); every other weight is zero."""
     cfg = di.configs.scaled(di.model_preset("tiny"), n_layers=1, hidden=hidden, n_heads=n_heads, head_dim=64, n_experts=experts, top_k=top_k,
-                            moe_inter=width, vocab=64, dtype=dtype, logit_scale=1.0)
+                            moe_inter=width, vocab=vocab, dtype=dtype, logit_scale=1.0)
     weights = di.make_weights(cfg, di.BASE_SEED)
     inp = di.make_workload_inputs(di.Workload("order", cfg, n_seq, block, prefix or 2, prefix or 10, threshold=2.0, seed_index=190))
     for name, a in weights["layers"][0].items():
@@ -178,3 +178,22 @@ def test_row_statistics_round_alike_in_every_form(more):
     for a, b in zip(*got):
         assert np.array_equal(a, b)
     assert len(np.unique(got[0][2])) > 63
+
+
+# The LM head takes half a task per wave at five, six and ten token tiles and whole tasks at three: a lane's sum of exponentials is
+# over the 32 ids that it has of a whole task, in their order, either way.  (The layer adds nothing, so the rows are the same.)
+@pytest.mark.parametrize("n_seq", [5, 6, 10])
+def test_sums_of_exponentials_run_on_from_half_to_half(n_seq):
+    got = []
+    for n in (3, n_seq):
+        cfg, weights, inp = model("bf16", n, 32, 128, 2, 1, 64, vocab=1102)
+        weights["emb"][...] = di.make_weights(cfg, di.BASE_SEED + 3)["emb"]
+        inp.block_tokens[...] = np.arange(n * 32).reshape(n, 32)
+        gpu = GpuRun(cfg, weights, inp, n * 32, 128)
+        gpu.ctx.kv.zero_()
+        gpu.set_state(inp.block_tokens, inp.mask_bits, inp.prefix_len)
+        state = gpu.step(2.0)
+        got.append((state["conf"][:3], state["argmax"][:3]))
+        gpu.close()
+    assert len(np.unique(got[0][0])) > 90
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
