@@ -319,31 +319,32 @@ __global__ __launch_bounds__(ATTN_WAVES * WAVE) void attention_kernel(const E* _
   // of N splits are under way together; they bypass the L2, so that one compute unit's fetch is the bound, and no more are issued than
   // for two, four, eight or sixteen splits (sixteen clamped loads for every count -> this: two splits, 64 tokens behind 768 keys 19.0 ->
   // 16.0 us for the launch, 12 sequences of 32 40.0 -> 36.8; eight splits of 4096 keys 22.4 -> 21.0;
-  // sixteen of 8000 25.6 -> 26.5, in two rounds of eight 26.7).
+  // sixteen of 8000 25.6 -> 26.5, in two rounds of eight 26.7).  Nor for rows past the tile's last query: one token behind 8000 keys
+  // 20.6, with the loads of all 32 rows 23.5.
   constexpr int ITEMS = TILE * HD / 4 / (ATTN_WAVES * WAVE);
   static_assert(ITEMS * ATTN_WAVES * WAVE == TILE * HD / 4, "whole items per thread");
-  float Ls[ITEMS];
-  f32x4 acc[ITEMS];
-#pragma unroll
-  for (int i = 0; i < ITEMS; ++i) {
-    Ls[i] = 0.f;
-    acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
   auto item_q = [&](int i) { return (int)(threadIdx.x + i * ATTN_WAVES * WAVE) / (HD / 4); };
   auto item_d = [&](int i) { return (int)(threadIdx.x + i * ATTN_WAVES * WAVE) % (HD / 4) * 4; };
+  float Ls[ITEMS];
+  f32x4 acc[ITEMS];
   auto fold = [&](auto C) {
     constexpr int N = decltype(C)::value;
     float ml[ITEMS][N][2], op[ITEMS][N][4];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i)
+    for (int i = 0; i < ITEMS; ++i) {
+      if (item_q(i) >= nvalid) continue;
 #pragma unroll
       for (int p = 0; p < N; ++p) {
         const uint32_t pb = pair_bytes + min(p, my_splits - 1) * part_bytes;
         coherent_load_n<2>(pr, pb + (TILE * HD + 2 * item_q(i)) * 4, ml[i][p]);
         coherent_load_n<4>(pr, pb + (item_q(i) * HD + item_d(i)) * 4, op[i][p]);
       }
+    }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
+      Ls[i] = 0.f;
+      acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (item_q(i) >= nvalid) continue;
       float Mx = -INFINITY;
 #pragma unroll
       for (int p = 0; p < N; ++p) Mx = p < my_splits ? fmaxf(Mx, ml[i][p][0]) : Mx;
