@@ -195,7 +195,7 @@ Workspace map_workspace(const dinfer_config& c, int max_seqs, int max_tokens) {
   w.cnt = cv.take((size_t)MAX_EXPERTS * 4);
   w.off = cv.take((size_t)OFF_INTS * 4);   // offsets, then running totals (gemm.hpp)
   w.perm = cv.take(T * K * 4);
-  w.shares = cv.take((size_t)(H / 64) * (max_tokens < ROUTER_SHARES_T ? max_tokens : ROUTER_SHARES_T) * MAX_EXPERTS * 4);   // of the router's logits
+  w.shares = cv.take(router_shares_bytes(c.dtype == DINFER_BF16, H, max_tokens));   // of the router's logits
   w.run_tokens = cv.take(T * 4);                 // token run and start positions of a vicinity-refresh forward
   w.run_base = cv.take((size_t)max_seqs * 4);
   w.n_finished = cv.take(4);                     // generation loop: sequences that have produced the end-of-sequence id

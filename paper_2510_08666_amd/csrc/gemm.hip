@@ -1281,12 +1281,13 @@ template <typename E> static bool configure_smooth() {
 // output projection's tasks; then softmax and the k selection rounds (ties to the lower expert id).  No sum between workgroups is left; up to 64
 // tokens the pairs are sorted by whoever needs them (PairIds).  Bound by one dependent round trip and the rounds' cross-lane steps.
 // Until the output projection left shares, one or two token tiles were contracted with the whole of K here by up to eight workgroups, with
-// a hand-off between them, and the last one selected and sorted: with events around the launch 14.3 -> 6.8 us at 32 tokens, 16.3 -> 6.8
-// at 64 (hidden 2048), the float32 test model 11.3 -> 6.7; the output projection takes 1.2 to 1.6 longer (3.1 with shares of 128 features),
-// the expert kernels up to 0.8.
-// More tokens: as the router kernel below and the permutation take it 18.9 us at 160 tokens and 21.5 at 512, with this kernel 13.1 and 13.1
-// (the output projection +1.3 to 1.6), as long as the projection takes its forms of one token tile (1024 tokens at hidden 2048; beyond, shares
-// of 8 KB a token would cost more than the contraction).  Eight tokens a workgroup: with 32, one compute unit fetches 256 KB, 17.2 us.
+// a hand-off between them, and the last one selected and sorted: with events around the launch 14.0 -> 6.8 us at 32 tokens, 16.1 -> 7.2
+// at 64 (hidden 2048, bfloat16), the float32 test model 10.8 -> 6.7; the output projection takes 2.9 and 2.4 longer in bfloat16, 1.1 and 2.7 in
+// float32, the expert kernels up to 0.8.
+// More tokens (float32): as the router kernel below and the permutation take it 34.0 us at 160 tokens and 35.9 at 512, with this kernel 11.9
+// and 12.8 (hidden 2048, the output projection +2.4; hidden 256 14.5 and 15.5 -> 12.0 and 11.4, +2.5), as long as the projection takes its
+// forms of one token tile (beyond, shares of 8 KB a token would cost more than the contraction).  Eight tokens a workgroup: with 32, one
+// compute unit fetches 256 KB.
 // ------------------------------------------------------------------------------------------------
 constexpr int SELECT_WAVES = 4;
 // HIST (more than 64 tokens): the workgroup leaves its tokens' pairs per expert for the permutation.  PARTS (bfloat16, shares that are

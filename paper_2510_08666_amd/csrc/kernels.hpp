@@ -152,14 +152,19 @@ struct OprojArgs {
   float* shares;
   int share_features;
 };
-// Features per share of the router's logits that the output projection leaves, or 0: a task's in its forms of up to 64 tokens
+// Features per share of the router's logits that the output projection leaves, or 0: then the router contracts by itself.
+// Bfloat16, up to 64 tokens: a chain of the contraction as the router itself sums it, with eight waves in every workgroup of the K
+// range and ROUTER_CHAIN k-steps (two tasks) in every wave at up to 32 tokens, half of them (a task) beyond, where hidden sizes divide
+// so.  Above 64 tokens a chain is an eighth of K, which runs through the tasks of several workgroups.  Sums in another order differ by
+// 1e-7, cached keys and values then round to other neighbours, and in 45 of 160 steps of sixteen layers one row's eighth
+// expert, a tie, was another one, with outputs up to 4e-2 apart (2-norm; the median 4e-4).
+// A float32 model rounds nothing to sixteen bits on the way, and its outputs move by 1e-6: a task's share in the forms of up to 64 tokens
 // and, of more tokens up to ROUTER_SHARES_T, in the dense ones of one token tile.
-// Up to 32 tokens in bfloat16, two tasks': a chain of the contraction as the router itself sums it, with eight waves in every
-// workgroup of the K range and ROUTER_CHAIN k-steps in every wave (where hidden sizes divide so; others are left to it).  Sums in
-// another order differ by 1e-7, cached keys and values then round to other neighbours, and in 45 of 160 steps of
-// sixteen layers one row's eighth expert, a tie, was another one, with outputs up to 4e-2 apart (2-norm; the median 4e-4).
-// A float32 model rounds nothing to sixteen bits on the way: its outputs move by 1e-6.
 constexpr int ROUTER_SHARES_T = 1024, ROUTER_WAVES = 8, ROUTER_CHAIN = 8;
+inline size_t router_shares_bytes(bool bf16, int H, int max_tokens) {
+  const int most = bf16 ? 64 : ROUTER_SHARES_T;
+  return (size_t)(H / 64) * (max_tokens < most ? max_tokens : most) * MAX_EXPERTS * 4;
+}
 int router_share_features(bool bf16, int D, int H, int T);
 void launch_oproj(bool bf16, const OprojArgs& a, hipStream_t st);
 

@@ -1,7 +1,8 @@
 """Steps whose router sums what the tasks of the output projection leave: one task, a few more than the 32 that are loaded
 together, the most there can be; one expert, counts that leave lanes without one, all 64.  Up to 64 tokens the expert kernels sort the
 routed pairs themselves: token counts at the edges of a wave's share of pairs and of the token tiles; beyond, the histograms of
-eight tokens feed the permutation: counts that end inside a histogram, a permutation group and a token tile."""
+eight tokens (float32; 32 in bfloat16, whose router contracts there) feed the permutation: counts that end inside a histogram, a permutation
+group and a token tile."""
 import numpy as np
 import pytest
 
@@ -20,7 +21,7 @@ def test_step_with_router_shares(n_seq, block, hidden, experts, top_k, width, dt
     check(n_seq, block, hidden, 1, experts, top_k, width, dtype)
 
 
-# (one head of 64: no dense form of the output projection, and no shares above 64 tokens in bfloat16)
+# (float32: one head of 64 has a dense form of the output projection, which leaves shares; bfloat16: none does)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("hidden,n_heads,experts,top_k", [(64, 2, 1, 1), (2112, 2, 33, 8), (4096, 2, 64, 5), (320, 1, 64, 8)])
 @pytest.mark.parametrize("n_seq,block", [(5, 13), (4, 24), (3, 43), (16, 33)])
